@@ -132,29 +132,32 @@ __device__ double vjp(const DevMech &m, double *lds, S y, double p, const double
 }
 
 // Solve (L U)^T x = b with the factors parked column-major in F: U^T z = b,
-// then L^T x = z.  Each unknown is a dot product of one stored column with
-// the solved part: one contiguous (conflict-free) LDS read per step and a
-// wave reduction.
+// then L^T x = z.  Row k of U (of L) is column k of the transposed factor:
+// lane j reads F[j FS + k], a stride of FS doubles, which is odd, so the 64
+// reads fall on different banks; the solved unknown is broadcast with
+// readlane and every lane behind it applies its entry.  (As dot products over
+// the stored columns instead, every unknown waited for a wave reduction: 112
+// of them one after another per solve.)
 template <int NP>
-__device__ double lu_solve_T(const double *F, double dinv, double b, int lane)
+__device__ __forceinline__ double lu_solve_T(const double *F, double dinv, double b, int lane)
 {
-    constexpr int FS = Lds<NP>::PS;
-    const int li = lane < NP ? lane : 0;
-    double z = 0.0;
-#pragma unroll 2
+    const double *Fr = F + (lane < NP ? lane : 0) * Lds<NP>::PS;
+#pragma unroll
     for (int k = 0; k < NP; ++k) {
-        const double u = F[k * FS + li];  // U_jk in lane j (j < k)
-        const double s = wave_sum(lane < k ? u * z : 0.0);
-        if (lane == k) z = (b - s) * dinv;
+        const double u = Fr[k];  // U_kj in lane j
+        if (lane == k) b *= dinv;
+        const double z = rdlane(b, k);
+        if (lane > k) b = fma(-u, z, b);
+        SC_FENCE_EVERY(k);
     }
-    double x = 0.0;
-#pragma unroll 2
-    for (int k = NP - 1; k >= 0; --k) {
-        const double l = F[k * FS + li];  // L_jk in lane j (j > k)
-        const double s = wave_sum(lane > k ? l * x : 0.0);
-        if (lane == k) x = z - s;
+#pragma unroll
+    for (int k = NP - 1; k > 0; --k) {
+        const double l = Fr[k];  // L_kj in lane j
+        const double x = rdlane(b, k);
+        if (lane < k) b = fma(-l, x, b);
+        SC_FENCE_EVERY(NP - 1 - k);
     }
-    return lane < NP ? x : 0.0;
+    return lane < NP ? b : 0.0;
 }
 
 // Reverse one replayed step: the attempt from y with size hc has just left
