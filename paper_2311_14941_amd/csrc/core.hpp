@@ -71,12 +71,46 @@ __device__ __forceinline__ double rdlane(double v, int lane)
     return __hiloint2double(hi, lo);
 }
 
-__device__ __forceinline__ double wave_sum(double v)
+// One step of a butterfly sum in registers: v plus the value a DPP control
+// brings from the same row of 16 lanes.
+template <int CTRL>
+__device__ __forceinline__ double add_dpp(double v)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, WAVE);
-    return v;
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return v + __hiloint2double(hi, lo);
 }
+
+// Sum over aligned groups of G lanes (16, 32 or 64), left in every lane of
+// the group: a butterfly over lane distances G/2, ..., 1, so the additions
+// and their order are those of xor shuffles.  The distances 32 and 16 are
+// half-wave and row swaps (a swap of v with itself leaves the low half in one
+// result and the high half in the other), 8 and 4 are rotations of a row
+// (after the step at distance 8 the row repeats with period 8, so a rotation
+// by 4 reads the lane at distance 4), 2 and 1 permute quads.  A shuffle is an
+// LDS permute whose round trip the next step waits for; a 64-lane sum took
+// about 900 cycles of the wave's chain with shuffles, 13 sums a step.
+template <int G>
+__device__ __forceinline__ double group_sum(double v)
+{
+    static_assert(G == 16 || G == 32 || G == 64, "aligned group of lanes");
+    if constexpr (G == 64) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+        v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+    }
+    if constexpr (G >= 32) {
+        const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+        v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+    }
+    v = add_dpp<0x128>(v);  // row_ror:8
+    v = add_dpp<0x124>(v);  // row_ror:4
+    v = add_dpp<0x4e>(v);   // quad_perm [2,3,0,1]
+    return add_dpp<0xb1>(v);  // quad_perm [1,0,3,2]
+}
+
+__device__ __forceinline__ double wave_sum(double v) { return group_sum<WAVE>(v); }
 
 __device__ __forceinline__ void wave_sync() { __syncthreads(); }
 

@@ -42,9 +42,7 @@ namespace scdev {
 template <int G>
 __device__ __forceinline__ double gsum(double v)
 {
-#pragma unroll
-    for (int off = G / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off, WAVE);
-    return v;
+    return group_sum<G>(v);
 }
 
 template <int G>
