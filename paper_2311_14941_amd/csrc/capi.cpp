@@ -24,6 +24,7 @@ struct sc_plan {
     int device = 0;
     int np = 0;
     scdev::DevMech dm{};
+    scdev::DevMech dms{};  // the sparse kernels' tables: species in elimination order
     bool sparse = false;  // sparse linear algebra kernels
     int vpl = 1;          // state components per lane of the sparse kernels
     scdev::DevSparse ds{};
@@ -335,26 +336,29 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
                                "algebra and N + 2 <= " + std::to_string(64 / o.cells_per_wave) + " positions");
     const int cpw = o.cells_per_wave ? o.cells_per_wave : cpw_max;
     scdev::DevSparse ds{};
+    sc::SparseDev sd;
     if (sparse) {
         const int NV = 64 / cpw * vpl;
         ds.cpw = cpw;
         ds.n = S.n;
         ds.nnz = S.nnz;
-        ds.nl_lu = (int)S.lu_b_lvl.size() - 1;
-        ds.nl_fw = (int)S.fw_lvl.size() - 1;
-        ds.nl_bw = (int)S.bw_lvl.size() - 1;
+        try {
+            sd = sc::sparse_device(mech->m, 64 / cpw);
+        } catch (...) {
+            return fail(SC_ENOMEM, "host allocation failed");
+        }
+        ds.nl = (int)sd.hb_lvl.size() - 2;
         ds.n_u = (int)S.lu_u.size();
-        ds.tail0 = S.tail0;
+        ds.dense0 = sd.dense0;
         ds.NV = NV;
         ds.E = 0;
-        ds.C = S.nnz + 1;  // E[nnz]: a slot kept at zero (the table sweeps' entry for rows without one)
+        ds.C = S.nnz + 1;  // E[nnz]: a slot kept at zero (the entry the operand tables give where there is none)
         ds.G = ds.C + NV;
         ds.H = ds.G + NV;
         ds.WD = ds.H + NV;
         ds.UA = ds.WD + NV;
         ds.U = ds.UA + NV;
-        ds.X = ds.U + 4 * NV;
-        ds.DINV = ds.X + S.n;
+        ds.DINV = ds.U + 4 * NV;
         ds.size = ds.DINV + S.n;
         hipDeviceProp_t prop;
         if (hipGetDeviceProperties(&prop, device) != hipSuccess) return fail(SC_EHIP, "hipGetDeviceProperties failed");
@@ -460,30 +464,27 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
         for (int q = 0; q < t.R; ++q)
             std::memcpy(&rxi[(size_t)q * sc::RXI_SIZE], &S.rxi[(size_t)order[q] * sc::RXI_SIZE],
                         sizeof(uint16_t) * sc::RXI_SIZE);
-        std::vector<int32_t> comp((size_t)scdev::CMP * (N + 1), -1);
-        for (int k = 0; k < N; ++k) {
-            int32_t *c = &comp[(size_t)scdev::CMP * k];
-            c[0] = S.pos[k];
-            c[1] = S.e_kk[k];
-            c[2] = S.e_kT[k];
-            c[3] = S.e_kS[k];
-            c[4] = S.e_Tk[k];
-            c[5] = S.e_Sk[k];
+        // the species table and the records with species in elimination order
+        std::vector<int32_t> perm(S.perm.begin(), S.perm.begin() + N + 1), pos(S.pos.begin(), S.pos.begin() + N + 1);
+        std::vector<double> sps(spv.size());
+        for (int a = 0; a < 9; ++a)
+            for (int k = 0; k < N; ++k) sps[(size_t)a * N + pos[k]] = spv[(size_t)a * N + k];
+        std::vector<scdev::RxRec> rxs(rx);
+        for (auto &r : rxs) {
+            for (int i = 0; i < r.nr; ++i) r.rsp[i] = pos[r.rsp[i]];
+            for (int i = 0; i < r.np; ++i) r.psp[i] = pos[r.psp[i]];
+            for (int e = 0; e < r.neff; ++e) r.esp[e] = pos[r.esp[e]];
         }
-        comp[(size_t)scdev::CMP * N] = S.pos[N];
-        comp[(size_t)scdev::CMP * N + 1] = S.e_TT;
-        comp[(size_t)scdev::CMP * N + 2] = S.e_SS;
+        p->dms = d;
         std::vector<uint16_t> emap(S.emap.size());
         for (size_t i = 0; i < emap.size(); ++i) emap[i] = S.emap[i] < 0 ? sc::NOENT : (uint16_t)S.emap[i];
         scdev::DevSparse &q = p->ds;
-        std::vector<uint64_t> lu_b(S.lu_b.begin(), S.lu_b.end());
-        ok = upload(p, S.lu_b_lvl, &q.lu_b_lvl) && upload(p, S.lu_c_lvl, &q.lu_c_lvl) &&
-             upload(p, S.fw_lvl, &q.fw_lvl) && upload(p, S.bw_lvl, &q.bw_lvl) && upload(p, lu_b, &q.lu_b) &&
-             upload(p, S.lu_u, &q.lu_u) && upload(p, S.diag, &q.diag) && upload(p, S.lu_c, &q.lu_c) &&
-             upload(p, S.fw, &q.fw) && upload(p, S.bw, &q.bw) && upload(p, rxi, &q.rxi) &&
-             upload(p, comp, &q.comp) && upload(p, emap, &q.emap) && upload(p, S.cstart, &q.cstart) &&
-             upload(p, S.cmask, &q.cmask) && upload(p, S.sweep_f, &q.swf) && upload(p, S.sweep_b, &q.swb) &&
-             upload(p, S.sweep_fi, &q.swfi) && upload(p, S.sweep_bi, &q.swbi);
+        ok = upload(p, sps, &p->dms.sp) && upload(p, rxs, &p->dms.rx) && upload(p, sd.hb_lvl, &q.hb_lvl) &&
+             upload(p, sd.hc_lvl, &q.hc_lvl) && upload(p, sd.hb, &q.hb) && upload(p, sd.hc, &q.hc) &&
+             upload(p, S.lu_u, &q.lu_u) && upload(p, S.diag, &q.diag) && upload(p, rxi, &q.rxi) &&
+             upload(p, sd.comp, &q.comp) && upload(p, perm, &q.perm) && upload(p, pos, &q.pos) &&
+             upload(p, emap, &q.emap) && upload(p, S.cstart, &q.cstart) && upload(p, sd.row, &q.row) &&
+             upload(p, sd.ga, &q.ga) && upload(p, sd.gb, &q.gb);
     }
     if (ok) {
         void *q = nullptr;
@@ -519,7 +520,7 @@ sc_status sc_rhs(sc_plan *plan, int64_t n, const double *T, const double *p, con
     DeviceGuard g(plan->device);
     hipError_t e =
         plan->sparse
-            ? scdev::launch_rhs_sp(plan->vpl, plan->dm, plan->ds, n, T, p, Y, ld, dlnA, fT, fY, (hipStream_t)stream)
+            ? scdev::launch_rhs_sp(plan->vpl, plan->dms, plan->ds, n, T, p, Y, ld, dlnA, fT, fY, (hipStream_t)stream)
             : scdev::launch_rhs(plan->np, plan->dm, n, T, p, Y, ld, dlnA, fT, fY, (hipStream_t)stream);
     return e == hipSuccess ? SC_OK : hip_fail(e, "rhs launch");
 }
@@ -531,7 +532,7 @@ sc_status sc_jacobian(sc_plan *plan, int64_t n, const double *T, const double *p
     if (s != SC_OK || n == 0) return s;
     DeviceGuard g(plan->device);
     hipError_t e = plan->sparse
-                       ? scdev::launch_jac_sp(plan->vpl, plan->dm, plan->ds, n, T, p, Y, ld, dlnA, J,
+                       ? scdev::launch_jac_sp(plan->vpl, plan->dms, plan->ds, n, T, p, Y, ld, dlnA, J,
                                               (hipStream_t)stream)
                        : scdev::launch_jac(plan->np, plan->dm, n, T, p, Y, ld, dlnA, J, (hipStream_t)stream);
     return e == hipSuccess ? SC_OK : hip_fail(e, "jacobian launch");
@@ -543,7 +544,7 @@ sc_status sc_linsolve(sc_plan *plan, int64_t n, const double *T, const double *p
     sc_status s = check_common(plan, n, ld, {T, p, Y, hg, b, x});
     if (s != SC_OK || n == 0) return s;
     DeviceGuard g(plan->device);
-    hipError_t e = plan->sparse ? scdev::launch_linsolve_sp(plan->vpl, plan->dm, plan->ds, n, T, p, Y, ld, dlnA, hg,
+    hipError_t e = plan->sparse ? scdev::launch_linsolve_sp(plan->vpl, plan->dms, plan->ds, n, T, p, Y, ld, dlnA, hg,
                                                             b, x, (hipStream_t)stream)
                                 : scdev::launch_linsolve(plan->np, plan->dm, n, T, p, Y, ld, dlnA, hg, b, x,
                                                          (hipStream_t)stream);
@@ -611,7 +612,7 @@ static sc_status integrate_impl(sc_plan *plan, int64_t n, const double *T0, cons
         }
         e = scdev::launch_zero_u64(queue, st);
         if (e == hipSuccess && plan->sparse)
-            e = scdev::launch_integrate_sp_persistent(plan->vpl, plan->dm, plan->ds, o, n, T0, p, Y0, ld, dt, dlnA,
+            e = scdev::launch_integrate_sp_persistent(plan->vpl, plan->dms, plan->ds, o, n, T0, p, Y0, ld, dt, dlnA,
                                                       h_io, T1, Y1, cell_status, n_acc, n_rej, queue, perm, tile,
                                                       grid, ref, st);
         else if (e == hipSuccess)
@@ -623,13 +624,13 @@ static sc_status integrate_impl(sc_plan *plan, int64_t n, const double *T0, cons
         if (grid <= 0) grid = 1;
         if (grid > n) grid = (int)n;
         if (plan->sparse)
-            e = scdev::launch_integrate_sp_static(plan->vpl, plan->dm, plan->ds, o, n, T0, p, Y0, ld, dt, dlnA, h_io,
+            e = scdev::launch_integrate_sp_static(plan->vpl, plan->dms, plan->ds, o, n, T0, p, Y0, ld, dt, dlnA, h_io,
                                                   T1, Y1, cell_status, n_acc, n_rej, grid, ref, st);
         else
             e = scdev::launch_integrate_static(plan->np, plan->dm, o, plan->opt.method, n, T0, p, Y0, ld, dt, dlnA,
                                                h_io, T1, Y1, cell_status, n_acc, n_rej, grid, ref, st);
     } else if (plan->sparse) {
-        e = scdev::launch_integrate_sp(plan->vpl, plan->dm, plan->ds, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1,
+        e = scdev::launch_integrate_sp(plan->vpl, plan->dms, plan->ds, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1,
                                        cell_status, n_acc, n_rej, ref, st);
     } else {
         e = scdev::launch_integrate(plan->np, plan->dm, o, plan->opt.method, n, T0, p, Y0, ld, dt, dlnA, h_io, T1,

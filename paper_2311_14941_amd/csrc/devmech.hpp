@@ -47,25 +47,26 @@ struct DevMech {
 };
 
 // The sparse kernels' view of a mechanism's compiled sparse algebra (device
-// pointers) and their per-cell LDS layout (offsets in doubles; NV = 64 VPL
-// doubles per state vector).
+// pointers) and their per-cell LDS layout (offsets in doubles; NV doubles per
+// state vector).  Their DevMech has the species in elimination order, so a
+// lane holds the same position as component and as matrix row.
 struct DevSparse {
-    int n, nnz, nl_lu, nl_fw, nl_bw, n_u;
-    int E, C, G, H, WD, UA, U, X, DINV, size;  // LDS offsets of one cell's region and its size (doubles)
+    int n, nnz, nl, n_u;
+    int E, C, G, H, WD, UA, U, DINV, size;  // LDS offsets of one cell's region and its size (doubles)
     int NV;   // vector stride: lanes per cell times slots per lane
     int cpw;  // cells per wave (1, 2 or 4): each cell takes 64 / cpw lanes
-    int tail0;  // first position of the dense trailing block (factorised in registers)
-    const int *lu_b_lvl, *lu_c_lvl, *fw_lvl, *bw_lvl;
-    const uint64_t *lu_b;  // widened to the c items' width: e_ik | e_kk << 16
-    const uint32_t *lu_u, *diag;
-    const uint64_t *lu_c, *fw, *bw;
+    int dense0;  // first position of the dense trailing block
+    const int *hb_lvl, *hc_lvl;  // levels of the pivots before it (nl of them, and one empty)
+    const uint32_t *hb;          // e_ik | e_kk << 16
+    const uint64_t *hc;          // e_ij | e_ik << 16 | e_kj << 32
+    const uint32_t *lu_u, *diag; // strict U entries with their pivot: e_kj | k << 16; diagonal entries
     const uint16_t *rxi;   // [R][RXI_SIZE], reaction execution order
-    const int32_t *comp;   // per species k: pos, e_kk, e_kT, e_kS, e_Tk, e_Sk; then pos_T, e_TT, e_SS
+    const uint16_t *comp;  // [position][8]: e_kk, e_kT, e_kS, e_Tk, e_Sk; at N: e_TT, e_SS
+    const int32_t *perm;   // position -> species (N: temperature)
+    const int32_t *pos;    // species -> position
     const uint16_t *emap;    // n * n: (row, column) position -> entry or NOENT, row-major
     const int32_t *cstart;   // n + 1: first entry of each column (entries are numbered column by column)
-    const uint64_t *cmask;   // 2 n: rows with an entry in column k, lanes 0-63 then 64-127
-    const uint32_t *swf, *swb;  // n <= 64: per column the strictly lower (upper) rows' mask and first entry
-    const uint16_t *swfi, *swbi;  // n <= 64: per column and row the lower (upper) entry, or nnz (zero slot)
+    const uint16_t *row, *ga, *gb;  // SparseDev's operand tables
     // interpolated thermodynamics (null: exact): per interval of ln T and
     // reaction (execution order) the 2 (ideg + 1) coefficients of -dG/RT and
     // dH/RT in t = 2 (ln T - u_i) iinvdu - 1
@@ -73,7 +74,6 @@ struct DevSparse {
     int ideg, inint;
     double iu0, iinvdu;
 };
-constexpr int CMP = 6;  // comp entries per species
 
 struct Opts {
     double rtol, atol;

@@ -96,6 +96,35 @@ struct SparseLU {
     int64_t flops_lu = 0, flops_solve = 0;
 };
 
+// Entry indices of the sparse kernels' operand tables are 16-bit byte
+// offsets into a cell's L+U entries for systems of up to 64 positions (at
+// most 64 * 64 entries), entry numbers beyond.
+constexpr int sparse_off(int n, int e) { return n <= 64 ? 8 * e : e; }
+
+// What the device reads of a mechanism's sparse algebra (built per plan from
+// SparseLU; `lanes` lanes hold one cell's positions, two slots each when
+// n > 64).  The pivots before dense0 are eliminated by levels, but only
+// their updates outside the dense trailing block [dense0, n) are scheduled
+// (hb, hc: as lu_b, lu_c): the block's Schur update A22 -= L21 U12 is a
+// dense product of the gathered operands (ga, gb), and holds 83% of the
+// scheduled updates of a 53-species mechanism, 94% of a 110-species one.
+struct SparseDev {
+    int dense0 = 0;
+    std::vector<int> hb_lvl, hc_lvl;
+    std::vector<uint32_t> hb;
+    std::vector<uint64_t> hc;
+    // per slot, lane and column the entry of the lane's row (else the zero
+    // slot nnz): what the solves read
+    std::vector<uint16_t> row;
+    int row_cols = 0;  // columns per lane in `row`
+    // operands of the Schur update in the matrix instruction's lane layout,
+    // pivots in steps of four.  n <= 64: [step][lane][A tile 0, A tile 1,
+    // B tile 0, B tile 1] in ga; beyond: [tile][lane][step, padded to 16]
+    // in ga (A) and gb (B)
+    std::vector<uint16_t> ga, gb;
+    std::vector<uint16_t> comp;  // per component (position order): its entries kk, kT, kS, Tk, Sk, padded to 8
+};
+
 enum RxKind { RX_PLAIN = 0, RX_THIRD = 1, RX_TROE = 2 };
 
 struct ParseError : std::runtime_error {
@@ -174,5 +203,8 @@ ThermoFit fit_thermo(const Mech &m, double Tmin, double Tmax, double tol, int de
 // The sparse compile (sparse.cpp): ordering, symbolic LU, schedules, entry
 // indices and counts of a parsed, validated mechanism.
 void compile_sparse(Mech &m);
+
+// The device tables of a compiled mechanism for `lanes` lanes per cell.
+SparseDev sparse_device(const Mech &m, int lanes);
 
 }  // namespace sc

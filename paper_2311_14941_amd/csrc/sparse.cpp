@@ -319,4 +319,93 @@ void compile_sparse(Mech &m)
     c.flops_step = c.flops_attempt + c.flops_accept;
 }
 
+SparseDev sparse_device(const Mech &m, int lanes)
+{
+    const SparseLU &S = m.sp;
+    const int n = S.n, N = m.N, zero = S.nnz;
+    const int slots = n <= 64 ? 1 : 2;
+    SparseDev D;
+    auto off = [&](int i, int j) {
+        const int e = i < n && j < n ? S.emap[(size_t)i * n + j] : -1;
+        return (uint16_t)sparse_off(n, e < 0 ? zero : e);
+    };
+    // the dense trailing block: up to 64 positions, the one factorised in
+    // registers; beyond, the whole full block (blocked elimination)
+    D.dense0 = S.tail0;
+    if (n > 64)
+        while (D.dense0 > 0) {
+            const int q = D.dense0 - 1;
+            bool full = true;
+            for (int i = q; i < n && full; ++i)
+                full = S.emap[(size_t)i * n + q] >= 0 && S.emap[(size_t)q * n + i] >= 0;
+            if (!full) break;
+            D.dense0 = q;
+        }
+    const int t0 = D.dense0;
+    // levels of the pivots before the block, as in the full schedule
+    std::vector<std::vector<int>> L(t0), U(t0);
+    std::vector<int> lev(n, 0);
+    int nl = 0;
+    for (int k = 0; k < t0; ++k) {
+        for (int i = k + 1; i < n; ++i) {
+            if (S.emap[(size_t)i * n + k] >= 0) L[k].push_back(i);
+            if (S.emap[(size_t)k * n + i] >= 0) U[k].push_back(i);
+        }
+        for (auto *v : {&L[k], &U[k]})
+            for (int i : *v) lev[i] = std::max(lev[i], lev[k] + 1);
+        nl = std::max(nl, lev[k] + 1);
+    }
+    auto E = [&](int i, int j) { return S.emap[(size_t)i * n + j]; };
+    D.hb_lvl.assign(1, 0);
+    D.hc_lvl.assign(1, 0);
+    for (int l = 0; l < nl; ++l) {
+        for (int k = 0; k < t0; ++k) {
+            if (lev[k] != l) continue;
+            for (int i : L[k]) D.hb.push_back((uint32_t)E(i, k) | (uint32_t)E(k, k) << 16);
+            for (int i : L[k])
+                for (int j : U[k])
+                    if (i < t0 || j < t0)
+                        D.hc.push_back((uint64_t)E(i, j) | (uint64_t)E(i, k) << 16 | (uint64_t)E(k, j) << 32);
+        }
+        D.hb_lvl.push_back((int)D.hb.size());
+        D.hc_lvl.push_back((int)D.hc.size());
+    }
+    D.hb_lvl.push_back((int)D.hb.size());  // an empty level after the last: the loads run one level ahead
+    D.hc_lvl.push_back((int)D.hc.size());
+    // solve operands: columns padded to what the sweeps read ahead
+    D.row_cols = lanes < 64 ? lanes : 64 * slots;
+    for (int s = 0; s < slots; ++s)
+        for (int l = 0; l < lanes; ++l)
+            for (int c = 0; c < D.row_cols; ++c) D.row.push_back(off(l + 64 * s, c));
+    // Schur operands: lane l holds A[row l % 16][pivot l / 16] and
+    // B[pivot l / 16][column l % 16]
+    const int steps = (t0 + 3) / 4;
+    auto pivot = [&](int s, int l) { return 4 * s + l / 16 < t0 ? 4 * s + l / 16 : n; };
+    if (n <= 64) {
+        for (int s = 0; s < steps; ++s)
+            for (int l = 0; l < 64; ++l) {
+                for (int t = 0; t < 2; ++t) D.ga.push_back(off(t0 + 16 * t + l % 16, pivot(s, l)));
+                for (int t = 0; t < 2; ++t) D.ga.push_back(off(pivot(s, l), t0 + 16 * t + l % 16));
+            }
+    } else {
+        const int pad = (steps + 15) / 16 * 16, tiles = (n - t0 + 15) / 16;
+        for (int t = 0; t < tiles; ++t)
+            for (int l = 0; l < 64; ++l)
+                for (int s = 0; s < pad; ++s) {
+                    D.ga.push_back(off(t0 + 16 * t + l % 16, pivot(s, l)));
+                    D.gb.push_back(off(pivot(s, l), t0 + 16 * t + l % 16));
+                }
+    }
+    // component entries by position (the borders are the last two)
+    D.comp.assign((size_t)8 * lanes * slots, 0);
+    for (int k = 0; k < N; ++k) {
+        uint16_t *c = &D.comp[(size_t)8 * S.pos[k]];
+        const int e[5] = {S.e_kk[k], S.e_kT[k], S.e_kS[k], S.e_Tk[k], S.e_Sk[k]};
+        for (int q = 0; q < 5; ++q) c[q] = (uint16_t)e[q];
+    }
+    D.comp[(size_t)8 * N] = (uint16_t)S.e_TT;
+    D.comp[(size_t)8 * N + 1] = (uint16_t)S.e_SS;
+    return D;
+}
+
 }  // namespace sc

@@ -1,9 +1,9 @@
 // Kernels with the sparse linear algebra (gfx950): one 64-lane wavefront per
 // cell, as in the dense kernels, but the iteration matrix lives in LDS as the
-// L+U entries of the bordered system the mechanism compiler built (sparse.cpp)
-// and is factorised and solved by following that compiler's static level
-// schedules.  State vectors hold VPL components per lane (component
-// c = lane + 64 v), so mechanisms of up to 127 species fit one wave.
+// L+U entries of the bordered system the mechanism compiler built
+// (sparse.cpp).  State vectors hold VPL components per lane (component
+// c = lane + 64 v, species in elimination order), so mechanisms of up to 126
+// species fit one wave; small ones run two or four cells per wave.
 //
 // The bordered system (order N + 2, unknowns z_k = x_k / W_k, x_T, sigma):
 //   row k:     z_k/hg - sum_m P_km z_m - us_k sigma - (P_kT/rho + ct us_k) x_T = b_k / W_k
@@ -17,15 +17,12 @@
 // volume).  Eliminating sigma gives back M = I/hg - J exactly (paper
 // Sec. 2.5: sparse analytical Jacobian, sparse algebra management).
 //
-// Every schedule phase is a list of independent items processed 64 at a
-// time, four groups in flight; items of one phase that update the same entry
-// use LDS atomics, so one wave's results do not depend on anything but the
-// schedule (bitwise equal across launch modes).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstdint>
 #include <type_traits>
+#include <utility>
 
 #include "core.hpp"
 
@@ -50,15 +47,6 @@ __device__ __forceinline__ double gbcast(double v, int k)
 {
     if constexpr (G == WAVE)
         return rdlane(v, k);
-    else
-        return __shfl(v, k, G);
-}
-
-template <int G>
-__device__ __forceinline__ int gbcast_i(int v, int k)
-{
-    if constexpr (G == WAVE)
-        return __builtin_amdgcn_readlane(v, k);
     else
         return __shfl(v, k, G);
 }
@@ -94,24 +82,24 @@ __device__ __forceinline__ double comp_T(const DevMech &m, const double (&y)[VPL
 }
 
 template <int VPL, int G = WAVE>
-__device__ __forceinline__ void load_state_v(const DevMech &m, const double *T, const double *Y, int64_t ld,
+__device__ __forceinline__ void load_state_v(const DevMech &m, const DevSparse &sp, const double *T, const double *Y, int64_t ld,
                                              int64_t cell, int lane, double (&y)[VPL])
 {
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int c = lane + G * v;
-        y[v] = c < m.N ? Y[(int64_t)c * ld + cell] : c == m.N ? T[cell] : 0.0;
+        y[v] = c < m.N ? Y[(int64_t)sp.perm[c] * ld + cell] : c == m.N ? T[cell] : 0.0;
     }
 }
 
 template <int VPL, int G = WAVE>
-__device__ __forceinline__ void store_state_v(const DevMech &m, double *T, double *Y, int64_t ld, int64_t cell,
+__device__ __forceinline__ void store_state_v(const DevMech &m, const DevSparse &sp, double *T, double *Y, int64_t ld, int64_t cell,
                                               int lane, const double (&y)[VPL])
 {
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int c = lane + G * v;
-        if (c < m.N) Y[(int64_t)c * ld + cell] = y[v];
+        if (c < m.N) Y[(int64_t)sp.perm[c] * ld + cell] = y[v];
         if (c == m.N) T[cell] = y[v];
     }
 }
@@ -342,78 +330,411 @@ __device__ __forceinline__ void jac_v(const DevMech &m, const DevSparse &sp, dou
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int c = lane + G * v;
+        const uint16_t *cm = sp.comp + 8 * c;
         if (c < N) {
-            const int32_t *cm = sp.comp + CMP * c;
             const double us = m.cv ? lds[sp.UA + c] : lds[sp.UA + c] / x.rho;
-            E[cm[1]] += inv_hg;
-            E[cm[2]] = E[cm[2]] / x.rho - ct * us;
-            E[cm[3]] = -us;
-            E[cm[4]] = (E[cm[4]] + tb + fT * m.Rgas * (th[v].cpR - one)) * icp;
-            E[cm[5]] = vs;
+            E[cm[0]] += inv_hg;
+            E[cm[1]] = E[cm[1]] / x.rho - ct * us;
+            E[cm[2]] = -us;
+            E[cm[3]] = (E[cm[3]] + tb + fT * m.Rgas * (th[v].cpR - one)) * icp;
+            E[cm[4]] = vs;
         } else if (c == N) {
             f[v] = fT;
-            const int32_t *cm = sp.comp + CMP * N;
             const double eT = m.cv ? 0.0 : Eu * x.invT;
-            E[cm[1]] = inv_hg + (E[cm[1]] / x.rho + eT + Scpf + fT * Sdcp) * icp;
-            E[cm[2]] = -1.0;
+            E[cm[0]] = inv_hg + (E[cm[0]] / x.rho + eT + Scpf + fT * Sdcp) * icp;
+            E[cm[1]] = -1.0;
         }
     }
     __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
-// schedules
+// linear algebra
 // ---------------------------------------------------------------------------
+// The entry an operand table names: a byte offset (n <= 64) or a number.
+template <int VPL>
+__device__ __forceinline__ double entry(const double *E, uint32_t o)
+{
+    return VPL == 1 ? *(const double *)((const char *)E + o) : E[o];
+}
+
+// v from lane K of each cell's group, K known at compile time: a row
+// broadcast of the DPP unit for 16 lanes; for 32, readlane of both groups and
+// a select.
+template <int G, int K>
+__device__ __forceinline__ double bcast(double v)
+{
+    static_assert(G == 16 || G == 32, "groups of several cells per wave");
+    if constexpr (G == 16) {
+        const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x150 + K, 0xf, 0xf, true);
+        const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x150 + K, 0xf, 0xf, true);
+        return __hiloint2double(hi, lo);
+    } else {
+        const double a = rdlane(v, K), b = rdlane(v, 32 + K);
+        return threadIdx.x & 32 ? b : a;
+    }
+}
+
+// z -= a z_K, z_K from lane K of the row of 16 lanes: one instruction (the
+// broadcast reads a register two wait states after it was written)
+template <int K>
+__device__ __forceinline__ void fmac_row(double &z, double a)
+{
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, -%1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(z) : "v"(a), "n"(K));
+}
+
+// f(0), ..., f(N - 1) with compile-time arguments
+template <int N, class F, int... I>
+__device__ __forceinline__ void unrolled_(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F &&f)
+{
+    unrolled_<N>(f, std::make_integer_sequence<int, N>{});
+}
+
+// The factors between the factorisation and the solves.  Several cells per
+// wave: each lane's row in registers, L and U apart with zeros elsewhere (16
+// lanes; the column sweep is then one multiply-add with a row broadcast) or in
+// one array (32 lanes: two arrays would not leave registers for the reaction
+// pass).  One cell per wave: in the entries in LDS.
+template <int VPL, int G>
+struct Factors {};
+template <>
+struct Factors<1, 16> {
+    double l[16], u[16], dinv;
+};
+template <>
+struct Factors<1, 32> {
+    double a[32], dinv;
+};
+
+// z -= a zk on the lanes above (below) K; the mask goes straight to the
+// execution mask, one scalar instruction, where a select costs three vector
+// ones.  `all` is the mask to go back to.  The scalar operand comes from
+// readlane: two wait states until a vector instruction may read it.
+template <int K>
+__device__ __forceinline__ void fma_above(double &z, double a, double zk, uint64_t all)
+{
+    asm volatile("s_lshl_b64 exec, -2, %3\n\ts_nop 1\n\tv_fma_f64 %0, -%1, %2, %0\n\ts_mov_b64 exec, %4"
+                 : "+v"(z)
+                 : "v"(a), "s"(zk), "n"(K), "s"(all)
+                 : "scc");
+}
+template <int K>
+__device__ __forceinline__ void fma_below(double &z, double a, double zk, uint64_t all)
+{
+    asm volatile("s_bfm_b64 exec, %3, 0\n\ts_nop 1\n\tv_fma_f64 %0, -%1, %2, %0\n\ts_mov_b64 exec, %4"
+                 : "+v"(z)
+                 : "v"(a), "s"(zk), "n"(K), "s"(all));
+}
+// the same with the lane in a scalar register
+__device__ __forceinline__ void fma_above(double &z, double a, double zk, int k, uint64_t all)
+{
+    asm volatile("s_lshl_b64 exec, -2, %3\n\ts_nop 1\n\tv_fma_f64 %0, -%1, %2, %0\n\ts_mov_b64 exec, %4"
+                 : "+v"(z)
+                 : "v"(a), "s"(zk), "s"(k), "s"(all)
+                 : "scc");
+}
+__device__ __forceinline__ void fma_below(double &z, double a, double zk, int k, uint64_t all)
+{
+    asm volatile("s_bfm_b64 exec, %3, 0\n\ts_nop 1\n\tv_fma_f64 %0, -%1, %2, %0\n\ts_mov_b64 exec, %4"
+                 : "+v"(z)
+                 : "v"(a), "s"(zk), "s"(k), "s"(all));
+}
+__device__ __forceinline__ uint64_t exec_mask()
+{
+    uint64_t m;
+    asm volatile("s_mov_b64 %0, exec" : "=s"(m));
+    return m;
+}
+
+// ---- several cells per wave: the factorisation in registers, row per lane --
+// n <= G rows, so the rows of a whole system fit one group's registers (2 G
+// of them); every pivot row is broadcast inside the group.  Padding rows and
+// columns hold zeros; pivots at or beyond n are skipped.
+template <int G>
+__device__ __forceinline__ void lu_group(const DevSparse &sp, const double *E, int lane, Factors<1, G> &f)
+{
+    const int n = sp.n;
+    double a[G];
+    const uint32_t *ix = (const uint32_t *)(sp.row + G * lane);
+#pragma unroll
+    for (int c = 0; c < G; c += 2) {
+        const uint32_t w = ix[c / 2];
+        a[c] = entry<1>(E, w & 0xffff);
+        a[c + 1] = entry<1>(E, w >> 16);
+    }
+    f.dinv = 0.0;
+    unrolled<G>([&](auto K) __attribute__((always_inline)) {
+        constexpr int k = K;
+        if (k < n) {
+            const double akk = bcast<G, k>(a[k]);
+            if (lane == k) f.dinv = 1.0 / akk;
+            const double l = lane > k ? a[k] / akk : 0.0;
+            if (lane > k) a[k] = l;
+#pragma unroll
+            for (int j = k + 1; j < G; ++j) {
+                if constexpr (G == 16)
+                    fmac_row<k>(a[j], l);
+                else
+                    a[j] = fma(-l, bcast<G, k>(a[j]), a[j]);
+            }
+        }
+    });
+    // U to a unit diagonal
+#pragma unroll
+    for (int c = 0; c < G; ++c) {
+        if constexpr (G == 16) {
+            f.l[c] = lane > c ? a[c] : 0.0;
+            f.u[c] = lane < c ? a[c] * f.dinv : 0.0;
+        } else {
+            f.a[c] = lane < c ? a[c] * f.dinv : a[c];
+        }
+    }
+}
+
+template <int G>
+__device__ __forceinline__ void sweeps_group(const DevSparse &sp, const Factors<1, G> &f, int lane, double &z)
+{
+    const int n = sp.n;
+    unrolled<G - 1>([&](auto K) __attribute__((always_inline)) {
+        constexpr int k = K;
+        if (k % 4 != 0 || k < n) {
+            if constexpr (G == 16)
+                fmac_row<k>(z, f.l[k]);
+            else
+                z = fma(lane > k ? -f.a[k] : 0.0, bcast<G, k>(z), z);
+        }
+    });
+    z *= f.dinv;
+    unrolled<G - 1>([&](auto K) __attribute__((always_inline)) {
+        constexpr int k = G - 1 - K;
+        if (k < n) {
+            if constexpr (G == 16)
+                fmac_row<k>(z, f.u[k]);
+            else
+                z = fma(lane < k ? -f.a[k] : 0.0, bcast<G, k>(z), z);
+        }
+    });
+}
+
+// ---- one cell per wave: levels, dense Schur update, register tail -----------
 __device__ __forceinline__ int lo16(uint64_t x) { return (int)(x & 0xffff); }
 __device__ __forceinline__ int mid16(uint64_t x) { return (int)((x >> 16) & 0xffff); }
 __device__ __forceinline__ int hi16(uint64_t x) { return (int)((x >> 32) & 0xffff); }
 
-// The first four G-item groups of a phase, loaded ahead (the loads of the
-// next phase are issued before the current one is processed, so their
-// latency overlaps its LDS work).
-struct Pre {
-    uint64_t it[4];
+// The first four groups of 64 items of a phase, loaded one level ahead, so
+// their memory latency overlaps the level before; groups past the phase's end
+// are skipped by a uniform branch.
+template <class I>
+struct Items {
+    I it[4];
+    int q0, q1;
 };
-template <int G>
-__device__ __forceinline__ Pre preload(const uint64_t *items, int q0, int q1, int lane)
+template <class I>
+__device__ __forceinline__ Items<I> items(const I *list, int q0, int q1, int lane)
 {
-    Pre p;
+    Items<I> p;
+    p.q0 = q0;
+    p.q1 = q1;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const int q = q0 + u * G + lane;
-        p.it[u] = q < q1 ? items[q] : ~0ull;
+        const int q = q0 + u * WAVE + lane;
+        p.it[u] = q < q1 ? list[q] : (I)0;
     }
     return p;
 }
 
-// l_ik = a_ik / a_kk for the items of one phase (b items: e_ik | e_kk << 16)
-__device__ __forceinline__ void lu_scale_items(double *E, const uint64_t (&it)[4])
+// l_ik = a_ik / a_kk (e_ik | e_kk << 16)
+__device__ __forceinline__ void lu_scale_items(double *E, const Items<uint32_t> &p, int lane)
 {
     double a[4], d[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const bool ok = it[u] != ~0ull;
-        a[u] = ok ? E[lo16(it[u])] : 0.0;
-        d[u] = ok ? E[mid16(it[u])] : 1.0;
+        if (p.q0 + u * WAVE >= p.q1) break;
+        a[u] = E[p.it[u] & 0xffff];
+        d[u] = E[p.it[u] >> 16];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (it[u] != ~0ull) E[lo16(it[u])] = a[u] / d[u];
+    for (int u = 0; u < 4; ++u) {
+        if (p.q0 + u * WAVE >= p.q1) break;
+        if (p.q0 + u * WAVE + lane < p.q1) E[p.it[u] & 0xffff] = a[u] / d[u];
+    }
 }
 
-// a_ij -= l_ik u_kj for the items of one phase (c items: e_ij | e_ik << 16 | e_kj << 32)
-__device__ __forceinline__ void lu_update_items(double *E, const uint64_t (&it)[4])
+// a_ij -= l_ik u_kj (e_ij | e_ik << 16 | e_kj << 32); items of one phase may
+// share a target: LDS additions
+__device__ __forceinline__ void lu_update_items(double *E, const Items<uint64_t> &p, int lane)
 {
     double a[4], b[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const bool ok = it[u] != ~0ull;
-        a[u] = ok ? E[mid16(it[u])] : 0.0;
-        b[u] = ok ? E[hi16(it[u])] : 0.0;
+        if (p.q0 + u * WAVE >= p.q1) break;
+        a[u] = E[mid16(p.it[u])];
+        b[u] = E[hi16(p.it[u])];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (it[u] != ~0ull) atomicAdd(&E[lo16(it[u])], -a[u] * b[u]);
+    for (int u = 0; u < 4; ++u) {
+        if (p.q0 + u * WAVE >= p.q1) break;
+        if (p.q0 + u * WAVE + lane < p.q1) atomicAdd(&E[lo16(p.it[u])], -a[u] * b[u]);
+    }
+}
+
+// The pivots before the dense block, level by level: their L entries, then
+// their updates of entries outside the block (the block's own updates are
+// left to the dense product).
+__device__ __forceinline__ void lu_levels(const DevSparse &sp, double *E, int lane)
+{
+    if (sp.nl == 0) return;
+    Items<uint32_t> pb = items(sp.hb, 0, sp.hb_lvl[1], lane);
+    Items<uint64_t> pc = items(sp.hc, 0, sp.hc_lvl[1], lane);
+#pragma unroll 1
+    for (int l = 0; l < sp.nl; ++l) {
+        const int b1 = sp.hb_lvl[l + 1], c1 = sp.hc_lvl[l + 1];
+        lu_scale_items(E, pb, lane);
+#pragma unroll 1
+        for (int q = pb.q0 + 4 * WAVE; q < b1; q += 4 * WAVE) lu_scale_items(E, items(sp.hb, q, b1, lane), lane);
+        pb = items(sp.hb, b1, sp.hb_lvl[l + 2], lane);
+        __syncthreads();
+        const int c0 = pc.q0;
+        if (c1 > c0) {
+            lu_update_items(E, pc, lane);
+#pragma unroll 1
+            for (int q = c0 + 4 * WAVE; q < c1; q += 4 * WAVE) lu_update_items(E, items(sp.hc, q, c1, lane), lane);
+            __syncthreads();
+        }
+        pc = items(sp.hc, c1, sp.hc_lvl[l + 2], lane);
+    }
+}
+
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+// acc -= A B on one 16 x 16 tile with four pivots: lane l gives A[l % 16][l / 16]
+// and B[l / 16][l % 16] and holds rows 4 r + l / 16 of column l % 16 (the
+// last argument negates A)
+__device__ __forceinline__ d4 tile_sub(double a, double b, d4 acc)
+{
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 1);
+}
+
+// Schur update of the dense block [t0, n) of up to 32 positions, A22 -= L21
+// U12, on the matrix cores: 2 x 2 tiles, pivots in steps of four, operands
+// gathered from the L+U entries through the tables (absent entries read the
+// zero slot).  Entry (i, j) of the block is the column's end minus n - i.
+// What this replaces: 6,160 scheduled multiply-adds (53 species) read their
+// indices from L2 in 33 dependent rounds and met in LDS additions.
+__device__ __forceinline__ void lu_schur(const DevSparse &sp, double *E, int lane, const uint2 (&g0)[8])
+{
+    const int n = sp.n, t0 = sp.dense0, steps = (t0 + 3) / 4;
+    if (steps == 0) return;
+    const int c = lane & 15, r0 = lane >> 4;
+    int base[2];
+    d4 acc[2][2];
+#pragma unroll
+    for (int tj = 0; tj < 2; ++tj) {
+        const int j = min(t0 + 16 * tj + c, n - 1);
+        base[tj] = sp.cstart[j + 1] - n + t0 + r0;  // entry (t0 + r0, j)
+#pragma unroll
+        for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[ti][tj][r] = E[base[tj] + 16 * ti + 4 * r];
+    }
+    const uint2 *g = (const uint2 *)sp.ga + lane;
+#pragma unroll 1
+    for (int s0 = 0; s0 < steps; s0 += 8) {
+        uint2 gi[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            if (s0 == 0)
+                gi[s] = g0[s];
+            else if (s0 + s < steps)
+                gi[s] = g[(s0 + s) * WAVE];
+        }
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            if (s0 + s >= steps) break;
+            const double a0 = entry<1>(E, gi[s].x & 0xffff), a1 = entry<1>(E, gi[s].x >> 16);
+            const double b0 = entry<1>(E, gi[s].y & 0xffff), b1 = entry<1>(E, gi[s].y >> 16);
+            acc[0][0] = tile_sub(a0, b0, acc[0][0]);
+            acc[0][1] = tile_sub(a0, b1, acc[0][1]);
+            acc[1][0] = tile_sub(a1, b0, acc[1][0]);
+            acc[1][1] = tile_sub(a1, b1, acc[1][1]);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+        for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (t0 + 16 * tj + c < n && t0 + 16 * ti + 4 * r + r0 < n) E[base[tj] + 16 * ti + 4 * r] = acc[ti][tj][r];
+    __syncthreads();
+}
+
+// The same for a block of any width: A22 -= L21 U12 over the block [t0, n)
+// with the pivots [k0, k1), operands A(tile, step) and B(tile, step) through
+// functors; 16 steps of four pivots at a time, one column of tiles at a time.
+template <class FA, class FB>
+__device__ __forceinline__ void lu_schur_wide(const DevSparse &sp, double *E, int lane, int t0, int steps, FA fa,
+                                              FB fb)
+{
+    const int n = sp.n, tiles = (n - t0 + 15) / 16;
+    const int c = lane & 15, r0 = lane >> 4;
+#pragma unroll 1
+    for (int s0 = 0; s0 < steps; s0 += 16) {
+#pragma unroll 1
+        for (int tj = 0; tj < tiles; ++tj) {
+            const int j = t0 + 16 * tj + c;
+            const int base = sp.cstart[min(j, n - 1) + 1] - n + t0 + r0;
+            double b[16];
+            fb(tj, s0, b);
+#pragma unroll 1
+            for (int ti = 0; ti < tiles; ++ti) {
+                double a[16];
+                fa(ti, s0, a);
+                double *e = E + base + 16 * ti;
+                const int i = t0 + 16 * ti + r0;
+                d4 acc;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[r] = i + 4 * r < n ? e[4 * r] : 0.0;
+#pragma unroll
+                for (int s = 0; s < 16; ++s) {
+                    if (s0 + s >= steps) break;
+                    acc = tile_sub(a[s], b[s], acc);
+                }
+                if (j < n) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (i + 4 * r < n) e[4 * r] = acc[r];
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Row broadcasts of one pivot row are read four columns at a time, so that
+// the wait a vector instruction needs after a readlane is spent reading the
+// next ones.
+template <int W, int K>
+__device__ __forceinline__ void apply_pivot(double (&a)[W], double l)
+{
+    constexpr int J0 = K + 1;
+#pragma unroll
+    for (int j = J0; j < W; j += 4) {
+        double u[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            if (j + d < W) u[d] = rdlane(a[j + d], K);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            if (j + d < W) a[j + d] = fma(-l, u[d], a[j + d]);
+    }
 }
 
 // The dense trailing block [t0, n) (w = n - t0 <= W positions, full L+U
@@ -425,13 +746,11 @@ __device__ __forceinline__ void lu_update_items(double *E, const uint64_t (&it)[
 // Padding (rows and columns from w to W) holds zeros and takes part
 // unconditionally: the loops have fixed trip counts, the array stays in
 // registers.  L is stored scaled (l_ik = a_ik / a_kk), U and the diagonal
-// as computed.  The same operations as the level schedule would perform,
-// without its barriers and schedule loads (one level per pivot in a dense
-// block).
-template <int G, int W>
-__device__ __forceinline__ void lu_tail(const DevSparse &sp, double *E, int lane)
+// as computed.
+template <int W>
+__device__ __forceinline__ void lu_tail(const DevSparse &sp, double *E, int t0, int lane)
 {
-    const int n = sp.n, t0 = sp.tail0, w = n - t0;
+    const int n = sp.n, w = n - t0;
     const bool row = lane < w;
     const int back = n - t0 - lane;  // entry (t0 + lane, c) = cstart[c + 1] - back
     const int cend = row ? sp.cstart[t0 + lane + 1] : 0;  // lane j: end of column t0 + j
@@ -440,333 +759,337 @@ __device__ __forceinline__ void lu_tail(const DevSparse &sp, double *E, int lane
     // alive until the stores)
 #pragma unroll
     for (int j = 0; j < W; ++j) {
-        const int e = gbcast_i<G>(cend, j) - back;
+        const int e = __builtin_amdgcn_readlane(cend, j) - back;
         const bool ok = j < w && row;
         const double x = E[ok ? e : 0];
         a[j] = ok ? x : 0.0;
     }
-#pragma unroll
-    for (int k = 0; k < W - 1; ++k) {
-        const double akk = gbcast<G>(a[k], k);
+    unrolled<W - 1>([&](auto K) __attribute__((always_inline)) {
+        constexpr int k = K;
+        const double akk = rdlane(a[k], k);
         const bool sub = row && lane > k;  // a row below the pivot
         const double l = sub ? a[k] / akk : 0.0;
         a[k] = sub ? l : a[k];
-#pragma unroll
-        for (int j = k + 1; j < W; ++j) a[j] = fma(-l, gbcast<G>(a[j], k), a[j]);
-    }
+        apply_pivot<W, k>(a, l);
+    });
 #pragma unroll
     for (int j = 0; j < W; ++j) {
-        const int e = gbcast_i<G>(cend, j) - back;
+        const int e = __builtin_amdgcn_readlane(cend, j) - back;
         if (j < w && row) E[e] = a[j];
     }
 }
 
-// Numeric LU of the formed matrix in E: the static level schedule of the
-// pivots before the dense tail, the tail in registers, then dinv = 1/u_kk
-// and the rows of U scaled to a unit diagonal.
-template <int VPL, int G>
-__device__ void lu_v(const DevSparse &sp, double *lds, int lane)
+// A panel of P <= 16 pivots [t, t + P) of a dense trailing block wider than
+// the 64 rows of the register tail: the panel's columns for all rows of the
+// block in registers (two rows per lane), then the panel's rows of U column
+// per lane, then the rest of the block on the matrix cores.
+__device__ __forceinline__ void lu_panel(const DevSparse &sp, double *E, int t, int P, int lane)
 {
-    double *E = lds + sp.E;
-    double *DINV = lds + sp.DINV;
-    Pre pre = preload<G>(sp.lu_b, sp.lu_b_lvl[0], sp.lu_b_lvl[1], lane);
-#pragma unroll 1
-    for (int l = 0; l < sp.nl_lu; ++l) {
-        const int b0 = sp.lu_b_lvl[l], b1 = sp.lu_b_lvl[l + 1];
-        const int c0 = sp.lu_c_lvl[l], c1 = sp.lu_c_lvl[l + 1];
-        Pre cur = pre;
-        pre = preload<G>(sp.lu_c, c0, c1, lane);
-        lu_scale_items(E, cur.it);
-#pragma unroll 1
-        for (int base = b0 + 4 * G; base < b1; base += 4 * G)
-            lu_scale_items(E, preload<G>(sp.lu_b, base, b1, lane).it);
-        __syncthreads();
-        cur = pre;
-        if (l + 1 < sp.nl_lu) pre = preload<G>(sp.lu_b, b1, sp.lu_b_lvl[l + 2], lane);
-        if (c1 > c0) {
-            lu_update_items(E, cur.it);
-#pragma unroll 1
-            for (int base = c0 + 4 * G; base < c1; base += 4 * G)
-                lu_update_items(E, preload<G>(sp.lu_c, base, c1, lane).it);
-            __syncthreads();
+    constexpr int W = 16;
+    const int n = sp.n, w = n - t;
+    double a[2][W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+        const int cend = sp.cstart[min(t + k, n - 1) + 1];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int i = lane + 64 * s;
+            a[s][k] = k < P && i < w ? E[cend - w + i] : 0.0;
         }
     }
-    // the tail width the kernel holds: one slot per lane (n <= 64) or two
-    constexpr int W = VPL == 1 ? (G < sc::SPARSE_TAIL_MAX ? G : sc::SPARSE_TAIL_MAX) : sc::SPARSE_TAIL_MAX_WIDE;
-    lu_tail<G, W>(sp, E, lane);
-    __syncthreads();
-#pragma unroll 1
-    for (int k = lane; k < sp.n; k += G) DINV[k] = 1.0 / E[sp.diag[k]];
-    __syncthreads();
-#pragma unroll 2
-    for (int q = lane; q < sp.n_u; q += G) {
-        const uint32_t it = sp.lu_u[q];
-        E[it & 0xffff] *= DINV[it >> 16];
-    }
-    __syncthreads();
-}
-
-// Solve M x = b with the factors in E (b, x: VPL components per lane).
-// The vector is moved to position order and swept in registers, one column
-// of L (then of the unit-diagonal U) per iteration: the pivot value is
-// broadcast with readlane and every lane whose row holds an entry in that
-// column updates its component.  Entries are numbered column by column, so
-// a lane's entry in column k is the column's start plus the number of
-// entries in the rows above it: a count of the column's row mask below the
-// lane (mbcnt), with the mask and start read as wave-uniform values.  No
-// barrier and no per-lane index load inside the sweeps.
-template <int VPL, int G = WAVE>
-__device__ __forceinline__ double rd_pos(const double (&z)[VPL], int k)
-{
-    if (VPL == 1 || k < 64) return gbcast<G>(z[0], k);
-    return gbcast<G>(z[VPL - 1], k - 64);
-}
-
-// bits of m below this lane's position in its group (mbcnt for a whole wave)
-template <int G>
-__device__ __forceinline__ int below(uint64_t m, int lane)
-{
-    if constexpr (G == WAVE)
-        return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    else
-        return __builtin_popcountll(m & ((1ull << lane) - 1));
-}
-
-template <int G>
-__device__ __forceinline__ uint64_t gbcast64(uint64_t v, int k)
-{
-    const uint32_t lo = (uint32_t)gbcast_i<G>((int)(uint32_t)v, k);
-    const uint32_t hi = (uint32_t)gbcast_i<G>((int)(uint32_t)(v >> 32), k);
-    return (uint64_t)hi << 32 | lo;
-}
-
-// The columns' row masks and entry starts, held one column per lane
-// (column lane + 64 w in slot w), loaded once per solve.
-template <int VPL, int G = WAVE>
-struct ColMeta {
-    uint64_t m0[VPL], m1[VPL];
-    int start[VPL];
-};
-
-template <int VPL, int G = WAVE>
-__device__ __forceinline__ ColMeta<VPL, G> col_meta(const DevSparse &sp, int lane)
-{
-    ColMeta<VPL, G> c;
+    unrolled<W>([&](auto K) __attribute__((always_inline)) {
+        constexpr int k = K;
+        if (k < P) {
+            const double akk = rdlane(a[0][k], k);
+            const double l0 = lane > k ? a[0][k] / akk : 0.0, l1 = a[1][k] / akk;
+            if (lane > k) a[0][k] = l0;
+            a[1][k] = l1;
 #pragma unroll
-    for (int w = 0; w < VPL; ++w) {
-        const int k = lane + G * w;
-        const bool ok = k < sp.n;
-        c.m0[w] = ok ? sp.cmask[2 * k] : 0;
-        c.m1[w] = ok && VPL > 1 ? sp.cmask[2 * k + 1] : 0;
-        c.start[w] = ok ? sp.cstart[k] : 0;
-    }
-    return c;
-}
-
-// This lane's factor value in column k for each slot (0 where its row has
-// no entry there).  An absent entry's index still lies inside the LDS
-// allocation (at most the column's end), and the select keeps whatever it
-// holds out of the result.
-template <int VPL, int G = WAVE>
-__device__ __forceinline__ void col_values(const ColMeta<VPL, G> &c, const double *E, int k, int lane,
-                                           double (&val)[VPL])
-{
-    const int w = VPL == 1 ? 0 : k >> 6, kk = k & 63;
-    const uint64_t m0 = gbcast64<G>(c.m0[w], kk);
-    const int base = gbcast_i<G>(c.start[w], kk);
-    val[0] = (m0 >> lane) & 1 ? E[base + below<G>(m0, lane)] : 0.0;
-    if (VPL > 1) {
-        const uint64_t m1 = gbcast64<G>(c.m1[w], kk);
-        val[VPL - 1] = (m1 >> lane) & 1 ? E[base + __builtin_popcountll(m0) + below<G>(m1, lane)] : 0.0;
-    }
-}
-
-// Column sweeps of a system of at most 64 positions (one slot per lane).
-// Lane k of each cell's group holds, for column k, the mask of the rows
-// below (forward) and above (backward) the diagonal that hold an entry and
-// the first of those entries; a sweep broadcasts them per column
-// (readlane, or a group shuffle), and a lane's entry is that start plus the
-// mask's bits below the lane.  The LDS read is unconditional (the index
-// never leaves the column's entries) and the lanes without an entry are
-// zeroed by a select on the mask; the select is applied one column later,
-// so the read of column k + 1 overlaps the update with column k.  No
-// branch, no barrier.
-// v where the lane's bit of the lane mask m is set, else 0 (one
-// v_cndmask per half with the mask as the lane condition)
-__device__ __forceinline__ double keep_lanes(uint64_t m, double v)
-{
-    const int lo = __double2loint(v), hi = __double2hiint(v);
-    int rlo, rhi;
-    asm("v_cndmask_b32 %0, 0, %1, %2" : "=v"(rlo) : "v"(lo), "s"(m));
-    asm("v_cndmask_b32 %0, 0, %1, %2" : "=v"(rhi) : "v"(hi), "s"(m));
-    return __hiloint2double(rhi, rlo);
-}
-
-struct SweepCol {
-    uint64_t msk;  // rows of the column holding an entry
-    double raw;    // the LDS word read for this lane (meaningless off the mask)
-};
-
-template <int G>
-__device__ __forceinline__ SweepCol sweep_col(int mlo, int mhi, int start, const double *E, int k, int lane)
-{
-    const uint64_t msk = (uint64_t)(uint32_t)gbcast_i<G>(mhi, k) << 32 | (uint32_t)gbcast_i<G>(mlo, k);
-    const int e = gbcast_i<G>(start, k) + below<G>(msk, lane);
-    return SweepCol{msk, E[e]};
-}
-
-// the column's value for this lane: with one cell per wave the mask is
-// wave-uniform and selects lanes directly; with several cells per wave it
-// differs per group and is tested per lane
-template <int G>
-__device__ __forceinline__ double sweep_value(const SweepCol &c, int lane)
-{
-    if constexpr (G == WAVE)
-        return keep_lanes(c.msk, c.raw);
-    else
-        return (c.msk >> lane) & 1 ? c.raw : 0.0;
-}
-
-// With several cells per wave a broadcast is a group shuffle (an LDS-path
-// permute) rather than a readlane, and the three per-column broadcasts of
-// mask and start cost more than a table: there each lane reads its entry
-// in column k from a per-column row table (the zero slot where it has
-// none), four columns ahead, and only the pivot value is broadcast.
-template <int G>
-__device__ __forceinline__ void sweeps_table(const DevSparse &sp, const double *E, const double *DINV, int n,
-                                             int lane, double &z)
-{
-    const int nc = n - 1, zero = sp.nnz;
-#pragma unroll
-    for (int dir = 0; dir < 2; ++dir) {
-        // forward: columns 0 .. n-2 (rows below); backward: n-1 .. 1 (rows above)
-        const uint16_t *ti = (dir == 0 ? sp.swfi : sp.swbi) + lane;
-        auto col = [&](int s) { return dir == 0 ? s : nc - s; };
-        int q[4];
-#pragma unroll
-        for (int d = 0; d < 4; ++d) q[d] = d < nc ? (int)ti[64 * col(d)] : zero;
-        double v = E[q[0]];
-        int s = 0;
-#pragma unroll 1
-        for (; s + 4 <= nc; s += 4) {
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const int c = s + d;
-                const double vn = c + 1 < nc ? E[q[(d + 1) & 3]] : 0.0;
-                q[d] = c + 4 < nc ? (int)ti[64 * col(c + 4)] : zero;
-                z = fma(-v, gbcast<G>(z, col(c)), z);
-                v = vn;
+            for (int j = k + 1; j < W; ++j) {
+                const double u = rdlane(a[0][j], k);
+                a[0][j] = fma(-l0, u, a[0][j]);
+                a[1][j] = fma(-l1, u, a[1][j]);
             }
         }
-#pragma unroll 1
-        for (; s < nc; ++s) {
-            const double vn = s + 1 < nc ? E[(int)ti[64 * col(s + 1)]] : 0.0;
-            z = fma(-v, gbcast<G>(z, col(s)), z);
-            v = vn;
-        }
-        if (dir == 0 && lane < n) z *= DINV[lane];
-    }
-}
-
-template <int G>
-__device__ __forceinline__ void sweeps_1(const DevSparse &sp, const double *E, const double *DINV, int n, int lane,
-                                         double &z)
-{
-    if constexpr (G < WAVE) {
-        sweeps_table<G>(sp, E, DINV, n, lane, z);
-        return;
-    }
-    const bool live = lane < n;
-    const uint32_t *f = sp.swf + 4 * (live ? lane : 0), *b = sp.swb + 4 * (live ? lane : 0);
-    const int flo = live ? (int)f[0] : 0, fhi = live ? (int)f[1] : 0, fst = live ? (int)f[2] : 0;
-    const int blo = live ? (int)b[0] : 0, bhi = live ? (int)b[1] : 0, bst = live ? (int)b[2] : 0;
-    // forward with the unit-diagonal L, k ascending
-    SweepCol nxt = sweep_col<G>(flo, fhi, fst, E, 0, lane);
-    for (int k = 0; k < n - 1; ++k) {
-        const SweepCol cur = nxt;
-        if (k + 1 < n - 1) nxt = sweep_col<G>(flo, fhi, fst, E, k + 1, lane);
-        z = fma(-sweep_value<G>(cur, lane), gbcast<G>(z, k), z);
-    }
-    if (live) z *= DINV[lane];
-    // backward with the unit-diagonal U, k descending
-    nxt = sweep_col<G>(blo, bhi, bst, E, n - 1, lane);
-    for (int k = n - 1; k > 0; --k) {
-        const SweepCol cur = nxt;
-        if (k > 1) nxt = sweep_col<G>(blo, bhi, bst, E, k - 1, lane);
-        z = fma(-sweep_value<G>(cur, lane), gbcast<G>(z, k), z);
-    }
-}
-
-template <int VPL, int G = WAVE>
-__device__ void solve_v(const DevMech &m, const DevSparse &sp, double *lds, const double (&b)[VPL], int lane,
-                        double (&x)[VPL])
-{
-    const int N = m.N, n = sp.n;
-    const double *E = lds + sp.E;
-    double *X = lds + sp.X;
-    const double *DINV = lds + sp.DINV;
-    const ColMeta<VPL, G> cm = col_meta<VPL, G>(sp, lane);
+    });
 #pragma unroll
-    for (int v = 0; v < VPL; ++v) {
-        const int c = lane + G * v;
-        if (c < N) X[sp.comp[CMP * c]] = b[v] * m.invW()[c];
-        if (c == N) X[sp.comp[CMP * N]] = b[v];
+    for (int k = 0; k < W; ++k) {
+        const int cend = sp.cstart[min(t + k, n - 1) + 1];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int i = lane + 64 * s;
+            if (k < P && i < w) E[cend - w + i] = a[s][k];
+        }
     }
-    if (lane == 0) X[n - 1] = 0.0;  // sigma row
+    // rows t .. t + P - 1 of the columns beyond the panel: U12 = L11^-1 A12,
+    // L11 broadcast from the lanes that hold it
+#pragma unroll 1
+    for (int j0 = t + P; j0 < n; j0 += WAVE) {
+        const int j = j0 + lane;
+        double *e = E + sp.cstart[min(j, n - 1) + 1] - w;  // entry (t, j)
+        double u[W];
+#pragma unroll
+        for (int k = 0; k < W; ++k) u[k] = k < P && j < n ? e[k] : 0.0;
+        unrolled<W>([&](auto K) __attribute__((always_inline)) {
+            constexpr int k = K;
+            if (k < P) {
+#pragma unroll
+                for (int m = k + 1; m < W; ++m) u[m] = fma(-rdlane(a[0][k], m), u[k], u[m]);
+            }
+        });
+#pragma unroll
+        for (int k = 0; k < W; ++k)
+            if (k < P && j < n) e[k] = u[k];
+    }
     __syncthreads();
+    const int t1 = t + P;
+    const int c = lane & 15, kk = lane >> 4;
+    lu_schur_wide(
+        sp, E, lane, t1, (P + 3) / 4,
+        [&](int ti, int, double (&v)[16]) {
+            const int i = t1 + 16 * ti + c;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int k = 4 * s + kk;
+                v[s] = k < P && i < n ? E[sp.cstart[t + k + 1] - n + i] : 0.0;
+            }
+        },
+        [&](int tj, int, double (&v)[16]) {
+            const int j = t1 + 16 * tj + c;
+            const double *e = E + sp.cstart[min(j, n - 1) + 1] - w;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int k = 4 * s + kk;
+                v[s] = k < P && j < n ? e[k] : 0.0;
+            }
+        });
+}
+
+// Numeric LU of the formed matrix in E, then dinv = 1/u_kk and the rows of U
+// scaled to a unit diagonal.
+template <int VPL, int G>
+__device__ void lu_v(const DevSparse &sp, double *lds, int lane, Factors<VPL, G> &fac)
+{
+    double *E = lds + sp.E;
+    if constexpr (G < WAVE) {
+        lu_group<G>(sp, E, lane, fac);
+        __syncthreads();
+        return;
+    } else {
+        double *DINV = lds + sp.DINV;
+        if constexpr (VPL == 1) {
+            // the Schur operands' indices, on their way during the levels
+            uint2 g0[8];
+            const uint2 *g = (const uint2 *)sp.ga + lane;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) g0[s] = 4 * s < sp.dense0 ? g[s * WAVE] : make_uint2(0, 0);
+            lu_levels(sp, E, lane);
+            lu_schur(sp, E, lane, g0);
+            lu_tail<sc::SPARSE_TAIL_MAX>(sp, E, sp.dense0, lane);
+        } else {
+            lu_levels(sp, E, lane);
+            const int t0 = sp.dense0, steps = (t0 + 3) / 4, pad = (steps + 15) / 16 * 16;
+            auto load = [&](const uint16_t *tab, int tile, int s0, double (&v)[16]) {
+                const uint32_t *q = (const uint32_t *)(tab + ((size_t)tile * WAVE + lane) * pad + s0);
+#pragma unroll
+                for (int s = 0; s < 16; s += 2) {
+                    const uint32_t w = q[s / 2];
+                    v[s] = E[w & 0xffff];
+                    v[s + 1] = E[w >> 16];
+                }
+            };
+            lu_schur_wide(
+                sp, E, lane, t0, steps, [&](int ti, int s0, double (&v)[16]) { load(sp.ga, ti, s0, v); },
+                [&](int tj, int s0, double (&v)[16]) { load(sp.gb, tj, s0, v); });
+            int t = t0;
+#pragma unroll 1
+            while (sp.n - t > sc::SPARSE_TAIL_MAX_WIDE) {
+                const int P = min(16, sp.n - t - sc::SPARSE_TAIL_MAX_WIDE);
+                lu_panel(sp, E, t, P, lane);
+                t += P;
+            }
+            lu_tail<sc::SPARSE_TAIL_MAX_WIDE>(sp, E, t, lane);
+        }
+        // the scaling's items, loaded while the diagonal is inverted
+        constexpr int UI = VPL == 1 ? 8 : 16;
+        uint32_t it[UI];
+#pragma unroll
+        for (int u = 0; u < UI; ++u) it[u] = u * WAVE + lane < sp.n_u ? sp.lu_u[u * WAVE + lane] : 0u;
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < VPL; ++v) {
+            const int k = lane + WAVE * v;
+            if (k < sp.n) DINV[k] = 1.0 / E[sp.diag[k]];
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int q = 0; q < sp.n_u; q += UI * WAVE) {
+            if (q > 0) {
+#pragma unroll
+                for (int u = 0; u < UI; ++u)
+                    it[u] = q + u * WAVE + lane < sp.n_u ? sp.lu_u[q + u * WAVE + lane] : 0u;
+            }
+            double x[UI];
+#pragma unroll
+            for (int u = 0; u < UI; ++u) x[u] = E[it[u] & 0xffff] * DINV[it[u] >> 16];
+#pragma unroll
+            for (int u = 0; u < UI; ++u)
+                if (q + u * WAVE + lane < sp.n_u) E[it[u] & 0xffff] = x[u];
+        }
+        __syncthreads();
+    }
+}
+
+// Solve M x = b with the factors (b, x: VPL components per lane; a lane holds
+// the same position as component and as row).  The vector is swept in
+// registers, one column of L (then of the unit-diagonal U) at a time: the
+// pivot value is broadcast with readlane and the lanes behind it apply their
+// entry of the column.
+//
+// The chain of 2 n broadcasts and multiply-adds bounds a solve, so nothing
+// else is on it: each lane's entries come eight columns at a time from LDS
+// through a table of its row, ahead of their use, and the lanes are masked by
+// the execution mask.  With each entry's place computed from the column's
+// mask at its turn a column took 189 cycles of a lone wave (53 species).
+__device__ __forceinline__ void sweeps(const DevSparse &sp, const double *E, const double *DINV, int lane,
+                                       double (&z)[1])
+{
+    const int n = sp.n;
+    const uint64_t all = exec_mask();
+    uint4 ix[8];  // byte offsets of the row's entries, 64 columns
+    const uint4 *t = (const uint4 *)(sp.row + 64 * lane);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) ix[b] = t[b];
+    const double dinv = lane < n ? DINV[lane] : 0.0;
+    auto load = [&](const uint4 &w, double (&v)[8]) {
+        v[0] = entry<1>(E, w.x & 0xffff);
+        v[1] = entry<1>(E, w.x >> 16);
+        v[2] = entry<1>(E, w.y & 0xffff);
+        v[3] = entry<1>(E, w.y >> 16);
+        v[4] = entry<1>(E, w.z & 0xffff);
+        v[5] = entry<1>(E, w.z >> 16);
+        v[6] = entry<1>(E, w.w & 0xffff);
+        v[7] = entry<1>(E, w.w >> 16);
+    };
+    double cur[8], nxt[8];
+    load(ix[0], cur);
+    unrolled<8>([&](auto B) __attribute__((always_inline)) {
+        constexpr int b = B;
+        if (8 * b < n) {
+            if constexpr (b < 7) load(ix[b + 1], nxt);
+            unrolled<8>([&](auto D) __attribute__((always_inline)) {
+                constexpr int k = 8 * b + D;
+                if constexpr (k < 63) fma_above<k>(z[0], cur[D], rdlane(z[0], k), all);
+            });
+#pragma unroll
+            for (int d = 0; d < 8; ++d) cur[d] = nxt[d];
+        }
+    });
+    z[0] *= dinv;
+    unrolled<8>([&](auto B) __attribute__((always_inline)) {
+        constexpr int b = 7 - B;
+        if (8 * b < n) {
+            // the block a column at n - 1 lies in is the first one read
+            if (8 * b + 8 >= n) load(ix[b], cur);
+            if constexpr (b > 0) load(ix[b - 1], nxt);
+            unrolled<8>([&](auto D) __attribute__((always_inline)) {
+                constexpr int k = 8 * b + 7 - D;
+                if constexpr (k > 0) fma_below<k>(z[0], cur[7 - D], rdlane(z[0], k), all);
+            });
+#pragma unroll
+            for (int d = 0; d < 8; ++d) cur[d] = nxt[d];
+        }
+    });
+}
+
+// Two rows per lane: columns in blocks of eight, their table entries loaded
+// two blocks and their values one block ahead.
+__device__ __forceinline__ void sweeps(const DevSparse &sp, const double *E, const double *DINV, int lane,
+                                       double (&z)[2])
+{
+    const int n = sp.n, nb = (n + 7) / 8;
+    const uint64_t all = exec_mask();
+    const uint4 *t0 = (const uint4 *)(sp.row + 128 * lane), *t1 = t0 + 64 * 16;
+    struct Blk {
+        double a[2][8];
+    };
+    struct Ix {
+        uint4 w[2];
+    };
+    auto index = [&](int b) { return Ix{{t0[b], t1[b]}}; };
+    auto load = [&](const Ix &x) {
+        Blk v;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const uint32_t w[4] = {x.w[s].x, x.w[s].y, x.w[s].z, x.w[s].w};
+#pragma unroll
+            for (int d = 0; d < 8; ++d) v.a[s][d] = E[d % 2 ? w[d / 2] >> 16 : w[d / 2] & 0xffff];
+        }
+        return v;
+    };
+    const double d0 = DINV[lane], d1 = lane + 64 < n ? DINV[lane + 64] : 0.0;
+    // blocks 0 .. nb - 1 forward, then nb - 1 .. 0 backward, one pipeline
+    auto blk = [&](int q) { return min(q < nb ? q : 2 * nb - 1 - q, nb - 1); };
+    Ix ix = index(blk(1));
+    Blk nxt = load(index(0));
+#pragma unroll 1
+    for (int q = 0; q < 2 * nb; ++q) {
+        const Blk cur = nxt;
+        nxt = load(ix);
+        ix = index(max(blk(q + 2), 0));
+        const int k0 = __builtin_amdgcn_readfirstlane(8 * blk(q));
+        if (q == nb) {
+            z[0] *= d0;
+            z[1] *= d1;
+        }
+        if (q < nb) {
+            if (k0 < 64) {
+#pragma unroll
+                for (int d = 0; d < 8; ++d) {
+                    const double zk = rdlane(z[0], k0 + d);
+                    z[1] = fma(-cur.a[1][d], zk, z[1]);
+                    fma_above(z[0], cur.a[0][d], zk, k0 + d, all);
+                }
+            } else {
+#pragma unroll
+                for (int d = 0; d < 8; ++d)
+                    fma_above(z[1], cur.a[1][d], rdlane(z[1], k0 + d - 64), k0 + d - 64, all);
+            }
+        } else if (k0 >= 64) {
+#pragma unroll
+            for (int d = 7; d >= 0; --d) {
+                const double zk = rdlane(z[1], k0 + d - 64);
+                z[0] = fma(-cur.a[0][d], zk, z[0]);
+                fma_below(z[1], cur.a[1][d], zk, k0 + d - 64, all);
+            }
+        } else {
+#pragma unroll
+            for (int d = 7; d >= 0; --d) fma_below(z[0], cur.a[0][d], rdlane(z[0], k0 + d), k0 + d, all);
+        }
+    }
+}
+
+template <int VPL, int G>
+__device__ void solve_v(const DevMech &m, const DevSparse &sp, double *lds, const Factors<VPL, G> &fac,
+                        const double (&b)[VPL], int lane, double (&x)[VPL])
+{
+    const int N = m.N;
+    // scaled unknowns z_k = x_k / W_k; the sigma row's right-hand side is zero
     double z[VPL];
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
-        const int q = lane + G * v;
-        z[v] = q < n ? X[q] : 0.0;
+        const int c = lane + G * v;
+        z[v] = c < N ? b[v] * m.invW()[c] : c == N ? b[v] : 0.0;
     }
-    if constexpr (VPL == 1) {
-        sweeps_1<G>(sp, E, DINV, n, lane, z[0]);
-    } else {
-    // forward: x_i -= l_ik x_k, k ascending, rows below the diagonal (the
-    // next column's values are read while this one is applied)
-    double nxt[VPL], cur[VPL];
-    col_values<VPL, G>(cm, E, 0, lane, nxt);
-    for (int k = 0; k < n - 1; ++k) {
-#pragma unroll
-        for (int v = 0; v < VPL; ++v) cur[v] = nxt[v];
-        if (k + 1 < n - 1) col_values<VPL, G>(cm, E, k + 1, lane, nxt);
-        const double zk = rd_pos<VPL, G>(z, k);
-#pragma unroll
-        for (int v = 0; v < VPL; ++v)
-            if (lane + G * v > k) z[v] = fma(-cur[v], zk, z[v]);
-    }
-#pragma unroll
-    for (int v = 0; v < VPL; ++v) {
-        const int q = lane + G * v;
-        if (q < n) z[v] *= DINV[q];
-    }
-    // backward with the unit-diagonal U: x_i -= u'_ik x_k, k descending,
-    // rows above the diagonal
-    col_values<VPL, G>(cm, E, n - 1, lane, nxt);
-    for (int k = n - 1; k > 0; --k) {
-#pragma unroll
-        for (int v = 0; v < VPL; ++v) cur[v] = nxt[v];
-        if (k > 1) col_values<VPL, G>(cm, E, k - 1, lane, nxt);
-        const double zk = rd_pos<VPL, G>(z, k);
-#pragma unroll
-        for (int v = 0; v < VPL; ++v)
-            if (lane + G * v < k) z[v] = fma(-cur[v], zk, z[v]);
-    }
-    }
-    __syncthreads();  // every lane has read X
-#pragma unroll
-    for (int v = 0; v < VPL; ++v) {
-        const int q = lane + G * v;
-        if (q < n) X[q] = z[v];
-    }
-    __syncthreads();
+    if constexpr (G < WAVE)
+        sweeps_group<G>(sp, fac, lane, z[0]);
+    else
+        sweeps(sp, lds + sp.E, lds + sp.DINV, lane, z);
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int c = lane + G * v;
-        x[v] = c < N ? X[sp.comp[CMP * c]] * m.W()[c] : c == N ? X[sp.comp[CMP * N]] : 0.0;
+        x[v] = c < N ? z[v] * m.W()[c] : c == N ? z[v] : 0.0;
     }
-    __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
@@ -782,7 +1105,8 @@ __device__ void ros_attempt_v(const DevMech &m, const DevSparse &sp, const Opts 
     const int NV = sp.NV;
     double f0[VPL], flast[VPL];
     jac_v<VPL, G>(m, sp, lds, y, p, dlnA, lane, 1.0 / (GAM * hc), f0);
-    lu_v<VPL, G>(sp, lds, lane);
+    Factors<VPL, G> fac;
+    lu_v<VPL, G>(sp, lds, lane, fac);
     const double ih = 1.0 / hc;
 #pragma unroll
     for (int v = 0; v < VPL; ++v) flast[v] = f0[v];
@@ -813,7 +1137,7 @@ __device__ void ros_attempt_v(const DevMech &m, const DevSparse &sp, const Opts 
             for (int j = 0; j < i; ++j) fi[v] += (TC[i][j] * ih) * U[j * NV + lane + G * v];
             if (lane + G * v >= n) fi[v] = 0.0;
         }
-        solve_v<VPL, G>(m, sp, lds, fi, lane, ui);
+        solve_v<VPL, G>(m, sp, lds, fac, fi, lane, ui);
 #pragma unroll
         for (int v = 0; v < VPL; ++v) U[i * NV + lane + G * v] = ui[v];
     }
@@ -880,7 +1204,7 @@ __device__ __forceinline__ void integrate_cell_v(const DevMech &m, const DevSpar
     // a cell mapped onto another cell's result is left to the mapping pass
     if (ref && ref[c] != c) return;
     double y[VPL];
-    load_state_v<VPL, G>(m, T0, Y0, ld, c, lane, y);
+    load_state_v<VPL, G>(m, sp, T0, Y0, ld, c, lane, y);
     const double p = P[c], dt = DT[c];
     int st = SC_CELL_OK;
     Ctl s = ctl_init(initial_step(h_io, c, dt), dt);
@@ -889,7 +1213,7 @@ __device__ __forceinline__ void integrate_cell_v(const DevMech &m, const DevSpar
     } else if (dt > 0.0) {
         st = advance_v<VPL, G>(m, sp, o, lds, y, p, dt, dlnA, lane, s);
     }
-    store_state_v<VPL, G>(m, T1, Y1, ld, c, lane, y);
+    store_state_v<VPL, G>(m, sp, T1, Y1, ld, c, lane, y);
     if (lane == 0) {
         status[c] = st;
         if (nacc_out) nacc_out[c] = s.nacc;
@@ -999,9 +1323,9 @@ __global__ void __launch_bounds__(WAVE) k_rhs_sp(DevMech mk, DevSparse spk, int6
     const int64_t c = (int64_t)blockIdx.x * CPW + grp;
     if (c >= n) return;
     double y[VPL], f[VPL];
-    load_state_v<VPL, G>(m, T, Y, ld, c, lane, y);
+    load_state_v<VPL, G>(m, sp, T, Y, ld, c, lane, y);
     rhs_v<VPL, G>(m, sp, ldsg, y, P[c], dlnA, lane, f);
-    store_state_v<VPL, G>(m, fT, fY, ld, c, lane, f);
+    store_state_v<VPL, G>(m, sp, fT, fY, ld, c, lane, f);
 }
 
 // The Jacobian J (dense output, [c][i][j] over (Y, T)) recovered from the
@@ -1021,7 +1345,7 @@ __global__ void __launch_bounds__(WAVE) k_jac_sp(DevMech mk, DevSparse spk, int6
     const int64_t c = (int64_t)blockIdx.x * CPW + grp;
     if (c >= n) return;
     double y[VPL], f[VPL];
-    load_state_v<VPL, G>(m, T, Y, ld, c, lane, y);
+    load_state_v<VPL, G>(m, sp, T, Y, ld, c, lane, y);
     jac_v<VPL, G>(m, sp, ldsg, y, P[c], dlnA, lane, 0.0, f);
     const double *E = ldsg + sp.E;
     const int N = m.N, nn = N + 1, ns = sp.n;
@@ -1033,11 +1357,11 @@ __global__ void __launch_bounds__(WAVE) k_jac_sp(DevMech mk, DevSparse spk, int6
 #pragma unroll 1
     for (int q = lane; q < nn * nn; q += G) {
         const int i = q / nn, j = q % nn;
-        const int pi = sp.comp[CMP * i], pj = sp.comp[CMP * j];  // comp[CMP * N] is pos_T
+        const int pi = sp.pos[i], pj = sp.pos[j];
         double val;
-        if (i < N && j < N) val = -(m.W()[i] * m.invW()[j]) * (A(pi, pj) + A(pi, pS) * A(pS, pj));
-        else if (i < N) val = -m.W()[i] * A(pi, pj);
-        else if (j < N) val = -A(pi, pj) * m.invW()[j];
+        if (i < N && j < N) val = -(m.W()[pi] * m.invW()[pj]) * (A(pi, pj) + A(pi, pS) * A(pS, pj));
+        else if (i < N) val = -m.W()[pi] * A(pi, pj);
+        else if (j < N) val = -A(pi, pj) * m.invW()[pj];
         else val = -A(pi, pj);
         J[(c * nn + i) * nn + j] = val;
     }
@@ -1056,20 +1380,21 @@ __global__ void __launch_bounds__(WAVE) k_linsolve_sp(DevMech mk, DevSparse spk,
     const int64_t c = (int64_t)blockIdx.x * CPW + grp;
     if (c >= n) return;
     double y[VPL], f[VPL], bb[VPL], xx[VPL];
-    load_state_v<VPL, G>(m, T, Y, ld, c, lane, y);
+    load_state_v<VPL, G>(m, sp, T, Y, ld, c, lane, y);
     jac_v<VPL, G>(m, sp, ldsg, y, P[c], dlnA, lane, 1.0 / hg[c], f);
-    lu_v<VPL, G>(sp, ldsg, lane);
+    Factors<VPL, G> fac;
+    lu_v<VPL, G>(sp, ldsg, lane, fac);
     const int nn = m.N + 1;
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int i = lane + G * v;
-        bb[v] = i < nn ? b[c * nn + i] : 0.0;
+        bb[v] = i < nn ? b[c * nn + sp.perm[i]] : 0.0;
     }
-    solve_v<VPL, G>(m, sp, ldsg, bb, lane, xx);
+    solve_v<VPL, G>(m, sp, ldsg, fac, bb, lane, xx);
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int i = lane + G * v;
-        if (i < nn) x[c * nn + i] = xx[v];
+        if (i < nn) x[c * nn + sp.perm[i]] = xx[v];
     }
 }
 

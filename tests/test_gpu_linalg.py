@@ -1,0 +1,54 @@
+"""The sparse kernels' factorisation and solves at the edges of their parts:
+rows in registers (two and four cells per wave), the dense Schur product with
+one, several and partly filled steps of four pivots and tiles of 16, the
+32-wide register tail, and blocks wider than the 64-row tail (one panel and
+several).  The solution of (I/hg - J) x = b is checked against the matrix
+from the oracle's complex-step Jacobian by its normwise backward error.  An
+unpivoted LU of a matrix whose diagonal dominates (small hg) has growth near
+one, so the bound is the usual n eps with a margin of about ten for the
+Jacobian's own rounding: 1e-12 holds up to n = 128."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# species, reactions, pool fraction, seed, cells per wave: positions N + 2,
+# first position of the dense block and its width
+MECHS = {
+    "4 cells, n = 16": (14, 56, 0.15, 401, 4),
+    "2 cells, n = 32": (30, 150, 0.3, 402, 2),
+    "1 cell, n = 26, dense from 5": (24, 120, 0.5, 400, 1),
+    "n = 57, dense from 30 (27 wide)": (55, 330, 0.15, 400, 1),
+    "n = 64, dense from 32, 24 levels": (62, 900, 0.6, 1, 1),
+    "n = 65, dense from 30 (35 wide)": (63, 400, 0.15, 400, 1),
+    "n = 112, dense from 38: one panel": (110, 700, 0.15, 110, 1),
+    "n = 128, dense from 27: three panels": (126, 2500, 0.5, 4, 1),
+}
+
+
+@pytest.mark.parametrize("key", list(MECHS))
+def test_linsolve_backward_error(key):
+    import torch
+
+    import paper_2311_14941_amd as sc
+    from oracle.oracle import Oracle
+    from synth.mechgen import make_mechanism
+    sc.ensure_built()
+    ns, nr, pf, seed, cpw = MECHS[key]
+    mech = make_mechanism(ns, nr, nr // 10, nr // 20, ["C", "H", "O", "N"], seed=seed, pool_frac=pf)
+    o = Oracle(mech.to_text())
+    plan = sc.Plan(sc.Mechanism(mech.to_text()), linalg="sparse", cells_per_wave=cpw)
+    rng = np.random.default_rng(ns)
+    nc = 7
+    T, p = rng.uniform(1000.0, 2000.0, nc), 101325.0 * rng.uniform(1.0, 5.0, nc)
+    Y = rng.dirichlet(np.ones(ns), nc)
+    b = rng.normal(size=(nc, ns + 1))
+    J = [o.jac_cs(np.append(Y[c], T[c]), p[c]) for c in range(nc)]
+    # every state's own scale: the diagonal exceeds its Jacobian's row sums
+    hg = np.array([0.25 / np.abs(j).sum(1).max() for j in J])
+    g = lambda a: torch.tensor(np.ascontiguousarray(a), device="cuda:0")
+    x = plan.linsolve(g(T), g(p), g(Y.T), g(hg), g(b)).cpu().numpy()
+    for c in range(nc):
+        M = np.eye(ns + 1) / hg[c] - J[c]
+        res = np.abs(M @ x[c] - b[c]).max() / (np.abs(M).max() * np.abs(x[c]).max() + np.abs(b[c]).max())
+        assert res < 1e-12, (key, c, res)
