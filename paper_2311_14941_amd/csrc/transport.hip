@@ -11,40 +11,65 @@
 // profile (Dirichlet), the other three are zero-gradient.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 namespace scdev {
 
-// one thread per (cell, component); components are species-major rows of
-// ld values (the library's state layout), cells row-major c = iy*nx + ix
+// One thread per cell and group of KC components (species-major rows of ld
+// values, cells row-major c = iy*nx + ix).  Bound by memory: a row is read
+// once from HBM (its north, south, east and west reads hit the caches) and
+// written once.  The cell's place and its two coefficients, an integer and
+// two double divisions, are taken once per KC values; with one thread per
+// value, divided out of a 64-bit index, the arithmetic was the bound.
+constexpr int KC = 6;
 __global__ void __launch_bounds__(256) k_transport2d(int nx, int ny, int ncomp, const double *in, int64_t ld,
                                                      const double *u, const double *dt, double dx, double D,
                                                      const double *inflow, double *out)
 {
     const int64_t n = (int64_t)nx * ny;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n * ncomp) return;
-    const int k = (int)(t / n);
-    const int64_t c = t - (int64_t)k * n;
-    const int iy = (int)(c / nx), ix = (int)(c - (int64_t)iy * nx);
-    const double *q = in + (int64_t)k * ld;
-    const double qc = q[c];
-    const double qw = ix > 0 ? q[c - 1] : inflow[(int64_t)k * ny + iy];
-    const double qe = ix < nx - 1 ? q[c + 1] : qc;
-    const double qs = iy > 0 ? q[c - nx] : qc;
-    const double qn = iy < ny - 1 ? q[c + nx] : qc;
+    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= n) return;
+    int iy, ix;
+    if (n <= INT32_MAX) {
+        iy = (int)((uint32_t)c / (uint32_t)nx);
+        ix = (int)((uint32_t)c - (uint32_t)iy * (uint32_t)nx);
+    } else {
+        iy = (int)(c / nx);
+        ix = (int)(c - (int64_t)iy * nx);
+    }
     const double co = u[c] * dt[c] / dx;
     const double fo = D * dt[c] / (dx * dx);
-    out[(int64_t)k * ld + c] = qc - co * (qc - qw) + fo * (qe + qw + qn + qs - 4.0 * qc);
+    const int64_t e = ix < nx - 1 ? 1 : 0, s = iy > 0 ? -nx : 0, nth = iy < ny - 1 ? nx : 0;
+    for (int64_t k0 = (int64_t)blockIdx.y * KC; k0 < ncomp; k0 += (int64_t)gridDim.y * KC) {
+        double v[KC][5];
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+            const int64_t kk = min(k0 + k, (int64_t)ncomp - 1);
+            const double *q = in + kk * ld + c;
+            const double *w = ix > 0 ? q - 1 : inflow + kk * ny + iy;
+            v[k][0] = q[0];
+            v[k][1] = *w;
+            v[k][2] = q[e];
+            v[k][3] = q[nth];
+            v[k][4] = q[s];
+        }
+#pragma unroll
+        for (int k = 0; k < KC; ++k)
+            if (k0 + k < ncomp)
+                out[(k0 + k) * ld + c] = v[k][0] - co * (v[k][0] - v[k][1]) +
+                                                  fo * (v[k][2] + v[k][1] + v[k][3] + v[k][4] - 4.0 * v[k][0]);
+    }
 }
 
 hipError_t launch_transport2d(int nx, int ny, int ncomp, const double *in, int64_t ld, const double *u,
                               const double *dt, double dx, double D, const double *inflow, double *out,
                               hipStream_t s)
 {
-    const int64_t total = (int64_t)nx * ny * ncomp;
-    const unsigned blocks = (unsigned)((total + 255) / 256);
-    hipLaunchKernelGGL(k_transport2d, dim3(blocks), dim3(256), 0, s, nx, ny, ncomp, in, ld, u, dt, dx, D, inflow,
+    const int64_t n = (int64_t)nx * ny;
+    const unsigned gx = (unsigned)((n + 255) / 256);
+    const unsigned gy = (unsigned)std::min<int64_t>((ncomp + (int64_t)KC - 1) / KC, 65535);
+    hipLaunchKernelGGL(k_transport2d, dim3(gx, gy), dim3(256), 0, s, nx, ny, ncomp, in, ld, u, dt, dx, D, inflow,
                        out);
     return hipGetLastError();
 }
