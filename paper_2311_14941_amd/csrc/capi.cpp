@@ -337,6 +337,7 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
     const int cpw = o.cells_per_wave ? o.cells_per_wave : cpw_max;
     scdev::DevSparse ds{};
     sc::SparseDev sd;
+    sc::SparseRx sx;
     if (sparse) {
         const int NV = 64 / cpw * vpl;
         ds.cpw = cpw;
@@ -344,27 +345,19 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
         ds.nnz = S.nnz;
         try {
             sd = sc::sparse_device(mech->m, 64 / cpw);
+            sx = sc::sparse_reactions(mech->m, 64 / cpw);
         } catch (...) {
             return fail(SC_ENOMEM, "host allocation failed");
         }
-        ds.nl = (int)sd.hb_lvl.size() - 2;
-        ds.n_u = (int)S.lu_u.size();
-        ds.dense0 = sd.dense0;
-        ds.NV = NV;
-        ds.E = 0;
-        ds.C = S.nnz + 1;  // E[nnz]: a slot kept at zero (the entry the operand tables give where there is none)
-        ds.G = ds.C + NV;
-        ds.H = ds.G + NV;
-        ds.WD = ds.H + NV;
-        ds.UA = ds.WD + NV;
-        ds.U = ds.UA + NV;
-        ds.DINV = ds.U + 4 * NV;
-        ds.size = ds.DINV + S.n;
+        ds.passes = sx.passes;
+        ds.n_tb = sx.n_tb;
+        ds.n_troe = sx.n_troe;
+        ds.size = scdev::SPL_E * NV + S.nnz + 1 + sc::SPARSE_TRASH;
+        // several cells per wave: regions half a bank row (16 doubles modulo
+        // 32) apart, so that the groups' like accesses fall on different banks
+        if (cpw > 1) ds.size += (16 - ds.size % 32 + 32) % 32;
         hipDeviceProp_t prop;
         if (hipGetDeviceProperties(&prop, device) != hipSuccess) return fail(SC_EHIP, "hipGetDeviceProperties failed");
-        // the register tail: at most sparse_tail_max(n) rows, and no more than a cell's lanes
-        if (S.n - S.tail0 > std::min(sc::sparse_tail_max(S.n), 64 / cpw))
-            return fail(SC_EUNSUPPORTED, "dense LU tail wider than a cell's lanes");
         if (sizeof(double) * (size_t)ds.size * cpw > prop.sharedMemPerBlock)
             return fail(SC_EUNSUPPORTED, "the sparse factors of this mechanism need " +
                                              std::to_string(sizeof(double) * ds.size) +
@@ -447,7 +440,7 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
         std::vector<double> tab(fit.coef.size());
         for (int iv = 0; iv < fit.nint; ++iv)
             for (int q = 0; q < t.R; ++q)
-                std::copy_n(&fit.coef[((size_t)iv * t.R + order[q]) * nc], nc, &tab[((size_t)iv * t.R + q) * nc]);
+                std::copy_n(&fit.coef[((size_t)iv * t.R + sx.order[q]) * nc], nc, &tab[((size_t)iv * t.R + q) * nc]);
         ok = upload(p, tab, &ds.itab);
         ds.ideg = fit.degree;
         ds.inint = fit.nint;
@@ -459,32 +452,27 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
     p->ds = ds;
     if (ok && sparse) {
         const int N = t.N;
-        // per-reaction entry indices in the execution order of the records
-        std::vector<uint16_t> rxi((size_t)t.R * sc::RXI_SIZE);
-        for (int q = 0; q < t.R; ++q)
-            std::memcpy(&rxi[(size_t)q * sc::RXI_SIZE], &S.rxi[(size_t)order[q] * sc::RXI_SIZE],
-                        sizeof(uint16_t) * sc::RXI_SIZE);
-        // the species table and the records with species in elimination order
+        // the species table in elimination order
         std::vector<int32_t> perm(S.perm.begin(), S.perm.begin() + N + 1), pos(S.pos.begin(), S.pos.begin() + N + 1);
         std::vector<double> sps(spv.size());
         for (int a = 0; a < 9; ++a)
             for (int k = 0; k < N; ++k) sps[(size_t)a * N + pos[k]] = spv[(size_t)a * N + k];
-        std::vector<scdev::RxRec> rxs(rx);
-        for (auto &r : rxs) {
-            for (int i = 0; i < r.nr; ++i) r.rsp[i] = pos[r.rsp[i]];
-            for (int i = 0; i < r.np; ++i) r.psp[i] = pos[r.psp[i]];
-            for (int e = 0; e < r.neff; ++e) r.esp[e] = pos[r.esp[e]];
-        }
+        std::vector<scdev::TroeRec> trs(sx.n_troe);
+        for (int k = 0; k < sx.n_troe; ++k) std::memcpy(&trs[k], &sx.troe[8 * (size_t)k], sizeof(scdev::TroeRec));
         p->dms = d;
-        std::vector<uint16_t> emap(S.emap.size());
-        for (size_t i = 0; i < emap.size(); ++i) emap[i] = S.emap[i] < 0 ? sc::NOENT : (uint16_t)S.emap[i];
+        std::vector<uint16_t> jmap((size_t)(N + 1) * (N + 1));
+        for (int i = 0; i <= N; ++i)
+            for (int j = 0; j <= N; ++j) {
+                const int e = S.emap[(size_t)S.pos[i] * S.n + S.pos[j]];
+                jmap[(size_t)i * (N + 1) + j] = (uint16_t)(e < 0 ? S.nnz : e);
+            }
         scdev::DevSparse &q = p->ds;
-        ok = upload(p, sps, &p->dms.sp) && upload(p, rxs, &p->dms.rx) && upload(p, sd.hb_lvl, &q.hb_lvl) &&
-             upload(p, sd.hc_lvl, &q.hc_lvl) && upload(p, sd.hb, &q.hb) && upload(p, sd.hc, &q.hc) &&
-             upload(p, S.lu_u, &q.lu_u) && upload(p, S.diag, &q.diag) && upload(p, rxi, &q.rxi) &&
+        ok = upload(p, sps, &p->dms.sp) && upload(p, sx.rec, &q.rec) &&
+             upload(p, sx.ix, &q.ix) && upload(p, sx.ixe, &q.ixe) && upload(p, sx.eam1, &q.eam1) && upload(p, trs, &q.troe) &&
              upload(p, sd.comp, &q.comp) && upload(p, perm, &q.perm) && upload(p, pos, &q.pos) &&
-             upload(p, emap, &q.emap) && upload(p, S.cstart, &q.cstart) && upload(p, sd.row, &q.row) &&
-             upload(p, sd.ga, &q.ga) && upload(p, sd.gb, &q.gb);
+             upload(p, jmap, &q.jmap) && upload(p, sd.row, &q.row) &&
+             upload(p, sd.low, &q.low) && upload(p, sd.up, &q.up) &&
+             upload(p, sd.blk, &q.blk);
     }
     if (ok) {
         void *q = nullptr;

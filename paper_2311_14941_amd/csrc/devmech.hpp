@@ -46,27 +46,29 @@ struct DevMech {
     __host__ __device__ const double *nasa() const { return sp + 2 * N; }  // [c*N + k]
 };
 
+// LDS of one cell in the sparse kernels, in doubles: fixed places first, so
+// they are immediate offsets of the LDS instructions, then the L+U entries, the
+// zero slot and the trash slots.  C and g/RT, and h/RT and the production
+// rate, are pairs: one address and one wide read serve both.
+constexpr int SPL_CG = 0, SPL_HW = 2, SPL_UA = 4, SPL_U = 5, SPL_DINV = 9, SPL_E = 10;  // times NV
+
 // The sparse kernels' view of a mechanism's compiled sparse algebra (device
-// pointers) and their per-cell LDS layout (offsets in doubles; NV doubles per
-// state vector).  Their DevMech has the species in elimination order, so a
+// pointers).  Their DevMech has the species in elimination order, so a
 // lane holds the same position as component and as matrix row.
 struct DevSparse {
-    int n, nnz, nl, n_u;
-    int E, C, G, H, WD, UA, U, DINV, size;  // LDS offsets of one cell's region and its size (doubles)
-    int NV;   // vector stride: lanes per cell times slots per lane
+    int n, nnz;
+    int size;  // LDS doubles of one cell's region
     int cpw;  // cells per wave (1, 2 or 4): each cell takes 64 / cpw lanes
-    int dense0;  // first position of the dense trailing block
-    const int *hb_lvl, *hc_lvl;  // levels of the pivots before it (nl of them, and one empty)
-    const uint32_t *hb;          // e_ik | e_kk << 16
-    const uint64_t *hc;          // e_ij | e_ik << 16 | e_kj << 32
-    const uint32_t *lu_u, *diag; // strict U entries with their pivot: e_kj | k << 16; diagonal entries
-    const uint16_t *rxi;   // [R][RXI_SIZE], reaction execution order
+    int passes, n_tb, n_troe;  // reaction passes; third-body and falloff reactions (the first ones)
+    const uint32_t *rec;       // SparseRx's tables
+    const uint16_t *ix, *ixe;
+    const double *eam1;
+    const TroeRec *troe;
     const uint16_t *comp;  // [position][8]: e_kk, e_kT, e_kS, e_Tk, e_Sk; at N: e_TT, e_SS
     const int32_t *perm;   // position -> species (N: temperature)
     const int32_t *pos;    // species -> position
-    const uint16_t *emap;    // n * n: (row, column) position -> entry or NOENT, row-major
-    const int32_t *cstart;   // n + 1: first entry of each column (entries are numbered column by column)
-    const uint16_t *row, *ga, *gb;  // SparseDev's operand tables
+    const uint16_t *jmap;    // (N + 1)^2: (row, column) component in species order -> entry (or the zero slot)
+    const uint16_t *row, *low, *up, *blk;  // SparseDev's operand tables
     // interpolated thermodynamics (null: exact): per interval of ln T and
     // reaction (execution order) the 2 (ideg + 1) coefficients of -dG/RT and
     // dH/RT in t = 2 (ln T - u_i) iinvdu - 1

@@ -103,25 +103,23 @@ constexpr int sparse_off(int n, int e) { return n <= 64 ? 8 * e : e; }
 
 // What the device reads of a mechanism's sparse algebra (built per plan from
 // SparseLU; `lanes` lanes hold one cell's positions, two slots each when
-// n > 64).  The pivots before dense0 are eliminated by levels, but only
-// their updates outside the dense trailing block [dense0, n) are scheduled
-// (hb, hc: as lu_b, lu_c): the block's Schur update A22 -= L21 U12 is a
-// dense product of the gathered operands (ga, gb), and holds 83% of the
-// scheduled updates of a 53-species mechanism, 94% of a 110-species one.
+// n > 64).  Absent entries, and rows and columns beyond n, name the zero slot
+// (entry nnz).
 struct SparseDev {
-    int dense0 = 0;
-    std::vector<int> hb_lvl, hc_lvl;
-    std::vector<uint32_t> hb;
-    std::vector<uint64_t> hc;
-    // per slot, lane and column the entry of the lane's row (else the zero
-    // slot nnz): what the solves read
-    std::vector<uint16_t> row;
-    int row_cols = 0;  // columns per lane in `row`
-    // operands of the Schur update in the matrix instruction's lane layout,
-    // pivots in steps of four.  n <= 64: [step][lane][A tile 0, A tile 1,
-    // B tile 0, B tile 1] in ga; beyond: [tile][lane][step, padded to 16]
-    // in ga (A) and gb (B)
-    std::vector<uint16_t> ga, gb;
+    // solve operands, per slot, lane and column the entry of the lane's row:
+    // the whole row (several cells per wave), or the strictly lower and the
+    // strictly upper part (one cell per wave)
+    std::vector<uint16_t> row, low, up;
+    // factorisation operands (one cell per wave) by block b of 16 pivots, in
+    // 16-byte words [word][lane], with c = lane % 16, g = lane / 16 and
+    // r = the blocks after b:
+    //   2 words   (b c, b k), k = 0..15: the diagonal block, a row per lane
+    //   2 words   (b k, b c) where c > k: its upper part, a column per lane
+    //   r words   block q: (b c, q 4m + g), m = 0..3, then (q 4m + g, b c)
+    //   r words   block q: (q c, b 4s + g), s = 0..3, then (b 4s + g, q c)
+    //   r r half words [q1][q2][lane]: (q1 4i + g, q2 c), i = 0..3
+    // one block's words after the other's
+    std::vector<uint16_t> blk;
     std::vector<uint16_t> comp;  // per component (position order): its entries kk, kT, kS, Tk, Sk, padded to 8
 };
 
@@ -206,5 +204,28 @@ void compile_sparse(Mech &m);
 
 // The device tables of a compiled mechanism for `lanes` lanes per cell.
 SparseDev sparse_device(const Mech &m, int lanes);
+
+// The reactions as the sparse kernels read them: `lanes` reactions per pass,
+// one per lane, padded with null reactions; every table in 16-byte words,
+// word w of a pass at [pass][w][lane], so a load is one contiguous burst.
+// Falloff reactions come first, then third-body ones, then the rest, each by
+// coefficients and side sizes, so that what only some reactions need is in
+// as few passes as can be.  Unused slots name a dummy species (index N + 1:
+// concentration 1, g = h = 0) and trash entries, so a pass has no per-lane
+// branches; what a whole pass does not need is skipped by the flags, which
+// every record of the pass carries.
+constexpr int RXW_WORDS = 3;  // lnA, b, Ea/R; side species (byte offsets, 16 per species); bits; enhanced species; index
+constexpr int RXW_IX = 6;     // entries: six rows of six slots and T, then the T row
+constexpr int RXW_IXE = 4;    // entries of the enhanced species: six rows of four, then the T row
+constexpr int SPARSE_TRASH = 16;  // entries that unused slots add to
+enum { RXF_THIRD_REAC = 1u << 27, RXF_THIRD_PROD = 1u << 28, RXF_NU = 1u << 29, RXF_TB = 1u << 30, RXF_TROE = 1u << 31 };
+struct SparseRx {
+    int passes = 0, n_tb = 0, n_troe = 0;
+    std::vector<int> order;  // execution position -> reaction
+    std::vector<uint32_t> rec;
+    std::vector<uint16_t> ix, ixe;
+    std::vector<double> eam1, troe;  // per third-body reaction 4 alpha - 1; per falloff reaction 8 (lnA0, b0, Ea0/R, a, 1/T3, 1/T1, T2)
+};
+SparseRx sparse_reactions(const Mech &m, int lanes);
 
 }  // namespace sc

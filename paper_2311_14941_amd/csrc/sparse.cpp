@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <array>
 #include <cstdint>
+#include <cstring>
 #include <numeric>
 #include <vector>
 
@@ -322,79 +323,50 @@ void compile_sparse(Mech &m)
 SparseDev sparse_device(const Mech &m, int lanes)
 {
     const SparseLU &S = m.sp;
-    const int n = S.n, N = m.N, zero = S.nnz;
+    const int n = S.n, N = m.N;
     const int slots = n <= 64 ? 1 : 2;
     SparseDev D;
     auto off = [&](int i, int j) {
         const int e = i < n && j < n ? S.emap[(size_t)i * n + j] : -1;
-        return (uint16_t)sparse_off(n, e < 0 ? zero : e);
+        return (uint16_t)sparse_off(n, e < 0 ? S.nnz : e);
     };
-    // the dense trailing block: up to 64 positions, the one factorised in
-    // registers; beyond, the whole full block (blocked elimination)
-    D.dense0 = S.tail0;
-    if (n > 64)
-        while (D.dense0 > 0) {
-            const int q = D.dense0 - 1;
-            bool full = true;
-            for (int i = q; i < n && full; ++i)
-                full = S.emap[(size_t)i * n + q] >= 0 && S.emap[(size_t)q * n + i] >= 0;
-            if (!full) break;
-            D.dense0 = q;
-        }
-    const int t0 = D.dense0;
-    // levels of the pivots before the block, as in the full schedule
-    std::vector<std::vector<int>> L(t0), U(t0);
-    std::vector<int> lev(n, 0);
-    int nl = 0;
-    for (int k = 0; k < t0; ++k) {
-        for (int i = k + 1; i < n; ++i) {
-            if (S.emap[(size_t)i * n + k] >= 0) L[k].push_back(i);
-            if (S.emap[(size_t)k * n + i] >= 0) U[k].push_back(i);
-        }
-        for (auto *v : {&L[k], &U[k]})
-            for (int i : *v) lev[i] = std::max(lev[i], lev[k] + 1);
-        nl = std::max(nl, lev[k] + 1);
-    }
-    auto E = [&](int i, int j) { return S.emap[(size_t)i * n + j]; };
-    D.hb_lvl.assign(1, 0);
-    D.hc_lvl.assign(1, 0);
-    for (int l = 0; l < nl; ++l) {
-        for (int k = 0; k < t0; ++k) {
-            if (lev[k] != l) continue;
-            for (int i : L[k]) D.hb.push_back((uint32_t)E(i, k) | (uint32_t)E(k, k) << 16);
-            for (int i : L[k])
-                for (int j : U[k])
-                    if (i < t0 || j < t0)
-                        D.hc.push_back((uint64_t)E(i, j) | (uint64_t)E(i, k) << 16 | (uint64_t)E(k, j) << 32);
-        }
-        D.hb_lvl.push_back((int)D.hb.size());
-        D.hc_lvl.push_back((int)D.hc.size());
-    }
-    D.hb_lvl.push_back((int)D.hb.size());  // an empty level after the last: the loads run one level ahead
-    D.hc_lvl.push_back((int)D.hc.size());
-    // solve operands: columns padded to what the sweeps read ahead
-    D.row_cols = lanes < 64 ? lanes : 64 * slots;
+    const uint16_t none = off(n, n);
     for (int s = 0; s < slots; ++s)
         for (int l = 0; l < lanes; ++l)
-            for (int c = 0; c < D.row_cols; ++c) D.row.push_back(off(l + 64 * s, c));
-    // Schur operands: lane l holds A[row l % 16][pivot l / 16] and
-    // B[pivot l / 16][column l % 16]
-    const int steps = (t0 + 3) / 4;
-    auto pivot = [&](int s, int l) { return 4 * s + l / 16 < t0 ? 4 * s + l / 16 : n; };
-    if (n <= 64) {
-        for (int s = 0; s < steps; ++s)
-            for (int l = 0; l < 64; ++l) {
-                for (int t = 0; t < 2; ++t) D.ga.push_back(off(t0 + 16 * t + l % 16, pivot(s, l)));
-                for (int t = 0; t < 2; ++t) D.ga.push_back(off(pivot(s, l), t0 + 16 * t + l % 16));
-            }
-    } else {
-        const int pad = (steps + 15) / 16 * 16, tiles = (n - t0 + 15) / 16;
-        for (int t = 0; t < tiles; ++t)
-            for (int l = 0; l < 64; ++l)
-                for (int s = 0; s < pad; ++s) {
-                    D.ga.push_back(off(t0 + 16 * t + l % 16, pivot(s, l)));
-                    D.gb.push_back(off(pivot(s, l), t0 + 16 * t + l % 16));
+            for (int c = 0; c < (lanes < 64 ? lanes : 64 * slots); ++c) {
+                const int i = l + 64 * s;
+                if (lanes < 64) D.row.push_back(off(i, c));
+                else {
+                    D.low.push_back(i > c ? off(i, c) : none);
+                    D.up.push_back(i < c ? off(i, c) : none);
                 }
+            }
+    const int nb = lanes < 64 ? 0 : (n + 15) / 16;
+    for (int b = 0; b < nb; ++b) {
+        // one word of every lane: f(lane, 0..7)
+        auto word = [&](auto f, int per) {
+            for (int l = 0; l < 64; ++l)
+                for (int h = 0; h < per; ++h) D.blk.push_back(f(l, h));
+        };
+        for (int w = 0; w < 2; ++w) word([&](int l, int h) { return off(16 * b + l % 16, 16 * b + 8 * w + h); }, 8);
+        for (int w = 0; w < 2; ++w)
+            word([&](int l, int h) {
+                const int c = l % 16, k = 8 * w + h;
+                return c > k ? off(16 * b + k, 16 * b + c) : none;
+            }, 8);
+        for (int q = b + 1; q < nb; ++q)
+            word([&](int l, int h) {
+                const int i = 16 * b + l % 16, j = 16 * q + 4 * (h % 4) + l / 16;
+                return h < 4 ? off(i, j) : off(j, i);
+            }, 8);
+        for (int q = b + 1; q < nb; ++q)
+            word([&](int l, int h) {
+                const int i = 16 * q + l % 16, k = 16 * b + 4 * (h % 4) + l / 16;
+                return h < 4 ? off(i, k) : off(k, i);
+            }, 8);
+        for (int q1 = b + 1; q1 < nb; ++q1)
+            for (int q2 = b + 1; q2 < nb; ++q2)
+                word([&](int l, int h) { return off(16 * q1 + 4 * h + l / 16, 16 * q2 + l % 16); }, 4);
     }
     // component entries by position (the borders are the last two)
     D.comp.assign((size_t)8 * lanes * slots, 0);
@@ -406,6 +378,112 @@ SparseDev sparse_device(const Mech &m, int lanes)
     D.comp[(size_t)8 * N] = (uint16_t)S.e_TT;
     D.comp[(size_t)8 * N + 1] = (uint16_t)S.e_SS;
     return D;
+}
+
+SparseRx sparse_reactions(const Mech &m, int lanes)
+{
+    const SparseLU &S = m.sp;
+    const Tables &t = m.tab;
+    const int R = t.R, N = t.N, n = S.n;
+    SparseRx X;
+    auto max_nu = [&](int j) {
+        int v = 1;
+        for (int i = 0; i < MAXSIDE; ++i) v = std::max({v, (int)t.rnu[i * R + j], (int)t.pnu[i * R + j]});
+        return v;
+    };
+    X.order.resize(R);
+    std::iota(X.order.begin(), X.order.end(), 0);
+    std::stable_sort(X.order.begin(), X.order.end(), [&](int a, int b) {
+        auto key = [&](int j) {
+            return std::array<int, 4>{-t.kind[j], -max_nu(j), -t.nr[j], -t.np[j]};
+        };
+        return key(a) < key(b);
+    });
+    for (int j = 0; j < R; ++j) {
+        X.n_tb += t.kind[j] != RX_PLAIN;
+        X.n_troe += t.kind[j] == RX_TROE;
+    }
+    X.passes = (R + lanes - 1) / lanes;
+    const int etp = (X.n_tb + lanes - 1) / lanes;
+    X.rec.assign((size_t)X.passes * RXW_WORDS * lanes * 4, 0);
+    X.ix.assign((size_t)X.passes * RXW_IX * lanes * 8, 0);
+    X.ixe.assign((size_t)etp * RXW_IXE * lanes * 8, 0);
+    X.eam1.assign((size_t)4 * X.n_tb, 0.0);
+    X.troe.assign((size_t)8 * X.n_troe, 0.0);
+    const uint32_t dummy = N + 1;
+    for (int p = 0; p < X.passes; ++p) {
+        uint32_t flags = 0;
+        for (int l = 0; l < lanes && p * lanes + l < R; ++l) {
+            const int j = X.order[p * lanes + l];
+            if (t.nr[j] > 2) flags |= RXF_THIRD_REAC;
+            if (t.np[j] > 2) flags |= RXF_THIRD_PROD;
+            if (max_nu(j) > 1) flags |= RXF_NU;
+            if (t.kind[j] != RX_PLAIN) flags |= RXF_TB;
+            if (t.kind[j] == RX_TROE) flags |= RXF_TROE;
+        }
+        for (int l = 0; l < lanes; ++l) {
+            const int q = p * lanes + l;
+            const bool live = q < R;
+            const int j = live ? X.order[q] : 0;
+            uint32_t w[4 * RXW_WORDS] = {};
+            const double d[3] = {live ? t.lnA[j] : -1e300, live ? t.b[j] : 0.0, live ? t.EaR[j] : 0.0};
+            std::memcpy(w, d, sizeof d);
+            uint32_t sl[2 * MAXSIDE], nu[2 * MAXSIDE], order[2] = {0, 0};
+            for (int i = 0; i < MAXSIDE; ++i) {
+                const bool ur = live && i < t.nr[j], up = live && i < t.np[j];
+                sl[i] = ur ? S.pos[t.rsp[i * R + j]] : dummy;
+                sl[3 + i] = up ? S.pos[t.psp[i * R + j]] : dummy;
+                nu[i] = ur ? t.rnu[i * R + j] : 0;
+                nu[3 + i] = up ? t.pnu[i * R + j] : 0;
+                order[0] += nu[i];
+                order[1] += nu[3 + i];
+            }
+            for (int i = 0; i < 3; ++i) w[6 + i] = 16 * sl[2 * i] | 16 * sl[2 * i + 1] << 16;
+            uint32_t bits = flags;
+            for (int i = 0; i < 6; ++i) bits |= nu[i] << (2 * i);
+            bits |= (live ? (uint32_t)(t.dnu[j] + 16) : 16u) << 12 | order[0] << 17 | order[1] << 21;
+            bits |= (live ? (uint32_t)t.kind[j] : 0u) << 25;
+            w[9] = bits;
+            uint32_t enh = 0;
+            for (int e = 0; e < MAXENH; ++e) {
+                const bool ue = live && e < t.neff[j];
+                enh |= (ue ? (uint32_t)S.pos[t.esp[e * R + j]] : dummy) << (8 * e);
+                if (live && t.kind[j] != RX_PLAIN) X.eam1[4 * (size_t)q + e] = ue ? t.eam1[e * R + j] : 0.0;
+            }
+            w[10] = enh;
+            w[11] = j;
+            if (live && t.kind[j] == RX_TROE)
+                for (int f = 0; f < 7; ++f) X.troe[8 * (size_t)q + f] = t.troe[(size_t)f * t.n_troe + t.tix[j]];
+            for (int c = 0; c < RXW_WORDS; ++c)
+                std::memcpy(&X.rec[(((size_t)p * RXW_WORDS + c) * lanes + l) * 4], w + 4 * c, 16);
+            // entries: slot s of row r where both are used, else trash
+            int junk = 0;
+            auto entry = [&](int row, int slot) {  // row 6: the T row; slot 10: the T column
+                const bool ur = row == 6 || nu[row] > 0;
+                const bool us = slot == 10 || (slot < 6 ? nu[slot] > 0 : live && slot - 6 < t.neff[j]);
+                const uint16_t *x = &S.rxi[(size_t)j * RXI_SIZE];
+                int e = live && ur && us ? (row == 6 ? x[RXI_TROW + slot] : x[row * RXI_ROW + slot]) : NOENT;
+                if (e == NOENT) e = S.nnz + 1 + (q + junk++) % SPARSE_TRASH;
+                return (uint16_t)sparse_off(n, e);
+            };
+            uint16_t ix[8 * RXW_IX], ixe[8 * RXW_IXE];
+            for (int r = 0; r < 6; ++r) {
+                for (int s = 0; s < 6; ++s) ix[7 * r + s] = entry(r, s);
+                ix[7 * r + 6] = entry(r, 10);
+            }
+            for (int s = 0; s < 6; ++s) ix[42 + s] = entry(6, s);
+            for (int c = 0; c < RXW_IX; ++c)
+                std::memcpy(&X.ix[(((size_t)p * RXW_IX + c) * lanes + l) * 8], ix + 8 * c, 16);
+            if (p < etp) {
+                for (int r = 0; r < 7; ++r)
+                    for (int e = 0; e < 4; ++e) ixe[4 * r + e] = entry(r, 6 + e);
+                for (int e = 28; e < 32; ++e) ixe[e] = 0;
+                for (int c = 0; c < RXW_IXE; ++c)
+                    std::memcpy(&X.ixe[(((size_t)p * RXW_IXE + c) * lanes + l) * 8], ixe + 8 * c, 16);
+            }
+        }
+    }
+    return X;
 }
 
 }  // namespace sc

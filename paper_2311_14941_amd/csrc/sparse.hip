@@ -60,6 +60,17 @@ __device__ __forceinline__ bool gany(bool b)
         return gsum<G>(b ? 1.0 : 0.0) > 0.0;
 }
 
+// Order between the LDS accesses of the wave's lanes.  A workgroup is one
+// wave, whose LDS instructions take effect in order: the compiler must not
+// move them across, but nothing has to be waited for (a workgroup barrier's
+// fence also waits for the loads sent ahead).
+__device__ __forceinline__ void lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------
 // helpers over VPL components per lane
 // ---------------------------------------------------------------------------
@@ -107,11 +118,20 @@ __device__ __forceinline__ void store_state_v(const DevMech &m, const DevSparse 
 // ---------------------------------------------------------------------------
 // thermodynamics, right-hand side and Jacobian terms
 // ---------------------------------------------------------------------------
-// Mixture state from y; writes C, g/RT, h/RT and clears the accumulators.
-template <int VPL, int G = WAVE>
-__device__ __forceinline__ Mix<> mixture_v(const DevMech &m, const DevSparse &sp, double *lds,
-                                           const double (&y)[VPL], double p, Thermo<> (&th)[VPL], int lane)
+// Address of species c's pair in the pair array at place `at` (SPL_CG, SPL_HW)
+template <int NV>
+__device__ __forceinline__ double *pair(double *lds, int at, int c)
 {
+    return lds + at * NV + 2 * c;
+}
+
+// Mixture state from y; writes C, g/RT, h/RT (and those of the dummy species
+// N + 1) and clears the accumulators.
+template <int VPL, int G = WAVE>
+__device__ __forceinline__ Mix<> mixture_v(const DevMech &m, double *lds, const double (&y)[VPL], double p,
+                                           Thermo<> (&th)[VPL], int lane)
+{
+    constexpr int NV = G * VPL;
     const int N = m.N;
     Mix<> x;
     x.T = comp_T<VPL, G>(m, y);
@@ -141,14 +161,13 @@ __device__ __forceinline__ Mix<> mixture_v(const DevMech &m, const DevSparse &sp
     }
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
-        const int c = lane + G * v;
-        if (c < N) {
-            lds[sp.C + c] = x.rho * yw[v];
-            lds[sp.G + c] = th[v].hRT - th[v].sR;
-            lds[sp.H + c] = th[v].hRT;
-            lds[sp.WD + c] = 0.0;
-        }
-        if (c <= N) lds[sp.UA + c] = 0.0;
+        const int c = lane + G * v;  // lanes beyond N hold zeros: the dummy needs only its concentration
+        double *cg = pair<NV>(lds, SPL_CG, c), *hw = pair<NV>(lds, SPL_HW, c);
+        cg[0] = c < N ? x.rho * yw[v] : 1.0;
+        cg[1] = th[v].hRT - th[v].sR;
+        hw[0] = th[v].hRT;
+        hw[1] = 0.0;
+        lds[SPL_UA * NV + c] = 0.0;
     }
     return x;
 }
@@ -176,34 +195,199 @@ __device__ __forceinline__ const double *thermo_block(const DevSparse &sp, int R
     return sp.itab + (size_t)iv * R * 2 * (sp.ideg + 1);
 }
 
-// f(y): dY_k/dt and dT/dt, VPL components per lane (0 beyond N).
+// One pass's record of this lane's reaction (SparseRx): three 16-byte words.
+struct Rec {
+    uint4 a, b, c;
+    __device__ __forceinline__ double lnA() const { return __hiloint2double(a.y, a.x); }
+    __device__ __forceinline__ double bT() const { return __hiloint2double(a.w, a.z); }
+    __device__ __forceinline__ double EaR() const { return __hiloint2double(b.y, b.x); }
+    __device__ __forceinline__ uint32_t slot(int i) const  // byte offset of a side species' pair
+    {
+        const uint32_t w = i < 2 ? b.z : i < 4 ? b.w : c.x;
+        return i % 2 ? w >> 16 : w & 0xffff;
+    }
+    __device__ __forceinline__ uint32_t bits() const { return c.y; }
+    __device__ __forceinline__ int nu(int i) const { return (c.y >> (2 * i)) & 3; }
+    __device__ __forceinline__ int dnu() const { return (int)((c.y >> 12) & 31) - 16; }
+    __device__ __forceinline__ int order(int side) const { return (c.y >> (17 + 4 * side)) & 15; }
+    __device__ __forceinline__ int kind() const { return (c.y >> 25) & 3; }
+    __device__ __forceinline__ uint32_t enh(int e) const { return ((c.z >> (8 * e)) & 0xff) << 4; }
+    __device__ __forceinline__ int orig() const { return c.w; }
+};
+template <int G>
+__device__ __forceinline__ Rec load_rx(const DevSparse &sp, int pass, int lane)
+{
+    const uint4 *q = (const uint4 *)sp.rec + (size_t)pass * sc::RXW_WORDS * G + lane;
+    return Rec{q[0], q[G], q[2 * G]};
+}
+
+// One reaction's rate of progress and, with JAC, its derivatives: d[0..5] with
+// respect to the side species' concentrations (what an unused slot holds goes
+// to the trash), dqM with respect to [M] (dq/dC of an enhanced species is dqM
+// times its alpha - 1), dT at fixed C, euler (the Euler remainder, or dqM in a
+// constant-volume reactor) and the reaction enthalpy / RT.  The arithmetic is
+// reaction()'s; the Euler remainder q - sum C dq/dC is taken from the
+// reaction's orders (C d(C^nu)/dC = nu C^nu).
+struct RxTerms {
+    double q, d[6], dqM, ea[sc::MAXENH], dT, euler, dH;
+};
+template <bool JAC, int NV>
+__device__ __forceinline__ RxTerms reaction_sp(const DevMech &m, const DevSparse &sp, double *lds, const Rec &r,
+                                               uint32_t flags, int j, const Mix<> &x, double dl, const double *itb,
+                                               double itt)
+{
+    RxTerms o;
+    double c[6], p[6], dp[6], nu[6];
+    double dG = 0.0, dH = 0.0;
+    const double lnkinf = r.lnA() + dl + r.bT() * x.lnT - r.EaR() * x.invT;
+    const double kinf = exp(lnkinf);
+    const char *cg = (const char *)(lds + SPL_CG * NV), *hw = (const char *)(lds + SPL_HW * NV);
+    double g[6], h[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        const double2 v = *(const double2 *)(cg + r.slot(i));
+        c[i] = v.x;
+        g[i] = v.y;
+        if (JAC) h[i] = *(const double *)(hw + r.slot(i));
+        p[i] = c[i];
+        dp[i] = nu[i] = 1.0;
+    }
+    if (flags & sc::RXF_NU) {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            const int v = r.nu(i);
+            nu[i] = v;
+            const double c2 = c[i] * c[i];
+            p[i] = v == 2 ? c2 : v == 3 ? c2 * c[i] : c[i];
+            dp[i] = v == 2 ? 2.0 * c[i] : v == 3 ? 3.0 * c2 : 1.0;
+        }
+    }
+    if (itb) {
+        const double *itc = itb + (size_t)min(j, m.R - 1) * 2 * (sp.ideg + 1);
+        dG = -poly_t(itc, sp.ideg, itt);
+        if (JAC) dH = poly_t(itc + sp.ideg + 1, sp.ideg, itt);
+    } else {
+        // an unused slot of a pass with larger coefficients has nu = 0 and
+        // the dummy's g = h = 0 in any other
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            dG += nu[3 + i] * g[3 + i] - nu[i] * g[i];
+            if (JAC) dH += nu[3 + i] * h[3 + i] - nu[i] * h[i];
+        }
+    }
+    const double dnu = r.dnu();
+    const double lnKc = -dG + dnu * (m.lnp0R - x.lnT);
+    const double M0 = x.p * x.invT / m.Rgas;
+    double M = M0, Me = 0.0;
+    if (flags & sc::RXF_TB) {
+#pragma unroll
+        for (int e = 0; e < sc::MAXENH; ++e) o.ea[e] = 0.0;
+        if (j < sp.n_tb) {
+#pragma unroll
+            for (int e = 0; e < sc::MAXENH; ++e) {
+                o.ea[e] = sp.eam1[4 * j + e];
+                Me += o.ea[e] * *(const double *)(cg + r.enh(e));
+            }
+        }
+        M += Me;
+    }
+    const int kind = r.kind();
+    double kf = kinf, phi = 0.0, dlnF_T = 0.0, dlnk0 = 0.0;
+    if ((flags & sc::RXF_TROE) && kind == sc::RX_TROE) {
+        const TroeRec tr = sp.troe[j];
+        const double lnk0 = tr.lnA0 + dl + tr.b0 * x.lnT - tr.Ea0R * x.invT;
+        const double Pr = exp(lnk0 - lnkinf) * M;
+        const double a = tr.a, iT3 = tr.iT3, iT1 = tr.iT1, T2 = tr.T2;
+        const double e3 = exp(-x.T * iT3), e1 = exp(-x.T * iT1), e2 = exp(-T2 * x.invT);
+        const double Fc = (1.0 - a) * e3 + a * e1 + e2;
+        const double L = log10(Fc);
+        const double cc = -0.4 - 0.67 * L, nn = 0.75 - 1.27 * L;
+        const double X = log10(Pr) + cc;
+        const double D = nn - 0.14 * X;
+        const double f = X / D;
+        const double opf = 1.0 + f * f;
+        const double lF = L / opf;
+        kf = kinf * (Pr / (1.0 + Pr)) * exp(2.302585092994046 * lF);
+        if (JAC) {
+            const double gg = -L * 2.0 * f / (opf * opf);
+            phi = 1.0 / (1.0 + Pr) + gg * (nn / (D * D));  // dln kf / dln Pr
+            const double dlF_dL = 1.0 / opf + gg * ((-0.67 * nn + 1.27 * X) / (D * D));
+            const double dFc = -(1.0 - a) * iT3 * e3 - a * iT1 * e1 + T2 * x.invT * x.invT * e2;
+            dlnF_T = dlF_dL * dFc / Fc;  // dln F/dT at fixed Pr
+            dlnk0 = (tr.b0 + tr.Ea0R * x.invT) * x.invT;
+        }
+    }
+    const double kr = kf * exp(-lnKc);
+    const double Rf = kf * (p[0] * p[1] * p[2]), Rr = kr * (p[3] * p[4] * p[5]);
+    const double q0 = Rf - Rr;
+    const bool third = (flags & sc::RXF_TB) && kind == sc::RX_THIRD;
+    const double fsc = third ? M : 1.0;
+    o.q = fsc * q0;
+    if (!JAC) return o;
+    const double F = fsc * kf, B = -fsc * kr;
+    o.d[0] = F * (p[1] * p[2]) * dp[0];
+    o.d[1] = F * (p[0] * p[2]) * dp[1];
+    o.d[2] = F * (p[0] * p[1]) * dp[2];
+    o.d[3] = B * (p[4] * p[5]) * dp[3];
+    o.d[4] = B * (p[3] * p[5]) * dp[4];
+    o.d[5] = B * (p[3] * p[4]) * dp[5];
+    const double dlnkinf = (r.bT() + r.EaR() * x.invT) * x.invT;
+    const double dlnKc = (dH - dnu) * x.invT;
+    double dlnkf = dlnkinf;
+    o.dqM = 0.0;
+    const double dMdT = m.cv ? 0.0 : -M0 * x.invT;
+    if (flags & sc::RXF_TB) {
+        if (kind == sc::RX_THIRD) {
+            o.dqM = q0;
+        } else if (kind == sc::RX_TROE) {
+            o.dqM = q0 * phi / M;
+            dlnkf = dlnkinf + phi * (dlnk0 - dlnkinf + dMdT / M) + dlnF_T;
+        }
+    }
+    o.dT = fsc * (q0 * dlnkf + Rr * dlnKc);
+    if (third) o.dT += q0 * dMdT;
+    // q - sum_s C_s dq/dC_s: (1 - order) of each direction, less the
+    // enhanced species' share of [M]
+    o.euler = m.cv ? o.dqM
+                   : fsc * ((1.0 - r.order(0)) * Rf - (1.0 - r.order(1)) * Rr) - o.dqM * Me;
+    o.dH = dH;
+    return o;
+}
+
+// f(y): dY_k/dt and dT/dt, VPL components per lane (0 beyond N).  Per pass
+// the record loads of the next are in flight; every lane adds through the
+// dummy species where its reaction has fewer.
 template <int VPL, int G = WAVE>
 __device__ __forceinline__ void rhs_v(const DevMech &m, const DevSparse &sp, double *lds, const double (&y)[VPL], double p,
                       const double *dlnA, int lane, double (&f)[VPL])
 {
-    const int N = m.N, R = m.R;
+    constexpr int NV = G * VPL;
+    const int N = m.N;
     Thermo<> th[VPL];
-    const Mix<> x = mixture_v<VPL, G>(m, sp, lds, y, p, th, lane);
+    Rec nxt = load_rx<G>(sp, 0, lane);
+    const Mix<> x = mixture_v<VPL, G>(m, lds, y, p, th, lane);
     double itt;
-    const double *itb = thermo_block(sp, R, x.lnT, itt);
-    __syncthreads();
+    const double *itb = thermo_block(sp, m.R, x.lnT, itt);
+    lds_sync();
+    char *wd = (char *)(lds + SPL_HW * NV + 1);
     // the reaction loop, compiled once with the tables and once without (the
     // exact path's code does not carry the tables' branches)
     auto pass = [&](auto tables) __attribute__((always_inline)) {
 #pragma unroll 1
-        for (int j = lane; j < R; j += G) {
-            const RxRec rr = load_rec(m, j);
-            const double dl = dlnA ? dlnA[rr.orig] : 0.0;
-            RxOut<> o;
-            if constexpr (decltype(tables)::value)
-                o = reaction<false>(m, lds, rr, x, dl, sp.C, sp.G, sp.H, 0, itb + (size_t)j * 2 * (sp.ideg + 1), itt,
-                                    sp.ideg);
-            else
-                o = reaction<false>(m, lds, rr, x, dl, sp.C, sp.G, sp.H);
+        for (int q = 0; q < sp.passes; ++q) {
+            const Rec r = nxt;
+            nxt = load_rx<G>(sp, min(q + 1, sp.passes - 1), lane);
+            const uint32_t flags = __builtin_amdgcn_readfirstlane(r.bits());
+            const double dl = dlnA ? dlnA[r.orig()] : 0.0;
+            const RxTerms o = reaction_sp<false, NV>(m, sp, lds, r, flags, q * G + lane, x, dl,
+                                                     decltype(tables)::value ? itb : nullptr, itt);
 #pragma unroll
-            for (int i = 0; i < sc::MAXSIDE; ++i) {
-                if (i < rr.nr) atomicAdd(&lds[sp.WD + rr.rsp[i]], -(double)rr.rnu[i] * o.q);
-                if (i < rr.np) atomicAdd(&lds[sp.WD + rr.psp[i]], (double)rr.pnu[i] * o.q);
+            for (int i = 0; i < 6; ++i) {
+                if (i == 2 && !(flags & sc::RXF_THIRD_REAC)) continue;
+                if (i == 5 && !(flags & sc::RXF_THIRD_PROD)) continue;
+                double v = i < 3 ? -o.q : o.q;
+                if (flags & sc::RXF_NU) v *= r.nu(i);
+                atomicAdd((double *)(wd + r.slot(i)), v);
             }
         }
     };
@@ -211,109 +395,149 @@ __device__ __forceinline__ void rhs_v(const DevMech &m, const DevSparse &sp, dou
         pass(std::true_type{});
     else
         pass(std::false_type{});
-    __syncthreads();
+    lds_sync();
     double hw[VPL];
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int c = lane + G * v;
         f[v] = hw[v] = 0.0;
         if (c < N) {
-            const double wd = lds[sp.WD + c];
-            f[v] = m.W()[c] * wd / x.rho;
-            hw[v] = (m.cv ? th[v].hRT - 1.0 : th[v].hRT) * wd;
+            const double wdk = pair<NV>(lds, SPL_HW, c)[1];
+            f[v] = m.W()[c] * wdk / x.rho;
+            hw[v] = (m.cv ? th[v].hRT - 1.0 : th[v].hRT) * wdk;
         }
     }
     const double fT = -m.Rgas * x.T * vsum<VPL, G>(hw) / (x.rho * x.cp);
 #pragma unroll
     for (int v = 0; v < VPL; ++v)
         if (lane + G * v == N) f[v] = fT;
-    __syncthreads();
+    lds_sync();
 }
 
 // Jacobian pass: f(y), and the bordered matrix of I/hg - J formed in the L+U
 // entries (fill entries zero).  The reaction loop scatters -nu dq/dC and
 // -nu dq/dT into the species rows and the reaction-enthalpy-weighted
 // derivatives into the temperature row; the border entries are finished per
-// state component after one barrier.
+// state component after one barrier.  The sums every reaction adds to, the
+// (T, T) entry and a constant-volume reactor's border term, stay in a register
+// per lane until the end (64 LDS additions to one address run one by one).
 template <int VPL, int G = WAVE>
 __device__ __forceinline__ void jac_v(const DevMech &m, const DevSparse &sp, double *lds, const double (&y)[VPL], double p,
                       const double *dlnA, int lane, double inv_hg, double (&f)[VPL])
 {
-    const int N = m.N, R = m.R;
-    double *E = lds + sp.E;
+    constexpr int NV = G * VPL;
+    const int N = m.N;
+    double *E = lds + SPL_E * NV;
     Thermo<> th[VPL];
-    const Mix<> x = mixture_v<VPL, G>(m, sp, lds, y, p, th, lane);
+    Rec nxt = load_rx<G>(sp, 0, lane);
+    const Mix<> x = mixture_v<VPL, G>(m, lds, y, p, th, lane);
 #pragma unroll 4
-    for (int e = lane; e <= sp.nnz; e += G) E[e] = 0.0;  // and the zero slot E[nnz]
-    __syncthreads();
+    for (int e = 2 * lane; e <= sp.nnz; e += 2 * G) *(double2 *)(E + e) = make_double2(0.0, 0.0);  // and the zero slot
+    lds_sync();
     const double RT = m.Rgas * x.T;
     double itt;
-    const double *itb = thermo_block(sp, R, x.lnT, itt);
+    const double *itb = thermo_block(sp, m.R, x.lnT, itt);
+    char *wd = (char *)(lds + SPL_HW * NV + 1), *ua = (char *)(lds + SPL_UA * NV);
+    auto add = [&](uint32_t o, double v) __attribute__((always_inline)) {
+        atomicAdd((double *)((char *)E + (VPL == 1 ? o : 8 * o)), v);
+    };
+    double tt = 0.0, tm = 0.0;
     auto pass = [&](auto tables) __attribute__((always_inline)) {
 #pragma unroll 1
-    for (int j = lane; j < R; j += G) {
-        const RxRec rr = load_rec(m, j);
-        const double dl = dlnA ? dlnA[rr.orig] : 0.0;
-        RxOut<> o;
-        if constexpr (decltype(tables)::value)
-            o = reaction<true>(m, lds, rr, x, dl, sp.C, sp.G, sp.H, 0, itb + (size_t)j * 2 * (sp.ideg + 1), itt,
-                               sp.ideg);
-        else
-            o = reaction<true>(m, lds, rr, x, dl, sp.C, sp.G, sp.H);
-        // the reaction's entry indices are loaded once its rate terms are
-        // done, so they do not hold registers through the rate arithmetic
-        __builtin_amdgcn_sched_barrier(0);
-        uint16_t ix[sc::RXI_SIZE];
-        __builtin_memcpy(ix, sp.rxi + (size_t)j * sc::RXI_SIZE, sizeof ix);
-        // temperature-row weight: the reaction enthalpy (constant pressure) or
-        // internal energy (constant volume), per unit of progress
-        const double dHJ = m.cv ? (o.dH - rr.dnu) * RT : o.dH * RT;
-        bool use[sc::NDEP];
+        for (int q = 0; q < sp.passes; ++q) {
+            const Rec r = nxt;
+            const uint4 *ip = (const uint4 *)sp.ix + (size_t)q * sc::RXW_IX * G + lane;
+            uint32_t ix[4 * sc::RXW_IX];
 #pragma unroll
-        for (int i = 0; i < sc::MAXSIDE; ++i) {
-            use[i] = i < rr.nr;
-            use[3 + i] = i < rr.np;
+            for (int c = 0; c < sc::RXW_IX; ++c) {
+                const uint4 w = ip[c * G];
+                ix[4 * c] = w.x, ix[4 * c + 1] = w.y, ix[4 * c + 2] = w.z, ix[4 * c + 3] = w.w;
+            }
+            nxt = load_rx<G>(sp, min(q + 1, sp.passes - 1), lane);
+            const uint32_t flags = __builtin_amdgcn_readfirstlane(r.bits());
+            const double dl = dlnA ? dlnA[r.orig()] : 0.0;
+            const int j = q * G + lane;
+            const RxTerms o = reaction_sp<true, NV>(m, sp, lds, r, flags, j, x, dl,
+                                                    decltype(tables)::value ? itb : nullptr, itt);
+            auto at = [&](int e) __attribute__((always_inline)) { return e % 2 ? ix[e / 2] >> 16 : ix[e / 2] & 0xffff; };
+            // temperature-row weight: the reaction enthalpy (constant pressure) or
+            // internal energy (constant volume), per unit of progress
+            const double dHJ = m.cv ? (o.dH - r.dnu()) * RT : o.dH * RT;
+            auto row = [&](auto I, auto NU) __attribute__((always_inline)) {
+                constexpr int i = I;
+                double w = i < 3 ? -1.0 : 1.0;
+                if (decltype(NU)::value) w *= r.nu(i);
+                // without coefficients the weight is a constant and the products fold to signs
+                atomicAdd((double *)(wd + r.slot(i)), w * o.q);
+                atomicAdd((double *)(ua + r.slot(i) / 2), w * o.euler);
+                add(at(7 * i), -w * o.d[0]);
+                add(at(7 * i + 1), -w * o.d[1]);
+                if (flags & sc::RXF_THIRD_REAC) add(at(7 * i + 2), -w * o.d[2]);
+                add(at(7 * i + 3), -w * o.d[3]);
+                add(at(7 * i + 4), -w * o.d[4]);
+                if (flags & sc::RXF_THIRD_PROD) add(at(7 * i + 5), -w * o.d[5]);
+                add(at(7 * i + 6), -w * o.dT);
+            };
+            auto rows = [&](auto NU) __attribute__((always_inline)) {
+                row(std::integral_constant<int, 0>{}, NU);
+                row(std::integral_constant<int, 1>{}, NU);
+                if (flags & sc::RXF_THIRD_REAC) row(std::integral_constant<int, 2>{}, NU);
+                row(std::integral_constant<int, 3>{}, NU);
+                row(std::integral_constant<int, 4>{}, NU);
+                if (flags & sc::RXF_THIRD_PROD) row(std::integral_constant<int, 5>{}, NU);
+            };
+            if (flags & sc::RXF_NU)
+                rows(std::true_type{});
+            else
+                rows(std::false_type{});
+#pragma unroll
+            for (int s = 0; s < 6; ++s) {
+                if (s == 2 && !(flags & sc::RXF_THIRD_REAC)) continue;
+                if (s == 5 && !(flags & sc::RXF_THIRD_PROD)) continue;
+                add(at(42 + s), dHJ * o.d[s]);
+            }
+            tt += dHJ * o.dT;
+            if (m.cv) tm += dHJ * o.euler;
+            if ((flags & sc::RXF_TB) && j < sp.n_tb) {
+                const uint4 *ep = (const uint4 *)sp.ixe + (size_t)q * sc::RXW_IXE * G + lane;
+                uint32_t ie[4 * sc::RXW_IXE];
+#pragma unroll
+                for (int c = 0; c < sc::RXW_IXE; ++c) {
+                    const uint4 w = ep[c * G];
+                    ie[4 * c] = w.x, ie[4 * c + 1] = w.y, ie[4 * c + 2] = w.z, ie[4 * c + 3] = w.w;
+                }
+#pragma unroll
+                for (int i = 0; i < 7; ++i) {
+                    const double w = i == 6 ? dHJ * o.dqM : (i < 3 ? o.dqM : -o.dqM) * r.nu(i < 6 ? i : 0);
+#pragma unroll
+                    for (int e = 0; e < sc::MAXENH; ++e) {
+                        const int k = 4 * i + e;
+                        add(k % 2 ? ie[k / 2] >> 16 : ie[k / 2] & 0xffff, w * o.ea[e]);
+                    }
+                }
+            }
         }
-#pragma unroll
-        for (int e = 0; e < sc::MAXENH; ++e) use[6 + e] = e < rr.neff;
-#pragma unroll
-        for (int r = 0; r < 2 * sc::MAXSIDE; ++r) {
-            const bool isr = r < sc::MAXSIDE;
-            const int ri = isr ? r : r - sc::MAXSIDE;
-            if (ri >= (isr ? rr.nr : rr.np)) continue;
-            const int row = isr ? rr.rsp[ri] : rr.psp[ri];
-            const double nu = isr ? -(double)rr.rnu[ri] : (double)rr.pnu[ri];
-            atomicAdd(&lds[sp.WD + row], nu * o.q);
-            atomicAdd(&lds[sp.UA + row], nu * o.euler);
-#pragma unroll
-            for (int s = 0; s < sc::NDEP; ++s)
-                if (use[s]) atomicAdd(&E[ix[r * sc::RXI_ROW + s]], -nu * o.d[s]);
-            atomicAdd(&E[ix[r * sc::RXI_ROW + sc::NDEP]], -nu * o.dT);
-        }
-#pragma unroll
-        for (int s = 0; s < sc::NDEP; ++s)
-            if (use[s]) atomicAdd(&E[ix[sc::RXI_TROW + s]], dHJ * o.d[s]);
-        atomicAdd(&E[ix[sc::RXI_TROW + sc::NDEP]], dHJ * o.dT);
-        if (m.cv) atomicAdd(&lds[sp.UA + N], dHJ * o.euler);
-    }
     };
     if (itb)
         pass(std::true_type{});
     else
         pass(std::false_type{});
-    __syncthreads();
+    lds_sync();
     const double one = m.cv ? 1.0 : 0.0;
-    double hw[VPL], eu[VPL], cpf[VPL], dcp[VPL];
+    double hw[VPL], eu[VPL], cpf[VPL], dcp[VPL], uak[VPL];
+    uint4 cm[VPL];
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int c = lane + G * v;
-        f[v] = hw[v] = eu[v] = cpf[v] = dcp[v] = 0.0;
+        cm[v] = ((const uint4 *)sp.comp)[c];
+        f[v] = hw[v] = eu[v] = cpf[v] = dcp[v] = uak[v] = 0.0;
         if (c < N) {
             const double Wk = m.W()[c], iw = m.invW()[c];
-            const double wd = lds[sp.WD + c], ua = lds[sp.UA + c];
-            f[v] = Wk * wd / x.rho;
-            hw[v] = (th[v].hRT - one) * wd;
-            eu[v] = th[v].hRT * ua / x.rho;      // (h_k/(R T W_k)) u_k, u_k = W_k UA_k / rho
+            const double wdk = pair<NV>(lds, SPL_HW, c)[1];
+            uak[v] = lds[SPL_UA * NV + c];
+            f[v] = Wk * wdk / x.rho;
+            hw[v] = (th[v].hRT - one) * wdk;
+            eu[v] = th[v].hRT * uak[v] / x.rho;      // (h_k/(R T W_k)) u_k, u_k = W_k UA_k / rho
             cpf[v] = (th[v].cpR - one) * f[v] * iw;
             dcp[v] = th[v].dcpR * y[v] * iw;
         }
@@ -322,30 +546,31 @@ __device__ __forceinline__ void jac_v(const DevMech &m, const DevSparse &sp, dou
     const double Eu = m.cv ? 0.0 : RT * vsum<VPL, G>(eu);
     const double Scpf = m.Rgas * vsum<VPL, G>(cpf);
     const double Sdcp = m.Rgas * vsum<VPL, G>(dcp);
+    const double TT = gsum<G>(tt);
     const double fT = -H / (x.rho * x.cp);
     const double vs = m.cv ? 1.0 : x.Wbar;
     const double ct = m.cv ? 0.0 : x.invT;
-    const double tb = m.cv ? lds[sp.UA + N] : x.Wbar * Eu;
+    const double tb = m.cv ? gsum<G>(tm) : x.Wbar * Eu;
     const double icp = 1.0 / x.cp;
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int c = lane + G * v;
-        const uint16_t *cm = sp.comp + 8 * c;
+        const int e0 = cm[v].x & 0xffff, e1 = cm[v].x >> 16, e2 = cm[v].y & 0xffff, e3 = cm[v].y >> 16, e4 = cm[v].z & 0xffff;
         if (c < N) {
-            const double us = m.cv ? lds[sp.UA + c] : lds[sp.UA + c] / x.rho;
-            E[cm[0]] += inv_hg;
-            E[cm[1]] = E[cm[1]] / x.rho - ct * us;
-            E[cm[2]] = -us;
-            E[cm[3]] = (E[cm[3]] + tb + fT * m.Rgas * (th[v].cpR - one)) * icp;
-            E[cm[4]] = vs;
+            const double us = m.cv ? uak[v] : uak[v] / x.rho;
+            E[e0] += inv_hg;
+            E[e1] = E[e1] / x.rho - ct * us;
+            E[e2] = -us;
+            E[e3] = (E[e3] + tb + fT * m.Rgas * (th[v].cpR - one)) * icp;
+            E[e4] = vs;
         } else if (c == N) {
             f[v] = fT;
             const double eT = m.cv ? 0.0 : Eu * x.invT;
-            E[cm[0]] = inv_hg + (E[cm[0]] / x.rho + eT + Scpf + fT * Sdcp) * icp;
-            E[cm[1]] = -1.0;
+            E[e0] = inv_hg + (TT / x.rho + eT + Scpf + fT * Sdcp) * icp;
+            E[e1] = -1.0;
         }
     }
-    __syncthreads();
+    lds_sync();
 }
 
 // ---------------------------------------------------------------------------
@@ -380,7 +605,51 @@ __device__ __forceinline__ double bcast(double v)
 template <int K>
 __device__ __forceinline__ void fmac_row(double &z, double a)
 {
-    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, -%1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(z) : "v"(a), "n"(K));
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, -%1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+&v"(z) : "v"(a), "n"(K));
+}
+// the same for four vectors
+template <int K>
+__device__ __forceinline__ void fmac_row4(double &x, double &y, double &z, double &w, double a)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %0, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %1, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %2, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %3, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+        : "+&v"(x), "+&v"(y), "+&v"(z), "+&v"(w)
+        : "v"(a), "n"(K));
+}
+// z -= a z_K on the lanes of the rows in ROWS
+template <int K, int ROWS>
+__device__ __forceinline__ void fmac_in(double &z, double a)
+{
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, -%1 row_newbcast:%2 row_mask:%3 bank_mask:0xf"
+        : "+&v"(z)
+        : "v"(a), "n"(K), "n"(ROWS));
+}
+// z -= sum a[i] x_{K + i}, i = 0..3, on the lanes of the rows in ROWS
+template <int K, int ROWS>
+__device__ __forceinline__ void fmac_by4(double &z, double x, const double *a)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %1, -%2 row_newbcast:%6 row_mask:%10 bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, -%3 row_newbcast:%7 row_mask:%10 bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, -%4 row_newbcast:%8 row_mask:%10 bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, -%5 row_newbcast:%9 row_mask:%10 bank_mask:0xf"
+        : "+&v"(z)
+        : "v"(x), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "n"(K), "n"(K + 1), "n"(K + 2), "n"(K + 3), "n"(ROWS));
+}
+// the lanes of row B of 16 in every row
+template <int B>
+__device__ __forceinline__ double spread_row(double v)
+{
+    auto half = [](int x) __attribute__((always_inline)) {
+        const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        const int y = B & 1 ? a[1] : a[0];
+        const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+        return (int)(B & 2 ? b[1] : b[0]);
+    };
+    return __hiloint2double(half(__double2hiint(v)), half(__double2loint(v)));
 }
 
 // f(0), ..., f(N - 1) with compile-time arguments
@@ -410,46 +679,6 @@ template <>
 struct Factors<1, 32> {
     double a[32], dinv;
 };
-
-// z -= a zk on the lanes above (below) K; the mask goes straight to the
-// execution mask, one scalar instruction, where a select costs three vector
-// ones.  `all` is the mask to go back to.  The scalar operand comes from
-// readlane: two wait states until a vector instruction may read it.
-template <int K>
-__device__ __forceinline__ void fma_above(double &z, double a, double zk, uint64_t all)
-{
-    asm volatile("s_lshl_b64 exec, -2, %3\n\ts_nop 1\n\tv_fma_f64 %0, -%1, %2, %0\n\ts_mov_b64 exec, %4"
-                 : "+v"(z)
-                 : "v"(a), "s"(zk), "n"(K), "s"(all)
-                 : "scc");
-}
-template <int K>
-__device__ __forceinline__ void fma_below(double &z, double a, double zk, uint64_t all)
-{
-    asm volatile("s_bfm_b64 exec, %3, 0\n\ts_nop 1\n\tv_fma_f64 %0, -%1, %2, %0\n\ts_mov_b64 exec, %4"
-                 : "+v"(z)
-                 : "v"(a), "s"(zk), "n"(K), "s"(all));
-}
-// the same with the lane in a scalar register
-__device__ __forceinline__ void fma_above(double &z, double a, double zk, int k, uint64_t all)
-{
-    asm volatile("s_lshl_b64 exec, -2, %3\n\ts_nop 1\n\tv_fma_f64 %0, -%1, %2, %0\n\ts_mov_b64 exec, %4"
-                 : "+v"(z)
-                 : "v"(a), "s"(zk), "s"(k), "s"(all)
-                 : "scc");
-}
-__device__ __forceinline__ void fma_below(double &z, double a, double zk, int k, uint64_t all)
-{
-    asm volatile("s_bfm_b64 exec, %3, 0\n\ts_nop 1\n\tv_fma_f64 %0, -%1, %2, %0\n\ts_mov_b64 exec, %4"
-                 : "+v"(z)
-                 : "v"(a), "s"(zk), "s"(k), "s"(all));
-}
-__device__ __forceinline__ uint64_t exec_mask()
-{
-    uint64_t m;
-    asm volatile("s_mov_b64 %0, exec" : "=s"(m));
-    return m;
-}
 
 // ---- several cells per wave: the factorisation in registers, row per lane --
 // n <= G rows, so the rows of a whole system fit one group's registers (2 G
@@ -521,95 +750,7 @@ __device__ __forceinline__ void sweeps_group(const DevSparse &sp, const Factors<
     });
 }
 
-// ---- one cell per wave: levels, dense Schur update, register tail -----------
-__device__ __forceinline__ int lo16(uint64_t x) { return (int)(x & 0xffff); }
-__device__ __forceinline__ int mid16(uint64_t x) { return (int)((x >> 16) & 0xffff); }
-__device__ __forceinline__ int hi16(uint64_t x) { return (int)((x >> 32) & 0xffff); }
-
-// The first four groups of 64 items of a phase, loaded one level ahead, so
-// their memory latency overlaps the level before; groups past the phase's end
-// are skipped by a uniform branch.
-template <class I>
-struct Items {
-    I it[4];
-    int q0, q1;
-};
-template <class I>
-__device__ __forceinline__ Items<I> items(const I *list, int q0, int q1, int lane)
-{
-    Items<I> p;
-    p.q0 = q0;
-    p.q1 = q1;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int q = q0 + u * WAVE + lane;
-        p.it[u] = q < q1 ? list[q] : (I)0;
-    }
-    return p;
-}
-
-// l_ik = a_ik / a_kk (e_ik | e_kk << 16)
-__device__ __forceinline__ void lu_scale_items(double *E, const Items<uint32_t> &p, int lane)
-{
-    double a[4], d[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        if (p.q0 + u * WAVE >= p.q1) break;
-        a[u] = E[p.it[u] & 0xffff];
-        d[u] = E[p.it[u] >> 16];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        if (p.q0 + u * WAVE >= p.q1) break;
-        if (p.q0 + u * WAVE + lane < p.q1) E[p.it[u] & 0xffff] = a[u] / d[u];
-    }
-}
-
-// a_ij -= l_ik u_kj (e_ij | e_ik << 16 | e_kj << 32); items of one phase may
-// share a target: LDS additions
-__device__ __forceinline__ void lu_update_items(double *E, const Items<uint64_t> &p, int lane)
-{
-    double a[4], b[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        if (p.q0 + u * WAVE >= p.q1) break;
-        a[u] = E[mid16(p.it[u])];
-        b[u] = E[hi16(p.it[u])];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        if (p.q0 + u * WAVE >= p.q1) break;
-        if (p.q0 + u * WAVE + lane < p.q1) atomicAdd(&E[lo16(p.it[u])], -a[u] * b[u]);
-    }
-}
-
-// The pivots before the dense block, level by level: their L entries, then
-// their updates of entries outside the block (the block's own updates are
-// left to the dense product).
-__device__ __forceinline__ void lu_levels(const DevSparse &sp, double *E, int lane)
-{
-    if (sp.nl == 0) return;
-    Items<uint32_t> pb = items(sp.hb, 0, sp.hb_lvl[1], lane);
-    Items<uint64_t> pc = items(sp.hc, 0, sp.hc_lvl[1], lane);
-#pragma unroll 1
-    for (int l = 0; l < sp.nl; ++l) {
-        const int b1 = sp.hb_lvl[l + 1], c1 = sp.hc_lvl[l + 1];
-        lu_scale_items(E, pb, lane);
-#pragma unroll 1
-        for (int q = pb.q0 + 4 * WAVE; q < b1; q += 4 * WAVE) lu_scale_items(E, items(sp.hb, q, b1, lane), lane);
-        pb = items(sp.hb, b1, sp.hb_lvl[l + 2], lane);
-        __syncthreads();
-        const int c0 = pc.q0;
-        if (c1 > c0) {
-            lu_update_items(E, pc, lane);
-#pragma unroll 1
-            for (int q = c0 + 4 * WAVE; q < c1; q += 4 * WAVE) lu_update_items(E, items(sp.hc, q, c1, lane), lane);
-            __syncthreads();
-        }
-        pc = items(sp.hc, c1, sp.hc_lvl[l + 2], lane);
-    }
-}
-
+// ---- one cell per wave: blocks of 16 pivots --------------------------------
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 // acc -= A B on one 16 x 16 tile with four pivots: lane l gives A[l % 16][l / 16]
@@ -620,475 +761,313 @@ __device__ __forceinline__ d4 tile_sub(double a, double b, d4 acc)
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 1);
 }
 
-// Schur update of the dense block [t0, n) of up to 32 positions, A22 -= L21
-// U12, on the matrix cores: 2 x 2 tiles, pivots in steps of four, operands
-// gathered from the L+U entries through the tables (absent entries read the
-// zero slot).  Entry (i, j) of the block is the column's end minus n - i.
-// What this replaces: 6,160 scheduled multiply-adds (53 species) read their
-// indices from L2 in 33 dependent rounds and met in LDS additions.
-__device__ __forceinline__ void lu_schur(const DevSparse &sp, double *E, int lane, const uint2 (&g0)[8])
+__device__ __forceinline__ uint32_t half_of(const uint4 &w, int h)
 {
-    const int n = sp.n, t0 = sp.dense0, steps = (t0 + 3) / 4;
-    if (steps == 0) return;
-    const int c = lane & 15, r0 = lane >> 4;
-    int base[2];
-    d4 acc[2][2];
-#pragma unroll
-    for (int tj = 0; tj < 2; ++tj) {
-        const int j = min(t0 + 16 * tj + c, n - 1);
-        base[tj] = sp.cstart[j + 1] - n + t0 + r0;  // entry (t0 + r0, j)
-#pragma unroll
-        for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[ti][tj][r] = E[base[tj] + 16 * ti + 4 * r];
-    }
-    const uint2 *g = (const uint2 *)sp.ga + lane;
-#pragma unroll 1
-    for (int s0 = 0; s0 < steps; s0 += 8) {
-        uint2 gi[8];
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            if (s0 == 0)
-                gi[s] = g0[s];
-            else if (s0 + s < steps)
-                gi[s] = g[(s0 + s) * WAVE];
-        }
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            if (s0 + s >= steps) break;
-            const double a0 = entry<1>(E, gi[s].x & 0xffff), a1 = entry<1>(E, gi[s].x >> 16);
-            const double b0 = entry<1>(E, gi[s].y & 0xffff), b1 = entry<1>(E, gi[s].y >> 16);
-            acc[0][0] = tile_sub(a0, b0, acc[0][0]);
-            acc[0][1] = tile_sub(a0, b1, acc[0][1]);
-            acc[1][0] = tile_sub(a1, b0, acc[1][0]);
-            acc[1][1] = tile_sub(a1, b1, acc[1][1]);
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int tj = 0; tj < 2; ++tj)
-#pragma unroll
-        for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (t0 + 16 * tj + c < n && t0 + 16 * ti + 4 * r + r0 < n) E[base[tj] + 16 * ti + 4 * r] = acc[ti][tj][r];
-    __syncthreads();
+    const uint32_t x = h < 2 ? w.x : h < 4 ? w.y : h < 6 ? w.z : w.w;
+    return h % 2 ? x >> 16 : x & 0xffff;
+}
+template <int VPL>
+__device__ __forceinline__ void put(double *E, uint32_t o, double v)
+{
+    if (VPL == 1)
+        *(double *)((char *)E + o) = v;
+    else
+        E[o] = v;
 }
 
-// The same for a block of any width: A22 -= L21 U12 over the block [t0, n)
-// with the pivots [k0, k1), operands A(tile, step) and B(tile, step) through
-// functors; 16 steps of four pivots at a time, one column of tiles at a time.
-template <class FA, class FB>
-__device__ __forceinline__ void lu_schur_wide(const DevSparse &sp, double *E, int lane, int t0, int steps, FA fa,
-                                              FB fb)
+// Numeric LU of the formed matrix in E, blocks of 16 pivots in position order:
+// L scaled, U scaled to a unit diagonal, 1/u_kk in DINV.  A broadcast of one
+// lane to the 16 of its row costs nothing inside a multiply-add (DPP), where
+// one to the whole wave takes two readlanes at twice a multiply-add's time
+// each; so everything of a block is laid out in rows of 16 lanes:
+//   - the diagonal block, a row per lane, the same in all four rows of lanes;
+//   - the block's rows of U, a row per lane, the columns dealt to the four
+//     rows of lanes, eliminated together with the diagonal block;
+//   - the block's columns of L, a column per lane, the rows dealt likewise,
+//     as L D by the unit upper part of the diagonal block;
+//   - the rest, A -= (L D) (D^-1 U), on the matrix cores.
+// Entries outside the pattern are read from the zero slot and stay zero in
+// exact zeros, so they are written back there and no lane is masked.  (The
+// elimination by levels of independent pivots it replaces took 48k cycles of
+// a lone wave on 53 species, waiting for 8 levels of indices from L2 and for
+// the broadcasts of a 30-wide register tail.)
+template <int VPL>
+__device__ __forceinline__ void lu_blocks(const DevSparse &sp, double *E, double *DINV, int lane)
 {
-    const int n = sp.n, tiles = (n - t0 + 15) / 16;
-    const int c = lane & 15, r0 = lane >> 4;
-#pragma unroll 1
-    for (int s0 = 0; s0 < steps; s0 += 16) {
-#pragma unroll 1
-        for (int tj = 0; tj < tiles; ++tj) {
-            const int j = t0 + 16 * tj + c;
-            const int base = sp.cstart[min(j, n - 1) + 1] - n + t0 + r0;
-            double b[16];
-            fb(tj, s0, b);
-#pragma unroll 1
-            for (int ti = 0; ti < tiles; ++ti) {
-                double a[16];
-                fa(ti, s0, a);
-                double *e = E + base + 16 * ti;
-                const int i = t0 + 16 * ti + r0;
-                d4 acc;
+    constexpr int Q = 4 * VPL - 1;  // most blocks after one
+    const int n = sp.n, nb = (n + 15) / 16;
+    const int c = lane & 15;
+    const uint4 *t = (const uint4 *)sp.blk + lane;
+    // a block's first words, loaded one block ahead
+    uint4 wd[4], wu[Q];
+    auto words = [&](int r) __attribute__((always_inline)) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc[r] = i + 4 * r < n ? e[4 * r] : 0.0;
+        for (int w = 0; w < 4; ++w) wd[w] = t[w * WAVE];
 #pragma unroll
-                for (int s = 0; s < 16; ++s) {
-                    if (s0 + s >= steps) break;
-                    acc = tile_sub(a[s], b[s], acc);
-                }
-                if (j < n) {
+        for (int q = 0; q < Q; ++q)
+            if (q < r) wu[q] = t[(4 + q) * WAVE];
+    };
+    words(nb - 1);
+#pragma unroll 1
+    for (int b = 0; b < nb; ++b) {
+        const int k0 = 16 * b, r = nb - 1 - b;
+        const uint4 id0 = wd[0], id1 = wd[1], it0 = wd[2], it1 = wd[3];
+        uint4 ul[Q];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (i + 4 * r < n) e[4 * r] = acc[r];
+        for (int q = 0; q < Q; ++q) ul[q] = wu[q];
+        const uint4 *ta = t + (4 + r) * WAVE;  // the rest of this block's words
+        const uint2 *ct = (const uint2 *)(t - lane + (4 + 2 * r) * WAVE) + lane;
+        t += (4 + 2 * r) * WAVE + r * r * (WAVE / 2);
+        double D[16], u[Q][4], x[Q][4];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) D[k] = entry<VPL>(E, half_of(k < 8 ? id0 : id1, k % 8));
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (q < r) {
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    u[q][h] = entry<VPL>(E, half_of(ul[q], h));
+                    x[q][h] = entry<VPL>(E, half_of(ul[q], 4 + h));
                 }
             }
-        }
-        __syncthreads();
-    }
-}
-
-// Row broadcasts of one pivot row are read four columns at a time, so that
-// the wait a vector instruction needs after a readlane is spent reading the
-// next ones.
-template <int W, int K>
-__device__ __forceinline__ void apply_pivot(double (&a)[W], double l)
-{
-    constexpr int J0 = K + 1;
-#pragma unroll
-    for (int j = J0; j < W; j += 4) {
-        double u[4];
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-            if (j + d < W) u[d] = rdlane(a[j + d], K);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-            if (j + d < W) a[j + d] = fma(-l, u[d], a[j + d]);
-    }
-}
-
-// The dense trailing block [t0, n) (w = n - t0 <= W positions, full L+U
-// pattern) in registers: lane r holds row t0 + r, columns t0..n-1.  The
-// rows of the block are the last w entries of each of its columns (entries
-// are numbered column by column), so no index table is read.  Right-looking
-// elimination: per pivot k, the pivot row is broadcast entry by entry and
-// every row below applies it; rows at or above the pivot multiply by zero.
-// Padding (rows and columns from w to W) holds zeros and takes part
-// unconditionally: the loops have fixed trip counts, the array stays in
-// registers.  L is stored scaled (l_ik = a_ik / a_kk), U and the diagonal
-// as computed.
-template <int W>
-__device__ __forceinline__ void lu_tail(const DevSparse &sp, double *E, int t0, int lane)
-{
-    const int n = sp.n, w = n - t0;
-    const bool row = lane < w;
-    const int back = n - t0 - lane;  // entry (t0 + lane, c) = cstart[c + 1] - back
-    const int cend = row ? sp.cstart[t0 + lane + 1] : 0;  // lane j: end of column t0 + j
-    double a[W];
-    // loads at a clamped index and selects (no lane mask per column is kept
-    // alive until the stores)
-#pragma unroll
-    for (int j = 0; j < W; ++j) {
-        const int e = __builtin_amdgcn_readlane(cend, j) - back;
-        const bool ok = j < w && row;
-        const double x = E[ok ? e : 0];
-        a[j] = ok ? x : 0.0;
-    }
-    unrolled<W - 1>([&](auto K) __attribute__((always_inline)) {
-        constexpr int k = K;
-        const double akk = rdlane(a[k], k);
-        const bool sub = row && lane > k;  // a row below the pivot
-        const double l = sub ? a[k] / akk : 0.0;
-        a[k] = sub ? l : a[k];
-        apply_pivot<W, k>(a, l);
-    });
-#pragma unroll
-    for (int j = 0; j < W; ++j) {
-        const int e = __builtin_amdgcn_readlane(cend, j) - back;
-        if (j < w && row) E[e] = a[j];
-    }
-}
-
-// A panel of P <= 16 pivots [t, t + P) of a dense trailing block wider than
-// the 64 rows of the register tail: the panel's columns for all rows of the
-// block in registers (two rows per lane), then the panel's rows of U column
-// per lane, then the rest of the block on the matrix cores.
-__device__ __forceinline__ void lu_panel(const DevSparse &sp, double *E, int t, int P, int lane)
-{
-    constexpr int W = 16;
-    const int n = sp.n, w = n - t;
-    double a[2][W];
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-        const int cend = sp.cstart[min(t + k, n - 1) + 1];
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int i = lane + 64 * s;
-            a[s][k] = k < P && i < w ? E[cend - w + i] : 0.0;
-        }
-    }
-    unrolled<W>([&](auto K) __attribute__((always_inline)) {
-        constexpr int k = K;
-        if (k < P) {
-            const double akk = rdlane(a[0][k], k);
-            const double l0 = lane > k ? a[0][k] / akk : 0.0, l1 = a[1][k] / akk;
-            if (lane > k) a[0][k] = l0;
-            a[1][k] = l1;
-#pragma unroll
-            for (int j = k + 1; j < W; ++j) {
-                const double u = rdlane(a[0][j], k);
-                a[0][j] = fma(-l0, u, a[0][j]);
-                a[1][j] = fma(-l1, u, a[1][j]);
-            }
-        }
-    });
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-        const int cend = sp.cstart[min(t + k, n - 1) + 1];
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int i = lane + 64 * s;
-            if (k < P && i < w) E[cend - w + i] = a[s][k];
-        }
-    }
-    // rows t .. t + P - 1 of the columns beyond the panel: U12 = L11^-1 A12,
-    // L11 broadcast from the lanes that hold it
-#pragma unroll 1
-    for (int j0 = t + P; j0 < n; j0 += WAVE) {
-        const int j = j0 + lane;
-        double *e = E + sp.cstart[min(j, n - 1) + 1] - w;  // entry (t, j)
-        double u[W];
-#pragma unroll
-        for (int k = 0; k < W; ++k) u[k] = k < P && j < n ? e[k] : 0.0;
-        unrolled<W>([&](auto K) __attribute__((always_inline)) {
+        if (r > 0) words(r - 1);
+        double dinv = 0.0;
+        unrolled<16>([&](auto K) __attribute__((always_inline)) {
             constexpr int k = K;
-            if (k < P) {
+            if (k0 + k < n) {
+                const double inv = 1.0 / bcast<16, k>(D[k]);
+                const double l = c > k ? D[k] * inv : 0.0;
+                dinv = c == k ? inv : dinv;
+                D[k] = c > k ? l : D[k];
+                if constexpr (k < 15) {
+                    fmac_row<k>(D[k + 1], l);
+                    constexpr int j0 = k + 2;
 #pragma unroll
-                for (int m = k + 1; m < W; ++m) u[m] = fma(-rdlane(a[0][k], m), u[k], u[m]);
+                    for (int j = j0; j + 3 < 16; j += 4) fmac_row4<k>(D[j], D[j + 1], D[j + 2], D[j + 3], l);
+#pragma unroll
+                    for (int j = j0 + (16 - j0) / 4 * 4; j < 16; ++j) fmac_row<k>(D[j], l);
+#pragma unroll
+                    for (int q = 0; q < Q; ++q)
+                        if (q < r) fmac_row4<k>(u[q][0], u[q][1], u[q][2], u[q][3], l);
+                }
             }
         });
 #pragma unroll
-        for (int k = 0; k < W; ++k)
-            if (k < P && j < n) e[k] = u[k];
+        for (int k = 0; k < 16; ++k) {
+            D[k] *= k > c ? dinv : 1.0;
+            put<VPL>(E, half_of(k < 8 ? id0 : id1, k % 8), D[k]);
+        }
+        if (lane < 16 && k0 + c < n) DINV[k0 + c] = dinv;
+        if (r == 0) break;
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (q < r) {
+#pragma unroll
+                for (int h = 0; h < 4; ++h) put<VPL>(E, half_of(ul[q], h), u[q][h] * dinv);
+            }
+        lds_sync();
+        uint4 ab[VPL == 1 ? Q : 1];
+        uint2 ci[VPL == 1 ? Q : 1][VPL == 1 ? Q : 1];
+        if constexpr (VPL == 1) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (q < r) {
+                    ab[q] = ta[q * WAVE];
+#pragma unroll
+                    for (int q1 = 0; q1 < Q; ++q1)
+                        if (q1 < r) ci[q1][q] = ct[(q1 * r + q) * WAVE];
+                }
+        }
+#pragma unroll
+        for (int k = 0; k < 15; ++k) D[k] = entry<VPL>(E, half_of(k < 8 ? it0 : it1, k % 8));
+        unrolled<15>([&](auto K) __attribute__((always_inline)) {
+            constexpr int k = K;
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (q < r) fmac_row4<k>(x[q][0], x[q][1], x[q][2], x[q][3], D[k]);
+        });
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (q < r) {
+#pragma unroll
+                for (int h = 0; h < 4; ++h) put<VPL>(E, half_of(ul[q], 4 + h), x[q][h]);
+            }
+        lds_sync();
+        auto tile = [&](const uint4 &wa, const uint2 &ci, const double (&B)[4]) __attribute__((always_inline)) {
+            const uint32_t co[4] = {ci.x & 0xffff, ci.x >> 16, ci.y & 0xffff, ci.y >> 16};
+            d4 acc;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] = entry<VPL>(E, co[i]);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) acc = tile_sub(entry<VPL>(E, half_of(wa, s)), B[s], acc);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) put<VPL>(E, co[i], acc[i]);
+        };
+        if constexpr (VPL == 1) {
+#pragma unroll
+            for (int q2 = 0; q2 < Q; ++q2) {
+                if (q2 < r) {
+                    double B[4];
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) B[s] = entry<VPL>(E, half_of(ab[q2], 4 + s));
+#pragma unroll
+                    for (int q1 = 0; q1 < Q; ++q1)
+                        if (q1 < r) tile(ab[q1], ci[q1][q2], B);
+                }
+            }
+        } else {
+            // up to 49 tiles: one loop, a tile's indices loaded during the one before
+            uint4 wa = ta[0], wb = wa;
+            uint2 cn = ct[0];
+            double B[4];
+#pragma unroll 1
+            for (int q = 0; q < r * r; ++q) {
+                const int q1 = q % r, nx = min(q + 1, r * r - 1);
+                if (q1 == 0) {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) B[s] = entry<VPL>(E, half_of(wb, 4 + s));
+                }
+                const uint4 w = wa;
+                const uint2 c2 = cn;
+                wa = ta[nx % r * WAVE];
+                wb = ta[nx / r * WAVE];
+                cn = ct[((nx % r) * r + nx / r) * WAVE];
+                tile(w, c2, B);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (q < r) {
+#pragma unroll
+                for (int h = 0; h < 4; ++h) put<VPL>(E, half_of(ul[q], 4 + h), x[q][h] * dinv);
+            }
+        lds_sync();
     }
-    __syncthreads();
-    const int t1 = t + P;
-    const int c = lane & 15, kk = lane >> 4;
-    lu_schur_wide(
-        sp, E, lane, t1, (P + 3) / 4,
-        [&](int ti, int, double (&v)[16]) {
-            const int i = t1 + 16 * ti + c;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int k = 4 * s + kk;
-                v[s] = k < P && i < n ? E[sp.cstart[t + k + 1] - n + i] : 0.0;
-            }
-        },
-        [&](int tj, int, double (&v)[16]) {
-            const int j = t1 + 16 * tj + c;
-            const double *e = E + sp.cstart[min(j, n - 1) + 1] - w;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int k = 4 * s + kk;
-                v[s] = k < P && j < n ? e[k] : 0.0;
-            }
-        });
+    lds_sync();
 }
 
-// Numeric LU of the formed matrix in E, then dinv = 1/u_kk and the rows of U
-// scaled to a unit diagonal.
 template <int VPL, int G>
-__device__ void lu_v(const DevSparse &sp, double *lds, int lane, Factors<VPL, G> &fac)
+__device__ __forceinline__ void lu_v(const DevSparse &sp, double *lds, int lane, Factors<VPL, G> &fac)
 {
-    double *E = lds + sp.E;
+    constexpr int NV = G * VPL;
+    double *E = lds + SPL_E * NV;
     if constexpr (G < WAVE) {
         lu_group<G>(sp, E, lane, fac);
-        __syncthreads();
-        return;
+        lds_sync();
     } else {
-        double *DINV = lds + sp.DINV;
-        if constexpr (VPL == 1) {
-            // the Schur operands' indices, on their way during the levels
-            uint2 g0[8];
-            const uint2 *g = (const uint2 *)sp.ga + lane;
-#pragma unroll
-            for (int s = 0; s < 8; ++s) g0[s] = 4 * s < sp.dense0 ? g[s * WAVE] : make_uint2(0, 0);
-            lu_levels(sp, E, lane);
-            lu_schur(sp, E, lane, g0);
-            lu_tail<sc::SPARSE_TAIL_MAX>(sp, E, sp.dense0, lane);
-        } else {
-            lu_levels(sp, E, lane);
-            const int t0 = sp.dense0, steps = (t0 + 3) / 4, pad = (steps + 15) / 16 * 16;
-            auto load = [&](const uint16_t *tab, int tile, int s0, double (&v)[16]) {
-                const uint32_t *q = (const uint32_t *)(tab + ((size_t)tile * WAVE + lane) * pad + s0);
-#pragma unroll
-                for (int s = 0; s < 16; s += 2) {
-                    const uint32_t w = q[s / 2];
-                    v[s] = E[w & 0xffff];
-                    v[s + 1] = E[w >> 16];
-                }
-            };
-            lu_schur_wide(
-                sp, E, lane, t0, steps, [&](int ti, int s0, double (&v)[16]) { load(sp.ga, ti, s0, v); },
-                [&](int tj, int s0, double (&v)[16]) { load(sp.gb, tj, s0, v); });
-            int t = t0;
-#pragma unroll 1
-            while (sp.n - t > sc::SPARSE_TAIL_MAX_WIDE) {
-                const int P = min(16, sp.n - t - sc::SPARSE_TAIL_MAX_WIDE);
-                lu_panel(sp, E, t, P, lane);
-                t += P;
-            }
-            lu_tail<sc::SPARSE_TAIL_MAX_WIDE>(sp, E, t, lane);
-        }
-        // the scaling's items, loaded while the diagonal is inverted
-        constexpr int UI = VPL == 1 ? 8 : 16;
-        uint32_t it[UI];
-#pragma unroll
-        for (int u = 0; u < UI; ++u) it[u] = u * WAVE + lane < sp.n_u ? sp.lu_u[u * WAVE + lane] : 0u;
-        __syncthreads();
-#pragma unroll
-        for (int v = 0; v < VPL; ++v) {
-            const int k = lane + WAVE * v;
-            if (k < sp.n) DINV[k] = 1.0 / E[sp.diag[k]];
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int q = 0; q < sp.n_u; q += UI * WAVE) {
-            if (q > 0) {
-#pragma unroll
-                for (int u = 0; u < UI; ++u)
-                    it[u] = q + u * WAVE + lane < sp.n_u ? sp.lu_u[q + u * WAVE + lane] : 0u;
-            }
-            double x[UI];
-#pragma unroll
-            for (int u = 0; u < UI; ++u) x[u] = E[it[u] & 0xffff] * DINV[it[u] >> 16];
-#pragma unroll
-            for (int u = 0; u < UI; ++u)
-                if (q + u * WAVE + lane < sp.n_u) E[it[u] & 0xffff] = x[u];
-        }
-        __syncthreads();
+        lu_blocks<VPL>(sp, E, lds + SPL_DINV * NV, lane);
     }
 }
 
 // Solve M x = b with the factors (b, x: VPL components per lane; a lane holds
-// the same position as component and as row).  The vector is swept in
-// registers, one column of L (then of the unit-diagonal U) at a time: the
-// pivot value is broadcast with readlane and the lanes behind it apply their
-// entry of the column.
-//
-// The chain of 2 n broadcasts and multiply-adds bounds a solve, so nothing
-// else is on it: each lane's entries come eight columns at a time from LDS
-// through a table of its row, ahead of their use, and the lanes are masked by
-// the execution mask.  With each entry's place computed from the column's
-// mask at its turn a column took 189 cycles of a lone wave (53 species).
+// the same position as component and as row), in blocks of 16 columns: the
+// chain through a block's 16 pivots runs inside the row of lanes that holds
+// them, one broadcasting multiply-add a pivot; the block's solution is then
+// spread to all four rows of lanes and the rows behind apply it, four
+// multiply-adds at a time off the chain.  Each lane's entries come a block
+// ahead from LDS through a table of its row (the zero slot where it has none
+// on that side).  (A column took 189 cycles of a lone wave with each entry's
+// place computed from the column's mask at its turn, 56 with the table and a
+// broadcast to the whole wave by two readlanes.)
+template <int VPL>
 __device__ __forceinline__ void sweeps(const DevSparse &sp, const double *E, const double *DINV, int lane,
-                                       double (&z)[1])
+                                       double (&z)[VPL])
 {
+    constexpr int NB = 4 * VPL;
     const int n = sp.n;
-    const uint64_t all = exec_mask();
-    uint4 ix[8];  // byte offsets of the row's entries, 64 columns
-    const uint4 *t = (const uint4 *)(sp.row + 64 * lane);
+    // tables: [slot][lane][64 VPL columns], two words per block
+    const uint4 *tl = (const uint4 *)sp.low + 8 * VPL * lane, *tu = (const uint4 *)sp.up + 8 * VPL * lane;
+    uint4 il[NB][VPL][2], iu[NB][VPL][2];
+    auto index = [&](const uint4 *t, int b, uint4 (&w)[VPL][2]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int b = 0; b < 8; ++b) ix[b] = t[b];
-    const double dinv = lane < n ? DINV[lane] : 0.0;
-    auto load = [&](const uint4 &w, double (&v)[8]) {
-        v[0] = entry<1>(E, w.x & 0xffff);
-        v[1] = entry<1>(E, w.x >> 16);
-        v[2] = entry<1>(E, w.y & 0xffff);
-        v[3] = entry<1>(E, w.y >> 16);
-        v[4] = entry<1>(E, w.z & 0xffff);
-        v[5] = entry<1>(E, w.z >> 16);
-        v[6] = entry<1>(E, w.w & 0xffff);
-        v[7] = entry<1>(E, w.w >> 16);
+        for (int s = 0; s < VPL; ++s) {
+            w[s][0] = t[s * WAVE * 8 * VPL + 2 * b];
+            w[s][1] = t[s * WAVE * 8 * VPL + 2 * b + 1];
+        }
     };
-    double cur[8], nxt[8];
-    load(ix[0], cur);
-    unrolled<8>([&](auto B) __attribute__((always_inline)) {
-        constexpr int b = B;
-        if (8 * b < n) {
-            if constexpr (b < 7) load(ix[b + 1], nxt);
-            unrolled<8>([&](auto D) __attribute__((always_inline)) {
-                constexpr int k = 8 * b + D;
-                if constexpr (k < 63) fma_above<k>(z[0], cur[D], rdlane(z[0], k), all);
-            });
+    auto load = [&](const uint4 (&w)[VPL][2], double (&a)[VPL][16]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int d = 0; d < 8; ++d) cur[d] = nxt[d];
+        for (int s = 0; s < VPL; ++s)
+#pragma unroll
+            for (int k = 0; k < 16; ++k) a[s][k] = entry<VPL>(E, half_of(w[s][k / 8], k % 8));
+    };
+    // the tables' words all at once: one trip to L2
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+        if (16 * b < n) index(tl, b, il[b]);
+#pragma unroll
+    for (int b = NB - 1; b >= 0; --b)
+        if (16 * b < n) index(tu, b, iu[b]);
+    double dinv[VPL];
+#pragma unroll
+    for (int s = 0; s < VPL; ++s) dinv[s] = lane + WAVE * s < n ? DINV[lane + WAVE * s] : 0.0;
+    double a[VPL][16], nx[VPL][16];
+    load(il[0], a);
+    unrolled<NB>([&](auto B) __attribute__((always_inline)) {
+        constexpr int b = B, s = b / 4, g = b % 4;
+        if (16 * b < n) {
+            if constexpr (b + 1 < NB) if (16 * b + 16 < n) load(il[b + 1], nx);
+            unrolled<15>([&](auto K) __attribute__((always_inline)) { fmac_in<K, 1 << g>(z[s], a[s][K]); });
+            if constexpr (b + 1 < NB) {
+                const double xb = spread_row<g>(z[s]);
+                constexpr int behind = 0xf & ~((2 << g) - 1);
+                unrolled<4>([&](auto K) __attribute__((always_inline)) {
+                    if constexpr (behind != 0) fmac_by4<4 * K, behind>(z[s], xb, &a[s][4 * K]);
+                    if constexpr (s + 1 < VPL) fmac_by4<4 * K, 0xf>(z[VPL - 1], xb, &a[VPL - 1][4 * K]);
+                });
+            }
+#pragma unroll
+            for (int v = 0; v < VPL; ++v)
+#pragma unroll
+                for (int k = 0; k < 16; ++k) a[v][k] = nx[v][k];
         }
     });
-    z[0] *= dinv;
-    unrolled<8>([&](auto B) __attribute__((always_inline)) {
-        constexpr int b = 7 - B;
-        if (8 * b < n) {
-            // the block a column at n - 1 lies in is the first one read
-            if (8 * b + 8 >= n) load(ix[b], cur);
-            if constexpr (b > 0) load(ix[b - 1], nxt);
-            unrolled<8>([&](auto D) __attribute__((always_inline)) {
-                constexpr int k = 8 * b + 7 - D;
-                if constexpr (k > 0) fma_below<k>(z[0], cur[7 - D], rdlane(z[0], k), all);
-            });
 #pragma unroll
-            for (int d = 0; d < 8; ++d) cur[d] = nxt[d];
+    for (int s = 0; s < VPL; ++s) z[s] *= dinv[s];
+    unrolled<NB>([&](auto B) __attribute__((always_inline)) {
+        constexpr int b = NB - 1 - B, s = b / 4, g = b % 4;
+        if (16 * b < n) {
+            if (16 * b + 16 >= n) load(iu[b], a);  // the first block taken
+            if constexpr (b > 0) load(iu[b - 1], nx);
+            unrolled<15>([&](auto K) __attribute__((always_inline)) { fmac_in<15 - K, 1 << g>(z[s], a[s][15 - K]); });
+            if constexpr (b > 0) {
+                const double xb = spread_row<g>(z[s]);
+                constexpr int behind = (1 << g) - 1;
+                unrolled<4>([&](auto K) __attribute__((always_inline)) {
+                    if constexpr (behind != 0) fmac_by4<4 * K, behind>(z[s], xb, &a[s][4 * K]);
+                    if constexpr (s > 0) fmac_by4<4 * K, 0xf>(z[0], xb, &a[0][4 * K]);
+                });
+            }
+#pragma unroll
+            for (int v = 0; v < VPL; ++v)
+#pragma unroll
+                for (int k = 0; k < 16; ++k) a[v][k] = nx[v][k];
         }
     });
-}
-
-// Two rows per lane: columns in blocks of eight, their table entries loaded
-// two blocks and their values one block ahead.
-__device__ __forceinline__ void sweeps(const DevSparse &sp, const double *E, const double *DINV, int lane,
-                                       double (&z)[2])
-{
-    const int n = sp.n, nb = (n + 7) / 8;
-    const uint64_t all = exec_mask();
-    const uint4 *t0 = (const uint4 *)(sp.row + 128 * lane), *t1 = t0 + 64 * 16;
-    struct Blk {
-        double a[2][8];
-    };
-    struct Ix {
-        uint4 w[2];
-    };
-    auto index = [&](int b) { return Ix{{t0[b], t1[b]}}; };
-    auto load = [&](const Ix &x) {
-        Blk v;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const uint32_t w[4] = {x.w[s].x, x.w[s].y, x.w[s].z, x.w[s].w};
-#pragma unroll
-            for (int d = 0; d < 8; ++d) v.a[s][d] = E[d % 2 ? w[d / 2] >> 16 : w[d / 2] & 0xffff];
-        }
-        return v;
-    };
-    const double d0 = DINV[lane], d1 = lane + 64 < n ? DINV[lane + 64] : 0.0;
-    // blocks 0 .. nb - 1 forward, then nb - 1 .. 0 backward, one pipeline
-    auto blk = [&](int q) { return min(q < nb ? q : 2 * nb - 1 - q, nb - 1); };
-    Ix ix = index(blk(1));
-    Blk nxt = load(index(0));
-#pragma unroll 1
-    for (int q = 0; q < 2 * nb; ++q) {
-        const Blk cur = nxt;
-        nxt = load(ix);
-        ix = index(max(blk(q + 2), 0));
-        const int k0 = __builtin_amdgcn_readfirstlane(8 * blk(q));
-        if (q == nb) {
-            z[0] *= d0;
-            z[1] *= d1;
-        }
-        if (q < nb) {
-            if (k0 < 64) {
-#pragma unroll
-                for (int d = 0; d < 8; ++d) {
-                    const double zk = rdlane(z[0], k0 + d);
-                    z[1] = fma(-cur.a[1][d], zk, z[1]);
-                    fma_above(z[0], cur.a[0][d], zk, k0 + d, all);
-                }
-            } else {
-#pragma unroll
-                for (int d = 0; d < 8; ++d)
-                    fma_above(z[1], cur.a[1][d], rdlane(z[1], k0 + d - 64), k0 + d - 64, all);
-            }
-        } else if (k0 >= 64) {
-#pragma unroll
-            for (int d = 7; d >= 0; --d) {
-                const double zk = rdlane(z[1], k0 + d - 64);
-                z[0] = fma(-cur.a[0][d], zk, z[0]);
-                fma_below(z[1], cur.a[1][d], zk, k0 + d - 64, all);
-            }
-        } else {
-#pragma unroll
-            for (int d = 7; d >= 0; --d) fma_below(z[0], cur.a[0][d], rdlane(z[0], k0 + d), k0 + d, all);
-        }
-    }
 }
 
 template <int VPL, int G>
-__device__ void solve_v(const DevMech &m, const DevSparse &sp, double *lds, const Factors<VPL, G> &fac,
+__device__ __forceinline__ void solve_v(const DevMech &m, const DevSparse &sp, double *lds, const Factors<VPL, G> &fac,
                         const double (&b)[VPL], int lane, double (&x)[VPL])
 {
     const int N = m.N;
     // scaled unknowns z_k = x_k / W_k; the sigma row's right-hand side is zero
-    double z[VPL];
+    double z[VPL], W[VPL];
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int c = lane + G * v;
-        z[v] = c < N ? b[v] * m.invW()[c] : c == N ? b[v] : 0.0;
+        const double iw = c < N ? m.invW()[c] : c == N ? 1.0 : 0.0;
+        W[v] = c < N ? m.W()[c] : c == N ? 1.0 : 0.0;  // loaded ahead of the sweeps
+        z[v] = b[v] * iw;
     }
     if constexpr (G < WAVE)
         sweeps_group<G>(sp, fac, lane, z[0]);
     else
-        sweeps(sp, lds + sp.E, lds + sp.DINV, lane, z);
+        sweeps<VPL>(sp, lds + SPL_E * G * VPL, lds + SPL_DINV * G * VPL, lane, z);
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int c = lane + G * v;
-        x[v] = c < N ? z[v] * m.W()[c] : c == N ? z[v] : 0.0;
+        x[v] = c <= N ? z[v] * W[v] : 0.0;
     }
 }
 
@@ -1096,13 +1075,13 @@ __device__ void solve_v(const DevMech &m, const DevSparse &sp, double *lds, cons
 // one Rosenbrock attempt and the integration of a cell
 // ---------------------------------------------------------------------------
 template <int VPL, int G = WAVE>
-__device__ void ros_attempt_v(const DevMech &m, const DevSparse &sp, const Opts &o, double *lds,
+__device__ __forceinline__ void ros_attempt_v(const DevMech &m, const DevSparse &sp, const Opts &o, double *lds,
                               const double (&y)[VPL], double p, const double *dlnA, int lane, double hc, double *err,
                               double (&ynew)[VPL])
 {
     const int n = m.N + 1;
-    double *U = lds + sp.U;
-    const int NV = sp.NV;
+    constexpr int NV = G * VPL;
+    double *U = lds + SPL_U * NV;
     double f0[VPL], flast[VPL];
     jac_v<VPL, G>(m, sp, lds, y, p, dlnA, lane, 1.0 / (GAM * hc), f0);
     Factors<VPL, G> fac;
@@ -1163,7 +1142,7 @@ __device__ void ros_attempt_v(const DevMech &m, const DevSparse &sp, const Opts 
 }
 
 template <int VPL, int G = WAVE>
-__device__ int advance_v(const DevMech &m, const DevSparse &sp, const Opts &o, double *lds, double (&y)[VPL],
+__device__ __forceinline__ int advance_v(const DevMech &m, const DevSparse &sp, const Opts &o, double *lds, double (&y)[VPL],
                          double p, double dt, const double *dlnA, int lane, Ctl &s)
 {
 #pragma unroll 1
@@ -1311,6 +1290,19 @@ __global__ void __launch_bounds__(WAVE) SP_OCC k_integrate_sp_static(DevMech mk,
                                  nrej, ref);
 }
 
+// Doubles of one cell's LDS in the right-hand side kernel: the pairs and the
+// Euler accumulator, without the L+U entries (2.5 KB a cell instead of 19 at
+// 53 species, so registers bound the waves in flight: 16 a CU instead of 8).
+template <int VPL, int G>
+constexpr int rhs_region() { return 5 * G * VPL + (G == 32 ? 16 : 0); }
+
+// Consecutive workgroups go to the eight dies in turn; the eight cells of a
+// 64-byte line of the state go to one, which reads the line once.
+__device__ __forceinline__ int64_t line_cell(int64_t b, int64_t n)
+{
+    return b / 64 * 64 + 64 <= n ? b / 64 * 64 + b % 8 * 8 + b / 8 % 8 : b;
+}
+
 template <int VPL, bool CV, int CPW, bool TB>
 __global__ void __launch_bounds__(WAVE) k_rhs_sp(DevMech mk, DevSparse spk, int64_t n, const double *T,
                                                  const double *P, const double *Y, int64_t ld, const double *dlnA,
@@ -1319,8 +1311,10 @@ __global__ void __launch_bounds__(WAVE) k_rhs_sp(DevMech mk, DevSparse spk, int6
     extern __shared__ double lds[];
     const DevMech m = fix_reactor<CV>(mk);
     const DevSparse sp = fix_tables<TB>(spk);
-    SP_GEOMETRY
-    const int64_t c = (int64_t)blockIdx.x * CPW + grp;
+    constexpr int G = WAVE / CPW;
+    const int lane = (int)threadIdx.x % G, grp = (int)threadIdx.x / G;
+    double *ldsg = lds + grp * rhs_region<VPL, G>();
+    const int64_t c = line_cell(blockIdx.x, gridDim.x) * CPW + grp;
     if (c >= n) return;
     double y[VPL], f[VPL];
     load_state_v<VPL, G>(m, sp, T, Y, ld, c, lane, y);
@@ -1347,23 +1341,37 @@ __global__ void __launch_bounds__(WAVE) k_jac_sp(DevMech mk, DevSparse spk, int6
     double y[VPL], f[VPL];
     load_state_v<VPL, G>(m, sp, T, Y, ld, c, lane, y);
     jac_v<VPL, G>(m, sp, ldsg, y, P[c], dlnA, lane, 0.0, f);
-    const double *E = ldsg + sp.E;
-    const int N = m.N, nn = N + 1, ns = sp.n;
-    const int pS = ns - 1;
-    auto A = [&](int pi, int pj) {
-        const uint16_t e = sp.emap[pi * ns + pj];
-        return e == sc::NOENT ? 0.0 : E[e];
-    };
+    // a row at a time, columns across the lanes (species order); what depends
+    // on the column only is taken once
+    const double *E = ldsg + SPL_E * G * VPL;
+    const int N = m.N, nn = N + 1;
+    double cj[VPL], sj[VPL];
+#pragma unroll
+    for (int v = 0; v < VPL; ++v) {
+        const int j = lane + G * v;
+        cj[v] = j < N ? m.invW()[sp.pos[j]] : 1.0;
+        sj[v] = j < N ? E[sp.comp[8 * sp.pos[j] + 4]] : 0.0;
+    }
 #pragma unroll 1
-    for (int q = lane; q < nn * nn; q += G) {
-        const int i = q / nn, j = q % nn;
-        const int pi = sp.pos[i], pj = sp.pos[j];
-        double val;
-        if (i < N && j < N) val = -(m.W()[pi] * m.invW()[pj]) * (A(pi, pj) + A(pi, pS) * A(pS, pj));
-        else if (i < N) val = -m.W()[pi] * A(pi, pj);
-        else if (j < N) val = -A(pi, pj) * m.invW()[pj];
-        else val = -A(pi, pj);
-        J[(c * nn + i) * nn + j] = val;
+    for (int i0 = 0; i0 < nn; i0 += 6) {
+        uint16_t e[6][VPL];
+        double a[6], w[6];
+#pragma unroll
+        for (int d = 0; d < 6; ++d) {
+            const int i = min(i0 + d, N), pi = sp.pos[i];
+            a[d] = i < N ? E[sp.comp[8 * pi + 2]] : 0.0;
+            w[d] = i < N ? m.W()[pi] : 1.0;
+#pragma unroll
+            for (int v = 0; v < VPL; ++v) e[d][v] = sp.jmap[i * nn + min(lane + G * v, N)];
+        }
+#pragma unroll
+        for (int d = 0; d < 6; ++d)
+#pragma unroll
+            for (int v = 0; v < VPL; ++v) {
+                const int j = lane + G * v;
+                if (i0 + d < nn && j < nn)
+                    J[(c * nn + i0 + d) * nn + j] = -(w[d] * cj[v]) * (E[e[d][v]] + a[d] * sj[v]);
+            }
     }
 }
 
@@ -1427,8 +1435,9 @@ hipError_t launch_rhs_sp(int vpl, const DevMech &m, const DevSparse &sp, int64_t
                          hipStream_t s)
 {
     const int cpw = sp.cpw;
-    SP_DISPATCH(hipLaunchKernelGGL(SP_KERNEL(k_rhs_sp), dim3(sp_blocks(n, cpw)), dim3(WAVE), sp_lds(sp, cpw), s, m,
-                                   sp, n, T, p, Y, ld, dlnA, fT, fY))
+    SP_DISPATCH(hipLaunchKernelGGL(SP_KERNEL(k_rhs_sp), dim3(sp_blocks(n, cpw)), dim3(WAVE),
+                                   (sizeof(double) * rhs_region<VPLV, WAVE / CPWV>() * cpw), s, m, sp, n, T, p, Y, ld,
+                                   dlnA, fT, fY))
 }
 
 hipError_t launch_jac_sp(int vpl, const DevMech &m, const DevSparse &sp, int64_t n, const double *T,
