@@ -211,9 +211,10 @@ SparseDev sparse_device(const Mech &m, int lanes);
 // Falloff reactions come first, then third-body ones, then the rest, each by
 // coefficients and side sizes, so that what only some reactions need is in
 // as few passes as can be.  Unused slots name a dummy species (index N + 1:
-// concentration 1, g = h = 0) and trash entries, so a pass has no per-lane
-// branches; what a whole pass does not need is skipped by the flags, which
-// every record of the pass carries.
+// concentration 1, g = h = 0) and trash entries, so the arithmetic has no
+// per-lane branches; what a whole pass does not need is skipped by the flags,
+// which every record of the pass carries, and a lane adds only for the slots
+// in use (coefficient above zero).
 constexpr int RXW_WORDS = 3;  // lnA, b, Ea/R; side species (byte offsets, 16 per species); bits; enhanced species; index
 constexpr int RXW_IX = 6;     // entries: six rows of six slots and T, then the T row
 constexpr int RXW_IXE = 4;    // entries of the enhanced species: six rows of four, then the T row

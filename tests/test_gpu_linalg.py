@@ -1,8 +1,8 @@
 """The sparse kernels' factorisation and solves at the edges of their parts:
-rows in registers (two and four cells per wave), the dense Schur product with
-one, several and partly filled steps of four pivots and tiles of 16, the
-32-wide register tail, and blocks wider than the 64-row tail (one panel and
-several).  The solution of (I/hg - J) x = b is checked against the matrix
+rows in registers (two and four cells per wave); blocks of 16 pivots with one
+state component per lane, the last one partly filled (n = 26, 57) and full
+(64), and with two (n = 65, 112 and 128: a block of one pivot, full ones and
+the largest).  The solution of (I/hg - J) x = b is checked against the matrix
 from the oracle's complex-step Jacobian by its normwise backward error.  An
 unpivoted LU of a matrix whose diagonal dominates (small hg) has growth near
 one, so the bound is the usual n eps with a margin of about ten for the
@@ -12,17 +12,16 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-# species, reactions, pool fraction, seed, cells per wave: positions N + 2,
-# first position of the dense block and its width
+# species, reactions, pool fraction, seed, cells per wave: positions N + 2
 MECHS = {
     "4 cells, n = 16": (14, 56, 0.15, 401, 4),
     "2 cells, n = 32": (30, 150, 0.3, 402, 2),
-    "1 cell, n = 26, dense from 5": (24, 120, 0.5, 400, 1),
-    "n = 57, dense from 30 (27 wide)": (55, 330, 0.15, 400, 1),
-    "n = 64, dense from 32, 24 levels": (62, 900, 0.6, 1, 1),
-    "n = 65, dense from 30 (35 wide)": (63, 400, 0.15, 400, 1),
-    "n = 112, dense from 38: one panel": (110, 700, 0.15, 110, 1),
-    "n = 128, dense from 27: three panels": (126, 2500, 0.5, 4, 1),
+    "1 cell, n = 26": (24, 120, 0.5, 400, 1),
+    "n = 57": (55, 330, 0.15, 400, 1),
+    "n = 64": (62, 900, 0.6, 1, 1),
+    "n = 65": (63, 400, 0.15, 400, 1),
+    "n = 112": (110, 700, 0.15, 110, 1),
+    "n = 128": (126, 2500, 0.5, 4, 1),
 }
 
 
