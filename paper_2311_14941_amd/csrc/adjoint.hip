@@ -131,35 +131,6 @@ __device__ double vjp(const DevMech &m, double *lds, S y, double p, const double
     return part(g);
 }
 
-// Solve (L U)^T x = b with the factors parked column-major in F: U^T z = b,
-// then L^T x = z.  Row k of U (of L) is column k of the transposed factor:
-// lane j reads F[j FS + k], a stride of FS doubles, which is odd, so the 64
-// reads fall on different banks; the solved unknown is broadcast with
-// readlane and every lane behind it applies its entry.  (As dot products over
-// the stored columns instead, every unknown waited for a wave reduction: 112
-// of them one after another per solve.)
-template <int NP>
-__device__ __forceinline__ double lu_solve_T(const double *F, double dinv, double b, int lane)
-{
-    const double *Fr = F + (lane < NP ? lane : 0) * Lds<NP>::PS;
-#pragma unroll
-    for (int k = 0; k < NP; ++k) {
-        const double u = Fr[k];  // U_kj in lane j
-        if (lane == k) b *= dinv;
-        const double z = rdlane(b, k);
-        if (lane > k) b = fma(-u, z, b);
-        SC_FENCE_EVERY(k);
-    }
-#pragma unroll
-    for (int k = NP - 1; k > 0; --k) {
-        const double l = Fr[k];  // L_kj in lane j
-        const double x = rdlane(b, k);
-        if (lane < k) b = fma(-l, x, b);
-        SC_FENCE_EVERY(NP - 1 - k);
-    }
-    return lane < NP ? b : 0.0;
-}
-
 // Reverse one replayed step: the attempt from y with size hc has just left
 // its stage vectors in U and its factors in F (dinv = 1/U_ii of this lane).
 // Returns lambda_n from lambda_{n+1}; adds the parameter adjoint to TH.
@@ -181,7 +152,7 @@ __device__ double step_adjoint(const DevMech &m, double *lds, double y, double p
     double lnew = lam;
 #pragma unroll 1
     for (int i = NS - 1; i >= 0; --i) {
-        const double w = lu_solve_T<NP>(F, dinv, lane < n ? UB[i * WAVE + lane] : 0.0, lane);
+        const double w = lu_solve<NP, true>(F, dinv, lane < n ? UB[i * WAVE + lane] : 0.0, lane);
         WS[i * WAVE + lane] = w;
         for (int j = 0; j < i; ++j) UB[j * WAVE + lane] += (TC[i][j] * ih) * w;
         const int reuse = TREUSE[i];

@@ -30,7 +30,8 @@ struct sc_plan {
     scdev::DevSparse ds{};
     std::vector<void *> allocs;
     unsigned long long *queue = nullptr;
-    int capacity = 0;
+    int capacity = 0;            // resident workgroups of the persistent kernel
+    int capacity_static = 0;     // and of the static one
     void *order_ws = nullptr;  // cell-ordering workspace (grown on demand)
     size_t order_ws_bytes = 0;
     int adj_capacity = 0;        // resident waves of the adjoint kernel
@@ -474,6 +475,25 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
              upload(p, sd.low, &q.low) && upload(p, sd.up, &q.up) &&
              upload(p, sd.blk, &q.blk);
     }
+    if (ok && nstate <= sc::MAX_STATE) {
+        sc::SparseRx dx;
+        std::vector<scdev::TroeRec> trd;
+        try {
+            dx = sc::dense_reactions(p->m);
+            trd.resize(dx.n_troe);
+        } catch (...) {
+            release(p);
+            delete p;
+            return fail(SC_ENOMEM, "host allocation failed");
+        }
+        for (int k = 0; k < dx.n_troe; ++k) std::memcpy(&trd[k], &dx.troe[8 * (size_t)k], sizeof(scdev::TroeRec));
+        scdev::DevRx &q = p->dm.pass;
+        q.passes = dx.passes;
+        q.n_tb = dx.n_tb;
+        q.n_troe = dx.n_troe;
+        ok = upload(p, dx.rec, &q.rec) && upload(p, dx.ix, &q.ix) && upload(p, dx.ixe, &q.ixe) &&
+             upload(p, dx.eam1, &q.eam1) && upload(p, trd, &q.troe);
+    }
     if (ok) {
         void *q = nullptr;
         ok = hipMalloc(&q, sizeof(unsigned long long)) == hipSuccess;
@@ -487,7 +507,10 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
         delete p;
         return fail(SC_ENOMEM, "device allocation/upload failed");
     }
-    p->capacity = sparse ? scdev::persistent_capacity_sp(vpl, p->ds, device) : scdev::persistent_capacity(p->np, device);
+    if (sparse)
+        scdev::capacity_sp(vpl, p->ds, device, p->capacity, p->capacity_static);
+    else
+        p->capacity = p->capacity_static = scdev::persistent_capacity(p->np, device);
     p->adj_capacity = nstate <= sc::MAX_STATE ? scdev::adjoint_capacity(p->np, d.R, device) : 0;
     *out = p;
     return SC_OK;
@@ -589,6 +612,7 @@ static sc_status integrate_impl(sc_plan *plan, int64_t n, const double *T0, cons
         int grid = plan->opt.grid > 0 ? plan->opt.grid : plan->capacity;
         if (grid <= 0) grid = 1;
         if (grid > tiles) grid = (int)tiles;
+        if (plan->sparse) grid = std::min(grid, 1 << 22);  // four waves each, within a launch's 2^32 threads
         int32_t *perm = nullptr;
         if (plan->opt.order != SC_ORDER_NONE) {
             if (noalloc)
@@ -598,7 +622,7 @@ static sc_status integrate_impl(sc_plan *plan, int64_t n, const double *T0, cons
                                        &perm, st);
             if (e != hipSuccess) return hip_fail(e, "cell ordering");
         }
-        e = scdev::launch_zero_u64(queue, st);
+        e = scdev::launch_set_u64(queue, plan->sparse ? scdev::queue_start_sp(plan->vpl, plan->ds, grid, tile) : 0, st);
         if (e == hipSuccess && plan->sparse)
             e = scdev::launch_integrate_sp_persistent(plan->vpl, plan->dms, plan->ds, o, n, T0, p, Y0, ld, dt, dlnA,
                                                       h_io, T1, Y1, cell_status, n_acc, n_rej, queue, perm, tile,
@@ -608,7 +632,7 @@ static sc_status integrate_impl(sc_plan *plan, int64_t n, const double *T0, cons
                                                    dlnA, h_io, T1, Y1, cell_status, n_acc, n_rej, queue, perm, tile,
                                                    grid, ref, st);
     } else if (plan->opt.mode == SC_MODE_STATIC) {
-        int grid = plan->opt.grid > 0 ? plan->opt.grid : plan->capacity;
+        int grid = plan->opt.grid > 0 ? plan->opt.grid : plan->capacity_static;
         if (grid <= 0) grid = 1;
         if (grid > n) grid = (int)n;
         if (plan->sparse)
@@ -619,7 +643,7 @@ static sc_status integrate_impl(sc_plan *plan, int64_t n, const double *T0, cons
                                                h_io, T1, Y1, cell_status, n_acc, n_rej, grid, ref, st);
     } else if (plan->sparse) {
         e = scdev::launch_integrate_sp(plan->vpl, plan->dms, plan->ds, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1,
-                                       cell_status, n_acc, n_rej, ref, st);
+                                       cell_status, n_acc, n_rej, ref, plan->capacity, st);
     } else {
         e = scdev::launch_integrate(plan->np, plan->dm, o, plan->opt.method, n, T0, p, Y0, ld, dt, dlnA, h_io, T1,
                                     Y1, cell_status, n_acc, n_rej, ref, st);
@@ -807,7 +831,7 @@ sc_status sc_adjoint(sc_plan *plan, int64_t n, const double *T0, const double *p
         if (e != hipSuccess) return hip_fail(e, "cell ordering");
         used += plan->order_ws_bytes;
     }
-    e = scdev::launch_zero_u64(plan->queue, st);
+    e = scdev::launch_set_u64(plan->queue, 0, st);
     if (e != hipSuccess) return hip_fail(e, "queue reset");
     const int64_t hcap = ((int64_t)plan->opt.max_steps + 31) / 32 * 32;
     e = scdev::launch_adjoint(plan->np, plan->dm, o, n, T0, p, Y0, ld, dt, dlnA, h0, gT1, gY1, gT0, gY0, gcell,

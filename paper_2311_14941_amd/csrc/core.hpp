@@ -24,6 +24,8 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
+#include <utility>
 
 #include "devmech.hpp"
 
@@ -112,7 +114,134 @@ __device__ __forceinline__ double group_sum(double v)
 
 __device__ __forceinline__ double wave_sum(double v) { return group_sum<WAVE>(v); }
 
+// v from lane K of each cell's group, K known at compile time: a row
+// broadcast of the DPP unit for 16 lanes; for 32, readlane of both groups and
+// a select.
+template <int G, int K>
+__device__ __forceinline__ double bcast(double v)
+{
+    static_assert(G == 16 || G == 32, "groups of several cells per wave");
+    if constexpr (G == 16) {
+        const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x150 + K, 0xf, 0xf, true);
+        const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x150 + K, 0xf, 0xf, true);
+        return __hiloint2double(hi, lo);
+    } else {
+        const double a = rdlane(v, K), b = rdlane(v, 32 + K);
+        return threadIdx.x & 32 ? b : a;
+    }
+}
+
+// z -= a z_K, z_K from lane K of the row of 16 lanes: one instruction (the
+// broadcast reads a register two wait states after it was written)
+template <int K>
+__device__ __forceinline__ void fmac_row(double &z, double a)
+{
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, -%1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+&v"(z) : "v"(a), "n"(K));
+}
+// the same for four vectors
+template <int K>
+__device__ __forceinline__ void fmac_row4(double &x, double &y, double &z, double &w, double a)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %0, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %1, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %2, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %3, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+        : "+&v"(x), "+&v"(y), "+&v"(z), "+&v"(w)
+        : "v"(a), "n"(K));
+}
+// z -= a z_K on the lanes of the rows in ROWS
+template <int K, int ROWS>
+__device__ __forceinline__ void fmac_in(double &z, double a)
+{
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, -%1 row_newbcast:%2 row_mask:%3 bank_mask:0xf"
+        : "+&v"(z)
+        : "v"(a), "n"(K), "n"(ROWS));
+}
+// z -= a x_K, x_K from lane K of the row
+template <int K>
+__device__ __forceinline__ void fmac_from(double &z, double x, double a)
+{
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, -%2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+        : "+&v"(z)
+        : "v"(x), "v"(a), "n"(K));
+}
+// x, y, z, w -= a times lane K of p, q, r, s
+template <int K>
+__device__ __forceinline__ void fmac_from4(double &x, double &y, double &z, double &w, double p, double q, double r,
+                                           double s, double a)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %4, -%8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %5, -%8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %6, -%8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %7, -%8 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+        : "+&v"(x), "+&v"(y), "+&v"(z), "+&v"(w)
+        : "v"(p), "v"(q), "v"(r), "v"(s), "v"(a), "n"(K));
+}
+// z -= sum a[i] x_{K + i}, i = 0..3, on the lanes of the rows in ROWS
+template <int K, int ROWS>
+__device__ __forceinline__ void fmac_by4(double &z, double x, const double *a)
+{
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %1, -%2 row_newbcast:%6 row_mask:%10 bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, -%3 row_newbcast:%7 row_mask:%10 bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, -%4 row_newbcast:%8 row_mask:%10 bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, -%5 row_newbcast:%9 row_mask:%10 bank_mask:0xf"
+        : "+&v"(z)
+        : "v"(x), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "n"(K), "n"(K + 1), "n"(K + 2), "n"(K + 3), "n"(ROWS));
+}
+// the lanes of row B of 16 in every row
+template <int B>
+__device__ __forceinline__ double spread_row(double v)
+{
+    auto half = [](int x) __attribute__((always_inline)) {
+        const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        const int y = B & 1 ? a[1] : a[0];
+        const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+        return (int)(B & 2 ? b[1] : b[0]);
+    };
+    return __hiloint2double(half(__double2hiint(v)), half(__double2loint(v)));
+}
+
+// f(0), ..., f(N - 1) with compile-time arguments
+template <int N, class F, int... I>
+__device__ __forceinline__ void unrolled_(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F &&f)
+{
+    unrolled_<N>(f, std::make_integer_sequence<int, N>{});
+}
+
+
 __device__ __forceinline__ void wave_sync() { __syncthreads(); }
+
+// Order between the LDS accesses of the wave's lanes.  A workgroup is one
+// wave, whose LDS instructions take effect in order: the compiler must not
+// move them across, but nothing has to be waited for (a workgroup barrier's
+// fence also waits for the loads sent ahead).
+__device__ __forceinline__ void lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Who works on a cell: here the one wave; the sparse kernels also know crews.
+struct Solo {
+    static constexpr int w = 1, rank = 0;
+    __device__ __forceinline__ void sync() const { lds_sync(); }
+    __device__ __forceinline__ void barrier() const {}
+    __device__ __forceinline__ void start(const DevRx &) const {}
+    __device__ __forceinline__ int first(const DevRx &sp) const { return sp.passes - 1; }
+    __device__ __forceinline__ int next(const DevRx &, int q) const { return q - 1; }
+    __device__ __forceinline__ void await(int) const {}
+    __device__ __forceinline__ void pass_on(int) const {}
+};
+
 
 // ---------------------------------------------------------------------------
 // Dual numbers (value, directional derivative): the chemistry below is
@@ -218,15 +347,21 @@ struct Lds {
     static constexpr int P = 0;          // NP x PS Jacobian terms, later the LU factors (stride NP)
     // the term region is also where the adjoint's dual passes keep the
     // derivatives of C, G, H, WD and of its own V vector (each at a fixed
-    // offset -C from the value), which ends 8 NP + NS WAVE doubles in
-    static constexpr int PREG = NP * PS > 8 * NP + NS * WAVE ? NP * PS : 8 * NP + NS * WAVE;
+    // offset -C from the value), which ends RXV + 2 NP + (NS + 1) WAVE doubles in
+    static constexpr int NV = WAVE + 2;     // species and dummy of the reaction passes, even
+    static constexpr int RXV = 5 * NV;      // their pairs and Euler terms
+    static constexpr int DUAL = RXV + 2 * NP + (NS + 1) * WAVE;
+    static constexpr int PREG = NP * PS > DUAL ? NP * PS : DUAL;
+    // the passes' vectors; the adjoint's products have theirs in the same place
+    static constexpr int RX = PREG;
     static constexpr int C = PREG;       // concentrations
     static constexpr int G = C + NP;     // g/RT
     static constexpr int H = G + NP;     // h/RT
     static constexpr int WD = H + NP;    // production-rate accumulator
     static constexpr int UA = WD + NP;   // Euler-term accumulator
-    static constexpr int IW = UA + NP;   // 1/W_c (0 for c >= N)
-    static constexpr int U = IW + NP;    // NS stage vectors, WAVE apart
+    static_assert(5 * NP <= RXV && PREG % 2 == 0, "the passes' pairs are read in one");
+    static constexpr int IW = RX + RXV;  // 1/W_c (0 for c >= N)
+    static constexpr int U = IW + WAVE;  // NS stage vectors, WAVE apart
     static constexpr int SIZE = U + NS * WAVE;
 };
 
@@ -265,9 +400,9 @@ __device__ __forceinline__ Thermo<S> nasa7(const DevMech &m, int k, S T, S lnT, 
 // writes C, g/RT, h/RT to LDS and clears the accumulators.  With S = Dual
 // the derivatives go toff doubles beyond the values.  p is the pressure, or
 // in a constant-volume reactor the density.
-template <int NP, class S = double>
-__device__ __forceinline__ Mix<S> mixture(const DevMech &m, double *lds, S y, double p, Thermo<S> &th, int lane,
-                                          int toff = 0)
+// the point itself; yw: the lane's Y/W
+template <class S>
+__device__ __forceinline__ Mix<S> mixture_point(const DevMech &m, S y, double p, Thermo<S> &th, int lane, S &yw)
 {
     const int N = m.N;
     Mix<S> x;
@@ -275,7 +410,8 @@ __device__ __forceinline__ Mix<S> mixture(const DevMech &m, double *lds, S y, do
     x.invT = 1.0 / x.T;
     x.lnT = log(x.T);
     x.p = p;
-    S yw = 0.0, cpw = 0.0;
+    yw = 0.0;
+    S cpw = 0.0;
     th = Thermo<S>{0.0, 0.0, 0.0, 0.0};
     if (lane < N) {
         th = nasa7<S>(m, lane, x.T, x.lnT, x.invT);
@@ -291,6 +427,15 @@ __device__ __forceinline__ Mix<S> mixture(const DevMech &m, double *lds, S y, do
     } else {
         x.rho = p * x.Wbar * x.invT / m.Rgas;
     }
+    return x;
+}
+template <int NP, class S = double>
+__device__ __forceinline__ Mix<S> mixture(const DevMech &m, double *lds, S y, double p, Thermo<S> &th, int lane,
+                                          int toff = 0)
+{
+    const int N = m.N;
+    S yw;
+    const Mix<S> x = mixture_point(m, y, p, th, lane, yw);
     if (lane < N) {
         lds_put(lds, Lds<NP>::C + lane, x.rho * yw, toff);
         lds_put(lds, Lds<NP>::G + lane, th.hRT - th.sR, toff);
@@ -471,86 +616,360 @@ __device__ __forceinline__ RxOut<S> reaction(const DevMech &m, const double *lds
     return o;
 }
 
-// Scatter a reaction's contributions: production rates (always) and, in the
-// Jacobian pass, the sparse analytical terms of every (row, slot) pair, the
-// temperature column and (weighted by the reaction enthalpy) the temperature row.
-template <int NP, bool JAC>
-__device__ __forceinline__ void scatter(const DevMech &m, double *lds, const RxRec &rr, const RxOut<> &o, double dHJ)
+// Address of species c's pair in the pair array at place `at` (SPL_CG, SPL_HW)
+template <int NV>
+__device__ __forceinline__ double *pair(double *lds, int at, int c)
 {
-    const int N = m.N;
-    const int nr = rr.nr, np = rr.np;
-    double *P = lds + Lds<NP>::P;
-    int col[sc::NDEP];
-    bool use[sc::NDEP];
-    if (JAC) {
-        const int ne = rr.neff;
+    return lds + at * NV + 2 * c;
+}
+
+// One pass's record of this lane's reaction (SparseRx): three 16-byte words.
+struct Rec {
+    uint4 a, b, c;
+    __device__ __forceinline__ double lnA() const { return __hiloint2double(a.y, a.x); }
+    __device__ __forceinline__ double bT() const { return __hiloint2double(a.w, a.z); }
+    __device__ __forceinline__ double EaR() const { return __hiloint2double(b.y, b.x); }
+    __device__ __forceinline__ uint32_t slot(int i) const  // byte offset of a side species' pair
+    {
+        const uint32_t w = i < 2 ? b.z : i < 4 ? b.w : c.x;
+        return i % 2 ? w >> 16 : w & 0xffff;
+    }
+    __device__ __forceinline__ uint32_t bits() const { return c.y; }
+    __device__ __forceinline__ int nu(int i) const { return (c.y >> (2 * i)) & 3; }
+    __device__ __forceinline__ int dnu() const { return (int)((c.y >> 12) & 31) - 16; }
+    __device__ __forceinline__ int order(int side) const { return (c.y >> (17 + 4 * side)) & 15; }
+    __device__ __forceinline__ int kind() const { return (c.y >> 25) & 3; }
+    __device__ __forceinline__ uint32_t enh(int e) const { return ((c.z >> (8 * e)) & 0xff) << 4; }
+    __device__ __forceinline__ int orig() const { return c.w; }
+};
+template <int G>
+__device__ __forceinline__ Rec load_rx(const DevRx &sp, int pass, int lane)
+{
+    const uint4 *q = (const uint4 *)sp.rec + (size_t)pass * sc::RXW_WORDS * G + lane;
+    return Rec{q[0], q[G], q[2 * G]};
+}
+
+// One reaction's rate of progress and, with JAC, its derivatives: d[0..5] with
+// respect to the side species' concentrations (what an unused slot holds goes
+// to the trash), dqM with respect to [M] (dq/dC of an enhanced species is dqM
+// times its alpha - 1), dT at fixed C, euler (the Euler remainder, or dqM in a
+// constant-volume reactor) and the reaction enthalpy / RT.  The arithmetic is
+// reaction()'s; the Euler remainder q - sum C dq/dC is taken from the
+// reaction's orders (C d(C^nu)/dC = nu C^nu).
+struct RxTerms {
+    double q, d[6], dqM, ea[sc::MAXENH], dT, euler, dH;
+};
+template <bool JAC, int NV>
+__device__ __forceinline__ RxTerms reaction_sp(const DevMech &m, const DevRx &sp, int ideg, double *lds, const Rec &r,
+                                               uint32_t flags, int j, const Mix<> &x, double dl, const double *itb,
+                                               double itt)
+{
+    RxTerms o;
+    double c[6], p[6], dp[6], nu[6];
+    double dG = 0.0, dH = 0.0;
+    // a falloff pass's other tables, loaded ahead of the work (they come from L2)
+    TroeRec tr;
+    if ((flags & sc::RXF_TROE) && j < sp.n_troe) tr = sp.troe[j];
+    if (flags & sc::RXF_TB) {
 #pragma unroll
-        for (int i = 0; i < sc::MAXSIDE; ++i) {
-            use[i] = i < nr;
-            col[i] = use[i] ? rr.rsp[i] : 0;
-            use[3 + i] = i < np;
-            col[3 + i] = use[3 + i] ? rr.psp[i] : 0;
-        }
+        for (int e = 0; e < sc::MAXENH; ++e) o.ea[e] = j < sp.n_tb ? sp.eam1[4 * j + e] : 0.0;
+    }
+    const double lnkinf = r.lnA() + dl + r.bT() * x.lnT - r.EaR() * x.invT;
+    const double kinf = exp(lnkinf);
+    const char *cg = (const char *)(lds + SPL_CG * NV), *hw = (const char *)(lds + SPL_HW * NV);
+    double g[6], h[6];
 #pragma unroll
-        for (int e = 0; e < sc::MAXENH; ++e) {
-            use[6 + e] = e < ne;
-            col[6 + e] = use[6 + e] ? rr.esp[e] : 0;
+    for (int i = 0; i < 6; ++i) {
+        const double2 v = *(const double2 *)(cg + r.slot(i));
+        c[i] = v.x;
+        g[i] = v.y;
+        if (JAC) h[i] = *(const double *)(hw + r.slot(i));
+        p[i] = c[i];
+        dp[i] = nu[i] = 1.0;
+    }
+    if (flags & sc::RXF_NU) {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            const int v = r.nu(i);
+            nu[i] = v;
+            const double c2 = c[i] * c[i];
+            p[i] = v == 2 ? c2 : v == 3 ? c2 * c[i] : c[i];
+            dp[i] = v == 2 ? 2.0 * c[i] : v == 3 ? 3.0 * c2 : 1.0;
         }
     }
-    // rows: reactants then products, unrolled over the slots so that the
-    // record's species and coefficients stay in registers (a rolled loop
-    // indexes them at run time and reloads them from memory every row)
+    if (itb) {
+        const double *itc = itb + (size_t)min(j, m.R - 1) * 2 * (ideg + 1);
+        dG = -poly_t(itc, ideg, itt);
+        if (JAC) dH = poly_t(itc + ideg + 1, ideg, itt);
+    } else {
+        // an unused slot of a pass with larger coefficients has nu = 0 and
+        // the dummy's g = h = 0 in any other
 #pragma unroll
-    for (int r = 0; r < 2 * sc::MAXSIDE; ++r) {
-        const bool isr = r < sc::MAXSIDE;
-        const int ri = isr ? r : r - sc::MAXSIDE;
-        if (ri >= (isr ? nr : np)) continue;
-        const int row = isr ? rr.rsp[ri] : rr.psp[ri];
-        const double nu = isr ? -(double)rr.rnu[ri] : (double)rr.pnu[ri];
-        atomicAdd(&lds[Lds<NP>::WD + row], nu * o.q);
+        for (int i = 0; i < 3; ++i) {
+            dG += nu[3 + i] * g[3 + i] - nu[i] * g[i];
+            if (JAC) dH += nu[3 + i] * h[3 + i] - nu[i] * h[i];
+        }
+    }
+    const double dnu = r.dnu();
+    const double lnKc = -dG + dnu * (m.lnp0R - x.lnT);
+    const double M0 = x.p * x.invT / m.Rgas;
+    double M = M0, Me = 0.0;
+    if (flags & sc::RXF_TB) {
+        if (j < sp.n_tb) {
+#pragma unroll
+            for (int e = 0; e < sc::MAXENH; ++e) Me += o.ea[e] * *(const double *)(cg + r.enh(e));
+        }
+        M += Me;
+    }
+    const int kind = r.kind();
+    double kf = kinf, phi = 0.0, dlnF_T = 0.0, dlnk0 = 0.0;
+    if ((flags & sc::RXF_TROE) && kind == sc::RX_TROE) {
+        const double lnk0 = tr.lnA0 + dl + tr.b0 * x.lnT - tr.Ea0R * x.invT;
+        const double Pr = exp(lnk0 - lnkinf) * M;
+        const double a = tr.a, iT3 = tr.iT3, iT1 = tr.iT1, T2 = tr.T2;
+        const double e3 = exp(-x.T * iT3), e1 = exp(-x.T * iT1), e2 = exp(-T2 * x.invT);
+        const double Fc = (1.0 - a) * e3 + a * e1 + e2;
+        const double L = log10(Fc);
+        const double cc = -0.4 - 0.67 * L, nn = 0.75 - 1.27 * L;
+        const double X = log10(Pr) + cc;
+        const double D = nn - 0.14 * X;
+        const double f = X / D;
+        const double opf = 1.0 + f * f;
+        const double lF = L / opf;
+        kf = kinf * (Pr / (1.0 + Pr)) * exp(2.302585092994046 * lF);
         if (JAC) {
-            atomicAdd(&lds[Lds<NP>::UA + row], nu * o.euler);
-            double *Prow = P + row * Lds<NP>::PS;
-#pragma unroll
-            for (int s = 0; s < sc::NDEP; ++s)
-                if (use[s]) atomicAdd(&Prow[col[s]], nu * o.d[s]);
-            atomicAdd(&Prow[N], nu * o.dT);
+            const double gg = -L * 2.0 * f / (opf * opf);
+            phi = 1.0 / (1.0 + Pr) + gg * (nn / (D * D));  // dln kf / dln Pr
+            const double dlF_dL = 1.0 / opf + gg * ((-0.67 * nn + 1.27 * X) / (D * D));
+            const double dFc = -(1.0 - a) * iT3 * e3 - a * iT1 * e1 + T2 * x.invT * x.invT * e2;
+            dlnF_T = dlF_dL * dFc / Fc;  // dln F/dT at fixed Pr
+            dlnk0 = (tr.b0 + tr.Ea0R * x.invT) * x.invT;
         }
     }
-    if (JAC) {
-#pragma unroll
-        for (int s = 0; s < sc::NDEP; ++s)
-            if (use[s]) atomicAdd(&P[N * Lds<NP>::PS + col[s]], dHJ * o.d[s]);
-        atomicAdd(&P[N * Lds<NP>::PS + N], dHJ * o.dT);
-        if (m.cv) atomicAdd(&lds[Lds<NP>::UA + N], dHJ * o.euler);
+    const double kr = kf * exp(-lnKc);
+    const double Rf = kf * (p[0] * p[1] * p[2]), Rr = kr * (p[3] * p[4] * p[5]);
+    const double q0 = Rf - Rr;
+    const bool third = (flags & sc::RXF_TB) && kind == sc::RX_THIRD;
+    const double fsc = third ? M : 1.0;
+    o.q = fsc * q0;
+    if (!JAC) return o;
+    const double F = fsc * kf, B = -fsc * kr;
+    o.d[0] = F * (p[1] * p[2]) * dp[0];
+    o.d[1] = F * (p[0] * p[2]) * dp[1];
+    o.d[2] = F * (p[0] * p[1]) * dp[2];
+    o.d[3] = B * (p[4] * p[5]) * dp[3];
+    o.d[4] = B * (p[3] * p[5]) * dp[4];
+    o.d[5] = B * (p[3] * p[4]) * dp[5];
+    const double dlnkinf = (r.bT() + r.EaR() * x.invT) * x.invT;
+    const double dlnKc = (dH - dnu) * x.invT;
+    double dlnkf = dlnkinf;
+    o.dqM = 0.0;
+    const double dMdT = m.cv ? 0.0 : -M0 * x.invT;
+    if (flags & sc::RXF_TB) {
+        if (kind == sc::RX_THIRD) {
+            o.dqM = q0;
+        } else if (kind == sc::RX_TROE) {
+            o.dqM = q0 * phi / M;
+            dlnkf = dlnkinf + phi * (dlnk0 - dlnkinf + dMdT / M) + dlnF_T;
+        }
     }
+    o.dT = fsc * (q0 * dlnkf + Rr * dlnKc);
+    if (third) o.dT += q0 * dMdT;
+    // q - sum_s C_s dq/dC_s: (1 - order) of each direction, less the
+    // enhanced species' share of [M]
+    o.euler = m.cv ? o.dqM
+                   : fsc * ((1.0 - r.order(0)) * Rf - (1.0 - r.order(1)) * Rr) - o.dqM * Me;
+    o.dH = dH;
+    return o;
+}
+
+// The reactions' production rates added up in the pairs: the passes of one wave
+// (or of its share of a crew's), nxt the first one's record.  A lane adds for
+// the slots its reaction uses only: at full occupancy the LDS additions bind,
+// about 14 cycles for 64 lanes and more where they meet in one address (with
+// every lane adding, the unused slots into trash entries, 65,536 evaluations
+// took 341 us instead of 262, 4,096 Jacobians 139 instead of 120, 16,384 cells
+// of 9 species 47 ms instead of 40).
+template <int G, int NV, bool TABLES, class CR>
+__device__ __forceinline__ void rhs_passes(const CR &crew, const DevMech &m, const DevRx &sp, int ideg, double *lds,
+                                           const Mix<> &x, const double *dlnA, int lane, const double *itb, double itt,
+                                           Rec nxt)
+{
+    char *wd = (char *)(lds + SPL_HW * NV + 1);
+#pragma unroll 1
+    for (int q = crew.first(sp), qn; q >= 0; q = qn) {
+        qn = crew.next(sp, q);
+        const Rec r = nxt;
+        nxt = load_rx<G>(sp, max(qn, 0), lane);
+        const uint32_t flags = __builtin_amdgcn_readfirstlane(r.bits());
+        const double dl = dlnA ? dlnA[r.orig()] : 0.0;
+        const RxTerms o = reaction_sp<false, NV>(m, sp, ideg, lds, r, flags, q * G + lane, x, dl,
+                                                 TABLES ? itb : nullptr, itt);
+        crew.await(q);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            if (i == 2 && !(flags & sc::RXF_THIRD_REAC)) continue;
+            if (i == 5 && !(flags & sc::RXF_THIRD_PROD)) continue;
+            double v = i < 3 ? -o.q : o.q;
+            if (flags & sc::RXF_NU) v *= r.nu(i);
+            if (r.nu(i) > 0) atomicAdd((double *)(wd + r.slot(i)), v);
+        }
+        crew.pass_on(q);
+    }
+}
+
+// The Jacobian pass's sums: the production rates and Euler terms, SGN nu dq/dC
+// and SGN nu dq/dT in the species rows of the entries E, the enthalpy-weighted
+// derivatives in the temperature row.  OFF: the entries are byte offsets,
+// otherwise numbers.  What every reaction adds to, the (T, T) entry and a
+// constant-volume reactor's border term, stays in a register per lane (64 LDS
+// additions to one address run one by one), a crew's in ts[0] and ts[NV]
+// between its waves.
+template <int G, int NV, bool OFF, int SGN, bool TABLES, class CR>
+__device__ __forceinline__ void jac_passes(const CR &crew, const DevMech &m, const DevRx &sp, int ideg, double *lds,
+                                           double *E, const Mix<> &x, double RT, const double *dlnA, int lane,
+                                           const double *itb, double itt, Rec nxt, double *ts, double &tt, double &tm)
+{
+    constexpr double sgn = SGN;
+    const int N = m.N;
+    char *wd = (char *)(lds + SPL_HW * NV + 1), *ua = (char *)(lds + SPL_UA * NV);
+    auto add = [&](uint32_t o, double v) __attribute__((always_inline)) {
+        atomicAdd((double *)((char *)E + (OFF ? o : 8 * o)), v);
+    };
+#pragma unroll 1
+    for (int q = crew.first(sp), qn; q >= 0; q = qn) {
+        qn = crew.next(sp, q);
+        const Rec r = nxt;
+        const uint4 *ip = (const uint4 *)sp.ix + (size_t)q * sc::RXW_IX * G + lane;
+        uint32_t ix[4 * sc::RXW_IX];
+#pragma unroll
+        for (int c = 0; c < sc::RXW_IX; ++c) {
+            const uint4 w = ip[c * G];
+            ix[4 * c] = w.x, ix[4 * c + 1] = w.y, ix[4 * c + 2] = w.z, ix[4 * c + 3] = w.w;
+        }
+        nxt = load_rx<G>(sp, max(qn, 0), lane);
+        const uint32_t flags = __builtin_amdgcn_readfirstlane(r.bits());
+        const double dl = dlnA ? dlnA[r.orig()] : 0.0;
+        const int j = q * G + lane;
+        const RxTerms o = reaction_sp<true, NV>(m, sp, ideg, lds, r, flags, j, x, dl,
+                                                TABLES ? itb : nullptr, itt);
+        auto at = [&](int e) __attribute__((always_inline)) { return e % 2 ? ix[e / 2] >> 16 : ix[e / 2] & 0xffff; };
+        // temperature-row weight: the reaction enthalpy (constant pressure) or
+        // internal energy (constant volume), per unit of progress
+        const double dHJ = m.cv ? (o.dH - r.dnu()) * RT : o.dH * RT;
+        uint32_t ie[4 * sc::RXW_IXE];
+        auto enhanced = [&]() __attribute__((always_inline)) {
+            const uint4 *ep = (const uint4 *)sp.ixe + (size_t)q * sc::RXW_IXE * G + lane;
+#pragma unroll
+            for (int c = 0; c < sc::RXW_IXE; ++c) {
+                const uint4 w = ep[c * G];
+                ie[4 * c] = w.x, ie[4 * c + 1] = w.y, ie[4 * c + 2] = w.z, ie[4 * c + 3] = w.w;
+            }
+        };
+        // a crew's wave loads them before its turn
+        if (!std::is_same_v<CR, Solo> && (flags & sc::RXF_TB) && j < sp.n_tb) enhanced();
+        crew.await(q);
+        auto row = [&](auto I, auto NU) __attribute__((always_inline)) {
+            constexpr int i = I;
+            if (r.nu(i) == 0) return;
+            double w = i < 3 ? -1.0 : 1.0;
+            if (decltype(NU)::value) w *= r.nu(i);
+            // without coefficients the weight is a constant and the products fold to signs
+            atomicAdd((double *)(wd + r.slot(i)), w * o.q);
+            atomicAdd((double *)(ua + r.slot(i) / 2), w * o.euler);
+            add(at(7 * i), sgn * w * o.d[0]);
+            add(at(7 * i + 1), sgn * w * o.d[1]);
+            if (r.nu(2) > 0) add(at(7 * i + 2), sgn * w * o.d[2]);
+            add(at(7 * i + 3), sgn * w * o.d[3]);
+            add(at(7 * i + 4), sgn * w * o.d[4]);
+            if (r.nu(5) > 0) add(at(7 * i + 5), sgn * w * o.d[5]);
+            add(at(7 * i + 6), sgn * w * o.dT);
+        };
+        auto rows = [&](auto NU) __attribute__((always_inline)) {
+            row(std::integral_constant<int, 0>{}, NU);
+            row(std::integral_constant<int, 1>{}, NU);
+            if (flags & sc::RXF_THIRD_REAC) row(std::integral_constant<int, 2>{}, NU);
+            row(std::integral_constant<int, 3>{}, NU);
+            row(std::integral_constant<int, 4>{}, NU);
+            if (flags & sc::RXF_THIRD_PROD) row(std::integral_constant<int, 5>{}, NU);
+        };
+        if (flags & sc::RXF_NU)
+            rows(std::true_type{});
+        else
+            rows(std::false_type{});
+#pragma unroll
+        for (int s = 0; s < 6; ++s) {
+            if ((s == 2 || s == 5) && r.nu(s) == 0) continue;
+            add(at(42 + s), dHJ * o.d[s]);
+        }
+        if (crew.w > 1) tt = ts[0], tm = ts[NV];
+        tt = fma(dHJ, o.dT, tt);
+        if (m.cv) tm = fma(dHJ, o.euler, tm);
+        if (crew.w > 1) ts[0] = tt, ts[NV] = tm;
+        if ((flags & sc::RXF_TB) && j < sp.n_tb) {
+            if (std::is_same_v<CR, Solo>) enhanced();
+#pragma unroll
+            for (int i = 0; i < 7; ++i) {
+                const double w = i == 6 ? dHJ * o.dqM : (i < 3 ? -sgn * o.dqM : sgn * o.dqM) * r.nu(i < 6 ? i : 0);
+#pragma unroll
+                for (int e = 0; e < sc::MAXENH; ++e) {
+                    const int k = 4 * i + e;
+                    if (r.enh(e) == 16u * (N + 1) || (i < 6 && r.nu(i) == 0)) continue;
+                    add(k % 2 ? ie[k / 2] >> 16 : ie[k / 2] & 0xffff, w * o.ea[e]);
+                }
+            }
+        }
+        crew.pass_on(q);
+    }
+}
+
+// mixture() for the reaction passes: C and g/RT, h/RT and the production rate
+// in pairs, and the dummy species' of a reaction's unused slots (N + 1, or one
+// behind the last lane)
+template <int NP>
+__device__ __forceinline__ Mix<> mixture_pairs(const DevMech &m, double *lds, double y, double p, Thermo<> &th,
+                                               int lane)
+{
+    constexpr int NV = Lds<NP>::NV;
+    double *v = lds + Lds<NP>::RX;
+    double yw;
+    const Mix<> x = mixture_point(m, y, p, th, lane, yw);
+    double *cg = pair<NV>(v, SPL_CG, lane), *hw = pair<NV>(v, SPL_HW, lane);
+    cg[0] = lane < m.N ? x.rho * yw : 1.0;
+    cg[1] = th.hRT - th.sR;
+    hw[0] = th.hRT;
+    hw[1] = 0.0;
+    v[SPL_UA * NV + lane] = 0.0;
+    // the two behind the lanes, by all of them
+    static_assert(NV == WAVE + 2);
+    cg = pair<NV>(v, SPL_CG, WAVE + lane % 2), hw = pair<NV>(v, SPL_HW, WAVE + lane % 2);
+    cg[0] = 1.0;
+    cg[1] = hw[0] = hw[1] = 0.0;
+    return x;
 }
 
 // Right-hand side f(y), lane-distributed (0 in padding lanes).
 template <int NP>
-__device__ double rhs(const DevMech &m, double *lds, double y, double p, const double *dlnA, int lane)
+__device__ __forceinline__ double rhs(const DevMech &m, double *lds, double y, double p, const double *dlnA, int lane)
 {
-    const int N = m.N, R = m.R;
+    const int N = m.N;
+    constexpr int NV = Lds<NP>::NV;
+    double *v = lds + Lds<NP>::RX;
     Thermo<> th;
-    const Mix<> x = mixture<NP>(m, lds, y, p, th, lane);
-    wave_sync();
-#pragma unroll 1
-    for (int j = lane; j < R; j += WAVE) {
-        const RxRec rr = load_rec(m, j);
-        const double dl = dlnA ? dlnA[rr.orig] : 0.0;
-        const RxOut<> o = reaction<false>(m, lds, rr, x, dl, Lds<NP>::C, Lds<NP>::G, Lds<NP>::H);
-        scatter<NP, false>(m, lds, rr, o, 0.0);
-    }
-    wave_sync();
+    const Rec first = load_rx<WAVE>(m.pass, m.pass.passes - 1, lane);
+    const Mix<> x = mixture_pairs<NP>(m, lds, y, p, th, lane);
+    lds_sync();
+    rhs_passes<WAVE, NV, false>(Solo{}, m, m.pass, 0, v, x, dlnA, lane, nullptr, 0.0, first);
+    lds_sync();
     double f = 0.0, hw = 0.0;
     if (lane < N) {
-        const double wd = lds[Lds<NP>::WD + lane];
+        const double wd = pair<NV>(v, SPL_HW, lane)[1];
         f = m.W()[lane] * wd / x.rho;
         hw = (m.cv ? th.hRT - 1.0 : th.hRT) * wd;  // h_k/RT, or u_k/RT at constant volume
     }
     const double H = m.Rgas * x.T * wave_sum(hw);
     if (lane == N) f = -H / (x.rho * x.cp);
-    wave_sync();
+    lds_sync();
     return f;
 }
 
@@ -562,75 +981,67 @@ struct RowCoef {
 
 // Jacobian pass: f(y) plus the analytical terms, finalised in LDS.
 template <int NP>
-__device__ double rhs_jac(const DevMech &m, double *lds, double y, double p, const double *dlnA, int lane,
+__device__ __forceinline__ double rhs_jac(const DevMech &m, double *lds, double y, double p, const double *dlnA, int lane,
                           RowCoef &rc)
 {
-    const int N = m.N, R = m.R;
-    double *P = lds + Lds<NP>::P;
+    const int N = m.N;
+    constexpr int NV = Lds<NP>::NV;
+    double *P = lds + Lds<NP>::P, *v = lds + Lds<NP>::RX;
     Thermo<> th;
-    const Mix<> x = mixture<NP>(m, lds, y, p, th, lane);
-    if (lane < NP) {
+    const Rec first = load_rx<WAVE>(m.pass, m.pass.passes - 1, lane);
+    const Mix<> x = mixture_pairs<NP>(m, lds, y, p, th, lane);
 #pragma unroll 4
-        for (int i = 0; i < NP; ++i) P[i * Lds<NP>::PS + lane] = 0.0;  // lane c clears column c
-    }
-    wave_sync();
+    for (int e = 2 * lane; e < NP * Lds<NP>::PS; e += 2 * WAVE) *(double2 *)(P + e) = make_double2(0.0, 0.0);
+    lds_sync();
     const double RT = m.Rgas * x.T;
-#pragma unroll 1
-    for (int j = lane; j < R; j += WAVE) {
-        const RxRec rr = load_rec(m, j);
-        const double dl = dlnA ? dlnA[rr.orig] : 0.0;
-        const RxOut<> o = reaction<true>(m, lds, rr, x, dl, Lds<NP>::C, Lds<NP>::G, Lds<NP>::H);
-        // temperature-row weight: the reaction's enthalpy, or at constant
-        // volume its internal energy (dH - dnu) R T
-        scatter<NP, true>(m, lds, rr, o, m.cv ? (o.dH - rr.dnu) * RT : o.dH * RT);
-    }
-    wave_sync();
+    double tt = 0.0, tm = 0.0;
+    jac_passes<WAVE, NV, true, 1, false>(Solo{}, m, m.pass, 0, v, P, x, RT, dlnA, lane, nullptr, 0.0, first, nullptr,
+                                         tt, tm);
+    lds_sync();
     // m.cv: the energy balance is on u_k = h_k - R T, the heat capacity c_v
     const double one = m.cv ? 1.0 : 0.0;
-    double f = 0.0, hw = 0.0, eu = 0.0, cpf = 0.0, dcp = 0.0, uk = 0.0, ua = 0.0, Wk = 0.0;
-    if (lane < N) {
-        Wk = m.W()[lane];
-        const double iw = m.invW()[lane];
-        const double wd = lds[Lds<NP>::WD + lane];
-        ua = lds[Lds<NP>::UA + lane];
-        f = Wk * wd / x.rho;
-        uk = Wk * ua / x.rho;
-        hw = (th.hRT - one) * wd;
-        eu = th.hRT * uk * iw;           // (h_k/(R T W_k)) u_k
-        cpf = (th.cpR - one) * f * iw;   // cp_k/(R W_k) f_k (cv_k at constant volume)
-        dcp = th.dcpR * y * iw;          // dcp_k/dT/(R W_k) Y_k
-    }
+    // No branches from here to the factorisation: the compiler puts the copies
+    // of the registers it keeps over it at the last point where branches join,
+    // and there before the join, where the lanes of one side miss them.
+    const bool own = lane < N;
+    const int k = min(lane, N - 1);
+    const double Wk = own ? m.W()[k] : 0.0, iw = own ? m.invW()[k] : 0.0;
+    const double wd = own ? pair<NV>(v, SPL_HW, lane)[1] : 0.0, ua = own ? v[SPL_UA * NV + lane] : 0.0;
+    double f = Wk * wd / x.rho;
+    const double uk = Wk * ua / x.rho;
+    const double hw = (th.hRT - one) * wd;
+    const double eu = th.hRT * uk * iw;           // (h_k/(R T W_k)) u_k
+    const double cpf = (th.cpR - one) * f * iw;   // cp_k/(R W_k) f_k (cv_k at constant volume)
+    const double dcp = th.dcpR * y * iw;          // dcp_k/dT/(R W_k) Y_k
     const double H = RT * wave_sum(hw);
     const double Eu = m.cv ? 0.0 : RT * wave_sum(eu);  // sum_k (h_k/W_k) u_k
     const double Scpf = m.Rgas * wave_sum(cpf);
     const double Sdcp = m.Rgas * wave_sum(dcp);
     const double fT = -H / (x.rho * x.cp);
-    if (lane == N) f = fT;
+    f = lane == N ? fT : f;
     // fold the column-dependent parts of the temperature row into P[N][*].
     // Constant pressure:
     //   J_Tm = -(1/cp) (1/W_m) (P_Tm + Wbar Eu + fT cp_m),
     //   J_TT = -(1/cp) (P_TT/rho + Eu/T + sum cp_k f_k/W_k + fT sum dcp_k Y_k/W_k);
     // constant volume (C_k = rho Y_k/W_k, no density border; the rank-one
-    // part of d[M]/dC accumulated in UA[N] for this row, UA[k] for row k):
-    //   J_Tm = -(1/cv) (1/W_m) (P_Tm + UA_N + fT cv_m),
+    // part of d[M]/dC accumulated in tb for this row, UA[k] for row k):
+    //   J_Tm = -(1/cv) (1/W_m) (P_Tm + tb + fT cv_m),
     //   J_TT = -(1/cv) (P_TT/rho + sum cv_k f_k/W_k + fT sum dcp_k Y_k/W_k)
     const int PS = Lds<NP>::PS;
-    const double tb = m.cv ? lds[Lds<NP>::UA + N] : x.Wbar * Eu;
-    if (lane < N) P[N * PS + lane] += tb + fT * m.Rgas * (th.cpR - one);
-    if (lane == N) P[N * PS + N] = P[N * PS + N] / x.rho + Eu * x.invT + Scpf + fT * Sdcp;
-    if (lane < NP) lds[Lds<NP>::IW + lane] = lane < N ? m.invW()[lane] : 0.0;
-    wave_sync();
+    const double TT = wave_sum(tt), tb = m.cv ? wave_sum(tm) : x.Wbar * Eu;
+    double *row = P + (lane <= N ? N * PS + lane : lane % 16 * PS + NP);  // the others': the column behind
+    *row = own ? *row + (tb + fT * m.Rgas * (th.cpR - one)) : TT / x.rho + Eu * x.invT + Scpf + fT * Sdcp;
+    lds[Lds<NP>::IW + lane] = iw;
+    lds_sync();
     const double invcp = 1.0 / x.cp;
-    if (lane < N) {
-        // species rows, constant pressure: J_km = (W_k/W_m) P_km + u_k Wbar/W_m,
-        // J_kT = (W_k/rho) P_kT + u_k/T; constant volume: J_km = (W_k/W_m)
-        // (P_km + UA_k), J_kT = (W_k/rho) P_kT
-        rc = m.cv ? RowCoef{Wk, Wk * ua, Wk / x.rho, 0.0} : RowCoef{Wk, uk * x.Wbar, Wk / x.rho, uk * x.invT};
-    } else if (lane == N) {
-        rc = RowCoef{-invcp, 0.0, -invcp, 0.0};
-    } else {
-        rc = RowCoef{0.0, 0.0, 0.0, 0.0};
-    }
+    // species rows, constant pressure: J_km = (W_k/W_m) P_km + u_k Wbar/W_m,
+    // J_kT = (W_k/rho) P_kT + u_k/T; constant volume: J_km = (W_k/W_m)
+    // (P_km + UA_k), J_kT = (W_k/rho) P_kT.  W_k, u_k and UA_k are zero in the
+    // other lanes.
+    rc.alpha = lane == N ? -invcp : Wk;
+    rc.beta = m.cv ? Wk * ua : uk * x.Wbar;
+    rc.alphaT = lane == N ? -invcp : Wk / x.rho;
+    rc.betaT = m.cv ? 0.0 : uk * x.invT;
     return f;
 }
 
@@ -663,65 +1074,144 @@ __device__ __forceinline__ void form_matrix(const DevMech &m, const double *lds,
     for (int c = 0; c < NP; ++c) a[c] = c == lane ? diag - a[c] : -a[c];
 }
 
-// In-register LU without pivoting, natural order; row i in lane i.  After the
-// call a[k] (k < lane) holds L (unit diagonal implied), a[k] (k >= lane) U,
-// and dinv = 1/U_ii.
+// LU without pivoting, natural order, of the rows in registers (row i in lane
+// i), parked in F column-major (F[c PS + i] = row i, column c): below the
+// diagonal L with a unit diagonal, above it U scaled to one, and in the
+// lanes' return value 1/U_ii.  A broadcast of one lane to the 16 of its row
+// costs nothing inside a multiply-add (DPP), where one to the whole wave takes
+// two readlanes at twice a multiply-add's time each; so the pivots go in
+// blocks of 16, whose rows S are copied to all four rows of lanes, and every
+// row of lanes eliminates in its copy and in its own rows from that.  The
+// block's columns leave for F and the others move to the front, so that one
+// piece of code does every block and stays in the instruction cache.  (As one
+// unrolled elimination with a readlane pair per entry, 64 KB of code, 53
+// species took 134k cycles of a lone wave, most of them waiting for
+// instructions; 45k now.)
 template <int NP>
-__device__ __forceinline__ void lu_factor(double (&a)[NP], double &dinv, int lane)
+__device__ __forceinline__ double lu_factor(double (&a)[NP], double *F, int lane)
 {
-    dinv = 0.0;
+    constexpr int PS = Lds<NP>::PS, NR = (NP + 15) / 16 * 16;  // columns, up to whole blocks
+    int c = lane & 15, row = lane >> 4;
+    double r[NR];
 #pragma unroll
-    for (int k = 0; k < NP; ++k) {
-        const double piv = rdlane(a[k], k);
-        const double inv = 1.0 / piv;
-        if (lane == k) dinv = inv;
-        const bool below = lane > k;
-        const double l = below ? a[k] * inv : 0.0;
-        if (below) a[k] = l;
+    for (int j = 0; j < NR; ++j) r[j] = j < NP ? a[j < NP ? j : 0] : 0.0;
+    double dinv = 0.0;
+#pragma unroll 1
+    for (int b = 0; b < NR / 16; ++b) {
+        asm volatile("" : "+v"(c), "+v"(row));  // the masks are cheaper made again than kept and spilled
+        const int k0 = 16 * b;
+        const bool in = row == b, after = row > b;
+        const int from = 4 * (k0 + c);
+        auto spread = [&](double v) __attribute__((always_inline)) {
+            return __hiloint2double(__builtin_amdgcn_ds_bpermute(from, __double2hiint(v)),
+                                    __builtin_amdgcn_ds_bpermute(from, __double2loint(v)));
+        };
+        double S[16], db = 0.0;
 #pragma unroll
-        for (int j = k + 1; j < NP; ++j) {
-            const double u = rdlane(a[j], k);
-            a[j] = fma(-l, u, a[j]);
-            SC_FENCE_EVERY(j - k - 1);
+        for (int j = 0; j < 16; ++j) S[j] = spread(r[j]);
+        unrolled<16>([&](auto K) __attribute__((always_inline)) {
+            constexpr int k = K;
+            if (NP % 16 == 0 || k < NP % 16 || k0 + k < NP) {
+                const double inv = 1.0 / bcast<16, k>(S[k]);
+                const double l = c > k ? S[k] * inv : 0.0, lr = after ? r[k] * inv : 0.0;
+                db = c == k ? inv : db;
+                S[k] = c > k ? l : S[k];
+                r[k] = after ? lr : r[k];
+                if constexpr (k < 15) fmac_row<k>(S[k + 1], l);
+                constexpr int j0 = k + 2;
+#pragma unroll
+                for (int j = j0; j + 3 < 16; j += 4) fmac_row4<k>(S[j], S[j + 1], S[j + 2], S[j + 3], l);
+#pragma unroll
+                for (int j = j0 + (j0 < 16 ? (16 - j0) / 4 * 4 : 0); j < 16; ++j) fmac_row<k>(S[j], l);
+#pragma unroll
+                for (int j = k + 1; j + 3 < 16; j += 4)
+                    fmac_from4<k>(r[j], r[j + 1], r[j + 2], r[j + 3], S[j], S[j + 1], S[j + 2], S[j + 3], lr);
+#pragma unroll
+                for (int j = k + 1 + (15 - k) / 4 * 4; j < 16; ++j) fmac_from<k>(r[j], S[j], lr);
+            }
+        });
+        dinv = in ? db : dinv;
+        double *Fb = F + k0 * PS + min(lane, NP);  // lanes without a row: the row behind
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (NP % 16 == 0 || k < NP % 16 || k0 + k < NP) Fb[k * PS] = in ? S[k] * (k > c ? db : 1.0) : r[k];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            S[k] = c > k ? S[k] : 0.0;
+            r[k] = after ? r[k] : 0.0;
         }
-        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 16; j < NR; j += 4)
+            if (k0 + j < NP) {
+                double s0 = spread(r[j]), s1 = spread(r[j + 1]), s2 = spread(r[j + 2]), s3 = spread(r[j + 3]);
+                unrolled<15>([&](auto K) __attribute__((always_inline)) { fmac_row4<K>(s0, s1, s2, s3, S[K]); });
+                unrolled<16>([&](auto K) __attribute__((always_inline)) {
+                    fmac_from4<K>(r[j], r[j + 1], r[j + 2], r[j + 3], s0, s1, s2, s3, r[K]);
+                });
+                r[j] = in ? s0 * db : r[j];
+                r[j + 1] = in ? s1 * db : r[j + 1];
+                r[j + 2] = in ? s2 * db : r[j + 2];
+                r[j + 3] = in ? s3 * db : r[j + 3];
+            }
+#pragma unroll
+        for (int j = 16; j < NR; ++j) r[j - 16] = r[j];
     }
+    return dinv;
 }
 
-// Park the factors in LDS, column-major (F[c*PS + i] = row i, column c), so
-// that every read in the triangular solves is one contiguous wave access.
-template <int NP>
-__device__ __forceinline__ void store_factors(double *F, const double (&a)[NP], int lane)
-{
-    if (lane < NP) {
-#pragma unroll
-        for (int c = 0; c < NP; ++c) {
-            F[c * Lds<NP>::PS + lane] = a[c];
-            SC_FENCE_EVERY(c);
-        }
-    }
-}
-
-// Solve (L U) x = b with the factors in LDS; b lane-distributed.
-template <int NP>
+// Solve with the factors in F, b lane-distributed: (L D U) x = b, or with
+// `transposed` the transpose, U^T D L^T.  Lane j's coefficient of unknown k is
+// the entry at (j, k), transposed (k, j); PS is odd, so both reads fall on
+// different banks.  The chain through a block's 16 unknowns runs inside the
+// row of lanes that holds them, one broadcasting multiply-add each; the
+// block's solution is then spread to all rows of lanes and those behind it
+// apply it, off the chain.
+template <int NP, bool transposed = false>
 __device__ __forceinline__ double lu_solve(const double *F, double dinv, double b, int lane)
 {
-    const int li = lane < NP ? lane : 0;
+    constexpr int PS = Lds<NP>::PS, NB = (NP + 15) / 16;
+    const double *Fl = F + (lane < NP ? lane : 0) * (transposed ? PS : 1);
+    asm volatile("" : "+v"(lane));  // the masks below are cheaper made again than kept and spilled
+    auto load = [&](int q, bool lower, double (&a)[16]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int k = 0; k < NP - 1; ++k) {
-        const double l = F[k * Lds<NP>::PS + li];
-        const double z = rdlane(b, k);
-        if (lane > k) b = fma(-l, z, b);
-        SC_FENCE_EVERY(k);
-    }
+        for (int i = 0; i < 16; ++i) {
+            const int k = 16 * q + i;
+            const double v = k < NP ? Fl[k * (transposed ? 1 : PS)] : 0.0;
+            a[i] = (lower ? lane > k : lane < k) ? v : 0.0;
+        }
+    };
+    double a[16], nx[16];
+    load(0, true, a);
+    unrolled<NB>([&](auto Q) __attribute__((always_inline)) {
+        constexpr int q = Q;
+        if constexpr (q + 1 < NB) load(q + 1, true, nx);
+        unrolled<15>([&](auto K) __attribute__((always_inline)) {
+            if constexpr (16 * q + K < NP) fmac_in<K, 1 << q>(b, a[K]);
+        });
+        if constexpr (q + 1 < NB) {
+            const double x = spread_row<q>(b);
+            constexpr int behind = 0xf & ~((2 << q) - 1);
+            unrolled<4>([&](auto K) __attribute__((always_inline)) { fmac_by4<4 * K, behind>(b, x, &a[4 * K]); });
 #pragma unroll
-    for (int k = NP - 1; k >= 0; --k) {
-        if (lane == k) b *= dinv;
-        const double z = rdlane(b, k);
-        const double u = F[k * Lds<NP>::PS + li];
-        if (lane < k) b = fma(-u, z, b);
-        SC_FENCE_EVERY(NP - 1 - k);
-    }
+            for (int i = 0; i < 16; ++i) a[i] = nx[i];
+        }
+    });
+    b *= dinv;
+    load(NB - 1, false, a);
+    unrolled<NB>([&](auto Q) __attribute__((always_inline)) {
+        constexpr int q = NB - 1 - Q;
+        if constexpr (q > 0) load(q - 1, false, nx);
+        unrolled<15>([&](auto K) __attribute__((always_inline)) {
+            if constexpr (16 * q + 15 - K < NP) fmac_in<15 - K, 1 << q>(b, a[15 - K]);
+        });
+        if constexpr (q > 0) {
+            const double x = spread_row<q>(b);
+            constexpr int behind = (1 << q) - 1;
+            unrolled<4>([&](auto K) __attribute__((always_inline)) { fmac_by4<4 * K, behind>(b, x, &a[4 * K]); });
+#pragma unroll
+            for (int i = 0; i < 16; ++i) a[i] = nx[i];
+        }
+    });
     return lane < NP ? b : 0.0;
 }
 
@@ -731,12 +1221,10 @@ template <int NP>
 __device__ __forceinline__ double factor_matrix(const DevMech &m, double *lds, const RowCoef &rc, int lane,
                                                 double inv_hg, double *F)
 {
-    double dinv;
     double a[NP];
     form_matrix<NP>(m, lds, rc, lane, inv_hg, a);
-    lu_factor<NP>(a, dinv, lane);
     wave_sync();  // every lane has read its row of the terms
-    store_factors<NP>(F, a, lane);
+    const double dinv = lu_factor<NP>(a, F, lane);
     wave_sync();
     return dinv;
 }
@@ -747,7 +1235,7 @@ __device__ __forceinline__ double factor_matrix(const DevMech &m, double *lds, c
 // Forward integration and adjoint replay both call this, so a replayed
 // step reproduces the recorded one bit for bit.
 template <int NP>
-__device__ double ros_attempt(const DevMech &m, const Opts &o, double *lds, double *F, double y, double p,
+__device__ __forceinline__ double ros_attempt(const DevMech &m, const Opts &o, double *lds, double *F, double y, double p,
                               const double *dlnA, int lane, double hc, double *err, double *dinv_out = nullptr)
 {
     const int n = m.N + 1;
@@ -806,7 +1294,7 @@ __device__ double ros_attempt(const DevMech &m, const Opts &o, double *lds, doub
 // row j - 1 in the stage-vector area U.
 constexpr int EXK = 4;
 template <int NP>
-__device__ double extrap_attempt(const DevMech &m, const Opts &o, double *lds, double y, double p,
+__device__ __forceinline__ double extrap_attempt(const DevMech &m, const Opts &o, double *lds, double y, double p,
                                  const double *dlnA, int lane, double H, double *err)
 {
     const int n = m.N + 1;
@@ -936,7 +1424,7 @@ __device__ __forceinline__ int ctl_end(Ctl &s, const Opts &o, double err, double
 // Returns the cell status; the controller state (step counts, proposed
 // next step) is left in s.
 template <int NP, int METH = SC_METHOD_ROS4>
-__device__ int advance(const DevMech &m, const Opts &o, double *lds, double &y, double p, double dt,
+__device__ __forceinline__ int advance(const DevMech &m, const Opts &o, double *lds, double &y, double p, double dt,
                        const double *dlnA, int lane, Ctl &s)
 {
 #pragma unroll 1

@@ -29,6 +29,15 @@ struct TroeRec {
     double lnA0, b0, Ea0R, a, iT3, iT1, T2, pad;
 };
 
+// The reactions as the kernels' passes read them (SparseRx's tables).
+struct DevRx {
+    int passes, n_tb, n_troe;  // reaction passes; third-body and falloff reactions (the first ones)
+    const uint32_t *rec;
+    const uint16_t *ix, *ixe;
+    const double *eam1;
+    const TroeRec *troe;
+};
+
 // A compiled mechanism on the device: species table sp = W[N] invW[N]
 // nasa[7][N] (species index fastest), one record per reaction and per Troe
 // reaction.  Three base pointers keep the kernels' scalar-register footprint
@@ -40,6 +49,7 @@ struct DevMech {
     const double *sp;
     const RxRec *rx;
     const TroeRec *troe;
+    DevRx pass;  // the dense kernels' packed passes
 
     __host__ __device__ const double *W() const { return sp; }
     __host__ __device__ const double *invW() const { return sp + N; }
@@ -55,15 +65,10 @@ constexpr int SPL_CG = 0, SPL_HW = 2, SPL_UA = 4, SPL_U = 5, SPL_DINV = 9, SPL_E
 // The sparse kernels' view of a mechanism's compiled sparse algebra (device
 // pointers).  Their DevMech has the species in elimination order, so a
 // lane holds the same position as component and as matrix row.
-struct DevSparse {
+struct DevSparse : DevRx {
     int n, nnz;
     int size;  // LDS doubles of one cell's region
     int cpw;  // cells per wave (1, 2 or 4): each cell takes 64 / cpw lanes
-    int passes, n_tb, n_troe;  // reaction passes; third-body and falloff reactions (the first ones)
-    const uint32_t *rec;       // SparseRx's tables
-    const uint16_t *ix, *ixe;
-    const double *eam1;
-    const TroeRec *troe;
     const uint16_t *comp;  // [position][8]: e_kk, e_kT, e_kS, e_Tk, e_Sk; at N: e_TT, e_SS
     const int32_t *perm;   // position -> species (N: temperature)
     const int32_t *pos;    // species -> position
@@ -112,7 +117,7 @@ hipError_t order_cells_in(int order, int64_t n, const double *dt, const int32_t 
 // device address, size and cell limit of the allocation-free entry point's
 // fixed scratch on `device` (which must be current)
 hipError_t noalloc_scratch(int device, void **ptr, size_t *bytes, int64_t *max_cells);
-hipError_t launch_zero_u64(unsigned long long *p, hipStream_t s);
+hipError_t launch_set_u64(unsigned long long *p, unsigned long long v, hipStream_t s);
 int persistent_capacity(int np, int device);
 
 // sparse linear algebra kernels (sparse.hip); vpl = state components per lane
@@ -128,7 +133,7 @@ hipError_t launch_linsolve_sp(int vpl, const DevMech &m, const DevSparse &sp, in
 hipError_t launch_integrate_sp(int vpl, const DevMech &m, const DevSparse &sp, const Opts &o, int64_t n,
                                const double *T0, const double *p, const double *Y0, int64_t ld, const double *dt,
                                const double *dlnA, double *h_io, double *T1, double *Y1, int32_t *st, int32_t *na,
-                               int32_t *nr, const int32_t *ref, hipStream_t s);
+                               int32_t *nr, const int32_t *ref, int crews, hipStream_t s);
 hipError_t launch_integrate_sp_persistent(int vpl, const DevMech &m, const DevSparse &sp, const Opts &o,
                                           int64_t n, const double *T0, const double *p, const double *Y0,
                                           int64_t ld, const double *dt, const double *dlnA, double *h_io,
@@ -140,7 +145,10 @@ hipError_t launch_integrate_sp_static(int vpl, const DevMech &m, const DevSparse
                                       const double *dt, const double *dlnA, double *h_io, double *T1, double *Y1,
                                       int32_t *st, int32_t *na, int32_t *nr, int grid, const int32_t *ref,
                                       hipStream_t s);
-int persistent_capacity_sp(int vpl, const DevSparse &sp, int device);
+// where the queue of a persistent launch starts: behind the workgroups' first tiles
+int64_t queue_start_sp(int vpl, const DevSparse &sp, int grid, int tile);
+// resident workgroups of the persistent and the static kernel (0 on failure)
+void capacity_sp(int vpl, const DevSparse &sp, int device, int &persistent, int &fixed);
 
 // zonal reference-cell mapping (mapping.hip): the zone table is cleared,
 // every mappable cell claims its zone (lowest index wins) and gets its

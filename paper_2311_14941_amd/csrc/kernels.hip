@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(WAVE) k_linsolve(DevMech mk, int64_t n, const 
 
 // One cell over [0, dt] with the method METH and error control.
 template <int NP, int METH>
-__device__ void integrate_cell(const DevMech &m, const Opts &o, double *lds, int64_t c, int lane, const double *T0,
+__device__ __forceinline__ void integrate_cell(const DevMech &m, const Opts &o, double *lds, int64_t c, int lane, const double *T0,
                                const double *P, const double *Y0, int64_t ld, const double *DT, const double *dlnA,
                                double *h_io, double *T1, double *Y1, int32_t *status, int32_t *nacc_out,
                                int32_t *nrej_out, const int32_t *ref)
@@ -165,7 +165,7 @@ __global__ void __launch_bounds__(WAVE) k_integrate_static(DevMech mk, Opts o, i
         integrate_cell<NP, METH>(m, o, lds, c, threadIdx.x, T0, P, Y0, ld, DT, dlnA, h_io, T1, Y1, status, nacc, nrej, ref);
 }
 
-__global__ void k_zero_u64(unsigned long long *p) { *p = 0ull; }
+__global__ void k_set_u64(unsigned long long *p, unsigned long long v) { *p = v; }
 
 __global__ void k_iota(int32_t *v, int64_t n)
 {
@@ -389,10 +389,10 @@ hipError_t noalloc_scratch(int device, void **ptr, size_t *bytes, int64_t *max_c
     return hipSuccess;
 }
 
-// clears the queue counter with a kernel (safe inside captured graphs)
-hipError_t launch_zero_u64(unsigned long long *p, hipStream_t s)
+// sets the queue counter with a kernel (safe inside captured graphs)
+hipError_t launch_set_u64(unsigned long long *p, unsigned long long v, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(1), 0, s, p);
+    hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(1), 0, s, p, v);
     return hipGetLastError();
 }
 

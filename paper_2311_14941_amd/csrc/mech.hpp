@@ -228,5 +228,8 @@ struct SparseRx {
     std::vector<double> eam1, troe;  // per third-body reaction 4 alpha - 1; per falloff reaction 8 (lnA0, b0, Ea0/R, a, 1/T3, 1/T1, T2)
 };
 SparseRx sparse_reactions(const Mech &m, int lanes);
+// and for the dense kernels: species in their own order, entries in the matrix
+// of n_padded rows of n_padded + 1 (byte offsets; N + 1 <= MAX_STATE)
+SparseRx dense_reactions(const Mech &m);
 
 }  // namespace sc

@@ -380,11 +380,15 @@ SparseDev sparse_device(const Mech &m, int lanes)
     return D;
 }
 
-SparseRx sparse_reactions(const Mech &m, int lanes)
+// pos(k): where the kernel has species k; entry(j, row, slot, junk): the entry
+// of reaction j's row (0..5: side slots, 6: the T row) in slot's column (0..5:
+// side slots, 6..9: enhanced species, 10: T), or where the junk-th of the
+// unused ones goes, the row or slot not in use (live false) or without entry
+template <class Pos, class Entry>
+static SparseRx reaction_passes(const Mech &m, int lanes, Pos pos, Entry place)
 {
-    const SparseLU &S = m.sp;
     const Tables &t = m.tab;
-    const int R = t.R, N = t.N, n = S.n;
+    const int R = t.R, N = t.N;
     SparseRx X;
     auto max_nu = [&](int j) {
         int v = 1;
@@ -431,8 +435,8 @@ SparseRx sparse_reactions(const Mech &m, int lanes)
             uint32_t sl[2 * MAXSIDE], nu[2 * MAXSIDE], order[2] = {0, 0};
             for (int i = 0; i < MAXSIDE; ++i) {
                 const bool ur = live && i < t.nr[j], up = live && i < t.np[j];
-                sl[i] = ur ? S.pos[t.rsp[i * R + j]] : dummy;
-                sl[3 + i] = up ? S.pos[t.psp[i * R + j]] : dummy;
+                sl[i] = ur ? pos(t.rsp[i * R + j]) : dummy;
+                sl[3 + i] = up ? pos(t.psp[i * R + j]) : dummy;
                 nu[i] = ur ? t.rnu[i * R + j] : 0;
                 nu[3 + i] = up ? t.pnu[i * R + j] : 0;
                 order[0] += nu[i];
@@ -447,7 +451,7 @@ SparseRx sparse_reactions(const Mech &m, int lanes)
             uint32_t enh = 0;
             for (int e = 0; e < MAXENH; ++e) {
                 const bool ue = live && e < t.neff[j];
-                enh |= (ue ? (uint32_t)S.pos[t.esp[e * R + j]] : dummy) << (8 * e);
+                enh |= (ue ? (uint32_t)pos(t.esp[e * R + j]) : dummy) << (8 * e);
                 if (live && t.kind[j] != RX_PLAIN) X.eam1[4 * (size_t)q + e] = ue ? t.eam1[e * R + j] : 0.0;
             }
             w[10] = enh;
@@ -461,10 +465,7 @@ SparseRx sparse_reactions(const Mech &m, int lanes)
             auto entry = [&](int row, int slot) {  // row 6: the T row; slot 10: the T column
                 const bool ur = row == 6 || nu[row] > 0;
                 const bool us = slot == 10 || (slot < 6 ? nu[slot] > 0 : live && slot - 6 < t.neff[j]);
-                const uint16_t *x = &S.rxi[(size_t)j * RXI_SIZE];
-                int e = live && ur && us ? (row == 6 ? x[RXI_TROW + slot] : x[row * RXI_ROW + slot]) : NOENT;
-                if (e == NOENT) e = S.nnz + 1 + (q + junk++) % SPARSE_TRASH;
-                return (uint16_t)sparse_off(n, e);
+                return place(j, row, slot, live && ur && us, q, junk);
             };
             uint16_t ix[8 * RXW_IX], ixe[8 * RXW_IXE];
             for (int r = 0; r < 6; ++r) {
@@ -484,6 +485,34 @@ SparseRx sparse_reactions(const Mech &m, int lanes)
         }
     }
     return X;
+}
+
+SparseRx sparse_reactions(const Mech &m, int lanes)
+{
+    const SparseLU &S = m.sp;
+    return reaction_passes(
+        m, lanes, [&](int k) { return S.pos[k]; },
+        [&](int j, int row, int slot, bool live, int q, int &junk) {
+            const uint16_t *x = &S.rxi[(size_t)j * RXI_SIZE];
+            int e = live ? (row == 6 ? x[RXI_TROW + slot] : x[row * RXI_ROW + slot]) : NOENT;
+            if (e == NOENT) e = S.nnz + 1 + (q + junk++) % SPARSE_TRASH;
+            return (uint16_t)sparse_off(S.n, e);
+        });
+}
+
+SparseRx dense_reactions(const Mech &m)
+{
+    const Tables &t = m.tab;
+    const int R = t.R, ps = m.n_padded + 1;
+    return reaction_passes(
+        m, 64, [](int k) { return k; },
+        [&](int j, int row, int slot, bool live, int q, int &junk) {
+            auto side = [&](int i) { return (int)(i < 3 ? t.rsp[i * R + j] : t.psp[(i - 3) * R + j]); };
+            // unused ones go to the column behind the matrix
+            const int r = live ? (row == 6 ? t.N : side(row)) : (q + junk++) % SPARSE_TRASH;
+            const int c = !live ? ps - 1 : slot == 10 ? t.N : slot < 6 ? side(slot) : (int)t.esp[(slot - 6) * R + j];
+            return (uint16_t)(8 * (r * ps + c));
+        });
 }
 
 }  // namespace sc

@@ -60,16 +60,85 @@ __device__ __forceinline__ bool gany(bool b)
         return gsum<G>(b ? 1.0 : 0.0) > 0.0;
 }
 
-// Order between the LDS accesses of the wave's lanes.  A workgroup is one
-// wave, whose LDS instructions take effect in order: the compiler must not
-// move them across, but nothing has to be waited for (a workgroup barrier's
-// fence also waits for the loads sent ahead).
-__device__ __forceinline__ void lds_sync()
+// Who works on a cell: one wave, or a crew of the workgroup's waves on one
+// LDS region.  Every wave of a crew holds the cell's state and takes its every
+// decision from the same numbers.  What splits are the passes over the
+// reactions and the tiles of the factorization; the passes' sums are added in
+// the order of the passes, so the results are those of one wave, bit for bit.
+__device__ __forceinline__ int64_t uniform(int64_t v)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    return (int64_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
+__device__ __forceinline__ double uniform(double v) { return __longlong_as_double(uniform((int64_t)__double_as_longlong(v))); }
+
+struct Crew {
+    int w, rank;  // w a power of two
+    int *turn;    // the pass whose sums are to be added next
+    uint64_t own; // the wave's passes, where there are at most 64
+    __device__ __forceinline__ void barrier() const
+    {
+        if (w > 1) __syncthreads();
+    }
+    __device__ __forceinline__ void sync() const
+    {
+        if (w > 1)
+            __syncthreads();
+        else
+            lds_sync();
+    }
+    // before the passes; a barrier follows
+    __device__ __forceinline__ void start(const DevRx &sp) const
+    {
+        if (rank == 0 && threadIdx.x % WAVE == 0) *turn = sp.passes - 1;
+    }
+    // The passes are taken from the last to the first, so that the long ones
+    // (the falloff reactions', about eight times the others' time) add at the
+    // end and nobody waits for them.  Those go round from the last wave on; of
+    // the others, the waves with one long pass less take eight more.
+    __device__ __forceinline__ bool mine(const DevRx &sp, int q) const
+    {
+        const int heavy = (sp.n_tb + WAVE - 1) / WAVE, i = sp.passes - 1 - q;
+        if (q < heavy) return w - 1 - (q & (w - 1)) == rank;
+        const int few = w - (heavy & (w - 1)), even = few == w ? sp.passes : (sp.passes - heavy - 8 * few) & -w;
+        return (i < even ? i & (w - 1) : (i - max(even, 0)) % few) == rank;
+    }
+    __device__ __forceinline__ int first(const DevRx &sp) const { return next(sp, sp.passes); }
+    // the wave's pass after q
+    __device__ __forceinline__ int next(const DevRx &sp, int q) const
+    {
+        if (w > 1 && sp.passes <= 64) {
+            const uint64_t left = q < 64 ? own & ((1ull << q) - 1) : own;
+            return left ? 63 - __builtin_clzll(left) : -1;
+        }
+        --q;
+        if (w > 1)
+            while (q >= 0 && !mine(sp, q)) --q;
+        return q;
+    }
+    __device__ __forceinline__ void join(const DevRx &sp, int waves, int wave)
+    {
+        w = waves, rank = wave, own = 0;
+        for (int q = 0; q < min(sp.passes, 64); ++q) own |= (uint64_t)mine(sp, q) << q;
+    }
+    __device__ __forceinline__ void await(int q) const
+    {
+        if (w > 1) {
+            while (__builtin_amdgcn_readfirstlane(
+                       __hip_atomic_load(turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != q) {}
+            lds_sync();
+        }
+    }
+    // (a wave's LDS operations take effect in order)
+    __device__ __forceinline__ void pass_on(int q) const
+    {
+        if (w > 1) {
+            lds_sync();
+            if (threadIdx.x % WAVE == 0)
+                __hip_atomic_store(turn, q - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+};
 
 // ---------------------------------------------------------------------------
 // helpers over VPL components per lane
@@ -118,18 +187,11 @@ __device__ __forceinline__ void store_state_v(const DevMech &m, const DevSparse 
 // ---------------------------------------------------------------------------
 // thermodynamics, right-hand side and Jacobian terms
 // ---------------------------------------------------------------------------
-// Address of species c's pair in the pair array at place `at` (SPL_CG, SPL_HW)
-template <int NV>
-__device__ __forceinline__ double *pair(double *lds, int at, int c)
-{
-    return lds + at * NV + 2 * c;
-}
-
 // Mixture state from y; writes C, g/RT, h/RT (and those of the dummy species
 // N + 1) and clears the accumulators.
-template <int VPL, int G = WAVE>
-__device__ __forceinline__ Mix<> mixture_v(const DevMech &m, double *lds, const double (&y)[VPL], double p,
-                                           Thermo<> (&th)[VPL], int lane)
+template <int VPL, int G, class CR>
+__device__ __forceinline__ Mix<> mixture_v(const CR &crew, const DevMech &m, const DevSparse &sp, double *lds, const double (&y)[VPL],
+                                           double p, Thermo<> (&th)[VPL], int lane)
 {
     constexpr int NV = G * VPL;
     const int N = m.N;
@@ -159,6 +221,8 @@ __device__ __forceinline__ Mix<> mixture_v(const DevMech &m, double *lds, const 
     } else {
         x.rho = p * x.Wbar * x.invT / m.Rgas;
     }
+    crew.start(sp);
+    if (crew.rank != 0) return x;
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int c = lane + G * v;  // lanes beyond N hold zeros: the dummy needs only its concentration
@@ -195,211 +259,27 @@ __device__ __forceinline__ const double *thermo_block(const DevSparse &sp, int R
     return sp.itab + (size_t)iv * R * 2 * (sp.ideg + 1);
 }
 
-// One pass's record of this lane's reaction (SparseRx): three 16-byte words.
-struct Rec {
-    uint4 a, b, c;
-    __device__ __forceinline__ double lnA() const { return __hiloint2double(a.y, a.x); }
-    __device__ __forceinline__ double bT() const { return __hiloint2double(a.w, a.z); }
-    __device__ __forceinline__ double EaR() const { return __hiloint2double(b.y, b.x); }
-    __device__ __forceinline__ uint32_t slot(int i) const  // byte offset of a side species' pair
-    {
-        const uint32_t w = i < 2 ? b.z : i < 4 ? b.w : c.x;
-        return i % 2 ? w >> 16 : w & 0xffff;
-    }
-    __device__ __forceinline__ uint32_t bits() const { return c.y; }
-    __device__ __forceinline__ int nu(int i) const { return (c.y >> (2 * i)) & 3; }
-    __device__ __forceinline__ int dnu() const { return (int)((c.y >> 12) & 31) - 16; }
-    __device__ __forceinline__ int order(int side) const { return (c.y >> (17 + 4 * side)) & 15; }
-    __device__ __forceinline__ int kind() const { return (c.y >> 25) & 3; }
-    __device__ __forceinline__ uint32_t enh(int e) const { return ((c.z >> (8 * e)) & 0xff) << 4; }
-    __device__ __forceinline__ int orig() const { return c.w; }
-};
-template <int G>
-__device__ __forceinline__ Rec load_rx(const DevSparse &sp, int pass, int lane)
-{
-    const uint4 *q = (const uint4 *)sp.rec + (size_t)pass * sc::RXW_WORDS * G + lane;
-    return Rec{q[0], q[G], q[2 * G]};
-}
-
-// One reaction's rate of progress and, with JAC, its derivatives: d[0..5] with
-// respect to the side species' concentrations (what an unused slot holds goes
-// to the trash), dqM with respect to [M] (dq/dC of an enhanced species is dqM
-// times its alpha - 1), dT at fixed C, euler (the Euler remainder, or dqM in a
-// constant-volume reactor) and the reaction enthalpy / RT.  The arithmetic is
-// reaction()'s; the Euler remainder q - sum C dq/dC is taken from the
-// reaction's orders (C d(C^nu)/dC = nu C^nu).
-struct RxTerms {
-    double q, d[6], dqM, ea[sc::MAXENH], dT, euler, dH;
-};
-template <bool JAC, int NV>
-__device__ __forceinline__ RxTerms reaction_sp(const DevMech &m, const DevSparse &sp, double *lds, const Rec &r,
-                                               uint32_t flags, int j, const Mix<> &x, double dl, const double *itb,
-                                               double itt)
-{
-    RxTerms o;
-    double c[6], p[6], dp[6], nu[6];
-    double dG = 0.0, dH = 0.0;
-    const double lnkinf = r.lnA() + dl + r.bT() * x.lnT - r.EaR() * x.invT;
-    const double kinf = exp(lnkinf);
-    const char *cg = (const char *)(lds + SPL_CG * NV), *hw = (const char *)(lds + SPL_HW * NV);
-    double g[6], h[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        const double2 v = *(const double2 *)(cg + r.slot(i));
-        c[i] = v.x;
-        g[i] = v.y;
-        if (JAC) h[i] = *(const double *)(hw + r.slot(i));
-        p[i] = c[i];
-        dp[i] = nu[i] = 1.0;
-    }
-    if (flags & sc::RXF_NU) {
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            const int v = r.nu(i);
-            nu[i] = v;
-            const double c2 = c[i] * c[i];
-            p[i] = v == 2 ? c2 : v == 3 ? c2 * c[i] : c[i];
-            dp[i] = v == 2 ? 2.0 * c[i] : v == 3 ? 3.0 * c2 : 1.0;
-        }
-    }
-    if (itb) {
-        const double *itc = itb + (size_t)min(j, m.R - 1) * 2 * (sp.ideg + 1);
-        dG = -poly_t(itc, sp.ideg, itt);
-        if (JAC) dH = poly_t(itc + sp.ideg + 1, sp.ideg, itt);
-    } else {
-        // an unused slot of a pass with larger coefficients has nu = 0 and
-        // the dummy's g = h = 0 in any other
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            dG += nu[3 + i] * g[3 + i] - nu[i] * g[i];
-            if (JAC) dH += nu[3 + i] * h[3 + i] - nu[i] * h[i];
-        }
-    }
-    const double dnu = r.dnu();
-    const double lnKc = -dG + dnu * (m.lnp0R - x.lnT);
-    const double M0 = x.p * x.invT / m.Rgas;
-    double M = M0, Me = 0.0;
-    if (flags & sc::RXF_TB) {
-#pragma unroll
-        for (int e = 0; e < sc::MAXENH; ++e) o.ea[e] = 0.0;
-        if (j < sp.n_tb) {
-#pragma unroll
-            for (int e = 0; e < sc::MAXENH; ++e) {
-                o.ea[e] = sp.eam1[4 * j + e];
-                Me += o.ea[e] * *(const double *)(cg + r.enh(e));
-            }
-        }
-        M += Me;
-    }
-    const int kind = r.kind();
-    double kf = kinf, phi = 0.0, dlnF_T = 0.0, dlnk0 = 0.0;
-    if ((flags & sc::RXF_TROE) && kind == sc::RX_TROE) {
-        const TroeRec tr = sp.troe[j];
-        const double lnk0 = tr.lnA0 + dl + tr.b0 * x.lnT - tr.Ea0R * x.invT;
-        const double Pr = exp(lnk0 - lnkinf) * M;
-        const double a = tr.a, iT3 = tr.iT3, iT1 = tr.iT1, T2 = tr.T2;
-        const double e3 = exp(-x.T * iT3), e1 = exp(-x.T * iT1), e2 = exp(-T2 * x.invT);
-        const double Fc = (1.0 - a) * e3 + a * e1 + e2;
-        const double L = log10(Fc);
-        const double cc = -0.4 - 0.67 * L, nn = 0.75 - 1.27 * L;
-        const double X = log10(Pr) + cc;
-        const double D = nn - 0.14 * X;
-        const double f = X / D;
-        const double opf = 1.0 + f * f;
-        const double lF = L / opf;
-        kf = kinf * (Pr / (1.0 + Pr)) * exp(2.302585092994046 * lF);
-        if (JAC) {
-            const double gg = -L * 2.0 * f / (opf * opf);
-            phi = 1.0 / (1.0 + Pr) + gg * (nn / (D * D));  // dln kf / dln Pr
-            const double dlF_dL = 1.0 / opf + gg * ((-0.67 * nn + 1.27 * X) / (D * D));
-            const double dFc = -(1.0 - a) * iT3 * e3 - a * iT1 * e1 + T2 * x.invT * x.invT * e2;
-            dlnF_T = dlF_dL * dFc / Fc;  // dln F/dT at fixed Pr
-            dlnk0 = (tr.b0 + tr.Ea0R * x.invT) * x.invT;
-        }
-    }
-    const double kr = kf * exp(-lnKc);
-    const double Rf = kf * (p[0] * p[1] * p[2]), Rr = kr * (p[3] * p[4] * p[5]);
-    const double q0 = Rf - Rr;
-    const bool third = (flags & sc::RXF_TB) && kind == sc::RX_THIRD;
-    const double fsc = third ? M : 1.0;
-    o.q = fsc * q0;
-    if (!JAC) return o;
-    const double F = fsc * kf, B = -fsc * kr;
-    o.d[0] = F * (p[1] * p[2]) * dp[0];
-    o.d[1] = F * (p[0] * p[2]) * dp[1];
-    o.d[2] = F * (p[0] * p[1]) * dp[2];
-    o.d[3] = B * (p[4] * p[5]) * dp[3];
-    o.d[4] = B * (p[3] * p[5]) * dp[4];
-    o.d[5] = B * (p[3] * p[4]) * dp[5];
-    const double dlnkinf = (r.bT() + r.EaR() * x.invT) * x.invT;
-    const double dlnKc = (dH - dnu) * x.invT;
-    double dlnkf = dlnkinf;
-    o.dqM = 0.0;
-    const double dMdT = m.cv ? 0.0 : -M0 * x.invT;
-    if (flags & sc::RXF_TB) {
-        if (kind == sc::RX_THIRD) {
-            o.dqM = q0;
-        } else if (kind == sc::RX_TROE) {
-            o.dqM = q0 * phi / M;
-            dlnkf = dlnkinf + phi * (dlnk0 - dlnkinf + dMdT / M) + dlnF_T;
-        }
-    }
-    o.dT = fsc * (q0 * dlnkf + Rr * dlnKc);
-    if (third) o.dT += q0 * dMdT;
-    // q - sum_s C_s dq/dC_s: (1 - order) of each direction, less the
-    // enhanced species' share of [M]
-    o.euler = m.cv ? o.dqM
-                   : fsc * ((1.0 - r.order(0)) * Rf - (1.0 - r.order(1)) * Rr) - o.dqM * Me;
-    o.dH = dH;
-    return o;
-}
-
 // f(y): dY_k/dt and dT/dt, VPL components per lane (0 beyond N).  Per pass
-// the record loads of the next are in flight.  A lane adds for the slots its
-// reaction uses only: at full occupancy the LDS additions bind, about 14
-// cycles for 64 lanes and more where they meet in one address (with every
-// lane adding, the unused slots into trash entries, 65,536 evaluations took
-// 341 us instead of 262, 4,096 Jacobians 139 instead of 120, 16,384 cells of
-// 9 species 47 ms instead of 40).
-template <int VPL, int G = WAVE>
-__device__ __forceinline__ void rhs_v(const DevMech &m, const DevSparse &sp, double *lds, const double (&y)[VPL], double p,
+// the record loads of the next are in flight.
+template <int VPL, int G, class CR>
+__device__ __forceinline__ void rhs_v(const CR &crew, const DevMech &m, const DevSparse &sp, double *lds, const double (&y)[VPL], double p,
                       const double *dlnA, int lane, double (&f)[VPL])
 {
     constexpr int NV = G * VPL;
     const int N = m.N;
     Thermo<> th[VPL];
-    Rec nxt = load_rx<G>(sp, 0, lane);
-    const Mix<> x = mixture_v<VPL, G>(m, lds, y, p, th, lane);
+    Rec nxt = load_rx<G>(sp, max(crew.first(sp), 0), lane);
+    const Mix<> x = mixture_v<VPL, G>(crew, m, sp, lds, y, p, th, lane);
     double itt;
     const double *itb = thermo_block(sp, m.R, x.lnT, itt);
-    lds_sync();
-    char *wd = (char *)(lds + SPL_HW * NV + 1);
-    // the reaction loop, compiled once with the tables and once without (the
-    // exact path's code does not carry the tables' branches)
-    auto pass = [&](auto tables) __attribute__((always_inline)) {
-#pragma unroll 1
-        for (int q = 0; q < sp.passes; ++q) {
-            const Rec r = nxt;
-            nxt = load_rx<G>(sp, min(q + 1, sp.passes - 1), lane);
-            const uint32_t flags = __builtin_amdgcn_readfirstlane(r.bits());
-            const double dl = dlnA ? dlnA[r.orig()] : 0.0;
-            const RxTerms o = reaction_sp<false, NV>(m, sp, lds, r, flags, q * G + lane, x, dl,
-                                                     decltype(tables)::value ? itb : nullptr, itt);
-#pragma unroll
-            for (int i = 0; i < 6; ++i) {
-                if (i == 2 && !(flags & sc::RXF_THIRD_REAC)) continue;
-                if (i == 5 && !(flags & sc::RXF_THIRD_PROD)) continue;
-                double v = i < 3 ? -o.q : o.q;
-                if (flags & sc::RXF_NU) v *= r.nu(i);
-                if (r.nu(i) > 0) atomicAdd((double *)(wd + r.slot(i)), v);
-            }
-        }
-    };
+    crew.sync();
+    // compiled once with the tables and once without (the exact path's code
+    // does not carry the tables' branches)
     if (itb)
-        pass(std::true_type{});
+        rhs_passes<G, NV, true>(crew, m, sp, sp.ideg, lds, x, dlnA, lane, itb, itt, nxt);
     else
-        pass(std::false_type{});
-    lds_sync();
+        rhs_passes<G, NV, false>(crew, m, sp, 0, lds, x, dlnA, lane, nullptr, 0.0, nxt);
+    crew.sync();
     double hw[VPL];
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
@@ -415,119 +295,42 @@ __device__ __forceinline__ void rhs_v(const DevMech &m, const DevSparse &sp, dou
 #pragma unroll
     for (int v = 0; v < VPL; ++v)
         if (lane + G * v == N) f[v] = fT;
-    lds_sync();
+    crew.sync();
 }
 
 // Jacobian pass: f(y), and the bordered matrix of I/hg - J formed in the L+U
 // entries (fill entries zero).  The reaction loop scatters -nu dq/dC and
 // -nu dq/dT into the species rows and the reaction-enthalpy-weighted
 // derivatives into the temperature row; the border entries are finished per
-// state component after one barrier.  The sums every reaction adds to, the
-// (T, T) entry and a constant-volume reactor's border term, stay in a register
-// per lane until the end (64 LDS additions to one address run one by one).
-template <int VPL, int G = WAVE>
-__device__ __forceinline__ void jac_v(const DevMech &m, const DevSparse &sp, double *lds, const double (&y)[VPL], double p,
+// state component after one barrier.
+template <int VPL, int G, class CR>
+__device__ __forceinline__ void jac_v(const CR &crew, const DevMech &m, const DevSparse &sp, double *lds, const double (&y)[VPL], double p,
                       const double *dlnA, int lane, double inv_hg, double (&f)[VPL])
 {
     constexpr int NV = G * VPL;
     const int N = m.N;
     double *E = lds + SPL_E * NV;
     Thermo<> th[VPL];
-    Rec nxt = load_rx<G>(sp, 0, lane);
-    const Mix<> x = mixture_v<VPL, G>(m, lds, y, p, th, lane);
+    Rec nxt = load_rx<G>(sp, max(crew.first(sp), 0), lane);
+    crew.barrier();  // what it clears has been read
+    const Mix<> x = mixture_v<VPL, G>(crew, m, sp, lds, y, p, th, lane);
+    double *const ts = lds + SPL_U * NV + lane;  // a crew's tt and tm
+    if (crew.rank == 0 && crew.w > 1) ts[0] = ts[NV] = 0.0;
+    // and the zero slot (the same number of turns for every lane)
 #pragma unroll 4
-    for (int e = 2 * lane; e <= sp.nnz; e += 2 * G) *(double2 *)(E + e) = make_double2(0.0, 0.0);  // and the zero slot
-    lds_sync();
+    for (int e = 2 * G * crew.rank; e <= sp.nnz; e += 2 * G * crew.w)
+        *(double2 *)(E + min(e + 2 * lane, sp.nnz & ~1)) = make_double2(0.0, 0.0);
+    crew.sync();
     const double RT = m.Rgas * x.T;
     double itt;
     const double *itb = thermo_block(sp, m.R, x.lnT, itt);
-    char *wd = (char *)(lds + SPL_HW * NV + 1), *ua = (char *)(lds + SPL_UA * NV);
-    auto add = [&](uint32_t o, double v) __attribute__((always_inline)) {
-        atomicAdd((double *)((char *)E + (VPL == 1 ? o : 8 * o)), v);
-    };
     double tt = 0.0, tm = 0.0;
-    auto pass = [&](auto tables) __attribute__((always_inline)) {
-#pragma unroll 1
-        for (int q = 0; q < sp.passes; ++q) {
-            const Rec r = nxt;
-            const uint4 *ip = (const uint4 *)sp.ix + (size_t)q * sc::RXW_IX * G + lane;
-            uint32_t ix[4 * sc::RXW_IX];
-#pragma unroll
-            for (int c = 0; c < sc::RXW_IX; ++c) {
-                const uint4 w = ip[c * G];
-                ix[4 * c] = w.x, ix[4 * c + 1] = w.y, ix[4 * c + 2] = w.z, ix[4 * c + 3] = w.w;
-            }
-            nxt = load_rx<G>(sp, min(q + 1, sp.passes - 1), lane);
-            const uint32_t flags = __builtin_amdgcn_readfirstlane(r.bits());
-            const double dl = dlnA ? dlnA[r.orig()] : 0.0;
-            const int j = q * G + lane;
-            const RxTerms o = reaction_sp<true, NV>(m, sp, lds, r, flags, j, x, dl,
-                                                    decltype(tables)::value ? itb : nullptr, itt);
-            auto at = [&](int e) __attribute__((always_inline)) { return e % 2 ? ix[e / 2] >> 16 : ix[e / 2] & 0xffff; };
-            // temperature-row weight: the reaction enthalpy (constant pressure) or
-            // internal energy (constant volume), per unit of progress
-            const double dHJ = m.cv ? (o.dH - r.dnu()) * RT : o.dH * RT;
-            auto row = [&](auto I, auto NU) __attribute__((always_inline)) {
-                constexpr int i = I;
-                if (r.nu(i) == 0) return;
-                double w = i < 3 ? -1.0 : 1.0;
-                if (decltype(NU)::value) w *= r.nu(i);
-                // without coefficients the weight is a constant and the products fold to signs
-                atomicAdd((double *)(wd + r.slot(i)), w * o.q);
-                atomicAdd((double *)(ua + r.slot(i) / 2), w * o.euler);
-                add(at(7 * i), -w * o.d[0]);
-                add(at(7 * i + 1), -w * o.d[1]);
-                if (r.nu(2) > 0) add(at(7 * i + 2), -w * o.d[2]);
-                add(at(7 * i + 3), -w * o.d[3]);
-                add(at(7 * i + 4), -w * o.d[4]);
-                if (r.nu(5) > 0) add(at(7 * i + 5), -w * o.d[5]);
-                add(at(7 * i + 6), -w * o.dT);
-            };
-            auto rows = [&](auto NU) __attribute__((always_inline)) {
-                row(std::integral_constant<int, 0>{}, NU);
-                row(std::integral_constant<int, 1>{}, NU);
-                if (flags & sc::RXF_THIRD_REAC) row(std::integral_constant<int, 2>{}, NU);
-                row(std::integral_constant<int, 3>{}, NU);
-                row(std::integral_constant<int, 4>{}, NU);
-                if (flags & sc::RXF_THIRD_PROD) row(std::integral_constant<int, 5>{}, NU);
-            };
-            if (flags & sc::RXF_NU)
-                rows(std::true_type{});
-            else
-                rows(std::false_type{});
-#pragma unroll
-            for (int s = 0; s < 6; ++s) {
-                if ((s == 2 || s == 5) && r.nu(s) == 0) continue;
-                add(at(42 + s), dHJ * o.d[s]);
-            }
-            tt += dHJ * o.dT;
-            if (m.cv) tm += dHJ * o.euler;
-            if ((flags & sc::RXF_TB) && j < sp.n_tb) {
-                const uint4 *ep = (const uint4 *)sp.ixe + (size_t)q * sc::RXW_IXE * G + lane;
-                uint32_t ie[4 * sc::RXW_IXE];
-#pragma unroll
-                for (int c = 0; c < sc::RXW_IXE; ++c) {
-                    const uint4 w = ep[c * G];
-                    ie[4 * c] = w.x, ie[4 * c + 1] = w.y, ie[4 * c + 2] = w.z, ie[4 * c + 3] = w.w;
-                }
-#pragma unroll
-                for (int i = 0; i < 7; ++i) {
-                    const double w = i == 6 ? dHJ * o.dqM : (i < 3 ? o.dqM : -o.dqM) * r.nu(i < 6 ? i : 0);
-#pragma unroll
-                    for (int e = 0; e < sc::MAXENH; ++e) {
-                        const int k = 4 * i + e;
-                        if (r.enh(e) == 16u * (N + 1) || (i < 6 && r.nu(i) == 0)) continue;
-                        add(k % 2 ? ie[k / 2] >> 16 : ie[k / 2] & 0xffff, w * o.ea[e]);
-                    }
-                }
-            }
-        }
-    };
     if (itb)
-        pass(std::true_type{});
+        jac_passes<G, NV, VPL == 1, -1, true>(crew, m, sp, sp.ideg, lds, E, x, RT, dlnA, lane, itb, itt, nxt, ts, tt, tm);
     else
-        pass(std::false_type{});
-    lds_sync();
+        jac_passes<G, NV, VPL == 1, -1, false>(crew, m, sp, 0, lds, E, x, RT, dlnA, lane, nullptr, 0.0, nxt, ts, tt, tm);
+    crew.sync();
+    if (crew.w > 1) tt = ts[0], tm = ts[NV];
     const double one = m.cv ? 1.0 : 0.0;
     double hw[VPL], eu[VPL], cpf[VPL], dcp[VPL], uak[VPL];
     uint4 cm[VPL];
@@ -561,6 +364,10 @@ __device__ __forceinline__ void jac_v(const DevMech &m, const DevSparse &sp, dou
     for (int v = 0; v < VPL; ++v) {
         const int c = lane + G * v;
         const int e0 = cm[v].x & 0xffff, e1 = cm[v].x >> 16, e2 = cm[v].y & 0xffff, e3 = cm[v].y >> 16, e4 = cm[v].z & 0xffff;
+        if constexpr (!std::is_same_v<CR, Solo>) {
+            if (c == N) f[v] = fT;
+            if (crew.rank != 0) continue;
+        }
         if (c < N) {
             const double us = m.cv ? uak[v] : uak[v] / x.rho;
             E[e0] += inv_hg;
@@ -575,7 +382,7 @@ __device__ __forceinline__ void jac_v(const DevMech &m, const DevSparse &sp, dou
             E[e1] = -1.0;
         }
     }
-    lds_sync();
+    crew.sync();
 }
 
 // ---------------------------------------------------------------------------
@@ -586,87 +393,6 @@ template <int VPL>
 __device__ __forceinline__ double entry(const double *E, uint32_t o)
 {
     return VPL == 1 ? *(const double *)((const char *)E + o) : E[o];
-}
-
-// v from lane K of each cell's group, K known at compile time: a row
-// broadcast of the DPP unit for 16 lanes; for 32, readlane of both groups and
-// a select.
-template <int G, int K>
-__device__ __forceinline__ double bcast(double v)
-{
-    static_assert(G == 16 || G == 32, "groups of several cells per wave");
-    if constexpr (G == 16) {
-        const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x150 + K, 0xf, 0xf, true);
-        const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x150 + K, 0xf, 0xf, true);
-        return __hiloint2double(hi, lo);
-    } else {
-        const double a = rdlane(v, K), b = rdlane(v, 32 + K);
-        return threadIdx.x & 32 ? b : a;
-    }
-}
-
-// z -= a z_K, z_K from lane K of the row of 16 lanes: one instruction (the
-// broadcast reads a register two wait states after it was written)
-template <int K>
-__device__ __forceinline__ void fmac_row(double &z, double a)
-{
-    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, -%1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+&v"(z) : "v"(a), "n"(K));
-}
-// the same for four vectors
-template <int K>
-__device__ __forceinline__ void fmac_row4(double &x, double &y, double &z, double &w, double a)
-{
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %0, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, %1, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %2, %2, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %3, %3, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
-        : "+&v"(x), "+&v"(y), "+&v"(z), "+&v"(w)
-        : "v"(a), "n"(K));
-}
-// z -= a z_K on the lanes of the rows in ROWS
-template <int K, int ROWS>
-__device__ __forceinline__ void fmac_in(double &z, double a)
-{
-    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, -%1 row_newbcast:%2 row_mask:%3 bank_mask:0xf"
-        : "+&v"(z)
-        : "v"(a), "n"(K), "n"(ROWS));
-}
-// z -= sum a[i] x_{K + i}, i = 0..3, on the lanes of the rows in ROWS
-template <int K, int ROWS>
-__device__ __forceinline__ void fmac_by4(double &z, double x, const double *a)
-{
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %1, -%2 row_newbcast:%6 row_mask:%10 bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %0, %1, -%3 row_newbcast:%7 row_mask:%10 bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %0, %1, -%4 row_newbcast:%8 row_mask:%10 bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %0, %1, -%5 row_newbcast:%9 row_mask:%10 bank_mask:0xf"
-        : "+&v"(z)
-        : "v"(x), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "n"(K), "n"(K + 1), "n"(K + 2), "n"(K + 3), "n"(ROWS));
-}
-// the lanes of row B of 16 in every row
-template <int B>
-__device__ __forceinline__ double spread_row(double v)
-{
-    auto half = [](int x) __attribute__((always_inline)) {
-        const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-        const int y = B & 1 ? a[1] : a[0];
-        const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
-        return (int)(B & 2 ? b[1] : b[0]);
-    };
-    return __hiloint2double(half(__double2hiint(v)), half(__double2loint(v)));
-}
-
-// f(0), ..., f(N - 1) with compile-time arguments
-template <int N, class F, int... I>
-__device__ __forceinline__ void unrolled_(F &&f, std::integer_sequence<int, I...>)
-{
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void unrolled(F &&f)
-{
-    unrolled_<N>(f, std::make_integer_sequence<int, N>{});
 }
 
 // The factors between the factorisation and the solves.  Several cells per
@@ -796,11 +522,21 @@ __device__ __forceinline__ void put(double *E, uint32_t o, double v)
 // elimination by levels of independent pivots it replaces took 48k cycles of
 // a lone wave on 53 species, waiting for 8 levels of indices from L2 and for
 // the broadcasts of a 30-wide register tail.)
-template <int VPL>
-__device__ __forceinline__ void lu_blocks(const DevSparse &sp, double *E, double *DINV, int lane)
+template <int VPL, class CR>
+__device__ __forceinline__ void lu_blocks(const CR &crew, const DevSparse &sp, double *E, double *DINV, int lane)
 {
     constexpr int Q = 4 * VPL - 1;  // most blocks after one
     const int n = sp.n, nb = (n + 15) / 16;
+    // this wave's blocks beside the diagonal one, and its tiles (VPL = 1)
+    uint32_t own = 0, mine = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        if ((q & (crew.w - 1)) == crew.rank) own |= 1u << q;
+        if (VPL == 1)
+#pragma unroll
+            for (int q2 = 0; q2 < Q; ++q2)
+                if (((q + 2 * q2) & (crew.w - 1)) == crew.rank) mine |= 1u << (q + Q * q2);
+    }
     const int c = lane & 15;
     const uint4 *t = (const uint4 *)sp.blk + lane;
     // a block's first words, loaded one block ahead
@@ -810,12 +546,13 @@ __device__ __forceinline__ void lu_blocks(const DevSparse &sp, double *E, double
         for (int w = 0; w < 4; ++w) wd[w] = t[w * WAVE];
 #pragma unroll
         for (int q = 0; q < Q; ++q)
-            if (q < r) wu[q] = t[(4 + q) * WAVE];
+            if (q < r && (own >> q & 1)) wu[q] = t[(4 + q) * WAVE];
     };
     words(nb - 1);
 #pragma unroll 1
     for (int b = 0; b < nb; ++b) {
         const int k0 = 16 * b, r = nb - 1 - b;
+        const uint32_t act = own & ((1u << r) - 1);
         const uint4 id0 = wd[0], id1 = wd[1], it0 = wd[2], it1 = wd[3];
         uint4 ul[Q];
 #pragma unroll
@@ -828,7 +565,7 @@ __device__ __forceinline__ void lu_blocks(const DevSparse &sp, double *E, double
         for (int k = 0; k < 16; ++k) D[k] = entry<VPL>(E, half_of(k < 8 ? id0 : id1, k % 8));
 #pragma unroll
         for (int q = 0; q < Q; ++q)
-            if (q < r) {
+            if (act >> q & 1) {
 #pragma unroll
                 for (int h = 0; h < 4; ++h) {
                     u[q][h] = entry<VPL>(E, half_of(ul[q], h));
@@ -853,24 +590,27 @@ __device__ __forceinline__ void lu_blocks(const DevSparse &sp, double *E, double
                     for (int j = j0 + (16 - j0) / 4 * 4; j < 16; ++j) fmac_row<k>(D[j], l);
 #pragma unroll
                     for (int q = 0; q < Q; ++q)
-                        if (q < r) fmac_row4<k>(u[q][0], u[q][1], u[q][2], u[q][3], l);
+                        if (act >> q & 1) fmac_row4<k>(u[q][0], u[q][1], u[q][2], u[q][3], l);
                 }
             }
         });
+        crew.barrier();  // the block has been read
+        if (crew.rank == 0) {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            D[k] *= k > c ? dinv : 1.0;
-            put<VPL>(E, half_of(k < 8 ? id0 : id1, k % 8), D[k]);
+            for (int k = 0; k < 16; ++k) {
+                D[k] *= k > c ? dinv : 1.0;
+                put<VPL>(E, half_of(k < 8 ? id0 : id1, k % 8), D[k]);
+            }
+            if (lane < 16 && k0 + c < n) DINV[k0 + c] = dinv;
         }
-        if (lane < 16 && k0 + c < n) DINV[k0 + c] = dinv;
         if (r == 0) break;
 #pragma unroll
         for (int q = 0; q < Q; ++q)
-            if (q < r) {
+            if (act >> q & 1) {
 #pragma unroll
                 for (int h = 0; h < 4; ++h) put<VPL>(E, half_of(ul[q], h), u[q][h] * dinv);
             }
-        lds_sync();
+        crew.sync();
         uint4 ab[VPL == 1 ? Q : 1];
         uint2 ci[VPL == 1 ? Q : 1][VPL == 1 ? Q : 1];
         if constexpr (VPL == 1) {
@@ -880,7 +620,7 @@ __device__ __forceinline__ void lu_blocks(const DevSparse &sp, double *E, double
                     ab[q] = ta[q * WAVE];
 #pragma unroll
                     for (int q1 = 0; q1 < Q; ++q1)
-                        if (q1 < r) ci[q1][q] = ct[(q1 * r + q) * WAVE];
+                        if (q1 < r && (mine >> (q1 + Q * q) & 1)) ci[q1][q] = ct[(q1 * r + q) * WAVE];
                 }
         }
 #pragma unroll
@@ -889,15 +629,15 @@ __device__ __forceinline__ void lu_blocks(const DevSparse &sp, double *E, double
             constexpr int k = K;
 #pragma unroll
             for (int q = 0; q < Q; ++q)
-                if (q < r) fmac_row4<k>(x[q][0], x[q][1], x[q][2], x[q][3], D[k]);
+                if (act >> q & 1) fmac_row4<k>(x[q][0], x[q][1], x[q][2], x[q][3], D[k]);
         });
 #pragma unroll
         for (int q = 0; q < Q; ++q)
-            if (q < r) {
+            if (act >> q & 1) {
 #pragma unroll
                 for (int h = 0; h < 4; ++h) put<VPL>(E, half_of(ul[q], 4 + h), x[q][h]);
             }
-        lds_sync();
+        crew.sync();
         auto tile = [&](const uint4 &wa, const uint2 &ci, const double (&B)[4]) __attribute__((always_inline)) {
             const uint32_t co[4] = {ci.x & 0xffff, ci.x >> 16, ci.y & 0xffff, ci.y >> 16};
             d4 acc;
@@ -917,18 +657,21 @@ __device__ __forceinline__ void lu_blocks(const DevSparse &sp, double *E, double
                     for (int s = 0; s < 4; ++s) B[s] = entry<VPL>(E, half_of(ab[q2], 4 + s));
 #pragma unroll
                     for (int q1 = 0; q1 < Q; ++q1)
-                        if (q1 < r) tile(ab[q1], ci[q1][q2], B);
+                        if (q1 < r && (mine >> (q1 + Q * q2) & 1)) tile(ab[q1], ci[q1][q2], B);
                 }
             }
         } else {
             // up to 49 tiles: one loop, a tile's indices loaded during the one before
-            uint4 wa = ta[0], wb = wa;
-            uint2 cn = ct[0];
+            const int first = min(crew.rank, r * r - 1);
+            uint4 wa = ta[first % r * WAVE], wb = ta[first / r * WAVE];
+            uint2 cn = ct[(first % r * r + first / r) * WAVE];
             double B[4];
+            int q0 = -1;
 #pragma unroll 1
-            for (int q = 0; q < r * r; ++q) {
-                const int q1 = q % r, nx = min(q + 1, r * r - 1);
-                if (q1 == 0) {
+            for (int q = crew.rank; q < r * r; q += crew.w) {
+                const int q2 = q / r, nx = min(q + crew.w, r * r - 1);
+                if (q2 != q0) {
+                    q0 = q2;
 #pragma unroll
                     for (int s = 0; s < 4; ++s) B[s] = entry<VPL>(E, half_of(wb, 4 + s));
                 }
@@ -940,19 +683,19 @@ __device__ __forceinline__ void lu_blocks(const DevSparse &sp, double *E, double
                 tile(w, c2, B);
             }
         }
+        crew.sync();
 #pragma unroll
         for (int q = 0; q < Q; ++q)
-            if (q < r) {
+            if (act >> q & 1) {
 #pragma unroll
                 for (int h = 0; h < 4; ++h) put<VPL>(E, half_of(ul[q], 4 + h), x[q][h] * dinv);
             }
-        lds_sync();
     }
-    lds_sync();
+    crew.sync();
 }
 
-template <int VPL, int G>
-__device__ __forceinline__ void lu_v(const DevSparse &sp, double *lds, int lane, Factors<VPL, G> &fac)
+template <int VPL, int G, class CR>
+__device__ __forceinline__ void lu_v(const CR &crew, const DevSparse &sp, double *lds, int lane, Factors<VPL, G> &fac)
 {
     constexpr int NV = G * VPL;
     double *E = lds + SPL_E * NV;
@@ -960,7 +703,7 @@ __device__ __forceinline__ void lu_v(const DevSparse &sp, double *lds, int lane,
         lu_group<G>(sp, E, lane, fac);
         lds_sync();
     } else {
-        lu_blocks<VPL>(sp, E, lds + SPL_DINV * NV, lane);
+        lu_blocks<VPL>(crew, sp, E, lds + SPL_DINV * NV, lane);
     }
 }
 
@@ -1079,8 +822,8 @@ __device__ __forceinline__ void solve_v(const DevMech &m, const DevSparse &sp, d
 // ---------------------------------------------------------------------------
 // one Rosenbrock attempt and the integration of a cell
 // ---------------------------------------------------------------------------
-template <int VPL, int G = WAVE>
-__device__ __forceinline__ void ros_attempt_v(const DevMech &m, const DevSparse &sp, const Opts &o, double *lds,
+template <int VPL, int G, class CR>
+__device__ __forceinline__ void ros_attempt_v(const CR &crew, const DevMech &m, const DevSparse &sp, const Opts &o, double *lds,
                               const double (&y)[VPL], double p, const double *dlnA, int lane, double hc, double *err,
                               double (&ynew)[VPL])
 {
@@ -1088,9 +831,9 @@ __device__ __forceinline__ void ros_attempt_v(const DevMech &m, const DevSparse 
     constexpr int NV = G * VPL;
     double *U = lds + SPL_U * NV;
     double f0[VPL], flast[VPL];
-    jac_v<VPL, G>(m, sp, lds, y, p, dlnA, lane, 1.0 / (GAM * hc), f0);
+    jac_v<VPL, G>(crew, m, sp, lds, y, p, dlnA, lane, 1.0 / (GAM * hc), f0);
     Factors<VPL, G> fac;
-    lu_v<VPL, G>(sp, lds, lane, fac);
+    lu_v<VPL, G>(crew, sp, lds, lane, fac);
     const double ih = 1.0 / hc;
 #pragma unroll
     for (int v = 0; v < VPL; ++v) flast[v] = f0[v];
@@ -1111,19 +854,22 @@ __device__ __forceinline__ void ros_attempt_v(const DevMech &m, const DevSparse 
                 ys[v] = y[v];
                 for (int j = 0; j < i; ++j) ys[v] += TA[i][j] * U[j * NV + lane + G * v];
             }
-            rhs_v<VPL, G>(m, sp, lds, ys, p, dlnA, lane, fi);
+            rhs_v<VPL, G>(crew, m, sp, lds, ys, p, dlnA, lane, fi);
 #pragma unroll
             for (int v = 0; v < VPL; ++v) flast[v] = fi[v];
         }
-        double ui[VPL];
 #pragma unroll
         for (int v = 0; v < VPL; ++v) {
             for (int j = 0; j < i; ++j) fi[v] += (TC[i][j] * ih) * U[j * NV + lane + G * v];
             if (lane + G * v >= n) fi[v] = 0.0;
         }
-        solve_v<VPL, G>(m, sp, lds, fac, fi, lane, ui);
+        if (crew.rank == 0) {  // one wave of a crew: four of them wait for the LDS
+            double ui[VPL];
+            solve_v<VPL, G>(m, sp, lds, fac, fi, lane, ui);
 #pragma unroll
-        for (int v = 0; v < VPL; ++v) U[i * NV + lane + G * v] = ui[v];
+            for (int v = 0; v < VPL; ++v) U[i * NV + lane + G * v] = ui[v];
+        }
+        crew.barrier();
     }
     double e2[VPL];
 #pragma unroll
@@ -1157,7 +903,7 @@ __device__ __forceinline__ int advance_v(const DevMech &m, const DevSparse &sp, 
         const int st = ctl_begin(s, o, dt, hc, last);
         if (st != SC_CELL_OK) return st;
         double err, ynew[VPL];
-        ros_attempt_v<VPL, G>(m, sp, o, lds, y, p, dlnA, lane, hc, &err, ynew);
+        ros_attempt_v<VPL, G>(Solo{}, m, sp, o, lds, y, p, dlnA, lane, hc, &err, ynew);
         const int r = ctl_end(s, o, err, hc, last, dt);
         if (r < 0) return -r;
         if (r == 1) {
@@ -1295,6 +1041,165 @@ __global__ void __launch_bounds__(WAVE) SP_OCC k_integrate_sp_static(DevMech mk,
                                  nrej, ref);
 }
 
+// The persistent launch of one cell per wave's 64 lanes: workgroups of several
+// waves.  With one slot per lane each wave has its own LDS region and works by
+// itself while the queue lasts; a wave that finds it empty waits, and when one
+// wave of the workgroup is left with a cell, all of them finish it as a crew.
+// With two slots (one or two cells' LDS in a CU) the workgroup is a crew from
+// the beginning.  Every wait ends: a wave with a cell always gets on, by itself
+// or as the crew, and the one that runs out last counts itself in as well.
+// (A step of 53 species takes a lone wave 62 us, a crew of four 54: the pivots'
+// chains and the solves do not split.  4,096 cells of 110 species, where the
+// LDS leaves half a CU's SIMDs without a wave otherwise: 48.0 -> 41.3 ms; eight
+// substeps of 300 cells of 53 species 42.0 -> 39.1 ms.)
+struct CrewShare {
+    int idle, owner, turn, pad;
+    int64_t next, i, end;
+    Ctl s;
+};
+constexpr int CREW_SHARE = 16;  // doubles ahead of the regions
+static_assert(sizeof(CrewShare) <= CREW_SHARE * sizeof(double));
+constexpr int crew_most(int vpl) { return vpl == 1 ? 4 : 2; }
+
+template <int VPL, bool CV, bool TB>
+__global__ void __launch_bounds__(crew_most(VPL) * WAVE) SP_OCC
+k_integrate_sp_crew(DevMech mk, DevSparse spk, Opts o, int64_t n, const double *T0, const double *P, const double *Y0,
+                    int64_t ld, const double *DT, const double *dlnA, double *h_io, double *T1, double *Y1,
+                    int32_t *status, int32_t *nacc, int32_t *nrej, unsigned long long *queue, const int32_t *perm,
+                    int tile, const int32_t *ref)
+{
+    extern __shared__ double lds[];
+    const DevMech m = fix_reactor<CV>(mk);
+    const DevSparse sp = fix_tables<TB>(spk);
+    constexpr int NV = WAVE * VPL;
+    CrewShare *sh = (CrewShare *)lds;
+    const int lane = (int)threadIdx.x % WAVE;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE), waves = (int)blockDim.x / WAVE;
+    if (threadIdx.x == 0) sh->idle = 0, sh->owner = -1;
+    __syncthreads();
+    // the first tiles go round the workgroups, the queue has those behind
+    Crew crew{1, 0, &sh->turn, 0};
+    if (VPL > 1) crew.join(sp, waves, wave);
+    double *L = lds + CREW_SHARE + (VPL == 1 ? (size_t)wave * sp.size : 0);
+    int64_t i = ((int64_t)(VPL == 1 ? wave : 0) * gridDim.x + blockIdx.x) * tile, end = min(i + tile, n);
+    bool busy = false;
+    double y[VPL], p = 0.0, dt = 0.0;
+    Ctl s = ctl_init(0.0, 0.0);
+#pragma unroll 1
+    while (true) {
+        int st = -1;  // the cell's status, once it ends
+        int64_t c = 0;
+        if (!busy) {
+            if (i >= end && (VPL > 1 || crew.w == 1)) {
+                int64_t next = n;
+                if (VPL > 1) {
+                    __syncthreads();
+                    if (queue && threadIdx.x == 0) sh->next = (int64_t)atomicAdd(queue, (unsigned long long)tile);
+                    __syncthreads();
+                    if (queue) next = sh->next;
+                } else if (queue && lane == 0) {
+                    next = (int64_t)atomicAdd(queue, (unsigned long long)tile);
+                }
+                i = uniform(next);
+                end = min(i + tile, n);
+            }
+            if (i < end) {
+                c = perm ? (int64_t)perm[i] : i;
+                if (ref && ref[c] != c) {  // left to the mapping pass
+                    ++i;
+                    continue;
+                }
+                load_state_v<VPL, WAVE>(m, sp, T0, Y0, ld, c, lane, y);
+                p = P[c], dt = DT[c];
+                s = ctl_init(initial_step(h_io, c, dt), dt);
+                busy = true;
+                if (bad_input_v<VPL, WAVE>(m, y, p, dt, lane))
+                    st = SC_CELL_BAD_INPUT;
+                else if (!(dt > 0.0))
+                    st = SC_CELL_OK;
+            } else if (VPL > 1 || crew.w > 1) {
+                break;
+            }
+        }
+        if (VPL == 1 && crew.w < waves && st < 0) {
+            int idle, owner = -1;
+            if (!busy) {
+                if (lane == 0) __hip_atomic_fetch_add(&sh->idle, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+                while (true) {
+                    // the count first: it is full only when no owner can come any more
+                    idle = __builtin_amdgcn_readfirstlane(
+                        __hip_atomic_load(&sh->idle, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
+                    owner = __builtin_amdgcn_readfirstlane(
+                        __hip_atomic_load(&sh->owner, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
+                    if (owner >= 0 || idle == waves) break;
+                    __builtin_amdgcn_s_sleep(16);
+                }
+                if (owner < 0) break;
+            } else {
+                idle = __builtin_amdgcn_readfirstlane(
+                    __hip_atomic_load(&sh->idle, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
+                if (idle == waves - 1) {
+                    owner = wave;
+#pragma unroll
+                    for (int v = 0; v < VPL; ++v) L[SPL_U * NV + lane + WAVE * v] = y[v];
+                    if (lane == 0) {
+                        sh->i = i, sh->end = end, sh->s = s;
+                        __hip_atomic_store(&sh->owner, wave, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                }
+            }
+            if (owner >= 0) {
+                __syncthreads();
+                L = lds + CREW_SHARE + (size_t)owner * sp.size;
+                i = uniform(sh->i), end = uniform(sh->end);
+                s.t = uniform(sh->s.t), s.h = uniform(sh->s.h), s.hnext = uniform(sh->s.hnext);
+                s.nacc = __builtin_amdgcn_readfirstlane(sh->s.nacc);
+                s.nrej = __builtin_amdgcn_readfirstlane(sh->s.nrej);
+                s.nonfinite = __builtin_amdgcn_readfirstlane(sh->s.nonfinite);
+                s.last_rej = __builtin_amdgcn_readfirstlane(sh->s.last_rej);
+#pragma unroll
+                for (int v = 0; v < VPL; ++v) y[v] = L[SPL_U * NV + lane + WAVE * v];
+                c = perm ? (int64_t)perm[i] : i;
+                p = P[c], dt = DT[c];
+                crew.join(sp, waves, wave);
+                busy = true;
+                __syncthreads();
+            }
+        }
+        if (st < 0) {
+            double hc;
+            bool last;
+            st = ctl_begin(s, o, dt, hc, last);
+            if (st == SC_CELL_OK) {
+                st = -1;
+                double err, ynew[VPL];
+                ros_attempt_v<VPL, WAVE>(crew, m, sp, o, L, y, p, dlnA, lane, hc, &err, ynew);
+                const int r = ctl_end(s, o, uniform(err), hc, last, dt);
+                if (r < 0) st = -r;
+                if (r == 1) {
+#pragma unroll
+                    for (int v = 0; v < VPL; ++v) y[v] = ynew[v];
+                    if (last) st = SC_CELL_OK;
+                }
+            }
+        }
+        if (st >= 0) {
+            if (crew.rank == 0) {
+                c = perm ? (int64_t)perm[i] : i;
+                store_state_v<VPL, WAVE>(m, sp, T1, Y1, ld, c, lane, y);
+                if (lane == 0) {
+                    status[c] = st;
+                    if (nacc) nacc[c] = s.nacc;
+                    if (nrej) nrej[c] = s.nrej;
+                    if (h_io && st == SC_CELL_OK && dt > 0.0) h_io[c] = s.hnext;
+                }
+            }
+            busy = false;
+            ++i;
+        }
+    }
+}
+
 // Doubles of one cell's LDS in the right-hand side kernel: the pairs and the
 // Euler accumulator, without the L+U entries (2.5 KB a cell instead of 19 at
 // 53 species, so registers bound the waves in flight: 16 a CU instead of 8).
@@ -1323,7 +1228,7 @@ __global__ void __launch_bounds__(WAVE) k_rhs_sp(DevMech mk, DevSparse spk, int6
     if (c >= n) return;
     double y[VPL], f[VPL];
     load_state_v<VPL, G>(m, sp, T, Y, ld, c, lane, y);
-    rhs_v<VPL, G>(m, sp, ldsg, y, P[c], dlnA, lane, f);
+    rhs_v<VPL, G>(Solo{}, m, sp, ldsg, y, P[c], dlnA, lane, f);
     store_state_v<VPL, G>(m, sp, fT, fY, ld, c, lane, f);
 }
 
@@ -1345,7 +1250,7 @@ __global__ void __launch_bounds__(WAVE) k_jac_sp(DevMech mk, DevSparse spk, int6
     if (c >= n) return;
     double y[VPL], f[VPL];
     load_state_v<VPL, G>(m, sp, T, Y, ld, c, lane, y);
-    jac_v<VPL, G>(m, sp, ldsg, y, P[c], dlnA, lane, 0.0, f);
+    jac_v<VPL, G>(Solo{}, m, sp, ldsg, y, P[c], dlnA, lane, 0.0, f);
     // a row at a time, columns across the lanes (species order); what depends
     // on the column only is taken once
     const double *E = ldsg + SPL_E * G * VPL;
@@ -1381,7 +1286,7 @@ __global__ void __launch_bounds__(WAVE) k_jac_sp(DevMech mk, DevSparse spk, int6
 }
 
 template <int VPL, bool CV, int CPW, bool TB>
-__global__ void __launch_bounds__(WAVE) k_linsolve_sp(DevMech mk, DevSparse spk, int64_t n, const double *T,
+__global__ void __launch_bounds__(VPL * WAVE) k_linsolve_sp(DevMech mk, DevSparse spk, int64_t n, const double *T,
                                                       const double *P, const double *Y, int64_t ld,
                                                       const double *dlnA, const double *hg, const double *b,
                                                       double *x)
@@ -1389,20 +1294,30 @@ __global__ void __launch_bounds__(WAVE) k_linsolve_sp(DevMech mk, DevSparse spk,
     extern __shared__ double lds[];
     const DevMech m = fix_reactor<CV>(mk);
     const DevSparse sp = fix_tables<TB>(spk);
-    SP_GEOMETRY
-    const int64_t c = (int64_t)blockIdx.x * CPW + grp;
+    // two waves a cell with two slots per lane: the LDS holds one or two cells
+    constexpr int G = WAVE / CPW;
+    const int lane = (int)threadIdx.x % G;
+    const int64_t c = (int64_t)blockIdx.x * CPW + (VPL == 1 ? (int)threadIdx.x / G : 0);
     if (c >= n) return;
+    double *ldsg = lds + (VPL == 1 ? (size_t)((int)threadIdx.x / G) * sp.size : CREW_SHARE);
+    std::conditional_t<VPL == 1, Solo, Crew> crew;
+    if constexpr (VPL > 1)
+    {
+        crew.turn = &((CrewShare *)lds)->turn;
+        crew.join(sp, VPL, __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE));
+    }
     double y[VPL], f[VPL], bb[VPL], xx[VPL];
     load_state_v<VPL, G>(m, sp, T, Y, ld, c, lane, y);
-    jac_v<VPL, G>(m, sp, ldsg, y, P[c], dlnA, lane, 1.0 / hg[c], f);
+    jac_v<VPL, G>(crew, m, sp, ldsg, y, P[c], dlnA, lane, 1.0 / hg[c], f);
     Factors<VPL, G> fac;
-    lu_v<VPL, G>(sp, ldsg, lane, fac);
+    lu_v<VPL, G>(crew, sp, ldsg, lane, fac);
     const int nn = m.N + 1;
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int i = lane + G * v;
         bb[v] = i < nn ? b[c * nn + sp.perm[i]] : 0.0;
     }
+    if (crew.rank != 0) return;
     solve_v<VPL, G>(m, sp, ldsg, fac, bb, lane, xx);
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
@@ -1433,6 +1348,18 @@ __global__ void __launch_bounds__(WAVE) k_linsolve_sp(DevMech mk, DevSparse spk,
 
 // LDS of one workgroup: one region of sp.size doubles per cell of the wave
 static size_t sp_lds(const DevSparse &sp, int cpw) { return sizeof(double) * (size_t)sp.size * cpw; }
+// Waves of a crew workgroup (a power of two): as many as their regions (one in
+// all with two slots per lane) leave room for in a CU's 160 KB
+static size_t crew_lds(int vpl, const DevSparse &sp, int waves)
+{
+    return sizeof(double) * (CREW_SHARE + (size_t)sp.size * (vpl == 1 ? waves : 1));
+}
+static int crew_waves(int vpl, const DevSparse &sp)
+{
+    int w = crew_most(vpl);
+    while (w > 1 && crew_lds(vpl, sp, w) > 160 * 1024) w /= 2;
+    return w;
+}
 static unsigned sp_blocks(int64_t n, int cpw) { return (unsigned)((n + cpw - 1) / cpw); }
 
 hipError_t launch_rhs_sp(int vpl, const DevMech &m, const DevSparse &sp, int64_t n, const double *T,
@@ -1458,18 +1385,27 @@ hipError_t launch_linsolve_sp(int vpl, const DevMech &m, const DevSparse &sp, in
                               const double *b, double *x, hipStream_t s)
 {
     const int cpw = sp.cpw;
-    SP_DISPATCH(hipLaunchKernelGGL(SP_KERNEL(k_linsolve_sp), dim3(sp_blocks(n, cpw)), dim3(WAVE), sp_lds(sp, cpw),
-                                   s, m, sp, n, T, p, Y, ld, dlnA, hg, b, x))
+    SP_DISPATCH(hipLaunchKernelGGL(SP_KERNEL(k_linsolve_sp), dim3(sp_blocks(n, cpw)), dim3(VPLV * WAVE),
+                                   (VPLV == 1 ? sp_lds(sp, cpw) : crew_lds(vpl, sp, VPLV)), s, m, sp, n, T, p, Y, ld, dlnA, hg, b, x))
 }
 
 hipError_t launch_integrate_sp(int vpl, const DevMech &m, const DevSparse &sp, const Opts &o, int64_t n,
                                const double *T0, const double *p, const double *Y0, int64_t ld, const double *dt,
                                const double *dlnA, double *h_io, double *T1, double *Y1, int32_t *st, int32_t *na,
-                               int32_t *nr, const int32_t *ref, hipStream_t s)
+                               int32_t *nr, const int32_t *ref, int crews, hipStream_t s)
 {
     const int cpw = sp.cpw;
-    SP_DISPATCH(hipLaunchKernelGGL(SP_KERNEL(k_integrate_sp), dim3(sp_blocks(n, cpw)), dim3(WAVE), sp_lds(sp, cpw),
-                                   s, m, sp, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1, st, na, nr, ref))
+    // crews where no cell waits for a workgroup then, or, with two slots per
+    // lane, where LDS bounds the cells of a CU and not waves (62 us a step
+    // without, 54 with; one of 110 species 166 and 149).  Four waves at most
+    // each, within a launch's 2^32 threads
+    const int tile = (int)((n >> 22) + 1);
+    if (cpw == 1 && (vpl == 2 || n <= crews))
+        return launch_integrate_sp_persistent(vpl, m, sp, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1, st, na, nr,
+                                              nullptr, nullptr, tile, (int)((n + tile - 1) / tile), ref, s);
+    SP_DISPATCH(if constexpr (VPLV == 1) hipLaunchKernelGGL(
+        SP_KERNEL(k_integrate_sp), dim3(sp_blocks(n, cpw)), dim3(WAVE), sp_lds(sp, cpw), s, m, sp, o, n, T0, p, Y0,
+        ld, dt, dlnA, h_io, T1, Y1, st, na, nr, ref))
 }
 
 hipError_t launch_integrate_sp_persistent(int vpl, const DevMech &m, const DevSparse &sp, const Opts &o,
@@ -1480,9 +1416,14 @@ hipError_t launch_integrate_sp_persistent(int vpl, const DevMech &m, const DevSp
                                           const int32_t *ref, hipStream_t s)
 {
     const int cpw = sp.cpw;
-    SP_DISPATCH(hipLaunchKernelGGL(SP_KERNEL(k_integrate_sp_persistent), dim3((unsigned)grid), dim3(WAVE),
-                                   sp_lds(sp, cpw), s, m, sp, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1, st, na,
-                                   nr, queue, perm, tile, ref))
+    const int waves = crew_waves(vpl, sp);
+    SP_DISPATCH(if constexpr (CPWV == 1) hipLaunchKernelGGL(
+                    (k_integrate_sp_crew<VPLV, CVV, TBV>), dim3((unsigned)grid), dim3(waves * WAVE),
+                    crew_lds(vpl, sp, waves), s, m, sp, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1, st, na, nr,
+                    queue, perm, tile, ref);
+                else hipLaunchKernelGGL(SP_KERNEL(k_integrate_sp_persistent), dim3((unsigned)grid), dim3(WAVE),
+                                        sp_lds(sp, cpw), s, m, sp, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1, st,
+                                        na, nr, queue, perm, tile, ref))
 }
 
 hipError_t launch_integrate_sp_static(int vpl, const DevMech &m, const DevSparse &sp, const Opts &o, int64_t n,
@@ -1498,18 +1439,31 @@ hipError_t launch_integrate_sp_static(int vpl, const DevMech &m, const DevSparse
                                    sp, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1, st, na, nr, group, ref))
 }
 
-int persistent_capacity_sp(int vpl, const DevSparse &sp, int device)
+int64_t queue_start_sp(int vpl, const DevSparse &sp, int grid, int tile)
 {
-    int per_cu = 0, cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return 0;
-    hipError_t e = hipErrorInvalidValue;
+    if (sp.cpw > 1) return 0;
+    return (int64_t)grid * tile * (vpl == 1 ? crew_waves(vpl, sp) : 1);
+}
+
+void capacity_sp(int vpl, const DevSparse &sp, int device, int &persistent, int &fixed)
+{
+    int cus = 0;
+    persistent = fixed = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return;
     const int cpw = sp.cpw;
-    auto occ = [&](auto kern) { return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, WAVE, sp_lds(sp, cpw)); };
-    if (vpl == 1 && cpw == 1) e = occ(k_integrate_sp_persistent<1, false, 1, false>);
-    else if (vpl == 1 && cpw == 2) e = occ(k_integrate_sp_persistent<1, false, 2, false>);
-    else if (vpl == 1 && cpw == 4) e = occ(k_integrate_sp_persistent<1, false, 4, false>);
-    else if (vpl == 2 && cpw == 1) e = occ(k_integrate_sp_persistent<2, false, 1, false>);
-    return e == hipSuccess ? per_cu * cus : 0;
+    auto occ = [&](auto kern, int threads, size_t bytes) {
+        int per_cu = 0;
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, bytes) == hipSuccess ? per_cu * cus : 0;
+    };
+    const int cw = crew_waves(vpl, sp);
+    auto set = [&](auto pers, auto stat) {
+        persistent = cpw == 1 ? occ(pers, cw * WAVE, crew_lds(vpl, sp, cw)) : occ(pers, WAVE, sp_lds(sp, cpw));
+        fixed = occ(stat, WAVE, sp_lds(sp, cpw));
+    };
+    if (vpl == 1 && cpw == 1) set(k_integrate_sp_crew<1, false, false>, k_integrate_sp_static<1, false, 1, false>);
+    else if (vpl == 1 && cpw == 2) set(k_integrate_sp_persistent<1, false, 2, false>, k_integrate_sp_static<1, false, 2, false>);
+    else if (vpl == 1 && cpw == 4) set(k_integrate_sp_persistent<1, false, 4, false>, k_integrate_sp_static<1, false, 4, false>);
+    else if (vpl == 2 && cpw == 1) set(k_integrate_sp_crew<2, false, false>, k_integrate_sp_static<2, false, 1, false>);
 }
 
 }  // namespace scdev
