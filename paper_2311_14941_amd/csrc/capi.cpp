@@ -851,8 +851,8 @@ sc_status sc_transport2d(int32_t nx, int32_t ny, int32_t ncomp, const double *in
                          void *stream)
 {
     if (nx <= 0 || ny <= 0 || ncomp <= 0) return fail(SC_EINVAL, "nx, ny and ncomp must be positive");
-    // one thread per value in 256-thread blocks on a one-dimensional grid,
-    // whose x dimension holds at most 2^31 - 1 blocks
+    // the values 256-thread blocks on a one-dimensional grid of at most
+    // 2^31 - 1 blocks cover with a thread each
     if ((int64_t)nx * ny * ncomp > (((int64_t)1 << 31) - 1) * 256)
         return fail(SC_EINVAL, "nx * ny * ncomp too large for one launch");
     if (ld < (int64_t)nx * ny) return fail(SC_EINVAL, "ld must be >= nx * ny");

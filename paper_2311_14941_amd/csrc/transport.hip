@@ -22,13 +22,27 @@ namespace scdev {
 // written once.  The cell's place and its two coefficients, an integer and
 // two double divisions, are taken once per KC values; with one thread per
 // value, divided out of a 64-bit index, the arithmetic was the bound.
+// Consecutive workgroups go to the eight dies in turn, each with its own L2: a
+// die takes a contiguous part of the work instead, so that the rows to the
+// north and south are in the L2 that read them, and the stores go past the
+// caches that hold those rows.  601 x 512 cells and 54 rows, 271 MB: 112 us with
+// a thread per value, 87 with six, 86 with the dies' parts, 82 with the stores;
+// 88, 86 and 85 with two, three and nine components a thread.
 constexpr int KC = 6;
+constexpr uint32_t DIES = 8;
 __global__ void __launch_bounds__(256) k_transport2d(int nx, int ny, int ncomp, const double *in, int64_t ld,
                                                      const double *u, const double *dt, double dx, double D,
                                                      const double *inflow, double *out)
 {
     const int64_t n = (int64_t)nx * ny;
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    uint32_t bx = blockIdx.x, by = blockIdx.y;
+    if ((uint64_t)gridDim.x * gridDim.y <= INT32_MAX) {
+        const uint32_t b = by * gridDim.x + bx, all = gridDim.x * gridDim.y, die = b % DIES;
+        const uint32_t t = die * (all / DIES) + min(die, all % DIES) + b / DIES;
+        by = t / gridDim.x;
+        bx = t - by * gridDim.x;
+    }
+    const int64_t c = (int64_t)bx * blockDim.x + threadIdx.x;
     if (c >= n) return;
     int iy, ix;
     if (n <= INT32_MAX) {
@@ -41,7 +55,7 @@ __global__ void __launch_bounds__(256) k_transport2d(int nx, int ny, int ncomp, 
     const double co = u[c] * dt[c] / dx;
     const double fo = D * dt[c] / (dx * dx);
     const int64_t e = ix < nx - 1 ? 1 : 0, s = iy > 0 ? -nx : 0, nth = iy < ny - 1 ? nx : 0;
-    for (int64_t k0 = (int64_t)blockIdx.y * KC; k0 < ncomp; k0 += (int64_t)gridDim.y * KC) {
+    for (int64_t k0 = (int64_t)by * KC; k0 < ncomp; k0 += (int64_t)gridDim.y * KC) {
         double v[KC][5];
 #pragma unroll
         for (int k = 0; k < KC; ++k) {
@@ -57,8 +71,8 @@ __global__ void __launch_bounds__(256) k_transport2d(int nx, int ny, int ncomp, 
 #pragma unroll
         for (int k = 0; k < KC; ++k)
             if (k0 + k < ncomp)
-                out[(k0 + k) * ld + c] = v[k][0] - co * (v[k][0] - v[k][1]) +
-                                                  fo * (v[k][2] + v[k][1] + v[k][3] + v[k][4] - 4.0 * v[k][0]);
+                __builtin_nontemporal_store(v[k][0] - co * (v[k][0] - v[k][1]) +
+                                                fo * (v[k][2] + v[k][1] + v[k][3] + v[k][4] - 4.0 * v[k][0]), out + (k0 + k) * ld + c);
     }
 }
 
