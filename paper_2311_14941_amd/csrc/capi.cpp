@@ -3,7 +3,6 @@
 
 #include <algorithm>
 #include <climits>
-#include <tuple>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -382,58 +381,16 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
     scdev::DevMech &d = p->dm;
     d.N = t.N;
     d.R = t.R;
-    d.nt = t.n_troe;
     d.cv = o.reactor == SC_REACTOR_CONST_V ? 1 : 0;
     d.Rgas = t.Rgas;
     d.lnp0R = std::log(t.p0 / t.Rgas);
-    // species table, reaction records, Troe records
+    // species table
     std::vector<double> spv;
     spv.reserve(9 * (size_t)t.N);
     spv.insert(spv.end(), t.W.begin(), t.W.end());
     spv.insert(spv.end(), t.invW.begin(), t.invW.end());
     spv.insert(spv.end(), t.nasa.begin(), t.nasa.end());
-    // execution order: plain, third-body, Troe; then by side sizes, so that
-    // the 64 reactions of a pass take the same branches (the original index
-    // is kept for per-reaction inputs)
-    std::vector<int> order(t.R);
-    for (int j = 0; j < t.R; ++j) order[j] = j;
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-        auto key = [&](int j) { return std::make_tuple(t.kind[j], t.neff[j] > 0, t.nr[j] + t.np[j]); };
-        return key(x) < key(y);
-    });
-    std::vector<scdev::RxRec> rx(t.R);
-    for (int q = 0; q < t.R; ++q) {
-        const int j = order[q];
-        scdev::RxRec &r = rx[q];
-        std::memset(&r, 0, sizeof r);
-        r.lnA = t.lnA[j];
-        r.b = t.b[j];
-        r.EaR = t.EaR[j];
-        r.kind = t.kind[j];
-        r.nr = t.nr[j];
-        r.np = t.np[j];
-        r.dnu = t.dnu[j];
-        r.neff = t.neff[j];
-        r.tix = t.tix[j];
-        for (int i = 0; i < sc::MAXSIDE; ++i) {
-            r.rsp[i] = t.rsp[i * t.R + j];
-            r.rnu[i] = t.rnu[i * t.R + j];
-            r.psp[i] = t.psp[i * t.R + j];
-            r.pnu[i] = t.pnu[i * t.R + j];
-        }
-        for (int e = 0; e < sc::MAXENH; ++e) {
-            r.esp[e] = t.esp[e * t.R + j];
-            r.eam1[e] = t.eam1[e * t.R + j];
-        }
-        r.orig = j;
-    }
-    std::vector<scdev::TroeRec> tr(t.n_troe > 0 ? t.n_troe : 1);
-    for (int k = 0; k < t.n_troe; ++k) {
-        const int nt = t.n_troe;
-        tr[k] = scdev::TroeRec{t.troe[0 * nt + k], t.troe[1 * nt + k], t.troe[2 * nt + k], t.troe[3 * nt + k],
-                               t.troe[4 * nt + k], t.troe[5 * nt + k], t.troe[6 * nt + k], 0.0};
-    }
-    bool ok = upload(p, spv, &d.sp) && upload(p, rx, &d.rx) && upload(p, tr, &d.troe);
+    bool ok = upload(p, spv, &d.sp);
     if (ok && fit.nint > 0) {
         // the table in the records' execution order: the 64 lanes of a pass
         // read 64 consecutive coefficient blocks of the cell's interval

@@ -346,20 +346,14 @@ struct Lds {
     static constexpr int PS = NP + 1;
     static constexpr int P = 0;          // NP x PS Jacobian terms, later the LU factors (stride NP)
     // the term region is also where the adjoint's dual passes keep the
-    // derivatives of C, G, H, WD and of its own V vector (each at a fixed
-    // offset -C from the value), which ends RXV + 2 NP + (NS + 1) WAVE doubles in
+    // derivatives of the pairs and of its own V vector (each at a fixed
+    // offset -RX from the value), which ends RXV + 2 NP + (NS + 1) WAVE doubles in
     static constexpr int NV = WAVE + 2;     // species and dummy of the reaction passes, even
     static constexpr int RXV = 5 * NV;      // their pairs and Euler terms
     static constexpr int DUAL = RXV + 2 * NP + (NS + 1) * WAVE;
     static constexpr int PREG = NP * PS > DUAL ? NP * PS : DUAL;
-    // the passes' vectors; the adjoint's products have theirs in the same place
-    static constexpr int RX = PREG;
-    static constexpr int C = PREG;       // concentrations
-    static constexpr int G = C + NP;     // g/RT
-    static constexpr int H = G + NP;     // h/RT
-    static constexpr int WD = H + NP;    // production-rate accumulator
-    static constexpr int UA = WD + NP;   // Euler-term accumulator
-    static_assert(5 * NP <= RXV && PREG % 2 == 0, "the passes' pairs are read in one");
+    static constexpr int RX = PREG;         // the passes' vectors
+    static_assert(PREG % 2 == 0, "the passes' pairs are read in one");
     static constexpr int IW = RX + RXV;  // 1/W_c (0 for c >= N)
     static constexpr int U = IW + WAVE;  // NS stage vectors, WAVE apart
     static constexpr int SIZE = U + NS * WAVE;
@@ -429,59 +423,6 @@ __device__ __forceinline__ Mix<S> mixture_point(const DevMech &m, S y, double p,
     }
     return x;
 }
-template <int NP, class S = double>
-__device__ __forceinline__ Mix<S> mixture(const DevMech &m, double *lds, S y, double p, Thermo<S> &th, int lane,
-                                          int toff = 0)
-{
-    const int N = m.N;
-    S yw;
-    const Mix<S> x = mixture_point(m, y, p, th, lane, yw);
-    if (lane < N) {
-        lds_put(lds, Lds<NP>::C + lane, x.rho * yw, toff);
-        lds_put(lds, Lds<NP>::G + lane, th.hRT - th.sR, toff);
-        lds_put(lds, Lds<NP>::H + lane, th.hRT, toff);
-        lds_put(lds, Lds<NP>::WD + lane, S(0.0), toff);
-        lds[Lds<NP>::UA + lane] = 0.0;
-    }
-    if (m.cv && lane == N) lds[Lds<NP>::UA + N] = 0.0;  // temperature-row accumulator (constant volume)
-    return x;
-}
-
-template <class S>
-__device__ __forceinline__ S ipow(S c, int nu)
-{
-    S r = c;
-    if (nu >= 2) r *= c;
-    if (nu >= 3) r *= c;
-    return r;
-}
-template <class S>
-__device__ __forceinline__ S dipow(S c, int nu)  // d(c^nu)/dc
-{
-    return nu == 1 ? S(1.0) : nu == 2 ? 2.0 * c : 3.0 * c * c;
-}
-
-// One reaction's rate of progress and, in the Jacobian pass, its derivatives
-// with respect to the slot species' concentrations and to T.  Slots: 0..2
-// reactants, 3..5 products, 6..9 enhanced third-body species.
-template <class S = double>
-struct RxOut {
-    S q;             // net rate of progress (mol/m^3/s)
-    S d[sc::NDEP];   // dq/dC of slot species
-    S dT;            // dq/dT at fixed C
-    S euler;         // q - sum_s C_s dq/dC_s
-    S dH;            // reaction enthalpy / RT
-};
-
-// A reaction's record in registers: one burst of wide loads issued together
-// (one memory round trip), so later uses of its fields wait on nothing.
-__device__ __forceinline__ RxRec load_rec(const DevMech &m, int j)
-{
-    RxRec r;
-    __builtin_memcpy(&r, &m.rx[j], sizeof(RxRec));
-    return r;
-}
-
 // Horner evaluation of the degree-d polynomial with coefficients c[0..d] at t
 __device__ __forceinline__ double poly_t(const double *c, int d, double t)
 {
@@ -489,131 +430,6 @@ __device__ __forceinline__ double poly_t(const double *c, int d, double t)
 #pragma unroll 1
     for (int q = d - 1; q >= 0; --q) p = fma(p, t, c[q]);
     return p;
-}
-
-// itc: with interpolated thermodynamics, this reaction's coefficients of
-// -dG/RT and dH/RT (degree ideg each, in the local coordinate it of the
-// cell's ln T interval) replace the sums over the species' g/RT and h/RT
-template <bool JAC, class S = double>
-__device__ __forceinline__ RxOut<S> reaction(const DevMech &m, const double *lds, const RxRec &rr, const Mix<S> &x,
-                                             double dl, int CO, int GO, int HO, int toff = 0,
-                                             const double *itc = nullptr, double it = 0.0, int ideg = 0)
-{
-    const int kind = rr.kind;
-    const int nr = rr.nr, np = rr.np;
-    const S lnkinf = rr.lnA + dl + rr.b * x.lnT - rr.EaR * x.invT;
-    const S kinf = exp(lnkinf);
-    int rn[sc::MAXSIDE], pn[sc::MAXSIDE];
-    S rc[sc::MAXSIDE], pc[sc::MAXSIDE];
-    S dG = 0.0, dH = 0.0;
-#pragma unroll
-    for (int i = 0; i < sc::MAXSIDE; ++i) {
-        const bool ur = i < nr, up = i < np;
-        const int rs = ur ? rr.rsp[i] : 0;
-        const int ps = up ? rr.psp[i] : 0;
-        rn[i] = ur ? rr.rnu[i] : 0;
-        pn[i] = up ? rr.pnu[i] : 0;
-        rc[i] = ur ? lds_get<S>(lds, CO + rs, toff) : S(1.0);
-        pc[i] = up ? lds_get<S>(lds, CO + ps, toff) : S(1.0);
-        if (itc) continue;
-        dG += pn[i] * (up ? lds_get<S>(lds, GO + ps, toff) : S(0.0)) -
-              rn[i] * (ur ? lds_get<S>(lds, GO + rs, toff) : S(0.0));
-        if (JAC)
-            dH += pn[i] * (up ? lds_get<S>(lds, HO + ps, toff) : S(0.0)) -
-                  rn[i] * (ur ? lds_get<S>(lds, HO + rs, toff) : S(0.0));
-    }
-    if (itc) {
-        dG = -poly_t(itc, ideg, it);
-        if (JAC) dH = poly_t(itc + ideg + 1, ideg, it);
-    }
-    const int dnu = rr.dnu;
-    const S lnKc = -dG + dnu * (m.lnp0R - x.lnT);
-    // third-body concentration, rewritten with sum_k C_k = p/(R T):
-    // [M] = p/(RT) + sum_enhanced (alpha - 1) C.  At constant pressure p/(RT)
-    // depends on T alone; at constant volume it is rho/Wbar, a function of
-    // every C_k (dM/dC_k = 1, the rank-one part the caller adds)
-    S M = 0.0;
-    const int ne = rr.neff;
-    S ec[sc::MAXENH];
-    double ea[sc::MAXENH];
-#pragma unroll
-    for (int e = 0; e < sc::MAXENH; ++e) {
-        const bool ue = e < ne;
-        ea[e] = ue ? rr.eam1[e] : 0.0;
-        ec[e] = ue ? lds_get<S>(lds, CO + rr.esp[e], toff) : S(0.0);
-    }
-    if (kind != sc::RX_PLAIN) {
-        M = x.p * x.invT / m.Rgas;
-#pragma unroll
-        for (int e = 0; e < sc::MAXENH; ++e) M += ea[e] * ec[e];
-    }
-    S kf = kinf, phi = 0.0, dlnF_T = 0.0, dlnk0 = 0.0;
-    if (kind == sc::RX_TROE) {
-        const TroeRec &tr = m.troe[rr.tix];
-        const S lnk0 = tr.lnA0 + dl + tr.b0 * x.lnT - tr.Ea0R * x.invT;
-        const S Pr = exp(lnk0 - lnkinf) * M;
-        const double a = tr.a, iT3 = tr.iT3, iT1 = tr.iT1, T2 = tr.T2;
-        const S e3 = exp(-x.T * iT3), e1 = exp(-x.T * iT1), e2 = exp(-T2 * x.invT);
-        const S Fc = (1.0 - a) * e3 + a * e1 + e2;
-        const S L = log10(Fc);
-        const S cc = -0.4 - 0.67 * L, nn = 0.75 - 1.27 * L;
-        const S X = log10(Pr) + cc;
-        const S D = nn - 0.14 * X;
-        const S f = X / D;
-        const S opf = 1.0 + f * f;
-        const S lF = L / opf;
-        kf = kinf * (Pr / (1.0 + Pr)) * exp(2.302585092994046 * lF);
-        if (JAC) {
-            const S g = -L * 2.0 * f / (opf * opf);
-            phi = 1.0 / (1.0 + Pr) + g * (nn / (D * D));  // dln kf / dln Pr
-            const S dlF_dL = 1.0 / opf + g * ((-0.67 * nn + 1.27 * X) / (D * D));
-            const S dFc = -(1.0 - a) * iT3 * e3 - a * iT1 * e1 + T2 * x.invT * x.invT * e2;
-            dlnF_T = dlF_dL * dFc / Fc;  // dln F/dT at fixed Pr
-            dlnk0 = (tr.b0 + tr.Ea0R * x.invT) * x.invT;
-        }
-    }
-    const S kr = kf * exp(-lnKc);
-    const S p0 = ipow(rc[0], rn[0]), p1 = ipow(rc[1], rn[1]), p2 = ipow(rc[2], rn[2]);
-    const S s0 = ipow(pc[0], pn[0]), s1 = ipow(pc[1], pn[1]), s2 = ipow(pc[2], pn[2]);
-    const S Rf = kf * (p0 * p1 * p2), Rr = kr * (s0 * s1 * s2);
-    const S q0 = Rf - Rr;
-    RxOut<S> o;
-    o.q = kind == sc::RX_THIRD ? q0 * M : q0;
-    if (!JAC) return o;
-    const S fsc = kind == sc::RX_THIRD ? M : S(1.0);
-    o.d[0] = nr > 0 ? fsc * kf * dipow(rc[0], rn[0]) * p1 * p2 : S(0.0);
-    o.d[1] = nr > 1 ? fsc * kf * dipow(rc[1], rn[1]) * p0 * p2 : S(0.0);
-    o.d[2] = nr > 2 ? fsc * kf * dipow(rc[2], rn[2]) * p0 * p1 : S(0.0);
-    o.d[3] = np > 0 ? -fsc * kr * dipow(pc[0], pn[0]) * s1 * s2 : S(0.0);
-    o.d[4] = np > 1 ? -fsc * kr * dipow(pc[1], pn[1]) * s0 * s2 : S(0.0);
-    o.d[5] = np > 2 ? -fsc * kr * dipow(pc[2], pn[2]) * s0 * s1 : S(0.0);
-    const S dlnkinf = (rr.b + rr.EaR * x.invT) * x.invT;
-    const S dlnKc = (dH - dnu) * x.invT;
-    const S dMdT = m.cv ? S(0.0) : -x.p * x.invT * x.invT / m.Rgas;
-    S dqM = 0.0;  // dq/d[M]
-    S dlnkf = dlnkinf;
-    if (kind == sc::RX_THIRD) {
-        dqM = q0;
-    } else if (kind == sc::RX_TROE) {
-        dqM = q0 * phi / M;
-        dlnkf = dlnkinf + phi * (dlnk0 - dlnkinf + dMdT / M) + dlnF_T;
-    }
-    S dT = q0 * dlnkf + Rr * dlnKc;
-    if (kind == sc::RX_THIRD) dT = M * dT + q0 * dMdT;
-#pragma unroll
-    for (int e = 0; e < sc::MAXENH; ++e) o.d[6 + e] = dqM * ea[e];
-    o.dT = dT;
-    S eu = o.q;
-#pragma unroll
-    for (int i = 0; i < sc::MAXSIDE; ++i)
-        eu -= (i < nr ? rc[i] : S(0.0)) * o.d[i] + (i < np ? pc[i] : S(0.0)) * o.d[3 + i];
-#pragma unroll
-    for (int e = 0; e < sc::MAXENH; ++e) eu -= ec[e] * o.d[6 + e];
-    // constant pressure: the Euler remainder; constant volume: dq/d[M], the
-    // weight of the rank-one part of dq/dC
-    o.euler = m.cv ? dqM : eu;
-    o.dH = dH;
-    return o;
 }
 
 // Address of species c's pair in the pair array at place `at` (SPL_CG, SPL_HW)
@@ -653,20 +469,32 @@ __device__ __forceinline__ Rec load_rx(const DevRx &sp, int pass, int lane)
 // respect to the side species' concentrations (what an unused slot holds goes
 // to the trash), dqM with respect to [M] (dq/dC of an enhanced species is dqM
 // times its alpha - 1), dT at fixed C, euler (the Euler remainder, or dqM in a
-// constant-volume reactor) and the reaction enthalpy / RT.  The arithmetic is
-// reaction()'s; the Euler remainder q - sum C dq/dC is taken from the
-// reaction's orders (C d(C^nu)/dC = nu C^nu).
+// constant-volume reactor) and the reaction enthalpy / RT.  The Euler remainder
+// q - sum C dq/dC is taken from the reaction's orders (C d(C^nu)/dC = nu C^nu).
+// With S = Dual the derivatives of the pairs lie toff doubles from the values.
+template <class S = double>
 struct RxTerms {
-    double q, d[6], dqM, ea[sc::MAXENH], dT, euler, dH;
+    S q, d[6], dqM;
+    double ea[sc::MAXENH];
+    S dT, euler, dH;
 };
-template <bool JAC, int NV>
-__device__ __forceinline__ RxTerms reaction_sp(const DevMech &m, const DevRx &sp, int ideg, double *lds, const Rec &r,
-                                               uint32_t flags, int j, const Mix<> &x, double dl, const double *itb,
-                                               double itt)
+template <class S>
+__device__ __forceinline__ S make(double v, double d)
 {
-    RxTerms o;
-    double c[6], p[6], dp[6], nu[6];
-    double dG = 0.0, dH = 0.0;
+    if constexpr (std::is_same_v<S, double>)
+        return v;
+    else
+        return S(v, d);
+}
+template <bool JAC, int NV, class S = double>
+__device__ __forceinline__ RxTerms<S> reaction_sp(const DevMech &m, const DevRx &sp, int ideg, double *lds, const Rec &r,
+                                               uint32_t flags, int j, const Mix<S> &x, double dl, const double *itb,
+                                               double itt, int toff = 0)
+{
+    RxTerms<S> o;
+    S c[6], p[6], dp[6];
+    double nu[6];
+    S dG = 0.0, dH = 0.0;
     // a falloff pass's other tables, loaded ahead of the work (they come from L2)
     TroeRec tr;
     if ((flags & sc::RXF_TROE) && j < sp.n_troe) tr = sp.troe[j];
@@ -674,27 +502,32 @@ __device__ __forceinline__ RxTerms reaction_sp(const DevMech &m, const DevRx &sp
 #pragma unroll
         for (int e = 0; e < sc::MAXENH; ++e) o.ea[e] = j < sp.n_tb ? sp.eam1[4 * j + e] : 0.0;
     }
-    const double lnkinf = r.lnA() + dl + r.bT() * x.lnT - r.EaR() * x.invT;
-    const double kinf = exp(lnkinf);
+    const S lnkinf = r.lnA() + dl + r.bT() * x.lnT - r.EaR() * x.invT;
+    const S kinf = exp(lnkinf);
     const char *cg = (const char *)(lds + SPL_CG * NV), *hw = (const char *)(lds + SPL_HW * NV);
-    double g[6], h[6];
+    S g[6], h[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
         const double2 v = *(const double2 *)(cg + r.slot(i));
-        c[i] = v.x;
-        g[i] = v.y;
-        if (JAC) h[i] = *(const double *)(hw + r.slot(i));
+        double2 t = make_double2(0.0, 0.0);
+        if (!std::is_same_v<S, double>) t = *(const double2 *)(cg + r.slot(i) + 8 * toff);
+        c[i] = make<S>(v.x, t.x);
+        g[i] = make<S>(v.y, t.y);
+        if (JAC)
+            h[i] = make<S>(*(const double *)(hw + r.slot(i)),
+                           std::is_same_v<S, double> ? 0.0 : *(const double *)(hw + r.slot(i) + 8 * toff));
         p[i] = c[i];
-        dp[i] = nu[i] = 1.0;
+        dp[i] = 1.0;
+        nu[i] = 1.0;
     }
     if (flags & sc::RXF_NU) {
 #pragma unroll
         for (int i = 0; i < 6; ++i) {
             const int v = r.nu(i);
             nu[i] = v;
-            const double c2 = c[i] * c[i];
+            const S c2 = c[i] * c[i];
             p[i] = v == 2 ? c2 : v == 3 ? c2 * c[i] : c[i];
-            dp[i] = v == 2 ? 2.0 * c[i] : v == 3 ? 3.0 * c2 : 1.0;
+            dp[i] = v == 2 ? 2.0 * c[i] : v == 3 ? 3.0 * c2 : S(1.0);
         }
     }
     if (itb) {
@@ -711,60 +544,61 @@ __device__ __forceinline__ RxTerms reaction_sp(const DevMech &m, const DevRx &sp
         }
     }
     const double dnu = r.dnu();
-    const double lnKc = -dG + dnu * (m.lnp0R - x.lnT);
-    const double M0 = x.p * x.invT / m.Rgas;
-    double M = M0, Me = 0.0;
+    const S lnKc = -dG + dnu * (m.lnp0R - x.lnT);
+    const S M0 = x.p * x.invT / m.Rgas;
+    S M = M0, Me = 0.0;
     if (flags & sc::RXF_TB) {
         if (j < sp.n_tb) {
 #pragma unroll
-            for (int e = 0; e < sc::MAXENH; ++e) Me += o.ea[e] * *(const double *)(cg + r.enh(e));
+            for (int e = 0; e < sc::MAXENH; ++e) Me += o.ea[e] * make<S>(*(const double *)(cg + r.enh(e)),
+                                                  std::is_same_v<S, double> ? 0.0 : *(const double *)(cg + r.enh(e) + 8 * toff));
         }
         M += Me;
     }
     const int kind = r.kind();
-    double kf = kinf, phi = 0.0, dlnF_T = 0.0, dlnk0 = 0.0;
+    S kf = kinf, phi = 0.0, dlnF_T = 0.0, dlnk0 = 0.0;
     if ((flags & sc::RXF_TROE) && kind == sc::RX_TROE) {
-        const double lnk0 = tr.lnA0 + dl + tr.b0 * x.lnT - tr.Ea0R * x.invT;
-        const double Pr = exp(lnk0 - lnkinf) * M;
+        const S lnk0 = tr.lnA0 + dl + tr.b0 * x.lnT - tr.Ea0R * x.invT;
+        const S Pr = exp(lnk0 - lnkinf) * M;
         const double a = tr.a, iT3 = tr.iT3, iT1 = tr.iT1, T2 = tr.T2;
-        const double e3 = exp(-x.T * iT3), e1 = exp(-x.T * iT1), e2 = exp(-T2 * x.invT);
-        const double Fc = (1.0 - a) * e3 + a * e1 + e2;
-        const double L = log10(Fc);
-        const double cc = -0.4 - 0.67 * L, nn = 0.75 - 1.27 * L;
-        const double X = log10(Pr) + cc;
-        const double D = nn - 0.14 * X;
-        const double f = X / D;
-        const double opf = 1.0 + f * f;
-        const double lF = L / opf;
+        const S e3 = exp(-x.T * iT3), e1 = exp(-x.T * iT1), e2 = exp(-T2 * x.invT);
+        const S Fc = (1.0 - a) * e3 + a * e1 + e2;
+        const S L = log10(Fc);
+        const S cc = -0.4 - 0.67 * L, nn = 0.75 - 1.27 * L;
+        const S X = log10(Pr) + cc;
+        const S D = nn - 0.14 * X;
+        const S f = X / D;
+        const S opf = 1.0 + f * f;
+        const S lF = L / opf;
         kf = kinf * (Pr / (1.0 + Pr)) * exp(2.302585092994046 * lF);
         if (JAC) {
-            const double gg = -L * 2.0 * f / (opf * opf);
+            const S gg = -L * 2.0 * f / (opf * opf);
             phi = 1.0 / (1.0 + Pr) + gg * (nn / (D * D));  // dln kf / dln Pr
-            const double dlF_dL = 1.0 / opf + gg * ((-0.67 * nn + 1.27 * X) / (D * D));
-            const double dFc = -(1.0 - a) * iT3 * e3 - a * iT1 * e1 + T2 * x.invT * x.invT * e2;
+            const S dlF_dL = 1.0 / opf + gg * ((-0.67 * nn + 1.27 * X) / (D * D));
+            const S dFc = -(1.0 - a) * iT3 * e3 - a * iT1 * e1 + T2 * x.invT * x.invT * e2;
             dlnF_T = dlF_dL * dFc / Fc;  // dln F/dT at fixed Pr
             dlnk0 = (tr.b0 + tr.Ea0R * x.invT) * x.invT;
         }
     }
-    const double kr = kf * exp(-lnKc);
-    const double Rf = kf * (p[0] * p[1] * p[2]), Rr = kr * (p[3] * p[4] * p[5]);
-    const double q0 = Rf - Rr;
+    const S kr = kf * exp(-lnKc);
+    const S Rf = kf * (p[0] * p[1] * p[2]), Rr = kr * (p[3] * p[4] * p[5]);
+    const S q0 = Rf - Rr;
     const bool third = (flags & sc::RXF_TB) && kind == sc::RX_THIRD;
-    const double fsc = third ? M : 1.0;
+    const S fsc = third ? M : S(1.0);
     o.q = fsc * q0;
     if (!JAC) return o;
-    const double F = fsc * kf, B = -fsc * kr;
+    const S F = fsc * kf, B = -fsc * kr;
     o.d[0] = F * (p[1] * p[2]) * dp[0];
     o.d[1] = F * (p[0] * p[2]) * dp[1];
     o.d[2] = F * (p[0] * p[1]) * dp[2];
     o.d[3] = B * (p[4] * p[5]) * dp[3];
     o.d[4] = B * (p[3] * p[5]) * dp[4];
     o.d[5] = B * (p[3] * p[4]) * dp[5];
-    const double dlnkinf = (r.bT() + r.EaR() * x.invT) * x.invT;
-    const double dlnKc = (dH - dnu) * x.invT;
-    double dlnkf = dlnkinf;
+    const S dlnkinf = (r.bT() + r.EaR() * x.invT) * x.invT;
+    const S dlnKc = (dH - dnu) * x.invT;
+    S dlnkf = dlnkinf;
     o.dqM = 0.0;
-    const double dMdT = m.cv ? 0.0 : -M0 * x.invT;
+    const S dMdT = m.cv ? S(0.0) : -M0 * x.invT;
     if (flags & sc::RXF_TB) {
         if (kind == sc::RX_THIRD) {
             o.dqM = q0;
@@ -803,7 +637,7 @@ __device__ __forceinline__ void rhs_passes(const CR &crew, const DevMech &m, con
         nxt = load_rx<G>(sp, max(qn, 0), lane);
         const uint32_t flags = __builtin_amdgcn_readfirstlane(r.bits());
         const double dl = dlnA ? dlnA[r.orig()] : 0.0;
-        const RxTerms o = reaction_sp<false, NV>(m, sp, ideg, lds, r, flags, q * G + lane, x, dl,
+        const RxTerms<> o = reaction_sp<false, NV>(m, sp, ideg, lds, r, flags, q * G + lane, x, dl,
                                                  TABLES ? itb : nullptr, itt);
         crew.await(q);
 #pragma unroll
@@ -851,7 +685,7 @@ __device__ __forceinline__ void jac_passes(const CR &crew, const DevMech &m, con
         const uint32_t flags = __builtin_amdgcn_readfirstlane(r.bits());
         const double dl = dlnA ? dlnA[r.orig()] : 0.0;
         const int j = q * G + lane;
-        const RxTerms o = reaction_sp<true, NV>(m, sp, ideg, lds, r, flags, j, x, dl,
+        const RxTerms<> o = reaction_sp<true, NV>(m, sp, ideg, lds, r, flags, j, x, dl,
                                                 TABLES ? itb : nullptr, itt);
         auto at = [&](int e) __attribute__((always_inline)) { return e % 2 ? ix[e / 2] >> 16 : ix[e / 2] & 0xffff; };
         // temperature-row weight: the reaction enthalpy (constant pressure) or
@@ -926,25 +760,25 @@ __device__ __forceinline__ void jac_passes(const CR &crew, const DevMech &m, con
 // mixture() for the reaction passes: C and g/RT, h/RT and the production rate
 // in pairs, and the dummy species' of a reaction's unused slots (N + 1, or one
 // behind the last lane)
-template <int NP>
-__device__ __forceinline__ Mix<> mixture_pairs(const DevMech &m, double *lds, double y, double p, Thermo<> &th,
-                                               int lane)
+template <int NP, class S = double>
+__device__ __forceinline__ Mix<S> mixture_pairs(const DevMech &m, double *lds, S y, double p, Thermo<S> &th, int lane,
+                                                int toff = 0)
 {
     constexpr int NV = Lds<NP>::NV;
-    double *v = lds + Lds<NP>::RX;
-    double yw;
-    const Mix<> x = mixture_point(m, y, p, th, lane, yw);
-    double *cg = pair<NV>(v, SPL_CG, lane), *hw = pair<NV>(v, SPL_HW, lane);
-    cg[0] = lane < m.N ? x.rho * yw : 1.0;
-    cg[1] = th.hRT - th.sR;
-    hw[0] = th.hRT;
-    hw[1] = 0.0;
-    v[SPL_UA * NV + lane] = 0.0;
-    // the two behind the lanes, by all of them
+    // species c's pairs (a Dual's derivatives toff doubles away) and Euler term
+    auto put = [&](int c, S conc, S g, S h) __attribute__((always_inline)) {
+        const int cg = Lds<NP>::RX + SPL_CG * NV + 2 * c, hw = Lds<NP>::RX + SPL_HW * NV + 2 * c;
+        lds_put(lds, cg, conc, toff);
+        lds_put(lds, cg + 1, g, toff);
+        lds_put(lds, hw, h, toff);
+        lds_put(lds, hw + 1, S(0.0), toff);
+        lds[Lds<NP>::RX + SPL_UA * NV + c] = 0.0;
+    };
+    S yw;
+    const Mix<S> x = mixture_point(m, y, p, th, lane, yw);
+    put(lane, lane < m.N ? x.rho * yw : S(1.0), th.hRT - th.sR, th.hRT);
     static_assert(NV == WAVE + 2);
-    cg = pair<NV>(v, SPL_CG, WAVE + lane % 2), hw = pair<NV>(v, SPL_HW, WAVE + lane % 2);
-    cg[0] = 1.0;
-    cg[1] = hw[0] = hw[1] = 0.0;
+    put(WAVE + lane % 2, S(1.0), S(0.0), S(0.0));  // the two behind the lanes, by all of them
     return x;
 }
 

@@ -11,20 +11,7 @@
 
 namespace scdev {
 
-// One reaction's parameters, read by the lane that handles the reaction
-// (160 bytes; the 64 lanes of a pass read 64 consecutive records).  Records
-// are in the compiler's execution order (by kind, then side sizes).
-struct RxRec {
-    double lnA, b, EaR;            // SI ln A (incl. the cgs conversion), b, Ea/R
-    double eam1[sc::MAXENH];       // alpha - 1 of the enhanced third-body species
-    int32_t kind, nr, np, dnu, neff, tix;
-    int32_t rsp[sc::MAXSIDE], rnu[sc::MAXSIDE], psp[sc::MAXSIDE], pnu[sc::MAXSIDE];
-    int32_t esp[sc::MAXENH];
-    int32_t orig;  // index of the reaction in the mechanism text (for dlnA)
-    int32_t pad[3];
-};
-static_assert(sizeof(RxRec) % 16 == 0, "record size");
-
+// A falloff reaction's low-pressure rate and blending parameters
 struct TroeRec {
     double lnA0, b0, Ea0R, a, iT3, iT1, T2, pad;
 };
@@ -39,16 +26,13 @@ struct DevRx {
 };
 
 // A compiled mechanism on the device: species table sp = W[N] invW[N]
-// nasa[7][N] (species index fastest), one record per reaction and per Troe
-// reaction.  Three base pointers keep the kernels' scalar-register footprint
-// small.
+// nasa[7][N] (species index fastest).  Few base pointers keep the kernels'
+// scalar-register footprint small.
 struct DevMech {
-    int N, R, nt;
+    int N, R;
     int cv;  // 1: constant-volume reactor (the per-cell p input is the density)
     double Rgas, lnp0R;  // lnp0R = ln(p0 / Rgas)
     const double *sp;
-    const RxRec *rx;
-    const TroeRec *troe;
     DevRx pass;  // the dense kernels' packed passes
 
     __host__ __device__ const double *W() const { return sp; }
