@@ -101,7 +101,7 @@ typedef enum {
  * in natural order (N <= 63).  SPARSE: the bordered system of order N+2
  * (species block with its fixed sparsity, then the temperature and density
  * borders) in LDS, factorised in the mechanism compiler's minimum-degree
- * order by its static level schedule (N <= 127).  AUTO: dense where it
+ * order in blocks of 16 pivots (N <= 127).  AUTO: dense where it
  * applies, else sparse. */
 typedef enum {
     SC_LINALG_AUTO = 0,
@@ -169,15 +169,14 @@ typedef struct {
      * schedule: the bordered system of order N + 2 in minimum-degree order */
     int32_t nnz_a_sparse;       /* structural entries of the bordered matrix */
     int32_t nnz_lu_sparse;      /* entries of L + U (with fill) */
-    int32_t lu_levels;          /* levels of the factorisation schedule */
+    int32_t lu_levels;          /* levels of the factorisation schedule (sc_mech_sparse_array's) */
     int32_t solve_levels;       /* levels of one forward + one backward solve */
     int64_t lu_updates_sparse;  /* Schur-complement updates of one factorisation */
     int64_t flops_lu_sparse;    /* one factorisation (division 1, fma 2) */
     int64_t flops_solve_sparse; /* one solve */
     int64_t flops_step_sparse;  /* one step with the sparse linear algebra */
-    int32_t lu_tail_sparse;     /* trailing positions whose L+U block is full: factorised in
-                                 * registers after the level schedule (its pivots are not in
-                                 * lu_levels; flops_lu_sparse counts them) */
+    int32_t lu_tail_sparse;     /* trailing positions whose L+U block is full (their pivots are
+                                 * not in lu_levels; flops_lu_sparse counts them) */
 } sc_mech_info;
 
 void sc_default_options(sc_options *opt);
@@ -193,7 +192,8 @@ sc_status sc_species_index(const sc_mech *mech, const char *name, int32_t *idx);
 
 /* One array of the mechanism compiler's sparse algebra (paper Sec. 2.5:
  * sparse analytical Jacobian, sparse algebra management of the mechanism),
- * host memory, for inspection and tests.  With out == NULL only *bytes is
+ * host memory, for inspection and tests (the kernels read operand tables
+ * made from the same factors, in blocks of 16 pivots).  With out == NULL only *bytes is
  * set (the size); else up to *bytes bytes are copied and *bytes is set to
  * the size.  Names (element type):
  *   "perm" (int32: position -> variable; species 0..N-1, N = T, N+1 = the

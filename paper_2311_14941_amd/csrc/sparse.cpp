@@ -1,7 +1,8 @@
 // The sparse compile of a mechanism (host side): the structural pattern of
 // the analytical Jacobian terms, a minimum-degree ordering of the species,
 // the bordered system, its symbolic LU, the static level schedules of the
-// factorisation and of the triangular solves, the entry each reaction's
+// factorisation and of the triangular solves (for inspection and tests), the
+// kernels' operand tables and reaction passes, the entry each reaction's
 // derivative terms land in, and the exact work of the schedule.
 //
 // The paper's chemistry library manages the sparse algebra of the mechanism
@@ -193,8 +194,8 @@ void compile_sparse(Mech &m)
     // 5. the dense trailing block: the widest [t, n) of at most
     //    sparse_tail_max(n) positions whose L+U pattern is full (the trailing
     //    Schur complement of a minimum-degree order fills in).  Its pivots
-    //    would take one level each; they are factorised in registers instead,
-    //    after the levels of the pivots before t.
+    //    would take one level each; the schedule leaves them out, to be
+    //    eliminated densely after the levels of the pivots before t.
     S.tail0 = n;
     while (S.tail0 > 0 && n - S.tail0 < sparse_tail_max(n)) {
         const int q = S.tail0 - 1;
