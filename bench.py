@@ -495,7 +495,9 @@ def kernel_name(launch, linalg, N, cpw=0):
     if linalg == "sparse" or (linalg == "auto" and N + 1 > 64):
         vpl = 1 if N + 2 <= 64 else 2
         g = resolved_cpw(linalg, N, cpw)
-        return {"plain": f"k_integrate_sp<{vpl},{g}>", "persistent": f"k_integrate_sp_persistent<{vpl},{g}>",
+        crew = f"k_integrate_sp_crew<{vpl}>"
+        return {"plain": crew if vpl == 2 else f"k_integrate_sp<{vpl},{g}>",
+                "persistent": crew if g == 1 else f"k_integrate_sp_persistent<{vpl},{g}>",
                 "static": f"k_integrate_sp_static<{vpl},{g}>"}[mode]
     npd = 16 if N + 1 <= 16 else 32 if N + 1 <= 32 else 56 if N + 1 <= 56 else 64
     return {"plain": f"k_integrate<{npd}>", "persistent": f"k_integrate_persistent<{npd}>",
