@@ -115,7 +115,7 @@ __device__ double vjp(const DevMech &m, double *lds, S y, double p, const double
         if ((flags & sc::RXF_TB) && j < sp.n_tb) {
 #pragma unroll
             for (int e = 0; e < sc::MAXENH; ++e)
-                if (r.enh(e) != 16u * (N + 1)) lds_add(lds, V + r.enh(e) / 16, s * (o.dqM * o.ea[e]), toff);
+                if (r.enh(e) != 16u * N) lds_add(lds, V + r.enh(e) / 16, s * (o.dqM * o.ea[e]), toff);
         }
         bacc += s * o.euler;
         tacc += s * o.dT;

@@ -536,7 +536,7 @@ __device__ __forceinline__ RxTerms<S> reaction_sp(const DevMech &m, const DevRx 
         if (JAC) dH = poly_t(itc + ideg + 1, ideg, itt);
     } else {
         // an unused slot of a pass with larger coefficients has nu = 0 and
-        // the dummy's g = h = 0 in any other
+        // its place's g = h = 0 in any other
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             dG += nu[3 + i] * g[3 + i] - nu[i] * g[i];
@@ -748,7 +748,7 @@ __device__ __forceinline__ void jac_passes(const CR &crew, const DevMech &m, con
 #pragma unroll
                 for (int e = 0; e < sc::MAXENH; ++e) {
                     const int k = 4 * i + e;
-                    if (r.enh(e) == 16u * (N + 1) || (i < 6 && r.nu(i) == 0)) continue;
+                    if (r.enh(e) == 16u * N || (i < 6 && r.nu(i) == 0)) continue;
                     add(k % 2 ? ie[k / 2] >> 16 : ie[k / 2] & 0xffff, w * o.ea[e]);
                 }
             }
@@ -758,8 +758,8 @@ __device__ __forceinline__ void jac_passes(const CR &crew, const DevMech &m, con
 }
 
 // mixture() for the reaction passes: C and g/RT, h/RT and the production rate
-// in pairs, and the dummy species' of a reaction's unused slots (N + 1, or one
-// behind the last lane)
+// in pairs; what an unused slot of a reaction reads lies in the temperature's
+// place N
 template <int NP, class S = double>
 __device__ __forceinline__ Mix<S> mixture_pairs(const DevMech &m, double *lds, S y, double p, Thermo<S> &th, int lane,
                                                 int toff = 0)
@@ -777,8 +777,6 @@ __device__ __forceinline__ Mix<S> mixture_pairs(const DevMech &m, double *lds, S
     S yw;
     const Mix<S> x = mixture_point(m, y, p, th, lane, yw);
     put(lane, lane < m.N ? x.rho * yw : S(1.0), th.hRT - th.sR, th.hRT);
-    static_assert(NV == WAVE + 2);
-    put(WAVE + lane % 2, S(1.0), S(0.0), S(0.0));  // the two behind the lanes, by all of them
     return x;
 }
 

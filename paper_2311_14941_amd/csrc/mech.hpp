@@ -210,8 +210,8 @@ SparseDev sparse_device(const Mech &m, int lanes);
 // word w of a pass at [pass][w][lane], so a load is one contiguous burst.
 // Falloff reactions come first, then third-body ones, then the rest, each by
 // coefficients and side sizes, so that what only some reactions need is in
-// as few passes as can be.  Unused slots name a dummy species (index N + 1:
-// concentration 1, g = h = 0) and trash entries, so the arithmetic has no
+// as few passes as can be.  Unused slots name the temperature's place as a
+// species (index N: concentration 1, g = h = 0) and trash entries, so the arithmetic has no
 // per-lane branches; what a whole pass does not need is skipped by the flags,
 // which every record of the pass carries, and a lane adds only for the slots
 // in use (coefficient above zero).

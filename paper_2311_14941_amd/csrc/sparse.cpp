@@ -415,7 +415,9 @@ static SparseRx reaction_passes(const Mech &m, int lanes, Pos pos, Entry place)
     X.ixe.assign((size_t)etp * RXW_IXE * lanes * 8, 0);
     X.eam1.assign((size_t)4 * X.n_tb, 0.0);
     X.troe.assign((size_t)8 * X.n_troe, 0.0);
-    const uint32_t dummy = N + 1;
+    // an unused slot names the place behind the species (the temperature's):
+    // there is one with the largest mechanism too
+    const uint32_t dummy = N;
     for (int p = 0; p < X.passes; ++p) {
         uint32_t flags = 0;
         for (int l = 0; l < lanes && p * lanes + l < R; ++l) {

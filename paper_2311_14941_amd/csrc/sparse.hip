@@ -187,8 +187,8 @@ __device__ __forceinline__ void store_state_v(const DevMech &m, const DevSparse 
 // ---------------------------------------------------------------------------
 // thermodynamics, right-hand side and Jacobian terms
 // ---------------------------------------------------------------------------
-// Mixture state from y; writes C, g/RT, h/RT (and those of the dummy species
-// N + 1) and clears the accumulators.
+// Mixture state from y; writes C, g/RT, h/RT (and what an unused slot of a
+// reaction reads, in the temperature's place) and clears the accumulators.
 template <int VPL, int G, class CR>
 __device__ __forceinline__ Mix<> mixture_v(const CR &crew, const DevMech &m, const DevSparse &sp, double *lds, const double (&y)[VPL],
                                            double p, Thermo<> (&th)[VPL], int lane)
@@ -225,7 +225,7 @@ __device__ __forceinline__ Mix<> mixture_v(const CR &crew, const DevMech &m, con
     if (crew.rank != 0) return x;
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
-        const int c = lane + G * v;  // lanes beyond N hold zeros: the dummy needs only its concentration
+        const int c = lane + G * v;  // lanes beyond the species hold zeros: unused slots need only a concentration
         double *cg = pair<NV>(lds, SPL_CG, c), *hw = pair<NV>(lds, SPL_HW, c);
         cg[0] = c < N ? x.rho * yw[v] : 1.0;
         cg[1] = th[v].hRT - th[v].sR;

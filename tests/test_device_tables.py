@@ -1,0 +1,96 @@
+"""CPU tests of the tables the kernels read (built per plan on the host, not
+reachable through the C ABI): tests/c/device_tables.cpp writes them out and
+they are checked here against the mechanism and the places the kernels have
+in LDS."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from synth.mechgen import make_mechanism
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2311_14941_amd", "csrc")
+
+# species, reactions, pool fraction, seed, lanes of one cell
+MECHS = {"14 x 16": (14, 56, 0.15, 401, 16), "30 x 32": (30, 150, 0.3, 402, 32), "24": (24, 120, 0.5, 400, 64),
+         "62": (62, 900, 0.6, 1, 64), "63": (63, 400, 0.15, 400, 64), "126": (126, 2500, 0.5, 4, 64),
+         "127": (127, 762, 0.15, 400, 64)}
+
+
+def mechanism(key):
+    ns, nr, pf, seed, lanes = MECHS[key]
+    return make_mechanism(ns, nr, nr // 10, nr // 20, ["C", "H", "O", "N"], seed=seed, pool_frac=pf), lanes
+
+
+@pytest.fixture(scope="module")
+def tables(tmp_path_factory):
+    d = tmp_path_factory.mktemp("device_tables")
+    exe = str(d / "device_tables")
+    subprocess.run(["g++", "-std=c++17", "-O1", f"-I{CSRC}", os.path.join(HERE, "c", "device_tables.cpp"),
+                    os.path.join(CSRC, "mech.cpp"), os.path.join(CSRC, "sparse.cpp"), "-o", exe], check=True)
+
+    def get(key):
+        mech, lanes = mechanism(key)
+        path = str(d / "mech.txt")
+        with open(path, "w") as f:
+            f.write(mech.to_text())
+        r = subprocess.run([exe, path, str(lanes)], capture_output=True)
+        assert r.returncode == 0, (r.returncode, r.stderr[-500:])
+        out, b, at = {}, r.stdout, 0
+        while at < len(b):
+            nl = b.index(b"\n", at)
+            name, kind, count = b[at:nl].decode().split()
+            a = np.frombuffer(b, dtype=kind, count=int(count), offset=nl + 1)
+            out[name] = a
+            at = nl + 1 + a.nbytes
+        return mech, lanes, out
+    return get
+
+
+def records(x, lanes):
+    """A table's records by execution position: side slots (pair numbers),
+    coefficients, enhanced species (pair numbers), reaction."""
+    passes = int(x["counts"][0])
+    w = x["rec"].reshape(passes, 3, lanes, 4).transpose(0, 2, 1, 3).reshape(passes * lanes, 12)
+    slot = np.stack([(w[:, 6 + i // 2] >> (16 * (i % 2))) & 0xFFFF for i in range(6)], 1) / 16
+    nu = np.stack([(w[:, 9] >> (2 * i)) & 3 for i in range(6)], 1)
+    enh = np.stack([(w[:, 10] >> (8 * i)) & 0xFF for i in range(4)], 1)
+    return slot, nu, enh, w[:, 11]
+
+
+def family(t, name):
+    return {k[len(name) + 1:]: v for k, v in t.items() if k.startswith(name + ".")}
+
+
+@pytest.mark.parametrize("key", list(MECHS))
+def test_slots_name_places_the_kernels_have(tables, key):
+    """Every slot of every record names a pair the kernels have: a used one
+    its species', an unused one a place that is no species' (the
+    temperature's).  The sparse kernels hold a cell's lanes times its slots per
+    lane of them, the dense ones a wave's."""
+    mech, lanes, t = tables(key)
+    N, R, n = (int(v) for v in t["size"][:3])
+    held = {"sparse": lanes * (1 if n <= 64 else 2), "dense": 64}
+    pos = {"sparse": t["pos"], "dense": np.arange(N + 1)}
+    for fam in held:
+        x = family(t, fam)
+        if not x:
+            assert fam == "dense" and N > 63
+            continue
+        slot, nu, enh, orig = records(x, lanes if fam == "sparse" else 64)
+        assert slot.max() < held[fam] and enh.max() < held[fam]
+        assert np.all(slot[nu == 0] >= N) and np.all(slot[nu > 0] < N)
+        assert sorted(orig[:R]) == list(range(R)) and np.all(nu[R:] == 0)
+        for q in range(R):
+            r = mech.reactions[orig[q]]
+            for i, side in enumerate((r.reac, r.prod)):
+                got = {int(s): int(v) for s, v in zip(slot[q, 3 * i:3 * i + 3], nu[q, 3 * i:3 * i + 3]) if v}
+                want = {}
+                for s, v in side:
+                    k = int(pos[fam][s])
+                    want[k] = want.get(k, 0) + v
+                assert got == want, (fam, q)
+            used = {int(pos[fam][k]) for k, a in r.eff.items() if a != 1.0}
+            assert {int(e) for e in enh[q] if e < N} == used, (fam, q)
