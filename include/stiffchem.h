@@ -101,8 +101,9 @@ typedef enum {
  * in natural order (N <= 63).  SPARSE: the bordered system of order N+2
  * (species block with its fixed sparsity, then the temperature and density
  * borders) in LDS, factorised in the mechanism compiler's minimum-degree
- * order in blocks of 16 pivots (N <= 127).  AUTO: dense where it
- * applies, else sparse. */
+ * order in blocks of 16 pivots (N <= 126; sc_rhs and sc_jacobian also take
+ * N = 127, the largest that loads, sc_linsolve and the integration return
+ * SC_EUNSUPPORTED for it).  AUTO: dense where it applies, else sparse. */
 typedef enum {
     SC_LINALG_AUTO = 0,
     SC_LINALG_DENSE = 1,

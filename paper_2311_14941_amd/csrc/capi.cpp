@@ -126,6 +126,18 @@ sc_status check_common(sc_plan *plan, int64_t n, int64_t ld, std::initializer_li
     return SC_OK;
 }
 
+// The sparse factorisation and solves hold two rows of the bordered system in
+// each of the 64 lanes: a mechanism whose state fits, but not its border
+// unknown, has rates and a Jacobian only.
+sc_status check_solve(const sc_plan *plan)
+{
+    if (plan->sparse && plan->ds.n > sc::MAX_SOLVE)
+        return fail(SC_EUNSUPPORTED, "the solves support up to " + std::to_string(sc::MAX_SOLVE - 2) +
+                                         " species (right-hand side and Jacobian " +
+                                         std::to_string(sc::MAX_STATE_SPARSE - 1) + ")");
+    return SC_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -510,7 +522,7 @@ sc_status sc_linsolve(sc_plan *plan, int64_t n, const double *T, const double *p
                       const double *dlnA, const double *hg, const double *b, double *x, void *stream)
 {
     sc_status s = check_common(plan, n, ld, {T, p, Y, hg, b, x});
-    if (s != SC_OK || n == 0) return s;
+    if (s != SC_OK || n == 0 || (s = check_solve(plan)) != SC_OK) return s;
     DeviceGuard g(plan->device);
     hipError_t e = plan->sparse ? scdev::launch_linsolve_sp(plan->vpl, plan->dms, plan->ds, n, T, p, Y, ld, dlnA, hg,
                                                             b, x, (hipStream_t)stream)
@@ -530,7 +542,7 @@ static sc_status integrate_impl(sc_plan *plan, int64_t n, const double *T0, cons
                          const int32_t *ref = nullptr)
 {
     sc_status s = check_common(plan, n, ld, {T0, p, Y0, dt, T1, Y1, cell_status});
-    if (s != SC_OK || n == 0) return s;
+    if (s != SC_OK || n == 0 || (s = check_solve(plan)) != SC_OK) return s;
     if (plan->opt.fixed_step && !h_io) return fail(SC_EINVAL, "fixed_step needs h_io (the step of each cell)");
     if (plan->opt.mode == SC_MODE_PERSISTENT && plan->opt.order == SC_ORDER_COST && (!n_acc || !n_rej))
         return fail(SC_EINVAL, "cost ordering needs the previous n_acc and n_rej");
@@ -691,7 +703,7 @@ sc_status sc_integrate_mapped(sc_plan *plan, int64_t n, const double *T0, const 
     if (T1 == T0 || Y1 == Y0)
         return fail(SC_EINVAL, "the mapped integration needs T1, Y1 apart from T0, Y0 (mapped cells add the "
                                "reference's change to their inputs)");
-    if (n == 0) return SC_OK;
+    if (n == 0 || (s = check_solve(plan)) != SC_OK) return s;
     DeviceGuard g(plan->device);
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = scdev::launch_map_classify(plan->mp, plan->m.N, n, T0, p, Y0, ld, dt, ref, st);

@@ -21,6 +21,7 @@ constexpr int MAXENH = 4;                   // enhanced third-body species per r
 constexpr int NDEP = 2 * MAXSIDE + MAXENH;  // dependency slots per reaction
 constexpr int MAX_STATE = 64;               // N + 1 supported by the dense one-wave kernels
 constexpr int MAX_STATE_SPARSE = 128;       // N + 1 supported by the sparse kernels (two components per lane)
+constexpr int MAX_SOLVE = 128;              // N + 2 their factorisation and solves hold (two rows per lane)
 // widest dense trailing block of the sparse LU held in registers: systems
 // of up to 64 positions (two waves per SIMD, a tighter register budget),
 // and wider ones (one wave per SIMD)

@@ -3,7 +3,8 @@
 // L+U entries of the bordered system the mechanism compiler built
 // (sparse.cpp).  State vectors hold VPL components per lane (component
 // c = lane + 64 v, species in elimination order), so mechanisms of up to 126
-// species fit one wave; small ones run two or four cells per wave.
+// species fit one wave (127 without the solves); small ones run two or four
+// cells per wave.
 //
 // The bordered system (order N + 2, unknowns z_k = x_k / W_k, x_T, sigma):
 //   row k:     z_k/hg - sum_m P_km z_m - us_k sigma - (P_kT/rho + ct us_k) x_T = b_k / W_k

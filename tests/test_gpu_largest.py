@@ -1,7 +1,8 @@
 """The largest mechanism that loads, 127 species: its 128 state components
 fill both slots of every lane.  Right-hand side against the oracle within
 rounding of its largest terms (as for the smaller mechanisms) and Jacobian
-against the oracle's complex steps, both reactors."""
+against the oracle's complex steps, both reactors.  The bordered system has
+one position more than the lanes hold rows: every solve is refused."""
 import numpy as np
 import pytest
 
@@ -54,3 +55,22 @@ def test_jacobian(case, reactor):
         ref = o.jac_cs(np.append(Y[c], T[c]), p[c], constv=reactor == "const_v")
         row = np.abs(ref).max(1, keepdims=True) + 1e-300
         assert (np.abs(J[c] - ref) / (1e-8 * np.abs(ref) + 1e-12 * row + 1e-20 * np.abs(ref).max())).max() <= 1.0
+
+
+@pytest.mark.parametrize("mode", ["plain", "persistent", "static"])
+def test_solves_are_refused(case, mode):
+    import paper_2311_14941_amd as sc
+    mech, o, cm, T, p, Y = case
+    T, p, Y = gpu(T, p, Y.T)
+    dt, b = gpu(np.full(NC, 1e-7), np.ones((NC, NS + 1)))
+    plan = sc.Plan(cm, mode=mode)
+    fuel, ox = np.zeros(NS), np.zeros(NS)
+    fuel[0], ox[1] = 1.0, 1.0
+    plan.set_mapping(fuel, ox, z_tol=0.1, dT=10.0)
+    for call in (lambda: plan.linsolve(T, p, Y, dt, b), lambda: plan.integrate(T, p, Y, dt),
+                 lambda: plan.integrate_noalloc(T, p, Y, dt), lambda: plan.integrate_mapped(T, p, Y, dt)):
+        with pytest.raises(sc.StiffchemError) as e:
+            call()
+        assert e.value.code == sc.SC_EUNSUPPORTED and "126" in str(e.value)
+    empty = plan.integrate(T[:0], p[:0], Y[:, :0], dt[:0])  # nothing to solve
+    assert empty["T"].numel() == 0
