@@ -203,7 +203,8 @@ sc_status sc_species_index(const sc_mech *mech, const char *name, int32_t *idx);
  *   "erow", "ecol" (int32: row and column position of each L+U entry;
  *     entries are numbered column by column, rows ascending),
  *   "cstart" (int32, n + 1: first entry of each column), "cmask" (uint64,
- *     2 per column: bit i of word i / 64 set when row i has an entry),
+ *     2 per column, 3 where n > 128: bit i of word i / 64 set when row i has
+ *     an entry),
  *   "sweep_f", "sweep_b" (uint32, n <= 64 only, 4 per column: mask of the
  *     rows below (above) the diagonal holding an entry, low and high word,
  *     and the first of those entries, then 0),

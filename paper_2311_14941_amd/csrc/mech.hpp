@@ -57,7 +57,7 @@ struct SparseLU {
     std::vector<int> erow, ecol;  // entry -> (row position, column position), column-major order
     std::vector<int> emap;        // n * n: (row position, column position) -> entry or -1
     std::vector<int> cstart;      // n + 1: first entry of each column
-    std::vector<uint64_t> cmask;  // 2 n: rows holding an entry in column j (bits 0-63, 64-127)
+    std::vector<uint64_t> cmask;  // per column two words (three where n > 128), bit i set where row i holds an entry
     // per column k of a system of at most 64 positions, 4 words each: the
     // rows below the diagonal holding an entry (mask low, high word) and the
     // first of those entries (forward sweep); the same for the rows above

@@ -153,14 +153,15 @@ void compile_sparse(Mech &m)
     // compute from the column's row mask)
     S.emap.assign((size_t)n * n, -1);
     S.cstart.assign(1, 0);
-    S.cmask.assign(2 * (size_t)n, 0);
+    const size_t mw = std::max(2, (n + 63) / 64);  // words of a column's row mask
+    S.cmask.assign(mw * n, 0);
     for (int j = 0; j < n; ++j) {
         for (int i = 0; i < n; ++i)
             if (F[i * n + j]) {
                 S.emap[i * n + j] = (int)S.erow.size();
                 S.erow.push_back(i);
                 S.ecol.push_back(j);
-                S.cmask[2 * j + i / 64] |= 1ull << (i % 64);
+                S.cmask[mw * j + i / 64] |= 1ull << (i % 64);
             }
         S.cstart.push_back((int)S.erow.size());
     }

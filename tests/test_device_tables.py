@@ -1,13 +1,15 @@
 """CPU tests of the tables the kernels read (built per plan on the host, not
 reachable through the C ABI): tests/c/device_tables.cpp writes them out and
 they are checked here against the mechanism and the places the kernels have
-in LDS."""
+in LDS.  That program is built with the standard library's bounds checks, so
+an index out of range while a mechanism compiles ends it."""
 import os
 import subprocess
 
 import numpy as np
 import pytest
 
+import paper_2311_14941_amd as sc
 from synth.mechgen import make_mechanism
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -28,7 +30,7 @@ def mechanism(key):
 def tables(tmp_path_factory):
     d = tmp_path_factory.mktemp("device_tables")
     exe = str(d / "device_tables")
-    subprocess.run(["g++", "-std=c++17", "-O1", f"-I{CSRC}", os.path.join(HERE, "c", "device_tables.cpp"),
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D_GLIBCXX_ASSERTIONS", f"-I{CSRC}", os.path.join(HERE, "c", "device_tables.cpp"),
                     os.path.join(CSRC, "mech.cpp"), os.path.join(CSRC, "sparse.cpp"), "-o", exe], check=True)
 
     def get(key):
@@ -94,3 +96,18 @@ def test_slots_name_places_the_kernels_have(tables, key):
                 assert got == want, (fam, q)
             used = {int(pos[fam][k]) for k, a in r.eff.items() if a != 1.0}
             assert {int(e) for e in enh[q] if e < N} == used, (fam, q)
+
+
+@pytest.mark.parametrize("key", ["24", "63", "126", "127"])
+def test_row_masks_of_the_columns(key):
+    """"cmask" has a bit for every row of a column, the 129th (of 127
+    species) in a third word."""
+    sc.ensure_built()
+    m = sc.Mechanism(mechanism(key)[0].to_text())
+    n = m.N + 2
+    words = 3 if n > 128 else 2
+    mask = m.sparse_array("cmask").reshape(n, words)
+    want = np.zeros((n, words), dtype=np.uint64)
+    for i, j in zip(m.sparse_array("erow"), m.sparse_array("ecol")):
+        want[j, i // 64] |= np.uint64(1) << np.uint64(i % 64)
+    assert np.array_equal(mask, want)
