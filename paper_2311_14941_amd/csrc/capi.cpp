@@ -351,7 +351,6 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
     sc::SparseDev sd;
     sc::SparseRx sx;
     if (sparse) {
-        const int NV = 64 / cpw * vpl;
         ds.cpw = cpw;
         ds.n = S.n;
         ds.nnz = S.nnz;
@@ -364,10 +363,7 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
         ds.passes = sx.passes;
         ds.n_tb = sx.n_tb;
         ds.n_troe = sx.n_troe;
-        ds.size = scdev::SPL_E * NV + S.nnz + 1 + sc::SPARSE_TRASH;
-        // several cells per wave: regions half a bank row (16 doubles modulo
-        // 32) apart, so that the groups' like accesses fall on different banks
-        if (cpw > 1) ds.size += (16 - ds.size % 32 + 32) % 32;
+        ds.size = sc::sparse_region(S.n, S.nnz, 64 / cpw);
         hipDeviceProp_t prop;
         if (hipGetDeviceProperties(&prop, device) != hipSuccess) return fail(SC_EHIP, "hipGetDeviceProperties failed");
         if (sizeof(double) * (size_t)ds.size * cpw > prop.sharedMemPerBlock)

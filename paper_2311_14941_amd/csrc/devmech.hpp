@@ -40,11 +40,7 @@ struct DevMech {
     __host__ __device__ const double *nasa() const { return sp + 2 * N; }  // [c*N + k]
 };
 
-// LDS of one cell in the sparse kernels, in doubles: fixed places first, so
-// they are immediate offsets of the LDS instructions, then the L+U entries, the
-// zero slot and the trash slots.  C and g/RT, and h/RT and the production
-// rate, are pairs: one address and one wide read serve both.
-constexpr int SPL_CG = 0, SPL_HW = 2, SPL_UA = 4, SPL_U = 5, SPL_DINV = 9, SPL_E = 10;  // times NV
+using sc::SPL_CG, sc::SPL_HW, sc::SPL_UA, sc::SPL_U, sc::SPL_DINV, sc::SPL_E;
 
 // The sparse kernels' view of a mechanism's compiled sparse algebra (device
 // pointers).  Their DevMech has the species in elimination order, so a

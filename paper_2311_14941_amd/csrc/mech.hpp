@@ -102,6 +102,24 @@ struct SparseLU {
 // most 64 * 64 entries), entry numbers beyond.
 constexpr int sparse_off(int n, int e) { return n <= 64 ? 8 * e : e; }
 
+constexpr int SPARSE_TRASH = 16;  // entries that unused slots of a reaction's record add to
+
+// LDS of one cell in the sparse kernels, in doubles: fixed places first, so
+// they are immediate offsets of the LDS instructions, then the L+U entries, the
+// zero slot and the trash slots.  C and g/RT, and h/RT and the production
+// rate, are pairs: one address and one wide read serve both.
+constexpr int SPL_CG = 0, SPL_HW = 2, SPL_UA = 4, SPL_U = 5, SPL_DINV = 9, SPL_E = 10;  // times NV
+static_assert(SPL_HW % 2 == 0 && SPL_E % 2 == 0, "pairs and cleared entries are 16-byte accesses");
+// Size of that region for `lanes` lanes a cell.  Regions follow each other in a
+// workgroup's LDS, so it is even: every pair stays 16-byte aligned.  Several
+// cells per wave: half a bank row (16 doubles modulo 32) apart, so that the
+// groups' like accesses fall on different banks.
+constexpr int sparse_region(int n, int nnz, int lanes)
+{
+    const int size = SPL_E * lanes * (n <= 64 ? 1 : 2) + nnz + 1 + SPARSE_TRASH;
+    return lanes < 64 ? size + (16 - size % 32 + 32) % 32 : size + size % 2;
+}
+
 // What the device reads of a mechanism's sparse algebra (built per plan from
 // SparseLU; `lanes` lanes hold one cell's positions, two slots each when
 // n > 64).  Absent entries, and rows and columns beyond n, name the zero slot
@@ -219,7 +237,6 @@ SparseDev sparse_device(const Mech &m, int lanes);
 constexpr int RXW_WORDS = 3;  // lnA, b, Ea/R; side species (byte offsets, 16 per species); bits; enhanced species; index
 constexpr int RXW_IX = 6;     // entries: six rows of six slots and T, then the T row
 constexpr int RXW_IXE = 4;    // entries of the enhanced species: six rows of four, then the T row
-constexpr int SPARSE_TRASH = 16;  // entries that unused slots add to
 enum { RXF_THIRD_REAC = 1u << 27, RXF_THIRD_PROD = 1u << 28, RXF_NU = 1u << 29, RXF_TB = 1u << 30, RXF_TROE = 1u << 31 };
 struct SparseRx {
     int passes = 0, n_tb = 0, n_troe = 0;

@@ -1060,6 +1060,7 @@ struct CrewShare {
 };
 constexpr int CREW_SHARE = 16;  // doubles ahead of the regions
 static_assert(sizeof(CrewShare) <= CREW_SHARE * sizeof(double));
+static_assert(CREW_SHARE % 2 == 0, "the regions' pairs are read in one");
 constexpr int crew_most(int vpl) { return vpl == 1 ? 4 : 2; }
 
 template <int VPL, bool CV, bool TB>
@@ -1205,7 +1206,11 @@ k_integrate_sp_crew(DevMech mk, DevSparse spk, Opts o, int64_t n, const double *
 // Euler accumulator, without the L+U entries (2.5 KB a cell instead of 19 at
 // 53 species, so registers bound the waves in flight: 16 a CU instead of 8).
 template <int VPL, int G>
-constexpr int rhs_region() { return 5 * G * VPL + (G == 32 ? 16 : 0); }
+constexpr int rhs_region()
+{
+    static_assert(5 * G * VPL % 2 == 0, "the pairs are read in one");
+    return 5 * G * VPL + (G == 32 ? 16 : 0);
+}
 
 // Consecutive workgroups go to the eight dies in turn; the eight cells of a
 // 64-byte line of the state go to one, which reads the line once.

@@ -40,6 +40,7 @@ int main(int argc, char **argv)
         const sc::Mech m = sc::load_mechanism(text.str());
         const sc::SparseDev d = sc::sparse_device(m, lanes);
         put("size", std::vector<int>{m.N, m.R, m.sp.n, m.sp.nnz, m.n_padded});
+        put("region", std::vector<int>{sc::sparse_region(m.sp.n, m.sp.nnz, lanes), sc::SPL_E});
         put("pos", m.sp.pos);
         put("erow", m.sp.erow);
         put("ecol", m.sp.ecol);

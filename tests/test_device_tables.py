@@ -111,3 +111,19 @@ def test_row_masks_of_the_columns(key):
     for i, j in zip(m.sparse_array("erow"), m.sparse_array("ecol")):
         want[j, i // 64] |= np.uint64(1) << np.uint64(i % 64)
     assert np.array_equal(mask, want)
+
+
+@pytest.mark.parametrize("key", list(MECHS))
+def test_regions_keep_the_pairs_aligned(tables, key):
+    """A cell's region in LDS holds its places, entries, the zero and the
+    trash slots; regions lie one behind the other, so the size is a multiple
+    of the 16 bytes the pairs are read in (also where the number of entries is
+    even, as with 24 and 126 species)."""
+    _, lanes, t = tables(key)
+    n, nnz = int(t["size"][2]), int(t["size"][3])
+    size, e0 = (int(v) for v in t["region"])
+    vectors = lanes * (1 if n <= 64 else 2)
+    assert size % 2 == 0 and e0 * vectors % 2 == 0
+    assert e0 * vectors + nnz + 1 + 16 <= size < e0 * vectors + nnz + 1 + 16 + 32
+    if lanes < 64:
+        assert size % 32 == 16
