@@ -120,6 +120,13 @@ constexpr int sparse_region(int n, int nnz, int lanes)
     return lanes < 64 ? size + (16 - size % 32 + 32) % 32 : size + size % 2;
 }
 
+// A wave of a workgroup of `waves` that finds the queue empty and has no cell,
+// w waves working as one (1 until the last cell is handed over): it leaves
+// where nobody can hand it a cell any more.  With two slots per lane the
+// workgroup works as one from the beginning; with one it waits for the last
+// cell first, if there is another wave to bring it.
+constexpr bool crew_leaves(int vpl, int w, int waves) { return vpl > 1 || w == waves; }
+
 // What the device reads of a mechanism's sparse algebra (built per plan from
 // SparseLU; `lanes` lanes hold one cell's positions, two slots each when
 // n > 64).  Absent entries, and rows and columns beyond n, name the zero slot

@@ -1119,7 +1119,7 @@ k_integrate_sp_crew(DevMech mk, DevSparse spk, Opts o, int64_t n, const double *
                     st = SC_CELL_BAD_INPUT;
                 else if (!(dt > 0.0))
                     st = SC_CELL_OK;
-            } else if (VPL > 1 || crew.w > 1) {
+            } else if (sc::crew_leaves(VPL, crew.w, waves)) {
                 break;
             }
         }

@@ -41,6 +41,11 @@ int main(int argc, char **argv)
         const sc::SparseDev d = sc::sparse_device(m, lanes);
         put("size", std::vector<int>{m.N, m.R, m.sp.n, m.sp.nnz, m.n_padded});
         put("region", std::vector<int>{sc::sparse_region(m.sp.n, m.sp.nnz, lanes), sc::SPL_E});
+        std::vector<int> leaves;
+        for (int vpl : {1, 2})
+            for (int waves : {1, 2, 4})
+                for (int w : {1, waves}) leaves.insert(leaves.end(), {vpl, w, waves, sc::crew_leaves(vpl, w, waves)});
+        put("leaves", leaves);
         put("pos", m.sp.pos);
         put("erow", m.sp.erow);
         put("ecol", m.sp.ecol);

@@ -127,3 +127,11 @@ def test_regions_keep_the_pairs_aligned(tables, key):
     assert e0 * vectors + nnz + 1 + 16 <= size < e0 * vectors + nnz + 1 + 16 + 32
     if lanes < 64:
         assert size % 32 == 16
+
+
+def test_waves_without_a_cell_leave_or_are_waited_for(tables):
+    """One slot per lane: a wave waits for the last cell while there is another
+    wave (it works alone, of several), and leaves otherwise, also as the only
+    wave of its workgroup.  Two slots: the workgroup leaves together."""
+    for vpl, w, waves, leaves in tables("24")[2]["leaves"].reshape(-1, 4):
+        assert leaves == (vpl == 2 or not (w == 1 and waves > 1)), (vpl, w, waves)
