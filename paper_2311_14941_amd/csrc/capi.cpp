@@ -29,8 +29,8 @@ struct sc_plan {
     scdev::DevSparse ds{};
     std::vector<void *> allocs;
     unsigned long long *queue = nullptr;
-    int capacity = 0;            // resident workgroups of the persistent kernel
-    int capacity_static = 0;     // and of the static one
+    int capacity = 0;            // resident workgroups of the dense persistent kernel
+    scdev::SpCapacity cap{};     // and of the sparse kernels
     void *order_ws = nullptr;  // cell-ordering workspace (grown on demand)
     size_t order_ws_bytes = 0;
     int adj_capacity = 0;        // resident waves of the adjoint kernel
@@ -124,6 +124,16 @@ sc_status check_common(sc_plan *plan, int64_t n, int64_t ld, std::initializer_li
     for (const void *q : ptrs)
         if (!q) return fail(SC_EINVAL, "required array pointer is NULL");
     return SC_OK;
+}
+
+// Waves of the integration's workgroups, one cell per wave or crew.  With two
+// slots per lane a batch ends with its longest cell, which a crew of two shortens
+// from the beginning: crews up to half as many cells again as are in flight (700
+// cells, 512 crews or 768 and more waves: 80 species 53.3 ms with crews, 56.7
+// without, 65 species 42.7 and 43.0; 1,100 cells 71.4 and 72.9, 55.5 and 44.6).
+int integrate_waves(const sc_plan *plan, int64_t n, int64_t limit)
+{
+    return sc::crew_choice(plan->vpl, plan->cap.groups, limit, plan->vpl == 2 ? n - n / 3 : n);
 }
 
 // The sparse factorisation and solves hold two rows of the bordered system in
@@ -473,9 +483,9 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
         return fail(SC_ENOMEM, "device allocation/upload failed");
     }
     if (sparse)
-        scdev::capacity_sp(vpl, p->ds, device, p->capacity, p->capacity_static);
+        p->cap = scdev::capacity_sp(vpl, p->ds, device);
     else
-        p->capacity = p->capacity_static = scdev::persistent_capacity(p->np, device);
+        p->capacity = scdev::persistent_capacity(p->np, device);
     p->adj_capacity = nstate <= sc::MAX_STATE ? scdev::adjoint_capacity(p->np, d.R, device) : 0;
     *out = p;
     return SC_OK;
@@ -520,8 +530,9 @@ sc_status sc_linsolve(sc_plan *plan, int64_t n, const double *T, const double *p
     sc_status s = check_common(plan, n, ld, {T, p, Y, hg, b, x});
     if (s != SC_OK || n == 0 || (s = check_solve(plan)) != SC_OK) return s;
     DeviceGuard g(plan->device);
+    const int waves = plan->vpl == 2 ? sc::crew_choice(2, plan->cap.solve, INT_MAX, n) : 1;
     hipError_t e = plan->sparse ? scdev::launch_linsolve_sp(plan->vpl, plan->dms, plan->ds, n, T, p, Y, ld, dlnA, hg,
-                                                            b, x, (hipStream_t)stream)
+                                                            b, x, waves, (hipStream_t)stream)
                                 : scdev::launch_linsolve(plan->np, plan->dm, n, T, p, Y, ld, dlnA, hg, b, x,
                                                          (hipStream_t)stream);
     return e == hipSuccess ? SC_OK : hip_fail(e, "linsolve launch");
@@ -574,7 +585,11 @@ static sc_status integrate_impl(sc_plan *plan, int64_t n, const double *T0, cons
         const int tile = plan->opt.tile;
         const int64_t per_pull = (int64_t)tile * (plan->sparse ? plan->ds.cpw : 1);  // cells one wave takes per pull
         int64_t tiles = (n + per_pull - 1) / per_pull;
-        int grid = plan->opt.grid > 0 ? plan->opt.grid : plan->capacity;
+        const int waves = plan->sparse && plan->ds.cpw == 1
+                              ? integrate_waves(plan, n, plan->opt.grid > 0 ? plan->opt.grid : INT_MAX) : 1;
+        int grid = plan->opt.grid > 0 ? plan->opt.grid
+                   : plan->sparse     ? plan->cap.groups[waves == 4 ? 2 : waves - 1]
+                                      : plan->capacity;
         if (grid <= 0) grid = 1;
         if (grid > tiles) grid = (int)tiles;
         if (plan->sparse) grid = std::min(grid, 1 << 22);  // four waves each, within a launch's 2^32 threads
@@ -587,17 +602,17 @@ static sc_status integrate_impl(sc_plan *plan, int64_t n, const double *T0, cons
                                        &perm, st);
             if (e != hipSuccess) return hip_fail(e, "cell ordering");
         }
-        e = scdev::launch_set_u64(queue, plan->sparse ? scdev::queue_start_sp(plan->vpl, plan->ds, grid, tile) : 0, st);
+        e = scdev::launch_set_u64(queue, plan->sparse ? scdev::queue_start_sp(plan->vpl, plan->ds, grid, tile, waves) : 0, st);
         if (e == hipSuccess && plan->sparse)
             e = scdev::launch_integrate_sp_persistent(plan->vpl, plan->dms, plan->ds, o, n, T0, p, Y0, ld, dt, dlnA,
                                                       h_io, T1, Y1, cell_status, n_acc, n_rej, queue, perm, tile,
-                                                      grid, ref, st);
+                                                      grid, waves, ref, st);
         else if (e == hipSuccess)
             e = scdev::launch_integrate_persistent(plan->np, plan->dm, o, plan->opt.method, n, T0, p, Y0, ld, dt,
                                                    dlnA, h_io, T1, Y1, cell_status, n_acc, n_rej, queue, perm, tile,
                                                    grid, ref, st);
     } else if (plan->opt.mode == SC_MODE_STATIC) {
-        int grid = plan->opt.grid > 0 ? plan->opt.grid : plan->capacity_static;
+        int grid = plan->opt.grid > 0 ? plan->opt.grid : plan->sparse ? plan->cap.fixed : plan->capacity;
         if (grid <= 0) grid = 1;
         if (grid > n) grid = (int)n;
         if (plan->sparse)
@@ -607,8 +622,15 @@ static sc_status integrate_impl(sc_plan *plan, int64_t n, const double *T0, cons
             e = scdev::launch_integrate_static(plan->np, plan->dm, o, plan->opt.method, n, T0, p, Y0, ld, dt, dlnA,
                                                h_io, T1, Y1, cell_status, n_acc, n_rej, grid, ref, st);
     } else if (plan->sparse) {
+        // workgroups of several waves: with one slot per lane where no cell
+        // waits for one (62 us a step of 53 species without, 54 with), with two
+        // as the queue's
+        const int most = plan->cap.groups[2] ? 2 : plan->cap.groups[1] ? 1 : 0;
+        const int waves = plan->ds.cpw > 1 ? 0
+                          : plan->vpl == 2 ? integrate_waves(plan, n, INT_MAX)
+                          : n <= plan->cap.groups[most] ? 1 << most : 0;
         e = scdev::launch_integrate_sp(plan->vpl, plan->dms, plan->ds, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1,
-                                       cell_status, n_acc, n_rej, ref, plan->capacity, st);
+                                       cell_status, n_acc, n_rej, ref, waves, st);
     } else {
         e = scdev::launch_integrate(plan->np, plan->dm, o, plan->opt.method, n, T0, p, Y0, ld, dt, dlnA, h_io, T1,
                                     Y1, cell_status, n_acc, n_rej, ref, st);

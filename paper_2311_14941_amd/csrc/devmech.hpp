@@ -109,26 +109,31 @@ hipError_t launch_jac_sp(int vpl, const DevMech &m, const DevSparse &sp, int64_t
                          hipStream_t s);
 hipError_t launch_linsolve_sp(int vpl, const DevMech &m, const DevSparse &sp, int64_t n, const double *T,
                               const double *p, const double *Y, int64_t ld, const double *dlnA, const double *hg,
-                              const double *b, double *x, hipStream_t s);
+                              const double *b, double *x, int waves, hipStream_t s);
 hipError_t launch_integrate_sp(int vpl, const DevMech &m, const DevSparse &sp, const Opts &o, int64_t n,
                                const double *T0, const double *p, const double *Y0, int64_t ld, const double *dt,
                                const double *dlnA, double *h_io, double *T1, double *Y1, int32_t *st, int32_t *na,
-                               int32_t *nr, const int32_t *ref, int crews, hipStream_t s);
+                               int32_t *nr, const int32_t *ref, int waves, hipStream_t s);
 hipError_t launch_integrate_sp_persistent(int vpl, const DevMech &m, const DevSparse &sp, const Opts &o,
                                           int64_t n, const double *T0, const double *p, const double *Y0,
                                           int64_t ld, const double *dt, const double *dlnA, double *h_io,
                                           double *T1, double *Y1, int32_t *st, int32_t *na, int32_t *nr,
                                           unsigned long long *queue, const int32_t *perm, int tile, int grid,
-                                          const int32_t *ref, hipStream_t s);
+                                          int waves, const int32_t *ref, hipStream_t s);
 hipError_t launch_integrate_sp_static(int vpl, const DevMech &m, const DevSparse &sp, const Opts &o, int64_t n,
                                       const double *T0, const double *p, const double *Y0, int64_t ld,
                                       const double *dt, const double *dlnA, double *h_io, double *T1, double *Y1,
                                       int32_t *st, int32_t *na, int32_t *nr, int grid, const int32_t *ref,
                                       hipStream_t s);
 // where the queue of a persistent launch starts: behind the workgroups' first tiles
-int64_t queue_start_sp(int vpl, const DevSparse &sp, int grid, int tile);
-// resident workgroups of the persistent and the static kernel (0 on failure)
-void capacity_sp(int vpl, const DevSparse &sp, int device, int &persistent, int &fixed);
+int64_t queue_start_sp(int vpl, const DevSparse &sp, int grid, int tile, int waves);
+// Resident workgroups (0 where there are none): of 1, 2 and 4 waves of the
+// persistent kernel (of one wave only with several cells per wave) and, with two
+// slots per lane, of the linear solve's; and of the static kernel.
+struct SpCapacity {
+    int groups[sc::CREW_SIZES], solve[sc::CREW_SIZES], fixed;
+};
+SpCapacity capacity_sp(int vpl, const DevSparse &sp, int device);
 
 // zonal reference-cell mapping (mapping.hip): the zone table is cleared,
 // every mappable cell claims its zone (lowest index wins) and gets its

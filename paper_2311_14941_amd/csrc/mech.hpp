@@ -9,6 +9,7 @@
 // analytical Jacobian terms, and count the work of every kernel phase.
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 #include <stdexcept>
 #include <string>
@@ -120,6 +121,33 @@ constexpr int sparse_region(int n, int nnz, int lanes)
     return lanes < 64 ? size + (16 - size % 32 + 32) % 32 : size + size % 2;
 }
 
+// Waves of a workgroup of the sparse kernels, 1, 2 or 4, for n cells:
+// groups[k] workgroups of 2^k waves are resident on the device, at most `limit`
+// of them are launched.  With one slot per lane each wave has a cell (and a
+// region of LDS) until the last ones are shared, with two the workgroup has one.
+// The choice is by the cells in flight at a time, then by the waves: a crew
+// gains less on a cell (four waves 1.2 times a step of one-slot mechanisms, two
+// 1.1 to 1.3 times of two-slot ones) than a CU loses with its cells.  Regions of
+// 20 to 27 KB (57 to 62 species) leave room for one workgroup of four waves, three
+// of two or seven of one; regions of 27 to 52 KB (63 to about 89 species) for two
+// crews of two or three to four single waves.  4,096 cells, waves by the rule
+// against the most that fit: 57 species 63.0 and 77.8 ms, 65 species 105.0 and
+// 161.0, 80 species 177 and 198, linear solves of 65 species 0.36 and 0.53 (ms).
+constexpr int CREW_SIZES = 3;
+// Workgroups of `bytes` each that a CU's LDS holds: 160 KB, given out in pieces
+// of 1,280 bytes (three times 54,000 bytes, of 90 species, would fit by the sum,
+// but do not: taken for three, 4,096 cells took 280 ms, with crews of two 226)
+constexpr int lds_held(size_t bytes) { return (int)(128 / ((bytes + 1279) / 1280)); }
+inline int crew_choice(int vpl, const int (&groups)[CREW_SIZES], int64_t limit, int64_t n)
+{
+    int waves = 1;
+    int64_t most = 0;
+    for (int k = 0; k < CREW_SIZES; ++k) {
+        const int64_t in_flight = std::min(n, std::min<int64_t>(groups[k], limit) << (vpl == 1 ? k : 0));
+        if (in_flight > 0 && in_flight >= most) most = in_flight, waves = 1 << k;
+    }
+    return waves;
+}
 // A wave of a workgroup of `waves` that finds the queue empty and has no cell,
 // w waves working as one (1 until the last cell is handed over): it leaves
 // where nobody can hand it a cell any more.  With two slots per lane the

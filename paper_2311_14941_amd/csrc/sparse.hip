@@ -20,6 +20,7 @@
 //
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <type_traits>
@@ -1042,12 +1043,12 @@ __global__ void __launch_bounds__(WAVE) SP_OCC k_integrate_sp_static(DevMech mk,
                                  nrej, ref);
 }
 
-// The persistent launch of one cell per wave's 64 lanes: workgroups of several
-// waves.  With one slot per lane each wave has its own LDS region and works by
-// itself while the queue lasts; a wave that finds it empty waits, and when one
-// wave of the workgroup is left with a cell, all of them finish it as a crew.
-// With two slots (one or two cells' LDS in a CU) the workgroup is a crew from
-// the beginning.  Every wait ends: a wave with a cell always gets on, by itself
+// The persistent launch of one cell per wave's 64 lanes: workgroups of one, two
+// or four waves (crew_choice).  With one slot per lane each wave has its own LDS
+// region and works by itself while the queue lasts; a wave that finds it empty
+// waits, and when one wave of the workgroup is left with a cell, all of them
+// finish it as a crew.  With two slots the workgroup has one region and is a crew
+// of its waves from the beginning.  Every wait ends: a wave with a cell always gets on, by itself
 // or as the crew, and the one that runs out last counts itself in as well.
 // (A step of 53 species takes a lone wave 62 us, a crew of four 54: the pivots'
 // chains and the solves do not split.  4,096 cells of 110 species, where the
@@ -1291,8 +1292,9 @@ __global__ void __launch_bounds__(WAVE) k_jac_sp(DevMech mk, DevSparse spk, int6
     }
 }
 
-template <int VPL, bool CV, int CPW, bool TB>
-__global__ void __launch_bounds__(VPL * WAVE) k_linsolve_sp(DevMech mk, DevSparse spk, int64_t n, const double *T,
+// W waves a cell (with two slots per lane two where they are a crew)
+template <int VPL, bool CV, int CPW, bool TB, int W>
+__global__ void __launch_bounds__(W * WAVE) k_linsolve_sp(DevMech mk, DevSparse spk, int64_t n, const double *T,
                                                       const double *P, const double *Y, int64_t ld,
                                                       const double *dlnA, const double *hg, const double *b,
                                                       double *x)
@@ -1300,17 +1302,15 @@ __global__ void __launch_bounds__(VPL * WAVE) k_linsolve_sp(DevMech mk, DevSpars
     extern __shared__ double lds[];
     const DevMech m = fix_reactor<CV>(mk);
     const DevSparse sp = fix_tables<TB>(spk);
-    // two waves a cell with two slots per lane: the LDS holds one or two cells
     constexpr int G = WAVE / CPW;
-    const int lane = (int)threadIdx.x % G;
-    const int64_t c = (int64_t)blockIdx.x * CPW + (VPL == 1 ? (int)threadIdx.x / G : 0);
+    const int lane = (int)threadIdx.x % G, grp = W == 1 ? (int)threadIdx.x / G : 0;
+    const int64_t c = (int64_t)blockIdx.x * CPW + grp;
     if (c >= n) return;
-    double *ldsg = lds + (VPL == 1 ? (size_t)((int)threadIdx.x / G) * sp.size : CREW_SHARE);
-    std::conditional_t<VPL == 1, Solo, Crew> crew;
-    if constexpr (VPL > 1)
-    {
+    double *ldsg = lds + (W == 1 ? (size_t)grp * sp.size : CREW_SHARE);
+    std::conditional_t<W == 1, Solo, Crew> crew;
+    if constexpr (W > 1) {
         crew.turn = &((CrewShare *)lds)->turn;
-        crew.join(sp, VPL, __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE));
+        crew.join(sp, W, __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE));
     }
     double y[VPL], f[VPL], bb[VPL], xx[VPL];
     load_state_v<VPL, G>(m, sp, T, Y, ld, c, lane, y);
@@ -1354,17 +1354,10 @@ __global__ void __launch_bounds__(VPL * WAVE) k_linsolve_sp(DevMech mk, DevSpars
 
 // LDS of one workgroup: one region of sp.size doubles per cell of the wave
 static size_t sp_lds(const DevSparse &sp, int cpw) { return sizeof(double) * (size_t)sp.size * cpw; }
-// Waves of a crew workgroup (a power of two): as many as their regions (one in
-// all with two slots per lane) leave room for in a CU's 160 KB
+// and of a crew workgroup: a region per wave, one in all with two slots per lane
 static size_t crew_lds(int vpl, const DevSparse &sp, int waves)
 {
     return sizeof(double) * (CREW_SHARE + (size_t)sp.size * (vpl == 1 ? waves : 1));
-}
-static int crew_waves(int vpl, const DevSparse &sp)
-{
-    int w = crew_most(vpl);
-    while (w > 1 && crew_lds(vpl, sp, w) > 160 * 1024) w /= 2;
-    return w;
 }
 static unsigned sp_blocks(int64_t n, int cpw) { return (unsigned)((n + cpw - 1) / cpw); }
 
@@ -1388,27 +1381,28 @@ hipError_t launch_jac_sp(int vpl, const DevMech &m, const DevSparse &sp, int64_t
 
 hipError_t launch_linsolve_sp(int vpl, const DevMech &m, const DevSparse &sp, int64_t n, const double *T,
                               const double *p, const double *Y, int64_t ld, const double *dlnA, const double *hg,
-                              const double *b, double *x, hipStream_t s)
+                              const double *b, double *x, int waves, hipStream_t s)
 {
     const int cpw = sp.cpw;
-    SP_DISPATCH(hipLaunchKernelGGL(SP_KERNEL(k_linsolve_sp), dim3(sp_blocks(n, cpw)), dim3(VPLV * WAVE),
-                                   (VPLV == 1 ? sp_lds(sp, cpw) : crew_lds(vpl, sp, VPLV)), s, m, sp, n, T, p, Y, ld, dlnA, hg, b, x))
+    auto launch = [&](auto kern, size_t bytes) {
+        hipLaunchKernelGGL(kern, dim3(sp_blocks(n, cpw)), dim3(waves * WAVE), bytes, s, m, sp, n, T, p, Y, ld, dlnA,
+                           hg, b, x);
+    };
+    SP_DISPATCH(if (VPLV == 2 && waves == 2) launch(k_linsolve_sp<VPLV, CVV, CPWV, TBV, VPLV>, crew_lds(vpl, sp, 2));
+                else launch(k_linsolve_sp<VPLV, CVV, CPWV, TBV, 1>, sp_lds(sp, cpw)))
 }
 
 hipError_t launch_integrate_sp(int vpl, const DevMech &m, const DevSparse &sp, const Opts &o, int64_t n,
                                const double *T0, const double *p, const double *Y0, int64_t ld, const double *dt,
                                const double *dlnA, double *h_io, double *T1, double *Y1, int32_t *st, int32_t *na,
-                               int32_t *nr, const int32_t *ref, int crews, hipStream_t s)
+                               int32_t *nr, const int32_t *ref, int waves, hipStream_t s)
 {
     const int cpw = sp.cpw;
-    // crews where no cell waits for a workgroup then, or, with two slots per
-    // lane, where LDS bounds the cells of a CU and not waves (62 us a step
-    // without, 54 with; one of 110 species 166 and 149).  Four waves at most
-    // each, within a launch's 2^32 threads
+    // a crew per cell; four waves at most each, within a launch's 2^32 threads
     const int tile = (int)((n >> 22) + 1);
-    if (cpw == 1 && (vpl == 2 || n <= crews))
+    if (waves > 0)
         return launch_integrate_sp_persistent(vpl, m, sp, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1, st, na, nr,
-                                              nullptr, nullptr, tile, (int)((n + tile - 1) / tile), ref, s);
+                                              nullptr, nullptr, tile, (int)((n + tile - 1) / tile), waves, ref, s);
     SP_DISPATCH(if constexpr (VPLV == 1) hipLaunchKernelGGL(
         SP_KERNEL(k_integrate_sp), dim3(sp_blocks(n, cpw)), dim3(WAVE), sp_lds(sp, cpw), s, m, sp, o, n, T0, p, Y0,
         ld, dt, dlnA, h_io, T1, Y1, st, na, nr, ref))
@@ -1419,10 +1413,9 @@ hipError_t launch_integrate_sp_persistent(int vpl, const DevMech &m, const DevSp
                                           int64_t ld, const double *dt, const double *dlnA, double *h_io,
                                           double *T1, double *Y1, int32_t *st, int32_t *na, int32_t *nr,
                                           unsigned long long *queue, const int32_t *perm, int tile, int grid,
-                                          const int32_t *ref, hipStream_t s)
+                                          int waves, const int32_t *ref, hipStream_t s)
 {
     const int cpw = sp.cpw;
-    const int waves = crew_waves(vpl, sp);
     SP_DISPATCH(if constexpr (CPWV == 1) hipLaunchKernelGGL(
                     (k_integrate_sp_crew<VPLV, CVV, TBV>), dim3((unsigned)grid), dim3(waves * WAVE),
                     crew_lds(vpl, sp, waves), s, m, sp, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1, st, na, nr,
@@ -1445,31 +1438,40 @@ hipError_t launch_integrate_sp_static(int vpl, const DevMech &m, const DevSparse
                                    sp, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1, st, na, nr, group, ref))
 }
 
-int64_t queue_start_sp(int vpl, const DevSparse &sp, int grid, int tile)
+int64_t queue_start_sp(int vpl, const DevSparse &sp, int grid, int tile, int waves)
 {
     if (sp.cpw > 1) return 0;
-    return (int64_t)grid * tile * (vpl == 1 ? crew_waves(vpl, sp) : 1);
+    return (int64_t)grid * tile * (vpl == 1 ? waves : 1);
 }
 
-void capacity_sp(int vpl, const DevSparse &sp, int device, int &persistent, int &fixed)
+SpCapacity capacity_sp(int vpl, const DevSparse &sp, int device)
 {
+    SpCapacity r{};
     int cus = 0;
-    persistent = fixed = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return r;
     const int cpw = sp.cpw;
     auto occ = [&](auto kern, int threads, size_t bytes) {
         int per_cu = 0;
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, bytes) == hipSuccess ? per_cu * cus : 0;
+        if (sc::lds_held(bytes) == 0 ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, bytes) != hipSuccess)
+            return 0;
+        return std::min(per_cu, sc::lds_held(bytes)) * cus;
     };
-    const int cw = crew_waves(vpl, sp);
     auto set = [&](auto pers, auto stat) {
-        persistent = cpw == 1 ? occ(pers, cw * WAVE, crew_lds(vpl, sp, cw)) : occ(pers, WAVE, sp_lds(sp, cpw));
-        fixed = occ(stat, WAVE, sp_lds(sp, cpw));
+        if (cpw > 1) r.groups[0] = occ(pers, WAVE, sp_lds(sp, cpw));
+        else
+            for (int k = 0; 1 << k <= crew_most(vpl); ++k) r.groups[k] = occ(pers, WAVE << k, crew_lds(vpl, sp, 1 << k));
+        r.fixed = occ(stat, WAVE, sp_lds(sp, cpw));
     };
     if (vpl == 1 && cpw == 1) set(k_integrate_sp_crew<1, false, false>, k_integrate_sp_static<1, false, 1, false>);
     else if (vpl == 1 && cpw == 2) set(k_integrate_sp_persistent<1, false, 2, false>, k_integrate_sp_static<1, false, 2, false>);
     else if (vpl == 1 && cpw == 4) set(k_integrate_sp_persistent<1, false, 4, false>, k_integrate_sp_static<1, false, 4, false>);
-    else if (vpl == 2 && cpw == 1) set(k_integrate_sp_crew<2, false, false>, k_integrate_sp_static<2, false, 1, false>);
+    else if (vpl == 2 && cpw == 1) {
+        set(k_integrate_sp_crew<2, false, false>, k_integrate_sp_static<2, false, 1, false>);
+        r.solve[0] = occ(k_linsolve_sp<2, false, 1, false, 1>, WAVE, sp_lds(sp, 1));
+        r.solve[1] = occ(k_linsolve_sp<2, false, 1, false, 2>, 2 * WAVE, crew_lds(vpl, sp, 2));
+    }
+    return r;
 }
 
 }  // namespace scdev

@@ -41,6 +41,17 @@ int main(int argc, char **argv)
         const sc::SparseDev d = sc::sparse_device(m, lanes);
         put("size", std::vector<int>{m.N, m.R, m.sp.n, m.sp.nnz, m.n_padded});
         put("region", std::vector<int>{sc::sparse_region(m.sp.n, m.sp.nnz, lanes), sc::SPL_E});
+        // waves a workgroup by the regions a CU of 160 KB holds, up to two waves
+        // per SIMD with one slot per lane, one with two: for 64 to 2^20 cells
+        const int vpl = m.sp.n <= 64 ? 1 : 2;
+        int groups[sc::CREW_SIZES] = {};
+        for (int k = 0; k < (vpl == 1 ? 3 : 2); ++k) {
+            const int bytes = 128 + 8 * sc::sparse_region(m.sp.n, m.sp.nnz, 64) * (vpl == 1 ? 1 << k : 1);
+            groups[k] = 256 * std::min(sc::lds_held(bytes), (vpl == 1 ? 8 : 4) >> k);
+        }
+        std::vector<int> crews(groups, groups + sc::CREW_SIZES);
+        for (int64_t n = 64; n <= 1 << 20; n *= 2) crews.push_back(sc::crew_choice(vpl, groups, 1 << 30, n));
+        put("crews", crews);
         std::vector<int> leaves;
         for (int vpl : {1, 2})
             for (int waves : {1, 2, 4})

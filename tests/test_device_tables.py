@@ -22,7 +22,7 @@ MECHS = {"14 x 16": (14, 56, 0.15, 401, 16), "30 x 32": (30, 150, 0.3, 402, 32),
 
 
 def mechanism(key):
-    ns, nr, pf, seed, lanes = MECHS[key]
+    ns, nr, pf, seed, lanes = MECHS.get(key) or key
     return make_mechanism(ns, nr, nr // 10, nr // 20, ["C", "H", "O", "N"], seed=seed, pool_frac=pf), lanes
 
 
@@ -135,3 +135,29 @@ def test_waves_without_a_cell_leave_or_are_waited_for(tables):
     wave of its workgroup.  Two slots: the workgroup leaves together."""
     for vpl, w, waves, leaves in tables("24")[2]["leaves"].reshape(-1, 4):
         assert leaves == (vpl == 2 or not (w == 1 and waves > 1)), (vpl, w, waves)
+
+
+# species (mechanisms of every range of LDS regions): waves a workgroup for few
+# cells and for many
+CREWS = {53: (4, 4), 57: (4, 1), 62: (4, 1), 63: (2, 1), 65: (2, 1), 80: (2, 1), 90: (2, 2), 96: (2, 2), 126: (2, 2)}
+
+
+@pytest.mark.parametrize("ns", list(CREWS))
+def test_waves_of_a_workgroup_by_the_cells_in_flight(tables, ns):
+    """Many cells: no choice of waves a workgroup keeps more cells on a CU than
+    the one taken; few: the most waves.  53 species hold two workgroups of four
+    waves, 57 to 62 one, three of two or seven of one; two slots per lane two
+    crews or more single waves up to 52 KB a cell."""
+    t = tables((ns, 6 * ns, 0.15, 400, 64))[2]
+    one = int(t["size"][2]) <= 64
+    groups, choice = t["crews"][:3], t["crews"][3:]
+    cells = groups * (1 << np.arange(3) if one else 1)
+    for k in range(3):
+        if groups[k]:  # what is taken to be resident is, in pieces of 1,280 bytes
+            size = 128 + 8 * int(t["region"][0]) * (1 << k if one else 1)
+            assert groups[k] // 256 * -(-size // 1280) * 1280 <= 160 * 1024
+    few, many = CREWS[ns]
+    assert choice[0] == few and choice[-1] == many
+    for n, w in zip(64 << np.arange(choice.size), choice):
+        flight = np.minimum(n, cells)
+        assert flight[int(w).bit_length() - 1] == flight.max(), (n, w)
