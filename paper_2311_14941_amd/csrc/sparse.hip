@@ -1384,9 +1384,14 @@ hipError_t launch_linsolve_sp(int vpl, const DevMech &m, const DevSparse &sp, in
                               const double *b, double *x, int waves, hipStream_t s)
 {
     const int cpw = sp.cpw;
+    // a launch has fewer than 2^32 threads: crews of two take their cells in parts
+    const int64_t part = waves == 2 ? 1 << 24 : n, nn = m.N + 1;
     auto launch = [&](auto kern, size_t bytes) {
-        hipLaunchKernelGGL(kern, dim3(sp_blocks(n, cpw)), dim3(waves * WAVE), bytes, s, m, sp, n, T, p, Y, ld, dlnA,
-                           hg, b, x);
+        for (int64_t c = 0; c < n; c += part) {
+            const int64_t k = std::min(part, n - c);
+            hipLaunchKernelGGL(kern, dim3(sp_blocks(k, cpw)), dim3(waves * WAVE), bytes, s, m, sp, k, T + c, p + c,
+                               Y + c, ld, dlnA, hg + c, b + c * nn, x + c * nn);
+        }
     };
     SP_DISPATCH(if (VPLV == 2 && waves == 2) launch(k_linsolve_sp<VPLV, CVV, CPWV, TBV, VPLV>, crew_lds(vpl, sp, 2));
                 else launch(k_linsolve_sp<VPLV, CVV, CPWV, TBV, 1>, sp_lds(sp, cpw)))

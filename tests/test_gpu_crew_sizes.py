@@ -63,3 +63,28 @@ def test_linear_solves_of_large_batches(case):
         e = min(a + 401, n)
         part = plan.linsolve(T[a:e].clone(), p[a:e].clone(), Y[:, a:e].contiguous(), hg[a:e].clone(), b[a:e].clone())
         assert torch.equal(part[keep[a:e]], x[a:e][keep[a:e]])
+
+
+def test_linear_solves_of_more_cells_than_a_launch_has_crews():
+    """Crews of two (90 species) of 2^25 + 5 cells would be 2^32 threads and
+    more: the parts' first and last cells solve as in a small call."""
+    import torch
+
+    import paper_2311_14941_amd as sc
+    from synth.mechgen import make_mechanism
+    sc.ensure_built()
+    ns, n = 90, 2 ** 25 + 5
+    mech = sc.Mechanism(make_mechanism(ns, 6 * ns, 54, 27, ["C", "H", "O", "N"], seed=400, pool_frac=0.15).to_text())
+    d = dict(dtype=torch.float64, device="cuda:0")
+    k = torch.arange(n, device="cuda:0")
+    T = 1000.0 + (k % 997).to(torch.float64)
+    p, hg = torch.full((n,), 2e5, **d), torch.full((n,), 1e-8, **d)
+    Y = torch.full((ns, n), 1.0 / ns, **d)
+    b = torch.ones((n, ns + 1), **d)
+    b[:, 0] = 1.0 + (k % 991).to(torch.float64)
+    plan = sc.Plan(mech, linalg="sparse")
+    x = plan.linsolve(T, p, Y, hg, b)
+    for c in (0, 2 ** 24, 2 ** 25, n):
+        i = torch.arange(max(c - 4, 0), min(c + 4, n), device="cuda:0")
+        part = plan.linsolve(T[i], p[i], Y[:, i].contiguous(), hg[i], b[i])
+        assert torch.equal(part, x[i]), c
