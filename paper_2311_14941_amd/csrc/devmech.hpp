@@ -49,7 +49,7 @@ struct DevSparse : DevRx {
     int n, nnz;
     int size;  // LDS doubles of one cell's region
     int cpw;  // cells per wave (1, 2 or 4): each cell takes 64 / cpw lanes
-    const uint16_t *comp;  // [position][8]: e_kk, e_kT, e_kS, e_Tk, e_Sk; at N: e_TT, e_SS
+    const uint16_t *comp;  // [position][8]: e_kk, e_kT, e_kS, e_Tk, e_Sk; at N: e_TT, e_SS; else trash entries
     const int32_t *perm;   // position -> species (N: temperature)
     const int32_t *pos;    // species -> position
     const uint16_t *jmap;    // (N + 1)^2: (row, column) component in species order -> entry (or the zero slot)

@@ -174,7 +174,9 @@ struct SparseDev {
     //   r r half words [q1][q2][lane]: (q1 4i + g, q2 c), i = 0..3
     // one block's words after the other's
     std::vector<uint16_t> blk;
-    std::vector<uint16_t> comp;  // per component (position order): its entries kk, kT, kS, Tk, Sk, padded to 8
+    // per component (position order) eight: its entries kk, kT, kS, Tk, Sk, the
+    // temperature's TT and SS; trash entries where it has none and behind
+    std::vector<uint16_t> comp;
 };
 
 enum RxKind { RX_PLAIN = 0, RX_THIRD = 1, RX_TROE = 2 };

@@ -370,8 +370,10 @@ SparseDev sparse_device(const Mech &m, int lanes)
             for (int q2 = b + 1; q2 < nb; ++q2)
                 word([&](int l, int h) { return off(16 * q1 + 4 * h + l / 16, 16 * q2 + l % 16); }, 4);
     }
-    // component entries by position (the borders are the last two)
-    D.comp.assign((size_t)8 * lanes * slots, 0);
+    // component entries by position (the borders are the last two), trash
+    // entries where a component has none
+    D.comp.resize((size_t)8 * lanes * slots);
+    for (size_t i = 0; i < D.comp.size(); ++i) D.comp[i] = (uint16_t)(S.nnz + 1 + i / 8 % SPARSE_TRASH);
     for (int k = 0; k < N; ++k) {
         uint16_t *c = &D.comp[(size_t)8 * S.pos[k]];
         const int e[5] = {S.e_kk[k], S.e_kT[k], S.e_kS[k], S.e_Tk[k], S.e_Sk[k]};

@@ -340,17 +340,17 @@ __device__ __forceinline__ void jac_v(const CR &crew, const DevMech &m, const De
     for (int v = 0; v < VPL; ++v) {
         const int c = lane + G * v;
         cm[v] = ((const uint4 *)sp.comp)[c];
-        f[v] = hw[v] = eu[v] = cpf[v] = dcp[v] = uak[v] = 0.0;
-        if (c < N) {
-            const double Wk = m.W()[c], iw = m.invW()[c];
-            const double wdk = pair<NV>(lds, SPL_HW, c)[1];
-            uak[v] = lds[SPL_UA * NV + c];
-            f[v] = Wk * wdk / x.rho;
-            hw[v] = (th[v].hRT - one) * wdk;
-            eu[v] = th[v].hRT * uak[v] / x.rho;      // (h_k/(R T W_k)) u_k, u_k = W_k UA_k / rho
-            cpf[v] = (th[v].cpR - one) * f[v] * iw;
-            dcp[v] = th[v].dcpR * y[v] * iw;
-        }
+        // no branches from here to the factorisation (see rhs_jac)
+        const bool own = c < N;
+        const int k = min(c, N - 1);
+        const double Wk = own ? m.W()[k] : 0.0, iw = own ? m.invW()[k] : 0.0;
+        const double wdk = own ? pair<NV>(lds, SPL_HW, c)[1] : 0.0;
+        uak[v] = own ? lds[SPL_UA * NV + c] : 0.0;
+        f[v] = Wk * wdk / x.rho;
+        hw[v] = (th[v].hRT - one) * wdk;
+        eu[v] = th[v].hRT * uak[v] / x.rho;      // (h_k/(R T W_k)) u_k, u_k = W_k UA_k / rho
+        cpf[v] = (th[v].cpR - one) * f[v] * iw;
+        dcp[v] = th[v].dcpR * y[v] * iw;
     }
     const double H = RT * vsum<VPL, G>(hw);
     const double Eu = m.cv ? 0.0 : RT * vsum<VPL, G>(eu);
@@ -362,27 +362,24 @@ __device__ __forceinline__ void jac_v(const CR &crew, const DevMech &m, const De
     const double ct = m.cv ? 0.0 : x.invT;
     const double tb = m.cv ? gsum<G>(tm) : x.Wbar * Eu;
     const double icp = 1.0 / x.cp;
+    const double MTT = inv_hg + (TT / x.rho + (m.cv ? 0.0 : Eu * x.invT) + Scpf + fT * Sdcp) * icp;
 #pragma unroll
     for (int v = 0; v < VPL; ++v) {
         const int c = lane + G * v;
         const int e0 = cm[v].x & 0xffff, e1 = cm[v].x >> 16, e2 = cm[v].y & 0xffff, e3 = cm[v].y >> 16, e4 = cm[v].z & 0xffff;
-        if constexpr (!std::is_same_v<CR, Solo>) {
-            if (c == N) f[v] = fT;
+        f[v] = c == N ? fT : f[v];
+        if constexpr (!std::is_same_v<CR, Solo>)
             if (crew.rank != 0) continue;
-        }
-        if (c < N) {
-            const double us = m.cv ? uak[v] : uak[v] / x.rho;
-            E[e0] += inv_hg;
-            E[e1] = E[e1] / x.rho - ct * us;
-            E[e2] = -us;
-            E[e3] = (E[e3] + tb + fT * m.Rgas * (th[v].cpR - one)) * icp;
-            E[e4] = vs;
-        } else if (c == N) {
-            f[v] = fT;
-            const double eT = m.cv ? 0.0 : Eu * x.invT;
-            E[e0] = inv_hg + (TT / x.rho + eT + Scpf + fT * Sdcp) * icp;
-            E[e1] = -1.0;
-        }
+        // the temperature's lane has (T, T) and the corner of the borders; what
+        // it and the lanes behind it do not have are trash entries
+        const bool own = c < N;
+        const double us = m.cv ? uak[v] : uak[v] / x.rho;
+        const double a0 = E[e0], a1 = E[e1], a3 = E[e3];
+        E[e0] = own ? a0 + inv_hg : MTT;
+        E[e1] = own ? a1 / x.rho - ct * us : -1.0;
+        E[e2] = -us;
+        E[e3] = (a3 + tb + fT * m.Rgas * (th[v].cpR - one)) * icp;
+        E[e4] = vs;
     }
     crew.sync();
 }

@@ -161,3 +161,22 @@ def test_waves_of_a_workgroup_by_the_cells_in_flight(tables, ns):
     for n, w in zip(64 << np.arange(choice.size), choice):
         flight = np.minimum(n, cells)
         assert flight[int(w).bit_length() - 1] == flight.max(), (n, w)
+
+
+@pytest.mark.parametrize("key", ["14 x 16", "30 x 32", "24", "63", "126"])
+def test_component_entries(tables, key):
+    """What each state component writes when the matrix is formed: its own
+    entries, and trash entries (behind the zero slot) where it has none, so
+    that every lane writes as many."""
+    _, lanes, t = tables(key)
+    N, _, n, nnz, _ = (int(v) for v in t["size"])
+    entry = -np.ones((n, n), dtype=int)
+    entry[t["erow"], t["ecol"]] = np.arange(nnz)
+    comp = t["comp"].reshape(-1, 8).astype(int)
+    T, S, k = N, N + 1, np.arange(N)
+    assert comp.shape[0] == lanes * (1 if n <= 64 else 2)
+    for q, e in enumerate((entry[k, k], entry[k, T], entry[k, S], entry[T, k], entry[S, k])):
+        assert np.array_equal(comp[:N, q], e)
+    assert comp[N, 0] == entry[T, T] and comp[N, 1] == entry[S, S]
+    rest = np.concatenate([comp[N, 2:].ravel(), comp[N + 1:].ravel()])
+    assert np.all((rest > nnz) & (rest <= nnz + 16))
