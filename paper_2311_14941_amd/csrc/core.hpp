@@ -344,18 +344,18 @@ struct Lds {
     // row stride of the Jacobian terms: lanes reading their own rows hit
     // addresses a stride apart; an odd stride spreads them over the banks
     static constexpr int PS = NP + 1;
-    static constexpr int P = 0;          // NP x PS Jacobian terms, later the LU factors (stride NP)
+    static constexpr int P = 0;          // NP x PS Jacobian terms, later the LU factors (stride PS)
     // the term region is also where the adjoint's dual passes keep the
     // derivatives of the pairs and of its own V vector (each at a fixed
-    // offset -RX from the value), which ends RXV + 2 NP + (NS + 1) WAVE doubles in
-    static constexpr int NV = WAVE + 2;     // species and dummy of the reaction passes, even
+    // offset -RX from the value), which ends 8 NP + NS WAVE doubles in
+    static constexpr int NV = NP;           // places of the passes' vectors: species, then the temperature's
     static constexpr int RXV = 5 * NV;      // their pairs and Euler terms
-    static constexpr int DUAL = RXV + 2 * NP + (NS + 1) * WAVE;
+    static constexpr int DUAL = RXV + 3 * NP + NS * WAVE;
     static constexpr int PREG = NP * PS > DUAL ? NP * PS : DUAL;
     static constexpr int RX = PREG;         // the passes' vectors
-    static_assert(PREG % 2 == 0, "the passes' pairs are read in one");
+    static_assert(PREG % 2 == 0 && NV % 2 == 0, "the passes' pairs are read in one");
     static constexpr int IW = RX + RXV;  // 1/W_c (0 for c >= N)
-    static constexpr int U = IW + WAVE;  // NS stage vectors, WAVE apart
+    static constexpr int U = IW + NP;    // NS stage vectors, WAVE apart
     static constexpr int SIZE = U + NS * WAVE;
 };
 
@@ -759,7 +759,8 @@ __device__ __forceinline__ void jac_passes(const CR &crew, const DevMech &m, con
 
 // mixture() for the reaction passes: C and g/RT, h/RT and the production rate
 // in pairs; what an unused slot of a reaction reads lies in the temperature's
-// place N
+// place N.  The lanes behind it hold the same (the last place, where there are
+// more lanes than places).
 template <int NP, class S = double>
 __device__ __forceinline__ Mix<S> mixture_pairs(const DevMech &m, double *lds, S y, double p, Thermo<S> &th, int lane,
                                                 int toff = 0)
@@ -776,7 +777,7 @@ __device__ __forceinline__ Mix<S> mixture_pairs(const DevMech &m, double *lds, S
     };
     S yw;
     const Mix<S> x = mixture_point(m, y, p, th, lane, yw);
-    put(lane, lane < m.N ? x.rho * yw : S(1.0), th.hRT - th.sR, th.hRT);
+    put(NP < WAVE ? min(lane, NV - 1) : lane, lane < m.N ? x.rho * yw : S(1.0), th.hRT - th.sR, th.hRT);
     return x;
 }
 
@@ -838,7 +839,7 @@ __device__ __forceinline__ double rhs_jac(const DevMech &m, double *lds, double 
     const bool own = lane < N;
     const int k = min(lane, N - 1);
     const double Wk = own ? m.W()[k] : 0.0, iw = own ? m.invW()[k] : 0.0;
-    const double wd = own ? pair<NV>(v, SPL_HW, lane)[1] : 0.0, ua = own ? v[SPL_UA * NV + lane] : 0.0;
+    const double wd = own ? pair<NV>(v, SPL_HW, k)[1] : 0.0, ua = own ? v[SPL_UA * NV + k] : 0.0;
     double f = Wk * wd / x.rho;
     const double uk = Wk * ua / x.rho;
     const double hw = (th.hRT - one) * wd;
@@ -863,7 +864,7 @@ __device__ __forceinline__ double rhs_jac(const DevMech &m, double *lds, double 
     const double TT = wave_sum(tt), tb = m.cv ? wave_sum(tm) : x.Wbar * Eu;
     double *row = P + (lane <= N ? N * PS + lane : lane % 16 * PS + NP);  // the others': the column behind
     *row = own ? *row + (tb + fT * m.Rgas * (th.cpR - one)) : TT / x.rho + Eu * x.invT + Scpf + fT * Sdcp;
-    lds[Lds<NP>::IW + lane] = iw;
+    lds[Lds<NP>::IW + (NP < WAVE ? min(lane, NP - 1) : lane)] = iw;  // zero from the temperature's place on
     lds_sync();
     const double invcp = 1.0 / x.cp;
     // species rows, constant pressure: J_km = (W_k/W_m) P_km + u_k Wbar/W_m,
