@@ -413,10 +413,10 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
         // the table in the records' execution order: the 64 lanes of a pass
         // read 64 consecutive coefficient blocks of the cell's interval
         const int nc = 2 * (fit.degree + 1);
-        std::vector<double> tab(fit.coef.size());
+        std::vector<double> tab((size_t)fit.nint * (t.R + 1) * nc, 0.0);
         for (int iv = 0; iv < fit.nint; ++iv)
             for (int q = 0; q < t.R; ++q)
-                std::copy_n(&fit.coef[((size_t)iv * t.R + sx.order[q]) * nc], nc, &tab[((size_t)iv * t.R + q) * nc]);
+                std::copy_n(&fit.coef[((size_t)iv * t.R + sx.order[q]) * nc], nc, &tab[((size_t)iv * (t.R + 1) + q) * nc]);
         ok = upload(p, tab, &ds.itab);
         ds.ideg = fit.degree;
         ds.inint = fit.nint;

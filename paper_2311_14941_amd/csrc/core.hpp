@@ -531,7 +531,9 @@ __device__ __forceinline__ RxTerms<S> reaction_sp(const DevMech &m, const DevRx 
         }
     }
     if (itb) {
-        const double *itc = itb + (size_t)min(j, m.R - 1) * 2 * (ideg + 1);
+        // the lanes behind the last reaction read a block of zeros: their rate
+        // constants are zero, and times 1/K_c beyond the largest double NaN
+        const double *itc = itb + (size_t)min(j, m.R) * 2 * (ideg + 1);
         dG = -poly_t(itc, ideg, itt);
         if (JAC) dH = poly_t(itc + ideg + 1, ideg, itt);
     } else {

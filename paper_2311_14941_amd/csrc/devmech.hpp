@@ -56,7 +56,7 @@ struct DevSparse : DevRx {
     const uint16_t *row, *low, *up, *blk;  // SparseDev's operand tables
     // interpolated thermodynamics (null: exact): per interval of ln T and
     // reaction (execution order) the 2 (ideg + 1) coefficients of -dG/RT and
-    // dH/RT in t = 2 (ln T - u_i) iinvdu - 1
+    // dH/RT in t = 2 (ln T - u_i) iinvdu - 1, then as many zeros
     const double *itab;
     int ideg, inint;
     double iu0, iinvdu;

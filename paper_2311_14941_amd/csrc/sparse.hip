@@ -258,7 +258,7 @@ __device__ __forceinline__ const double *thermo_block(const DevSparse &sp, int R
     if (!(uu >= 0.0) || !(uu < (double)sp.inint)) return nullptr;
     const int iv = (int)uu;
     t = 2.0 * (uu - iv) - 1.0;
-    return sp.itab + (size_t)iv * R * 2 * (sp.ideg + 1);
+    return sp.itab + (size_t)iv * (R + 1) * 2 * (sp.ideg + 1);
 }
 
 // f(y): dY_k/dt and dT/dt, VPL components per lane (0 beyond N).  Per pass
