@@ -180,3 +180,159 @@ def test_component_entries(tables, key):
     assert comp[N, 0] == entry[T, T] and comp[N, 1] == entry[S, S]
     rest = np.concatenate([comp[N, 2:].ravel(), comp[N + 1:].ravel()])
     assert np.all((rest > nnz) & (rest <= nnz + 16))
+
+
+def _entries(t):
+    n, nnz = int(t["size"][2]), int(t["size"][3])
+    entry = -np.ones((n, n), dtype=int)
+    entry[t["erow"], t["ecol"]] = np.arange(nnz)
+    return n, nnz, entry
+
+
+def _numbers(a, n):
+    """Entry numbers of an operand table: byte offsets up to 64 positions."""
+    a = a.astype(int)
+    if n > 64:
+        return a
+    assert np.all(a % 8 == 0)
+    return a // 8
+
+
+@pytest.mark.parametrize("key", list(MECHS))
+@pytest.mark.parametrize("fam", ["sparse", "dense"])
+def test_entries_of_the_reactions(tables, key, fam):
+    """Every derivative of every reaction is added to its row's and column's
+    entry where both are in use, and to a trash entry otherwise."""
+    mech, lanes, t = tables(key)
+    x = family(t, fam)
+    if not x:
+        return
+    N, R, n, nnz, npad = (int(v) for v in t["size"])
+    lanes = lanes if fam == "sparse" else 64
+    slot, nu, enh, orig = records(x, lanes)
+    passes, n_tb, _ = (int(v) for v in x["counts"])
+    unpack = lambda a, w: a.reshape(-1, w, lanes, 8).transpose(0, 2, 1, 3).reshape(-1, 8 * w)
+    ix, ixe = unpack(x["ix"], 6), unpack(x["ixe"], 4)
+    if fam == "sparse":
+        entry = _entries(t)[2]
+        place = lambda r, c: entry[r, c]
+        ix, ixe = _numbers(ix, n), _numbers(ixe, n)
+        trash = lambda e: (e > nnz) & (e <= nnz + 16)
+    else:
+        place = lambda r, c: r * (npad + 1) + c
+        ix, ixe = ix.astype(int) // 8, ixe.astype(int) // 8
+        trash = lambda e: e % (npad + 1) == npad  # the column behind the matrix
+    kinds = [mech.reactions[orig[q]].kind for q in range(R)]
+    assert sum(k != "plain" for k in kinds) == n_tb and all(k != "plain" for k in kinds[:n_tb])
+    for q in range(passes * lanes):
+        rows = [int(slot[q, r]) if nu[q, r] else -1 for r in range(6)] + [N if q < R else -1]
+        cols = [int(slot[q, s]) if nu[q, s] else -1 for s in range(6)]
+        used = [int(e) if e < N and q < n_tb else -1 for e in enh[q]]
+        for r in range(7):
+            at = [(ix[q, 7 * r + s] if r < 6 else ix[q, 42 + s], cols[s]) for s in range(6)]
+            if r < 6:
+                at.append((ix[q, 7 * r + 6], N if q < R else -1))
+            if q < n_tb:
+                at += [(ixe[q, 4 * r + e], used[e]) for e in range(4)]
+            for e, c in at:
+                if rows[r] >= 0 and c >= 0:
+                    assert e == place(rows[r], c) >= 0, (q, r, c)
+                else:
+                    assert trash(e), (q, r, c, e)
+
+
+@pytest.mark.parametrize("key", ["14 x 16", "30 x 32"])
+def test_rows_of_several_cells_per_wave(tables, key):
+    """A lane's row of the matrix, column by column, the zero slot outside."""
+    _, lanes, t = tables(key)
+    n, nnz, entry = _entries(t)
+    row = _numbers(t["row"], n).reshape(lanes, lanes)
+    want = np.full((lanes, lanes), nnz)
+    want[:n, :n] = np.where(entry >= 0, entry, nnz)
+    assert np.array_equal(row, want)
+
+
+def _lu_from_tables(t, E):
+    """The kernels' elimination in blocks of 16 pivots, replayed from the
+    operand tables alone; returns 1/u_kk."""
+    n = int(t["size"][2])
+    nb = (n + 15) // 16
+    c, g = np.arange(64) % 16, np.arange(64) // 16
+    words, at = _numbers(t["blk"], n), 0
+
+    def take(count, per):
+        nonlocal at
+        w = words[at:at + count * 64 * per].reshape(count, 64, per)
+        at += w.size
+        return w
+
+    dinv = np.zeros(n)
+    for b in range(nb):
+        r, k0 = nb - 1 - b, 16 * b
+        diag = take(2, 8).transpose(1, 0, 2).reshape(64, 16)
+        upper = take(2, 8).transpose(1, 0, 2).reshape(64, 16)
+        ul, ab, ci = take(r, 8), take(r, 8), take(r * r, 4)
+        D, u, x = E[diag], E[ul[:, :, :4]], E[ul[:, :, 4:]]
+        di = np.zeros(64)
+        for k in range(min(16, n - k0)):
+            lead = 16 * g + k  # lane k of each row of lanes
+            inv = 1.0 / D[lead, k]
+            l = np.where(c > k, D[:, k] * inv, 0.0)
+            di = np.where(c == k, inv, di)
+            D[:, k + 1:] -= D[lead, k + 1:] * l[:, None]
+            D[:, k] = np.where(c > k, l, D[:, k])
+            u -= u[:, lead] * l[None, :, None]
+        D *= np.where(np.arange(16)[None, :] > c[:, None], di[:, None], 1.0)
+        E[diag] = D
+        dinv[k0:k0 + 16] = di[:16][:n - k0]
+        E[ul[:, :, :4]] = u * di[None, :, None]
+        U = E[upper]
+        for k in range(15):
+            x -= x[:, 16 * g + k] * U[None, :, k, None]
+        E[ul[:, :, 4:]] = x
+        for q1 in range(r):
+            for q2 in range(r):
+                A, B = E[ab[q1][:, :4]], E[ab[q2][:, 4:]]
+                e = ci[q1 * r + q2]
+                C = np.zeros((16, 16))
+                for i in range(4):
+                    C[4 * i + g, c] = E[e[:, i]]
+                for s in range(4):
+                    As, Bs = np.zeros((16, 4)), np.zeros((4, 16))
+                    As[c, g], Bs[g, c] = A[:, s], B[:, s]
+                    C -= As @ Bs
+                for i in range(4):
+                    E[e[:, i]] = C[4 * i + g, c]
+        E[ul[:, :, 4:]] = x * di[None, :, None]
+        assert E[int(t["size"][3])] == 0.0  # the zero slot
+    assert at == words.size
+    return dinv
+
+
+@pytest.mark.parametrize("key", [(14, 56, 0.15, 401, 64), "24", (55, 330, 0.15, 400, 64), "62", "63", (110, 700, 0.15, 110, 64),
+                                 "126"], ids=["16", "26", "57", "64", "65", "112", "128"])
+def test_blocked_elimination_and_sweeps_solve_like_numpy(tables, key):
+    """The factorisation and the two sweeps of one cell per wave from their
+    operand tables alone, for n = 16 to 128 positions: equal to
+    numpy.linalg.solve on random diagonally dominant matrices of the pattern."""
+    _, _, t = tables(key)
+    n, nnz, entry = _entries(t)
+    slots = 1 if n <= 64 else 2
+    rng = np.random.default_rng(n)
+    A = np.where(entry >= 0, rng.normal(size=(n, n)), 0.0)
+    A[np.arange(n), np.arange(n)] = n + rng.uniform(1, 2, n)
+    E = np.zeros(nnz + 17)
+    E[entry[entry >= 0]] = A[entry >= 0]
+    dinv = _lu_from_tables(t, E)
+    row = lambda a: E[_numbers(a, n).reshape(64 * slots, 64 * slots)]
+    low, up = row(t["low"]), row(t["up"])
+    b = rng.normal(size=n)
+    z = np.concatenate([b, np.zeros(64 * slots - n)])
+    for k in range(n):
+        z -= low[:, k] * z[k]
+    z[:n] *= dinv
+    for k in range(n - 1, -1, -1):
+        z -= up[:, k] * z[k]
+    assert not z[n:].any()
+    x = np.linalg.solve(A, b)
+    assert np.allclose(z[:n], x, rtol=1e-12, atol=1e-12 * np.abs(x).max())

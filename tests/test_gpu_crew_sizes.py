@@ -88,3 +88,38 @@ def test_linear_solves_of_more_cells_than_a_launch_has_crews():
         i = torch.arange(max(c - 4, 0), min(c + 4, n), device="cuda:0")
         part = plan.linsolve(T[i], p[i], Y[:, i].contiguous(), hg[i], b[i])
         assert torch.equal(part, x[i]), c
+
+
+@pytest.mark.parametrize("ns,copies", [(57, 13), (65, 11)])
+def test_more_reaction_passes_than_a_crew_keeps_in_a_word(ns, copies):
+    """More than 64 passes of 64 reactions: a crew's waves find their passes by
+    the rule instead of the word they keep.  Copies of every reaction, the
+    added ones at a rate constant of 1e-290; bit for bit the static launch."""
+    import copy
+
+    import torch
+
+    import paper_2311_14941_amd as sc
+    from synth.mechgen import make_mechanism
+    sc.ensure_built()
+    mech = make_mechanism(ns, 6 * ns, 6 * ns // 10, 6 * ns // 20, ["C", "H", "O", "N"], seed=400, pool_frac=0.15)
+    base, mech.reactions = mech.reactions, []
+    for r in base:
+        none = copy.deepcopy(r)
+        none.log10A = -290.0
+        if none.kind == "troe":
+            none.troe = (-290.0, *none.troe[1:])
+        mech.reactions += [r] + [none] * (copies - 1)
+    assert len(mech.reactions) > 4096
+    rng = np.random.default_rng(ns)
+    g = lambda a: torch.tensor(np.ascontiguousarray(a), device="cuda:0")
+    n = 9
+    a = (g(rng.uniform(1000.0, 2000.0, n)), g(101325.0 * rng.uniform(1.0, 5.0, n)), g(rng.dirichlet(np.ones(ns), n).T),
+         g(10.0 ** rng.uniform(-10.0, -9.0, n)))
+    m = sc.Mechanism(mech.to_text())
+    kw = dict(linalg="sparse", rtol=1e-4, atol=1e-10, max_steps=300)
+    ref = sc.Plan(m, mode="static", **kw).integrate(*a)
+    for cfg in (dict(mode="plain"), dict(mode="persistent"), dict(mode="persistent", grid=1)):
+        r = sc.Plan(m, **cfg, **kw).integrate(*a)
+        for k in ("status", "T", "Y", "n_acc", "n_rej"):
+            assert torch.equal(r[k], ref[k]), (cfg, k)
