@@ -417,11 +417,12 @@ size_t lds_bytes_adj(int R)
 
 int adjoint_slot_checkpoints() { return NCK; }
 
-hipError_t launch_vjp(int np, const DevMech &m, int64_t n, const double *T, const double *p, const double *Y,
-                      int64_t ld, const double *dlnA, const double *wT, const double *wY, double *gT, double *gY,
+// the first `cells` of n cells (n: the distance of gcell's rows)
+hipError_t launch_vjp(int np, const DevMech &m, int64_t cells, int64_t n, const double *T, const double *p,
+                      const double *Y, int64_t ld, const double *dlnA, const double *wT, const double *wY, double *gT, double *gY,
                       double *gcell, hipStream_t s)
 {
-    SC_DISPATCH_A(np, hipLaunchKernelGGL(k_vjp<NPV>, dim3((unsigned)n), dim3(WAVE), lds_bytes_adj<NPV>(m.R), s, m,
+    SC_DISPATCH_A(np, hipLaunchKernelGGL(k_vjp<NPV>, dim3((unsigned)cells), dim3(WAVE), lds_bytes_adj<NPV>(m.R), s, m,
                                          n, T, p, Y, ld, dlnA, wT, wY, gT, gY, gcell));
     return hipGetLastError();
 }

@@ -126,6 +126,18 @@ sc_status check_common(sc_plan *plan, int64_t n, int64_t ld, std::initializer_li
     return SC_OK;
 }
 
+// A launch has fewer than 2^32 threads (it wraps beyond, without an error): calls
+// of a workgroup of one or two waves per cell take their cells in parts, and a
+// grid has at most WAVES waves.
+constexpr int64_t PART = 1 << 24, WAVES = 1 << 25;
+template <class F>
+hipError_t in_parts(int64_t n, F launch)
+{
+    hipError_t e = hipSuccess;
+    for (int64_t c = 0; c < n && e == hipSuccess; c += PART) e = launch(c, std::min(PART, n - c));
+    return e;
+}
+
 // Waves of the integration's workgroups, one cell per wave or crew.  With two
 // slots per lane a batch ends with its longest cell, which a crew of two shortens
 // from the beginning: crews up to half as many cells again as are in flight (700
@@ -504,10 +516,12 @@ sc_status sc_rhs(sc_plan *plan, int64_t n, const double *T, const double *p, con
     sc_status s = check_common(plan, n, ld, {T, p, Y, fT, fY});
     if (s != SC_OK || n == 0) return s;
     DeviceGuard g(plan->device);
-    hipError_t e =
-        plan->sparse
-            ? scdev::launch_rhs_sp(plan->vpl, plan->dms, plan->ds, n, T, p, Y, ld, dlnA, fT, fY, (hipStream_t)stream)
-            : scdev::launch_rhs(plan->np, plan->dm, n, T, p, Y, ld, dlnA, fT, fY, (hipStream_t)stream);
+    hipStream_t st = (hipStream_t)stream;
+    hipError_t e = in_parts(n, [&](int64_t c, int64_t k) {
+        return plan->sparse ? scdev::launch_rhs_sp(plan->vpl, plan->dms, plan->ds, k, T + c, p + c, Y + c, ld, dlnA,
+                                                   fT + c, fY + c, st)
+                            : scdev::launch_rhs(plan->np, plan->dm, k, T + c, p + c, Y + c, ld, dlnA, fT + c, fY + c, st);
+    });
     return e == hipSuccess ? SC_OK : hip_fail(e, "rhs launch");
 }
 
@@ -517,10 +531,13 @@ sc_status sc_jacobian(sc_plan *plan, int64_t n, const double *T, const double *p
     sc_status s = check_common(plan, n, ld, {T, p, Y, J});
     if (s != SC_OK || n == 0) return s;
     DeviceGuard g(plan->device);
-    hipError_t e = plan->sparse
-                       ? scdev::launch_jac_sp(plan->vpl, plan->dms, plan->ds, n, T, p, Y, ld, dlnA, J,
-                                              (hipStream_t)stream)
-                       : scdev::launch_jac(plan->np, plan->dm, n, T, p, Y, ld, dlnA, J, (hipStream_t)stream);
+    hipStream_t st = (hipStream_t)stream;
+    const int64_t nn = plan->m.N + 1;
+    hipError_t e = in_parts(n, [&](int64_t c, int64_t k) {
+        return plan->sparse ? scdev::launch_jac_sp(plan->vpl, plan->dms, plan->ds, k, T + c, p + c, Y + c, ld, dlnA,
+                                                   J + c * nn * nn, st)
+                            : scdev::launch_jac(plan->np, plan->dm, k, T + c, p + c, Y + c, ld, dlnA, J + c * nn * nn, st);
+    });
     return e == hipSuccess ? SC_OK : hip_fail(e, "jacobian launch");
 }
 
@@ -531,10 +548,14 @@ sc_status sc_linsolve(sc_plan *plan, int64_t n, const double *T, const double *p
     if (s != SC_OK || n == 0 || (s = check_solve(plan)) != SC_OK) return s;
     DeviceGuard g(plan->device);
     const int waves = plan->vpl == 2 ? sc::crew_choice(2, plan->cap.solve, INT_MAX, n) : 1;
-    hipError_t e = plan->sparse ? scdev::launch_linsolve_sp(plan->vpl, plan->dms, plan->ds, n, T, p, Y, ld, dlnA, hg,
-                                                            b, x, waves, (hipStream_t)stream)
-                                : scdev::launch_linsolve(plan->np, plan->dm, n, T, p, Y, ld, dlnA, hg, b, x,
-                                                         (hipStream_t)stream);
+    hipStream_t st = (hipStream_t)stream;
+    const int64_t nn = plan->m.N + 1;
+    hipError_t e = in_parts(n, [&](int64_t c, int64_t k) {
+        return plan->sparse ? scdev::launch_linsolve_sp(plan->vpl, plan->dms, plan->ds, k, T + c, p + c, Y + c, ld, dlnA,
+                                                        hg + c, b + c * nn, x + c * nn, waves, st)
+                            : scdev::launch_linsolve(plan->np, plan->dm, k, T + c, p + c, Y + c, ld, dlnA, hg + c,
+                                                     b + c * nn, x + c * nn, st);
+    });
     return e == hipSuccess ? SC_OK : hip_fail(e, "linsolve launch");
 }
 
@@ -592,7 +613,7 @@ static sc_status integrate_impl(sc_plan *plan, int64_t n, const double *T0, cons
                                       : plan->capacity;
         if (grid <= 0) grid = 1;
         if (grid > tiles) grid = (int)tiles;
-        if (plan->sparse) grid = std::min(grid, 1 << 22);  // four waves each, within a launch's 2^32 threads
+        grid = (int)std::min<int64_t>(grid, WAVES / (plan->sparse ? 4 : 1));
         int32_t *perm = nullptr;
         if (plan->opt.order != SC_ORDER_NONE) {
             if (noalloc)
@@ -611,10 +632,16 @@ static sc_status integrate_impl(sc_plan *plan, int64_t n, const double *T0, cons
             e = scdev::launch_integrate_persistent(plan->np, plan->dm, o, plan->opt.method, n, T0, p, Y0, ld, dt,
                                                    dlnA, h_io, T1, Y1, cell_status, n_acc, n_rej, queue, perm, tile,
                                                    grid, ref, st);
-    } else if (plan->opt.mode == SC_MODE_STATIC) {
-        int grid = plan->opt.grid > 0 ? plan->opt.grid : plan->sparse ? plan->cap.fixed : plan->capacity;
+    } else if (plan->opt.mode == SC_MODE_STATIC || (plan->sparse ? plan->vpl == 1 && n > WAVES * plan->ds.cpw : n > WAVES)) {
+        // (more cells than a plain launch has waves: a group of them for each,
+        // with the same results)
+        int grid = plan->opt.mode == SC_MODE_PLAIN ? (int)WAVES
+                   : plan->opt.grid > 0            ? plan->opt.grid
+                   : plan->sparse                  ? plan->cap.fixed
+                                                   : plan->capacity;
         if (grid <= 0) grid = 1;
         if (grid > n) grid = (int)n;
+        grid = (int)std::min(grid, (int)WAVES);
         if (plan->sparse)
             e = scdev::launch_integrate_sp_static(plan->vpl, plan->dms, plan->ds, o, n, T0, p, Y0, ld, dt, dlnA, h_io,
                                                   T1, Y1, cell_status, n_acc, n_rej, grid, ref, st);
@@ -745,8 +772,10 @@ sc_status sc_vjp(sc_plan *plan, int64_t n, const double *T, const double *p, con
         return fail(SC_EUNSUPPORTED, "the VJP supports up to " + std::to_string(sc::MAX_STATE - 1) + " species");
     if (n == 0) return SC_OK;
     DeviceGuard g(plan->device);
-    hipError_t e = scdev::launch_vjp(plan->np, plan->dm, n, T, p, Y, ld, dlnA, wT, wY, gT, gY, g_dlnA_cell,
-                                     (hipStream_t)stream);
+    hipError_t e = in_parts(n, [&](int64_t c, int64_t k) {
+        return scdev::launch_vjp(plan->np, plan->dm, k, n, T + c, p + c, Y + c, ld, dlnA, wT + c, wY + c, gT + c, gY + c,
+                                 g_dlnA_cell ? g_dlnA_cell + c : nullptr, (hipStream_t)stream);
+    });
     return e == hipSuccess ? SC_OK : hip_fail(e, "vjp launch");
 }
 

@@ -153,7 +153,7 @@ hipError_t launch_map_apply(int N, int64_t n, const int32_t *ref, const double *
                             hipStream_t s);
 
 // adjoint (adjoint.hip)
-hipError_t launch_vjp(int np, const DevMech &m, int64_t n, const double *T, const double *p, const double *Y,
+hipError_t launch_vjp(int np, const DevMech &m, int64_t cells, int64_t n, const double *T, const double *p, const double *Y,
                       int64_t ld, const double *dlnA, const double *wT, const double *wY, double *gT, double *gY,
                       double *gcell, hipStream_t s);
 hipError_t launch_adjoint(int np, const DevMech &m, const Opts &o, int64_t n, const double *T0, const double *p,

@@ -1381,14 +1381,9 @@ hipError_t launch_linsolve_sp(int vpl, const DevMech &m, const DevSparse &sp, in
                               const double *b, double *x, int waves, hipStream_t s)
 {
     const int cpw = sp.cpw;
-    // a launch has fewer than 2^32 threads: crews of two take their cells in parts
-    const int64_t part = waves == 2 ? 1 << 24 : n, nn = m.N + 1;
     auto launch = [&](auto kern, size_t bytes) {
-        for (int64_t c = 0; c < n; c += part) {
-            const int64_t k = std::min(part, n - c);
-            hipLaunchKernelGGL(kern, dim3(sp_blocks(k, cpw)), dim3(waves * WAVE), bytes, s, m, sp, k, T + c, p + c,
-                               Y + c, ld, dlnA, hg + c, b + c * nn, x + c * nn);
-        }
+        hipLaunchKernelGGL(kern, dim3(sp_blocks(n, cpw)), dim3(waves * WAVE), bytes, s, m, sp, n, T, p, Y, ld, dlnA,
+                           hg, b, x);
     };
     SP_DISPATCH(if (VPLV == 2 && waves == 2) launch(k_linsolve_sp<VPLV, CVV, CPWV, TBV, VPLV>, crew_lds(vpl, sp, 2));
                 else launch(k_linsolve_sp<VPLV, CVV, CPWV, TBV, 1>, sp_lds(sp, cpw)))
@@ -1400,7 +1395,8 @@ hipError_t launch_integrate_sp(int vpl, const DevMech &m, const DevSparse &sp, c
                                int32_t *nr, const int32_t *ref, int waves, hipStream_t s)
 {
     const int cpw = sp.cpw;
-    // a crew per cell; four waves at most each, within a launch's 2^32 threads
+    // a crew per cell, or where they would be more than a launch's 2^32
+    // threads, four waves each, per tile of cells
     const int tile = (int)((n >> 22) + 1);
     if (waves > 0)
         return launch_integrate_sp_persistent(vpl, m, sp, o, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1, st, na, nr,
