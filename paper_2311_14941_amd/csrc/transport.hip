@@ -32,7 +32,7 @@ constexpr int KC = 6;
 constexpr uint32_t DIES = 8;
 __global__ void __launch_bounds__(256) k_transport2d(int nx, int ny, int ncomp, const double *in, int64_t ld,
                                                      const double *u, const double *dt, double dx, double D,
-                                                     const double *inflow, double *out)
+                                                     const double *inflow, double *out, int64_t c0)
 {
     const int64_t n = (int64_t)nx * ny;
     uint32_t bx = blockIdx.x, by = blockIdx.y;
@@ -42,7 +42,7 @@ __global__ void __launch_bounds__(256) k_transport2d(int nx, int ny, int ncomp, 
         by = t / gridDim.x;
         bx = t - by * gridDim.x;
     }
-    const int64_t c = (int64_t)bx * blockDim.x + threadIdx.x;
+    const int64_t c = c0 + (int64_t)bx * blockDim.x + threadIdx.x;
     if (c >= n) return;
     int iy, ix;
     if (n <= INT32_MAX) {
@@ -80,11 +80,13 @@ hipError_t launch_transport2d(int nx, int ny, int ncomp, const double *in, int64
                               const double *dt, double dx, double D, const double *inflow, double *out,
                               hipStream_t s)
 {
-    const int64_t n = (int64_t)nx * ny;
-    const unsigned gx = (unsigned)((n + 255) / 256);
+    const int64_t n = (int64_t)nx * ny, part = (int64_t)1 << 31;  // cells of one launch, below its 2^32 threads
     const unsigned gy = (unsigned)std::min<int64_t>((ncomp + (int64_t)KC - 1) / KC, 65535);
-    hipLaunchKernelGGL(k_transport2d, dim3(gx, gy), dim3(256), 0, s, nx, ny, ncomp, in, ld, u, dt, dx, D, inflow,
-                       out);
+    for (int64_t c0 = 0; c0 < n; c0 += part) {
+        const unsigned gx = (unsigned)((std::min(part, n - c0) + 255) / 256);
+        hipLaunchKernelGGL(k_transport2d, dim3(gx, gy), dim3(256), 0, s, nx, ny, ncomp, in, ld, u, dt, dx, D, inflow,
+                           out, c0);
+    }
     return hipGetLastError();
 }
 

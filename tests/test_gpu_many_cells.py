@@ -1,7 +1,8 @@
 """Calls of more cells than a launch's 2^32 threads hold a wave each (2^26):
 9 species, 2^26 + 5 cells, every entry point that takes a workgroup per cell,
 dense and sparse (one cell per wave).  The first and last cells and those
-around the parts' ends are as in small calls, bit for bit."""
+around the parts' ends are as in small calls, bit for bit.  The transport step,
+a thread per cell, with 2^32 and more."""
 import numpy as np
 import pytest
 
@@ -71,3 +72,25 @@ def test_integration(case, linalg, mode):
         assert torch.equal(out[k][..., i], ref[k]), k
     assert int((out["n_acc"] > 0).sum()) == i.numel()
     assert torch.equal(out["T"][dt == 0.0], T[dt == 0.0]) and int(out["status"].max()) == 0
+
+
+def test_transport():
+    """The last rows of a grid of 65,536 x 65,537 cells are those of the same
+    rows by themselves (their south row is not compared: it is a boundary
+    there)."""
+    import torch
+
+    import paper_2311_14941_amd as sc
+    sc.ensure_built()
+    nx, ny, part = 65536, 65537, 5
+    d = dict(dtype=torch.float64, device="cuda:0")
+    q, u, dt = torch.full((1, nx * ny), 0.25, **d), torch.full((nx * ny,), 3.0, **d), torch.full((nx * ny,), 1e-4, **d)
+    tail = slice(nx * (ny - part), None)
+    q[0, tail] = torch.rand(nx * part, **d)
+    inflow = torch.rand((1, ny), **d)
+    out = sc.transport2d(nx, ny, q, u, dt, 1e-3, 2e-4, inflow)
+    ref = sc.transport2d(nx, part, q[:, tail].contiguous(), u[tail].clone(), dt[tail].clone(), 1e-3, 2e-4,
+                         inflow[:, ny - part:].contiguous())
+    assert torch.equal(out[0, nx * (ny - part + 1):], ref[0, nx:])
+    first = slice(0, nx)  # a row of 0.25 within rows of 0.25, its inflow apart
+    assert torch.equal(out[0, first][2:], q[0, first][2:])
