@@ -26,8 +26,10 @@ FLAGS = [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
          # the step kernels are far longer than their registers reach: constants
          # and conditions are made again where they are used (hoisted out of the
          # reaction loops they were spilled to vector lanes and scratch: 97
-         # registers of the one-wave kernel's, 16 now; 16,384 cells of 9
-         # species 39.8 -> 34.2 ms)
+         # registers of the one-wave kernel's, 18 now; 16,384 cells of 9
+         # species 39.8 -> 34.2 ms).  What the compiler keeps in accumulation
+         # registers and scratch is checked on the built library
+         # (tests/test_codegen.py)
          "-mllvm", "-disable-machine-licm", "-mllvm", "-sink-insts-to-avoid-spills",
          f"-I{INC}", f"-I{CSRC}"]
 

@@ -1,8 +1,8 @@
 // Device building blocks shared by the forward and adjoint kernels: the
 // Rosenbrock tableau, wave helpers, the per-cell LDS layout, thermodynamics,
 // reaction rates with their analytical derivatives, the right-hand side and
-// Jacobian passes, the in-register LU and the solves, one Rosenbrock attempt
-// and the step-size controller.
+// Jacobian passes (both families'), the dense LU and solves, one Rosenbrock
+// attempt and the step-size controller.
 //
 // Work decomposition: one 64-lane wavefront integrates one cell (one
 // independent homogeneous reactor, paper Sec. 1).  Inside the wave
@@ -12,9 +12,10 @@
 //     derivatives with lanes over reactions (Sec. 2.5: sparse analytical
 //     Jacobian), scattering into LDS with LDS floating-point atomics;
 //   - the iteration matrix I/(h gamma) - J is formed in VGPRs, row i in lane
-//     i, factorised without pivoting in a fixed order by a fully unrolled
-//     right-looking LU whose pivot rows are broadcast with readlane, and then
-//     parked in LDS (column-major, conflict-free) for the triangular solves;
+//     i, and factorised without pivoting in a fixed order, in blocks of 16
+//     pivots whose rows are broadcast inside the multiply-adds; the factors
+//     leave for LDS block by block (column-major, an odd stride) for the
+//     triangular solves;
 //   - the Rosenbrock stepper and its error/step-size controller run uniformly
 //     per wave (no divergence: every lane follows its cell's control flow).
 // Everything is FP64.
@@ -219,10 +220,14 @@ __device__ __forceinline__ void unrolled(F &&f)
 
 __device__ __forceinline__ void wave_sync() { __syncthreads(); }
 
-// Order between the LDS accesses of the wave's lanes.  A workgroup is one
-// wave, whose LDS instructions take effect in order: the compiler must not
-// move them across, but nothing has to be waited for (a workgroup barrier's
-// fence also waits for the loads sent ahead).
+// Order between the LDS accesses of the wave's lanes.  A wave's LDS
+// instructions take effect in order: the compiler must not move them across,
+// but nothing has to be waited for (a workgroup barrier's fence also waits for
+// the loads sent ahead).  Between the waves of a workgroup it orders only this:
+// what a wave wrote or added before a store is there for whoever reads that
+// store's value, since the LDS takes the instructions of one wave one after the
+// other (a crew's turn counter is handed on so); everything else goes through
+// barriers.
 __device__ __forceinline__ void lds_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

@@ -23,9 +23,7 @@ constexpr int NDEP = 2 * MAXSIDE + MAXENH;  // dependency slots per reaction
 constexpr int MAX_STATE = 64;               // N + 1 supported by the dense one-wave kernels
 constexpr int MAX_STATE_SPARSE = 128;       // N + 1 supported by the sparse kernels (two components per lane)
 constexpr int MAX_SOLVE = 128;              // N + 2 their factorisation and solves hold (two rows per lane)
-// widest dense trailing block of the sparse LU held in registers: systems
-// of up to 64 positions (two waves per SIMD, a tighter register budget),
-// and wider ones (one wave per SIMD)
+// widest dense trailing block the level schedule leaves out (sc_mech_sparse_array)
 constexpr int SPARSE_TAIL_MAX = 32;
 constexpr int SPARSE_TAIL_MAX_WIDE = 64;
 constexpr int sparse_tail_max(int n) { return n <= 64 ? SPARSE_TAIL_MAX : SPARSE_TAIL_MAX_WIDE; }
@@ -49,8 +47,11 @@ constexpr uint16_t NOENT = 0xffff;
 // the density term of constant pressure, or the total concentration of
 // constant volume).  The species block is put in minimum-degree order, the
 // borders last, so no fill enters the species block from them.  The
-// symbolic LU (right-looking, no pivoting) fixes the L+U pattern; the
-// numeric work is a static schedule in levels of independent operations.
+// symbolic LU (right-looking, no pivoting) fixes the L+U pattern.  The kernels
+// read operand tables made from it (SparseDev, SparseRx); the schedule in levels
+// of independent operations and the row masks and sweep tables below count the
+// work and serve sc_mech_sparse_array, for inspection and tests: no kernel reads
+// them.
 struct SparseLU {
     int n = 0, nnz = 0;
     std::vector<int> perm;        // position -> variable (species 0..N-1, N = T, N + 1 = sigma)
@@ -65,8 +66,7 @@ struct SparseLU {
     // the diagonal (backward sweep)
     std::vector<uint32_t> sweep_f, sweep_b;
     // n <= 64: per column k and row i (64 rows per column), the entry of
-    // (i, k) below (sweep_fi) or above (sweep_bi) the diagonal, else nnz (a
-    // slot the kernels keep at zero)
+    // (i, k) below (sweep_fi) or above (sweep_bi) the diagonal, else nnz
     std::vector<uint16_t> sweep_fi, sweep_bi;
     std::vector<uint8_t> apat;    // n * n: structural pattern of the bordered matrix (before fill)
     // LU, level by level: scale the L entries of the level's pivots
@@ -78,14 +78,14 @@ struct SparseLU {
     std::vector<uint32_t> lu_u;           // strict U entries with their pivot: e_kj | k << 16 (row scaling)
     // the dense trailing block [tail0, n) (full L+U pattern, at most
     // sparse_tail_max(n) positions): its pivots are not in the level schedule
-    // but factorised in registers after it
+    // but eliminated densely after it
     int tail0 = 0;
     std::vector<uint32_t> diag;           // diagonal entry of each position
     // triangular solves (unit L, then the row-scaled unit U): items
     // i | p << 16 | e << 32 meaning x_i -= value(e) x_p, level by level
     std::vector<int> fw_lvl, bw_lvl;
     std::vector<uint64_t> fw, bw;
-    // transposed solves (U'^T, then L^T) for the adjoint
+    // transposed solves (U'^T, then L^T)
     std::vector<int> tfw_lvl, tbw_lvl;
     std::vector<uint64_t> tfw, tbw;
     std::vector<uint16_t> rxi;            // [R][RXI_SIZE] entry indices per reaction, original order

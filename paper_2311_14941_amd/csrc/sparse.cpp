@@ -147,10 +147,7 @@ void compile_sparse(Mech &m)
         for (int i : Lc[k])
             for (int j : Ur[k]) F[i * n + j] = 1;
     }
-    // entries numbered column by column, rows ascending within a column, so
-    // a column's entries are contiguous: the entry of (i, j) is the column's
-    // start plus the number of its rows above i (what the device solves
-    // compute from the column's row mask)
+    // entries numbered column by column, rows ascending within a column
     S.emap.assign((size_t)n * n, -1);
     S.cstart.assign(1, 0);
     const size_t mw = std::max(2, (n + 63) / 64);  // words of a column's row mask

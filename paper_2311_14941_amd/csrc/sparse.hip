@@ -957,9 +957,10 @@ __device__ __forceinline__ void integrate_cell_v(const DevMech &m, const DevSpar
 // One-wave mechanisms (VPL = 1) run two waves per SIMD: their LDS allows it
 // (under 20 KB per cell up to 53 species) and the second wave hides the
 // first's LDS, memory and broadcast latencies.  The register cap this
-// implies spills about a hundred registers to scratch, outside the inner
-// loops; measured on the 53-species batch it is still 1.6x faster than one
-// wave per SIMD.
+// implies spills 13 to 39 registers to scratch with one cell per wave, 33 to 61
+// with four and 63 to 100 with two (whose rows in registers are the longest),
+// outside the inner loops.  With two slots per lane (398 to 418 registers) one
+// wave takes a SIMD and nothing is spilled.
 #define SP_OCC __attribute__((amdgpu_waves_per_eu(VPL == 1 ? 2 : 1, VPL == 1 ? 2 : 1)))
 // CPW cells per wave: each cell takes G = 64 / CPW lanes and its own LDS
 // region (sp.size doubles); lane = threadIdx.x % G, group = threadIdx.x / G.
