@@ -71,16 +71,20 @@ def build(force=True, jobs=3):
 
 C_CHECK_SRC = os.path.join(ROOT, "tests", "c", "c_abi_check.c")
 C_CHECK = os.path.join(OBJDIR, "c_abi_check")
+MEMORY_SRC = os.path.join(ROOT, "tests", "c", "host_memory_check.cpp")
+MEMORY_CHECK = os.path.join(OBJDIR, "host_memory_check")
 
 
 def build_c_check():
     """The plain-C program that drives the C ABI without Python (used by the
-    GPU tests): gcc, HIP runtime headers, linked against the library."""
+    GPU tests), and the one whose host allocations fail: gcc, HIP runtime
+    headers, linked against the library."""
     os.makedirs(OBJDIR, exist_ok=True)
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(HIPCC)))
-    _run(["gcc", "-std=c11", "-O2", "-Wall", "-D__HIP_PLATFORM_AMD__", f"-I{rocm}/include", f"-I{INC}",
-          C_CHECK_SRC, "-o", C_CHECK, f"-L{rocm}/lib", "-lamdhip64", f"-L{HERE}", "-lstiffchem",
-          f"-Wl,-rpath,{rocm}/lib", "-Wl,-rpath,$ORIGIN/.."])
+    for cc, src, exe in (["gcc", "-std=c11"], C_CHECK_SRC, C_CHECK), (["g++", "-std=c++17"], MEMORY_SRC, MEMORY_CHECK):
+        _run([*cc, "-O2", "-Wall", "-D__HIP_PLATFORM_AMD__", f"-I{rocm}/include", f"-I{INC}",
+              src, "-o", exe, f"-L{rocm}/lib", "-lamdhip64", f"-L{HERE}", "-lstiffchem", "-ldl",
+              f"-Wl,-rpath,{rocm}/lib", "-Wl,-rpath,$ORIGIN/.."])
     return C_CHECK
 
 

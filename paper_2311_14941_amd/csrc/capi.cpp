@@ -5,6 +5,7 @@
 #include <climits>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -57,6 +58,23 @@ sc_status hip_fail(hipError_t e, const char *what)
     return fail(SC_EHIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+// The entry points that allocate on the host: an allocation that fails ends the
+// call with a status, not with an exception through the caller's C frames.
+template <class F>
+sc_status guarded(F call)
+{
+    try {
+        return call();
+    } catch (...) {
+        try {
+            g_err = "host allocation failed";
+        } catch (...) {
+            g_err.clear();
+        }
+        return SC_ENOMEM;
+    }
+}
+
 template <class T>
 bool upload(sc_plan *p, const std::vector<T> &v, const T **out)
 {
@@ -83,6 +101,14 @@ void release(sc_plan *p)
     p->order_ws_bytes = p->adj_ws_bytes = p->gcell_ws_bytes = 0;
     (void)hipSetDevice(cur);
 }
+
+struct Discard {
+    void operator()(sc_plan *p) const
+    {
+        release(p);
+        delete p;
+    }
+};
 
 struct DeviceGuard {
     int prev = 0;
@@ -190,19 +216,21 @@ sc_status sc_mech_load(const char *text, size_t len, sc_mech **out)
     if (!out) return fail(SC_EINVAL, "out is NULL");
     *out = nullptr;
     if (!text) return fail(SC_EINVAL, "text is NULL");
-    try {
-        auto *h = new sc_mech{sc::load_mechanism(std::string(text, len))};
-        *out = h;
-        return SC_OK;
-    } catch (const sc::Unsupported &e) {
-        return fail(SC_EUNSUPPORTED, e.what());
-    } catch (const sc::ParseError &e) {
-        return fail(SC_EPARSE, e.what());
-    } catch (const std::bad_alloc &) {
-        return fail(SC_ENOMEM, "host allocation failed");
-    } catch (const std::exception &e) {
-        return fail(SC_EPARSE, e.what());
-    }
+    return guarded([&] {
+        try {
+            auto *h = new sc_mech{sc::load_mechanism(std::string(text, len))};
+            *out = h;
+            return SC_OK;
+        } catch (const sc::Unsupported &e) {
+            return fail(SC_EUNSUPPORTED, e.what());
+        } catch (const sc::ParseError &e) {
+            return fail(SC_EPARSE, e.what());
+        } catch (const std::bad_alloc &) {
+            throw;
+        } catch (const std::exception &e) {
+            return fail(SC_EPARSE, e.what());
+        }
+    });
 }
 
 void sc_mech_free(sc_mech *mech) { delete mech; }
@@ -246,20 +274,24 @@ sc_status sc_mech_thermo_fit(const sc_mech *mech, double Tmin, double Tmax, doub
                              size_t *ncoef)
 {
     if (!mech) return fail(SC_EINVAL, "mech is NULL");
-    sc::ThermoFit f;
-    try {
-        f = sc::fit_thermo(mech->m, Tmin, Tmax, tol, degree);
-    } catch (const std::exception &e) {
-        return fail(SC_EINVAL, std::string("thermo interpolation: ") + e.what());
-    }
-    if (degree_out) *degree_out = f.degree;
-    if (nint_out) *nint_out = f.nint;
-    if (max_err_out) *max_err_out = f.max_err;
-    if (ncoef) {
-        if (coef) std::copy_n(f.coef.begin(), std::min(*ncoef, f.coef.size()), coef);
-        *ncoef = f.coef.size();
-    }
-    return SC_OK;
+    return guarded([&] {
+        sc::ThermoFit f;
+        try {
+            f = sc::fit_thermo(mech->m, Tmin, Tmax, tol, degree);
+        } catch (const std::bad_alloc &) {
+            throw;
+        } catch (const std::exception &e) {
+            return fail(SC_EINVAL, std::string("thermo interpolation: ") + e.what());
+        }
+        if (degree_out) *degree_out = f.degree;
+        if (nint_out) *nint_out = f.nint;
+        if (max_err_out) *max_err_out = f.max_err;
+        if (ncoef) {
+            if (coef) std::copy_n(f.coef.begin(), std::min(*ncoef, f.coef.size()), coef);
+            *ncoef = f.coef.size();
+        }
+        return SC_OK;
+    });
 }
 
 sc_status sc_mech_sparse_array(const sc_mech *mech, const char *name, void *out, size_t *bytes)
@@ -314,7 +346,7 @@ sc_status sc_species_index(const sc_mech *mech, const char *name, int32_t *idx)
     return SC_OK;
 }
 
-sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt, sc_plan **out)
+static sc_status create_plan(const sc_mech *mech, int device, const sc_options *opt, sc_plan **out)
 {
     if (!out) return fail(SC_EINVAL, "out is NULL");
     *out = nullptr;
@@ -353,6 +385,8 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
     if (o.thermo_tol > 0.0) {
         try {
             fit = sc::fit_thermo(mech->m, o.thermo_Tmin, o.thermo_Tmax, o.thermo_tol, o.thermo_degree);
+        } catch (const std::bad_alloc &) {
+            throw;
         } catch (const std::exception &e) {
             return fail(SC_EINVAL, std::string("thermo interpolation: ") + e.what());
         }
@@ -376,12 +410,8 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
         ds.cpw = cpw;
         ds.n = S.n;
         ds.nnz = S.nnz;
-        try {
-            sd = sc::sparse_device(mech->m, 64 / cpw);
-            sx = sc::sparse_reactions(mech->m, 64 / cpw);
-        } catch (...) {
-            return fail(SC_ENOMEM, "host allocation failed");
-        }
+        sd = sc::sparse_device(mech->m, 64 / cpw);
+        sx = sc::sparse_reactions(mech->m, 64 / cpw);
         ds.passes = sx.passes;
         ds.n_tb = sx.n_tb;
         ds.n_troe = sx.n_troe;
@@ -396,16 +426,12 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
     }
     DeviceGuard g(device);
     if (!g.ok) return fail(SC_EHIP, "hipSetDevice failed");
-    sc_plan *p = nullptr;
-    try {
-        p = new sc_plan();
-        p->m = mech->m;
-    } catch (...) {
-        delete p;
-        return fail(SC_ENOMEM, "host allocation failed");
-    }
-    p->opt = o;
+    std::unique_ptr<sc_plan, Discard> plan(new sc_plan());
+    sc_plan *p = plan.get();
     p->device = device;
+    p->allocs.reserve(64);  // of device arrays: noted without another allocation
+    p->m = mech->m;
+    p->opt = o;
     p->np = p->m.n_padded;
     const sc::Tables &t = p->m.tab;
     scdev::DevMech &d = p->dm;
@@ -463,16 +489,8 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
              upload(p, sd.blk, &q.blk);
     }
     if (ok && nstate <= sc::MAX_STATE) {
-        sc::SparseRx dx;
-        std::vector<scdev::TroeRec> trd;
-        try {
-            dx = sc::dense_reactions(p->m);
-            trd.resize(dx.n_troe);
-        } catch (...) {
-            release(p);
-            delete p;
-            return fail(SC_ENOMEM, "host allocation failed");
-        }
+        const sc::SparseRx dx = sc::dense_reactions(p->m);
+        std::vector<scdev::TroeRec> trd(dx.n_troe);
         for (int k = 0; k < dx.n_troe; ++k) std::memcpy(&trd[k], &dx.troe[8 * (size_t)k], sizeof(scdev::TroeRec));
         scdev::DevRx &q = p->dm.pass;
         q.passes = dx.passes;
@@ -489,18 +507,19 @@ sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt,
             p->queue = static_cast<unsigned long long *>(q);
         }
     }
-    if (!ok) {
-        release(p);
-        delete p;
-        return fail(SC_ENOMEM, "device allocation/upload failed");
-    }
+    if (!ok) return fail(SC_ENOMEM, "device allocation/upload failed");
     if (sparse)
         p->cap = scdev::capacity_sp(vpl, p->ds, device);
     else
         p->capacity = scdev::persistent_capacity(p->np, device);
     p->adj_capacity = nstate <= sc::MAX_STATE ? scdev::adjoint_capacity(p->np, d.R, device) : 0;
-    *out = p;
+    *out = plan.release();
     return SC_OK;
+}
+
+sc_status sc_plan_create(const sc_mech *mech, int device, const sc_options *opt, sc_plan **out)
+{
+    return guarded([&] { return create_plan(mech, device, opt, out); });
 }
 
 void sc_plan_free(sc_plan *plan)
@@ -679,7 +698,7 @@ sc_status sc_integrate_noalloc(sc_plan *plan, int64_t n, const double *T0, const
     return integrate_impl(plan, n, T0, p, Y0, ld, dt, dlnA, h_io, T1, Y1, cell_status, n_acc, n_rej, stream, true);
 }
 
-sc_status sc_plan_set_mapping(sc_plan *plan, const double *Y_fuel, const double *Y_ox, const sc_mapping *opt)
+static sc_status set_mapping(sc_plan *plan, const double *Y_fuel, const double *Y_ox, const sc_mapping *opt)
 {
     if (!plan || !Y_fuel || !Y_ox || !opt) return fail(SC_EINVAL, "NULL argument");
     const sc::Mech &m = plan->m;
@@ -736,6 +755,11 @@ sc_status sc_plan_set_mapping(sc_plan *plan, const double *Y_fuel, const double 
     plan->mp.np = (int)np;
     plan->mapping = true;
     return SC_OK;
+}
+
+sc_status sc_plan_set_mapping(sc_plan *plan, const double *Y_fuel, const double *Y_ox, const sc_mapping *opt)
+{
+    return guarded([&] { return set_mapping(plan, Y_fuel, Y_ox, opt); });
 }
 
 sc_status sc_integrate_mapped(sc_plan *plan, int64_t n, const double *T0, const double *p, const double *Y0,
